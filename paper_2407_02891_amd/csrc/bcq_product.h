@@ -1,0 +1,399 @@
+// Dense product of the quantiser on the matrix cores:  C[r][c] = sum_k A[k][r] * B[k][c]  (not public).
+//
+// A is [K][R] with pitch lda, B is [K][C] with pitch ldb, binary32, "k-major" (both pitches and R, C multiples of 4,
+// all pointers 16-byte aligned).  What happens to the finished tile is the mode:
+//   kQuadForm   part[tile column][r] = sum over the tile's columns c of C'[r][c] * E[c][r], where C' takes B[k][c] with the
+//               weight 1 for k < c, 1/2 for k = c and 0 for k > c: half of the quadratic form of a symmetric B if
+//               E = A.  The k range of a tile stops at its last column.  (out is [tile column][ldo], E has pitch ldo)
+//   kAddTwiceSymmetric   out[r][c] += 2 C[r][c], B = A: only the tiles on and above the diagonal are computed and each
+//               element is added to both out[r][c] and out[c][r]
+//   kSubtract   out[r][c] -= C[r][c]
+//   kStore      out[r][c] = C[r][c], B[k][c] = 0 for k > c   
+//   kStoreNegated   out[r][c] = -C[r][c], A[k][r] = 0 for k < r
+//
+// Arithmetic.  The binary32 matrix instruction (v_mfma_f32_32x32x2_f32) runs at 1/16 of the rate of the binary16 ones
+// (v_mfma_f32_16x16x32_f16).  So every operand value x is split, after scaling by a power of two s that belongs to its
+// row or column of the product, into two binary16 numbers,
+//     hi = rne16(s x),   lo = rne16(s x - hi),      |s x - hi - lo| <= 2^-24 |s x|  (or 2^-25, see below),
+// and the product is lo hi' + hi lo' + hi hi', three instructions that accumulate in binary32; the dropped lo lo' is
+// below 2^-24 of the term.  The accumulator is rounded three times per 16 values of k (measured: the instruction over 32
+// values rounds twice) instead of 16 times, so the result is closer to the binary64 one: 2-norm error of 2 X^T X with
+// standard normal X against binary64, binary32 instruction / this, 256 samples 2.9e-7 / 1.9e-7, 2048 samples
+// 8.2e-7 / 5.0e-7 (up to 32 samples the representation shows: 7.3e-8 / 8.6e-8 at 16).
+// The scales: binary16 reaches from 2^-24 to 2^16, so s is chosen from the largest magnitude in the first 32 values of
+// the row or column, which it puts at 2^4..2^5: later values may be 2^11 times larger, and the smallest step, 2^-25, is
+// 2^-29 of that largest value.  The largest magnitude of all values is tracked on the way; a tile with a row or column
+// outside 4 <= s max |x| <= 60000 at the end (none in a usual layer) is computed once more with s from the true maximum.
+// A value that is not finite makes every sum it enters not finite.
+//
+// Work split.  A workgroup of four waves owns a 128 x 128 tile of C, a wave a 64 x 64 quarter as 4 x 4 accumulators of
+// 16 x 16; a step takes 32 values of k.  Wave w brings the eight rows 8 w .. 8 w + 7 of the step, lane l the columns 2 l
+// and 2 l + 1 of both operands (eight 8-byte loads each, the rows of a wave contiguous), splits them in registers (2.5
+// vector instructions per value) and stores one 16-byte octet of k values per column and half: the layout in which the
+// matrix instruction takes its operands.  Two stages in LDS (64 KB) with one barrier per step; two workgroups per
+// compute unit, so that one's loads and splits run under the other's matrix instructions.  The loop has no branch around
+// its loads (buffer descriptors end at the k range), so that the compiler interleaves the vector instructions with the
+// matrix instructions: with branches the same loop was 25 % slower.
+// What bounds it: about 200 vector instructions (800 clocks) against 48 matrix instructions (768 clocks) per wave and step,
+// two waves per SIMD: both pipes are half busy.  Measured (binary32 instruction before / now): quadratic form of a 7168 x
+// 7168 layer 3.32 / 1.31 ms per candidate (840 TFLOP/s of binary16 products; a large library product of that type reaches
+// 1230 on this card), 2 X^T X over 4 x 2048 samples of 7168 channels 7.17 / 2.08 ms.
+// An octet of column c sits at position c ^ ((c >> 4) & 1): the 16 lanes that a 16-byte LDS access serves together then
+// touch 16 different 16-byte columns both when the pairs of columns are written and when 16 consecutive ones are read.
+//
+// Tiles are taken in blocks of 4 x 4 per XCD (workgroup numbers go round the eight XCDs), so that the workgroups that
+// share an L2 at a time share their operand panels.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <type_traits>
+
+#include "bcq_device.h"
+
+namespace bcq {
+
+typedef _Float16 prod_f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 prod_f16x2 __attribute__((ext_vector_type(2)));
+typedef unsigned prod_u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned prod_u32x2 __attribute__((ext_vector_type(2)));
+typedef float prod_f32x4 __attribute__((ext_vector_type(4)));
+
+enum ProductMode { kQuadForm = 0, kSubtract = 1, kAddTwiceSymmetric = 2, kStore = 3, kStoreNegated = 4 };
+
+constexpr int kProdTile = 128, kProdStep = 32, kProdBlock = 4;  // tile edge, k values per step, tiles per block edge
+
+struct ProductArgs {
+    const float *A, *B, *E;
+    float *out;
+    int lda, R, ldb, C, K, ldo;
+    int triangular_b;  // kStore: B[k][c] = 0 for k > c
+};
+
+// Number of workgroups, and the tile of one.  Blocks of 4 x 4 tiles are numbered row by row (only those on and above the
+// diagonal for kAddTwiceSymmetric; column by column from the last one for kQuadForm, whose last columns have the longest k
+// range).
+// Each XCD takes a contiguous run of blocks where all tiles cost the same, else every eighth block.
+template <int MODE>
+static inline int product_blocks(int R, int C)
+{
+    const int br = (R + kProdTile * kProdBlock - 1) / (kProdTile * kProdBlock);
+    const int bc = (C + kProdTile * kProdBlock - 1) / (kProdTile * kProdBlock);
+    return MODE == kAddTwiceSymmetric ? br * (br + 1) / 2 : br * bc;
+}
+
+template <int MODE>
+__device__ __forceinline__ bool product_tile(int wg, int wgs, int R, int C, int *tile_row, int *tile_col)
+{
+    const int ntr = (R + kProdTile - 1) / kProdTile, ntc = (C + kProdTile - 1) / kProdTile;
+    const int br = (ntr + kProdBlock - 1) / kProdBlock, bc = (ntc + kProdBlock - 1) / kProdBlock;
+    const int xcd = wg & 7, j = wg >> 3, t = j & (kProdBlock * kProdBlock - 1), per_xcd = wgs / (8 * kProdBlock * kProdBlock);
+    const bool uneven = MODE == kQuadForm || MODE == kStore || MODE == kStoreNegated;
+    int s = uneven ? (j / (kProdBlock * kProdBlock)) * 8 + xcd : xcd * per_xcd + j / (kProdBlock * kProdBlock);
+    int b_row, b_col;
+    if (MODE == kAddTwiceSymmetric) {
+        if (s >= br * (br + 1) / 2) return false;
+        b_row = 0;
+        while (s >= br - b_row) s -= br - b_row++;
+        b_col = b_row + s;
+    } else {
+        if (s >= br * bc) return false;
+        if (MODE == kQuadForm) {
+            b_col = s / br;
+            b_row = s - b_col * br;
+            b_col = bc - 1 - b_col;
+        } else {
+            b_row = s / bc;
+            b_col = s - b_row * bc;
+        }
+    }
+    *tile_row = b_row * kProdBlock + t / kProdBlock;
+    *tile_col = b_col * kProdBlock + t % kProdBlock;
+    return *tile_row < ntr && *tile_col < ntc && (MODE != kAddTwiceSymmetric || *tile_col >= *tile_row);
+}
+
+// Exponent of the power of two that puts a magnitude (as float bits) at 2^target .. 2^(target + 1), kept to those a
+// normal binary32 number can hold.
+__device__ __forceinline__ int product_shift(unsigned magnitude, int target)
+{
+    const int e = target - ((int)(magnitude >> 23) - 127);
+    return e < -126 ? -126 : (e > 126 ? 126 : e);
+}
+
+template <int MODE>
+__global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t stage[2][2][2][4][kProdTile * 16];  // [stage][A, B][hi, lo][octet][column]
+    __shared__ unsigned largest[2][kProdTile];  // largest magnitude per row of A's tile, column of B's tile (float bits)
+    __shared__ unsigned largest_of_tile[2];
+    __shared__ int shift[2][kProdTile];  // exponents of the scales
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lo = lane & 15, hi = lane >> 4, wr = wave >> 1, wc = wave & 1;
+    int tile_row, tile_col;
+    if (!product_tile<MODE>(blockIdx.x, gridDim.x, p.R, p.C, &tile_row, &tile_col)) return;
+    const int r0 = tile_row * kProdTile, c0 = tile_col * kProdTile;
+
+    // k range of the tile: what a triangular operand leaves
+    int k_begin = 0, k_end = p.K;
+    if (MODE == kQuadForm && k_end > c0 + kProdTile) k_end = c0 + kProdTile;
+    if (MODE == kStore && p.triangular_b && k_end > c0 + kProdTile) k_end = c0 + kProdTile;
+    if (MODE == kStoreNegated) k_begin = r0;
+    const int steps = (k_end - k_begin + kProdStep - 1) / kProdStep;
+
+    // Rows k .. k + 7 of an operand's panel as a buffer: reads beyond the k range come back as zeros without touching
+    // memory, so the loads need no branch.  Columns beyond the operand read the row that follows (inside the buffer, whose
+    // end is the last valid value of the last row) and only reach results that are dropped.
+    const float *const panel[2] = {p.A + r0, p.B + c0};
+    const int pitch[2] = {p.lda, p.ldb}, width[2] = {p.R - r0, p.C - c0};
+    prod_u32x2 raw[2][8];
+    auto load = [&](int step) {
+        const int k = k_begin + step * kProdStep + 8 * wave;
+        const int rows = k_end - k < 0 ? 0 : (k_end - k < 8 ? k_end - k : 8);
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+            const unsigned bytes = rows ? 4u * ((unsigned)(rows - 1) * (unsigned)pitch[o] + (unsigned)width[o]) : 0u;
+            const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<float *>(panel[o] + (size_t)(rows ? k : k_begin) * pitch[o]), 0, (int)bytes, kRawBufferFlags);
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                raw[o][j] = __builtin_amdgcn_raw_buffer_load_b64(rsrc, 8 * lane, 4 * j * pitch[o], 0);
+        }
+    };
+    auto weigh = [&](int step) {  // kQuadForm: B on and beyond its diagonal
+        const int k0 = k_begin + step * kProdStep + 8 * wave;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int c = c0 + 2 * lane + e;
+                const float v = __uint_as_float(raw[1][j][e]);
+                raw[1][j][e] = __float_as_uint(k0 + j < c ? v : (k0 + j == c ? 0.5f * v : 0.0f));
+            }
+    };
+    float top[2][2] = {{0.f, 0.f}, {0.f, 0.f}};  // largest magnitudes seen by this lane
+    auto track = [&]() {
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) top[o][e] = fmaxf(top[o][e], fabsf(__uint_as_float(raw[o][j][e])));
+    };
+    auto publish = [&]() {  // the lanes' maxima into `largest`
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) atomicMax(&largest[o][2 * lane + e], __float_as_uint(top[o][e]));
+    };
+    float s[2][2];
+    const int at = (2 * lane) ^ ((lane >> 3) & 1);  // position of the lane's first column; the second one's is at ^ 1
+    auto split_store = [&](int buf) {
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                prod_u32x4 h, l;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float v0 = __uint_as_float(raw[o][2 * j][e]), v1 = __uint_as_float(raw[o][2 * j + 1][e]);
+                    unsigned pair = __builtin_bit_cast(unsigned, prod_f16x2{(_Float16)(v0 * s[o][e]), (_Float16)(v1 * s[o][e])});
+                    asm("" : "+v"(pair));  // one packed conversion serves both uses
+                    h[j] = pair;
+                    const prod_f16x2 hp = __builtin_bit_cast(prod_f16x2, pair);
+                    l[j] = __builtin_bit_cast(unsigned, prod_f16x2{(_Float16)fmaf(v0, s[o][e], -(float)hp[0]),
+                                                                  (_Float16)fmaf(v1, s[o][e], -(float)hp[1])});
+                }
+                *reinterpret_cast<prod_u32x4 *>(&stage[buf][o][0][wave][(at ^ e) * 16]) = h;
+                *reinterpret_cast<prod_u32x4 *>(&stage[buf][o][1][wave][(at ^ e) * 16]) = l;
+            }
+    };
+
+    prod_f32x4 acc[4][4];
+    auto clear = [&]() {
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) acc[a][b] = prod_f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    auto multiply = [&](int buf) {
+        prod_f16x8 a[2][4], b[2][4];  // [hi, lo][tile]
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                a[x][t] = *reinterpret_cast<const prod_f16x8 *>(&stage[buf][0][x][hi][(wr * 64 + t * 16 + (lo ^ (t & 1))) * 16]);
+                b[x][t] = *reinterpret_cast<const prod_f16x8 *>(&stage[buf][1][x][hi][(wc * 64 + t * 16 + (lo ^ (t & 1))) * 16]);
+            }
+#pragma unroll
+        for (int x = 0; x < 3; ++x)  // lo hi', hi lo', hi hi'
+#pragma unroll
+            for (int ta = 0; ta < 4; ++ta)
+#pragma unroll
+                for (int tb = 0; tb < 4; ++tb)
+                    acc[ta][tb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[x == 0][ta], b[x == 1][tb], acc[ta][tb], 0, 0, 0);
+    };
+    // Steps [from, to): while a step is multiplied, the next one is split and stored to the other stage and the one
+    // after it is requested.
+    auto run = [&](int from, int to, auto weighed) {
+        for (int step = from; step < to; ++step) {
+            multiply(step & 1);
+            if (decltype(weighed)::value) weigh(step + 1);
+            track();
+            split_store((step & 1) ^ 1);
+            load(step + 2);
+            __syncthreads();  // the other stage is complete, and everyone is done reading this one
+        }
+    };
+    // kQuadForm: the accumulators' contribution to the quadratic form, and a fresh start.  Once per 1024 values of k: the
+    // shorter sums lose less to rounding.
+    prod_f32x4 sum[4];
+    auto contract = [&]() {
+        const int columns = width[1] < kProdTile ? width[1] : kProdTile;
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(p.E + (size_t)c0 * p.ldo + r0), 0, 4 * ((columns - 1) * p.ldo + width[0]), kRawBufferFlags);
+#pragma unroll
+        for (int tb = 0; tb < 4; ++tb) {
+            const int cl = wc * 64 + tb * 16 + lo;
+            prod_f32x4 e[4];
+#pragma unroll
+            for (int ta = 0; ta < 4; ++ta)
+                e[ta] = __builtin_bit_cast(prod_f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                           rsrc, 4 * (cl * p.ldo + wr * 64 + ta * 16 + 4 * hi), 0, 0));
+            if (cl < columns) {
+                const int shift_c = -shift[1][cl];
+#pragma unroll
+                for (int ta = 0; ta < 4; ++ta)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) sum[ta][i] = fmaf(ldexpf(acc[ta][tb][i], shift_c), e[ta][i], sum[ta][i]);
+            }
+        }
+        clear();
+    };
+    for (int attempt = 0;; ++attempt) {
+        load(0);
+        if (MODE == kQuadForm && c0 < kProdStep) weigh(0);
+        track();
+        if (attempt == 0) {
+            largest[tid >> 7][tid & 127] = 0u;
+            if (tid < 2) largest_of_tile[tid] = 0u;
+            __syncthreads();
+            publish();
+#pragma unroll
+            for (int o = 0; o < 2; ++o) {
+                float m = fmaxf(top[o][0], top[o][1]);
+#pragma unroll
+                for (int d = 32; d > 0; d >>= 1) m = fmaxf(m, __shfl_xor(m, d));
+                if (lane == 0) atomicMax(&largest_of_tile[o], __float_as_uint(m));
+            }
+            __syncthreads();
+        }
+        {
+            // first pass: the first step's largest value goes to 2^4 (a row or column that is zero there takes the
+            // tile's); second pass: the largest of all values goes to 2^14
+            const int o = tid >> 7;
+            const unsigned m = largest[o][tid & 127];
+            shift[o][tid & 127] = attempt ? product_shift(m, 14) : product_shift(m ? m : largest_of_tile[o], 4);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) s[o][e] = ldexpf(1.0f, shift[o][2 * lane + e]);
+        clear();
+        split_store(0);
+        load(1);
+        __syncthreads();
+        if constexpr (MODE == kQuadForm) {
+            const int plain = c0 / kProdStep - 1;  // the last steps, which reach the diagonal, are weighed one step ahead
+            constexpr int kChunk = 1024 / kProdStep;
+#pragma unroll
+            for (int ta = 0; ta < 4; ++ta) sum[ta] = prod_f32x4{0.f, 0.f, 0.f, 0.f};
+            int step = 0;
+            while (step < plain) {
+                const int to = plain - step < kChunk ? plain : step + kChunk;
+                run(step, to, std::false_type{});
+                if (to < plain) contract();
+                step = to;
+            }
+            run(step, steps, std::true_type{});
+        } else {
+            run(0, steps, std::false_type{});
+        }
+        if (attempt) break;
+        publish();
+        __syncthreads();
+        const int o = tid >> 7;
+        const float most = ldexpf(__uint_as_float(largest[o][tid & 127]), shift[o][tid & 127]);
+        const bool bad = (tid & 127) < width[o] && (!(most <= 60000.0f) || (most < 4.0f && most > 0.0f));
+        if (!__syncthreads_or(bad)) break;
+    }
+
+    // element i of a 16 x 16 accumulator: row 4 hi + i, column lo; the scales are taken out again
+    if constexpr (MODE != kQuadForm) {
+#pragma unroll
+        for (int tb = 0; tb < 4; ++tb) {
+            const int cl = wc * 64 + tb * 16 + lo, c = c0 + cl;
+            const int shift_c = shift[1][cl];
+#pragma unroll
+            for (int ta = 0; ta < 4; ++ta) {
+                    const int rl = wr * 64 + ta * 16 + 4 * hi, r = r0 + rl;  // R is a multiple of 4
+                    if (r >= p.R || c >= p.C) continue;
+                    float v[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[i] = ldexpf(acc[ta][tb][i], -(shift[0][rl + i] + shift_c));
+                    if constexpr (MODE == kAddTwiceSymmetric) {
+                        if (r > c) continue;  // (a group of four rows that crosses the diagonal is handled below)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (r + i <= c) p.out[(size_t)(r + i) * p.ldo + c] += 2.0f * v[i];
+                        float *o = p.out + (size_t)c * p.ldo + r;
+                        if (r + 3 < c) {
+                            prod_f32x4 w = *reinterpret_cast<prod_f32x4 *>(o);
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) w[i] += 2.0f * v[i];
+                            *reinterpret_cast<prod_f32x4 *>(o) = w;
+                        } else {
+#pragma unroll
+                            for (int i = 0; i < 4; ++i)
+                                if (r + i < c) o[i] += 2.0f * v[i];
+                        }
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            float *o = p.out + (size_t)(r + i) * p.ldo + c;
+                            if (MODE == kSubtract) *o -= v[i];
+                            if (MODE == kStore) *o = v[i];
+                            if (MODE == kStoreNegated) *o = -v[i];
+                        }
+                    }
+                }
+        }
+    } else {
+        float *red = reinterpret_cast<float *>(&stage[0][0][0][0][0]);  // [2 column halves][128 rows], free after the loop's last barrier
+        contract();
+#pragma unroll
+        for (int ta = 0; ta < 4; ++ta)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int rl = wr * 64 + ta * 16 + 4 * hi + i;
+                float all = sum[ta][i];
+#pragma unroll
+                for (int d = 1; d < 16; d <<= 1) all += __shfl_xor(all, d);
+                if (lo == 0) red[wc * kProdTile + rl] = ldexpf(all, -shift[0][rl]);
+            }
+        __syncthreads();
+        if (tid < kProdTile && r0 + tid < p.R) p.out[(size_t)tile_col * p.ldo + r0 + tid] = red[tid] + red[kProdTile + tid];
+    }
+}
+
+template <int MODE>
+static void launch_product(hipStream_t stream, const float *A, int lda, int R, const float *B, int ldb, int C, int K, float *out,
+                           int ldo, const float *E = nullptr, bool triangular_b = false)
+{
+    ProductArgs p = {A, B, E, out, lda, R, ldb, C, K, ldo, triangular_b ? 1 : 0};
+    const int blocks = (product_blocks<MODE>(R, C) + 7) / 8 * 8;
+    hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)(blocks * kProdBlock * kProdBlock)), dim3(256), 0, stream, p);
+}
+
+}  // namespace bcq

@@ -14,12 +14,14 @@
 //            upper Cholesky factor of H^-1 (Eq. 2 in its usual one-factorisation form).
 //
 // The integer decisions (rounding to the linear grid, nearest BCchoice) are taken in binary64 from
-// binary64 copies of the binary32 inputs; the quadratic form and the GPTQ updates run in binary32.
+// binary64 copies of the binary32 inputs; the quadratic form and the GPTQ updates accumulate in binary32
+// (the dense products with operands split into pairs of binary16 numbers, see bcq_product.h).
 #include <algorithm>
 #include <vector>
 
 #include "bcq_internal.h"
 #include "bcq_device.h"
+#include "bcq_product.h"
 #include "bcq_tying.h"
 
 namespace bcq {
@@ -87,8 +89,7 @@ __device__ __forceinline__ int quant_int(double w, double S, double qbias, int n
 // ---------------------------------------------------------------------------------
 // Both steps work on transposed binary32 copies, [column k][row m] with the row index fastest and a
 // pitch Mp = M rounded up to 4: one thread per row then reads and writes coalesced, and both dense
-// products below take their operands "k-major" (a tile is 16 values of the summation index by 128
-// contiguous floats).  Workspace, in floats:
+// products (bcq_product.h) take their operands "k-major" (the summation index is the slow one).  Workspace, in floats:
 //   Wt [N][Mp] | Dt [N][Mp] | part [ceil(N/128)][Mp] | wmin, wmax, best [3][Mp] | Err [128][Mp]
 struct QuantWorkspace {
     int Mp, ntile;
@@ -136,158 +137,12 @@ __global__ void transpose_kernel(int M, int Mp, int N, const float *__restrict__
 }
 
 // ---------------------------------------------------------------------------------
-// dense product on the matrix cores, binary32:  C[r][c] = sum_k A[k][r] * B[k][c]
-// ---------------------------------------------------------------------------------
-// A is [K][R] with pitch lda, B is [K][C] with pitch ldb (both pitches and R, C multiples of 4, all
-// pointers 16-byte aligned).  A workgroup of four waves owns a 128 x 128 tile of C, a wave a 64 x 64
-// quarter as 2 x 2 v_mfma_f32_32x32x2_f32 accumulators; the operand tiles (16 k x 128) go through
-// LDS, double-buffered, the next pair of tiles travelling through registers while the current one
-// is multiplied.  What happens to the finished tile is the caller's epilogue:
-//   kQuadForm   part[tile row][c] = sum over the tile's rows r of C[r][c] * E[r][c]; A symmetric, E = B
-//               (the k range stops at the tile's last row, see the loader)
-//   kSubtract   Out[r][c] -= C[r][c]
-//   kAddTwice   Out[r][c] += 2 C[r][c]
-//   kStore      Out[r][c] = C[r][c];   kStoreNegated   Out[r][c] = -C[r][c]
-// (Out and E have pitch ldo; for kQuadForm Out is [tile row][ldo].)
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4v __attribute__((ext_vector_type(4)));
-enum { kQuadForm = 0, kSubtract = 1, kAddTwice = 2, kStore = 3, kStoreNegated = 4 };
-constexpr int kTile = 128, kStep = 16;
-
-__device__ __forceinline__ f32x4v load4_or_zero(const float *base, size_t pitch, int k, int K, int x, int X)
-{
-    if (k < K && x < X) return *reinterpret_cast<const f32x4v *>(base + (size_t)k * pitch + x);
-    return f32x4v{0.f, 0.f, 0.f, 0.f};
-}
-
-template <int MODE>
-__global__ __launch_bounds__(256) void mfma_kmajor_kernel(const float *__restrict__ A, int lda, int R,
-                                                          const float *__restrict__ B, int ldb, int C, int K,
-                                                          float *__restrict__ out, int ldo, const float *__restrict__ E)
-{
-    __shared__ __attribute__((aligned(16))) float As[2][kStep][kTile];
-    __shared__ __attribute__((aligned(16))) float Bs[2][kStep][kTile];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int lo = lane & 31, hi = lane >> 5;
-    const int wr = wave >> 1, wc = wave & 1;
-    // kQuadForm: the tile rows with the longest k range are dispatched first
-    const int tile_row = MODE == kQuadForm ? (int)(gridDim.y - 1 - blockIdx.y) : (int)blockIdx.y;
-    const int r0 = tile_row * kTile, c0 = blockIdx.x * kTile;
-    // loader: thread t brings rows t/32 and t/32 + 8 of a 16 x 128 tile, four floats at column 4 (t%32)
-    const int lk = tid >> 5, lx = (tid & 31) * 4;
-
-    f32x16 acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.0f;
-
-    // kQuadForm: A is symmetric (the Hessian) and the caller wants sum_r E[r][c] C[r][c] with E = B, i.e.
-    // b^T A b: the terms k > r are folded onto k < r (weight 2, diagonal 1), which halves the k range.
-    const int Kend = MODE == kQuadForm ? (K < r0 + kTile ? K : r0 + kTile) : K;
-    auto load_a = [&](int k) {
-        f32x4v v = load4_or_zero(A, lda, k, Kend, r0 + lx, R);
-        if (MODE == kQuadForm) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int r = r0 + lx + e;
-                v[e] *= k < r ? 2.0f : (k == r ? 1.0f : 0.0f);
-            }
-        }
-        return v;
-    };
-    f32x4v ra[2], rb[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        ra[h] = load_a(lk + 8 * h);
-        rb[h] = load4_or_zero(B, ldb, lk + 8 * h, Kend, c0 + lx, C);
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        *reinterpret_cast<f32x4v *>(&As[0][lk + 8 * h][lx]) = ra[h];
-        *reinterpret_cast<f32x4v *>(&Bs[0][lk + 8 * h][lx]) = rb[h];
-    }
-    __syncthreads();
-    int buf = 0;
-    for (int k0 = 0; k0 < Kend; k0 += kStep) {
-        const bool more = k0 + kStep < Kend;
-        if (more) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                ra[h] = load_a(k0 + kStep + lk + 8 * h);
-                rb[h] = load4_or_zero(B, ldb, k0 + kStep + lk + 8 * h, Kend, c0 + lx, C);
-            }
-        }
-#pragma unroll
-        for (int s = 0; s < kStep / 2; ++s) {
-            const float a0 = As[buf][2 * s + hi][wr * 64 + lo], a1 = As[buf][2 * s + hi][wr * 64 + 32 + lo];
-            const float b0 = Bs[buf][2 * s + hi][wc * 64 + lo], b1 = Bs[buf][2 * s + hi][wc * 64 + 32 + lo];
-            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
-        }
-        if (more) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                *reinterpret_cast<f32x4v *>(&As[buf ^ 1][lk + 8 * h][lx]) = ra[h];
-                *reinterpret_cast<f32x4v *>(&Bs[buf ^ 1][lk + 8 * h][lx]) = rb[h];
-            }
-        }
-        __syncthreads();  // the other buffer is complete, and everyone is done reading this one
-        buf ^= 1;
-    }
-
-    // element i of a 32 x 32 accumulator: row 8 (i/4) + 4 hi + i%4, column lo
-    if constexpr (MODE != kQuadForm) {
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                const int c = c0 + wc * 64 + b * 32 + lo;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int r = r0 + wr * 64 + a * 32 + 8 * (i >> 2) + 4 * hi + (i & 3);
-                    if (r < R && c < C) {
-                        float *o = out + (size_t)r * ldo + c;
-                        if (MODE == kSubtract) *o -= acc[a][b][i];
-                        if (MODE == kAddTwice) *o += 2.0f * acc[a][b][i];
-                        if (MODE == kStore) *o = acc[a][b][i];
-                        if (MODE == kStoreNegated) *o = -acc[a][b][i];
-                    }
-                }
-            }
-    } else {
-        float *red = &As[0][0][0];  // [2 row halves][128 columns], free after the loop's last barrier
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const int c = c0 + wc * 64 + b * 32 + lo;
-            float sum = 0.0f;
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int r = r0 + wr * 64 + a * 32 + 8 * (i >> 2) + 4 * hi + (i & 3);
-                    if (r < R && c < C) sum = fmaf(acc[a][b][i], E[(size_t)r * ldo + c], sum);
-                }
-            sum += __shfl_xor(sum, 32);
-            if (hi == 0) red[wr * kTile + wc * 64 + b * 32 + lo] = sum;
-        }
-        __syncthreads();
-        if (tid < kTile && c0 + tid < C) out[(size_t)tile_row * ldo + c0 + tid] = red[tid] + red[kTile + tid];
-    }
-}
-
-// ---------------------------------------------------------------------------------
 // Hessian of the layer-wise objective (Sec. II-A): H += 2 X^T X for T more calibration inputs
 // ---------------------------------------------------------------------------------
 hipError_t launch_quant_hessian(int N, int T, const float *X, float *H, hipStream_t stream)
 {
     // X is [T][N]: k-major for both operands, C[r][c] = sum_t X[t][r] X[t][c]
-    hipLaunchKernelGGL((mfma_kmajor_kernel<kAddTwice>), dim3((N + kTile - 1) / kTile, (N + kTile - 1) / kTile), dim3(256),
-                       0, stream, X, N, N, X, N, N, T, H, N, nullptr);
+    launch_product<kAddTwiceSymmetric>(stream, X, N, N, X, N, N, T, H, N);
     return hipGetLastError();
 }
 
@@ -297,7 +152,7 @@ hipError_t launch_quant_hessian(int N, int T, const float *X, float *H, hipStrea
 // With H_d = H + lambda I = R R^T, R UPPER triangular (a Cholesky factorisation taken from the last
 // row upwards), H_d^-1 = R^-T R^-1, so U = R^-1.  Both steps are blocked by 128 columns; the diagonal
 // blocks are factored and inverted by one workgroup in LDS, everything else is the k-major product
-// above (K = 128 panels and trailing updates for R; growing K for the off-diagonal blocks of U).
+// of bcq_product.h (K = 128 panels and trailing updates for R; growing K for the off-diagonal blocks of U).
 // Working matrices (binary32, pitch N): Hw = H_d (consumed), Rt = R^T, Ut = U^T, T = one panel.
 constexpr int kFactorBlock = 128;
 
@@ -435,14 +290,6 @@ size_t quant_factor_workspace_bytes(int N)
     return (floats * 4 + 255) / 256 * 256;
 }
 
-template <int MODE>
-static void product(hipStream_t stream, const float *A, int lda, int R, const float *B, int ldb, int C, int K, float *out,
-                    int ldo)
-{
-    hipLaunchKernelGGL((mfma_kmajor_kernel<MODE>), dim3((C + kTile - 1) / kTile, (R + kTile - 1) / kTile), dim3(256), 0,
-                       stream, A, lda, R, B, ldb, C, K, out, ldo, nullptr);
-}
-
 // Off-diagonal blocks of U = R^-1 for the rows / columns [lo, hi) (the diagonal blocks are in place):
 // with the range cut at a block boundary, U12 = -U11 (R12 U22), both factors from the two halves.
 static void invert_range(hipStream_t stream, int N, int lo, int hi, const float *Rt, float *U, float *Ut, float *T)
@@ -454,9 +301,9 @@ static void invert_range(hipStream_t stream, int N, int lo, int hi, const float 
     invert_range(stream, N, mid, hi, Rt, U, Ut, T);
     const int rows = mid - lo, cols = hi - mid;
     // T[i][c] = sum_m R[lo + i][mid + m] U[mid + m][mid + c]
-    product<kStore>(stream, Rt + (size_t)mid * N + lo, N, rows, U + (size_t)mid * N + mid, N, cols, cols, T, cols);
+    launch_product<kStore>(stream, Rt + (size_t)mid * N + lo, N, rows, U + (size_t)mid * N + mid, N, cols, cols, T, cols, nullptr, true);
     // U[lo + r][mid + c] = -sum_j U[lo + r][lo + j] T[j][c]
-    product<kStoreNegated>(stream, Ut + (size_t)lo * N + lo, N, rows, T, cols, cols, rows, U + (size_t)lo * N + mid, N);
+    launch_product<kStoreNegated>(stream, Ut + (size_t)lo * N + lo, N, rows, T, cols, cols, rows, U + (size_t)lo * N + mid, N);
     hipLaunchKernelGGL(transpose_block_kernel, dim3((cols + 31) / 32, (rows + 31) / 32), dim3(32, 8), 0, stream, rows, cols,
                        U + (size_t)lo * N + mid, N, Ut + (size_t)mid * N + lo, N);
 }
@@ -487,9 +334,9 @@ hipError_t launch_quant_factor(int N, float damp, const float *H, float *U, void
         hipLaunchKernelGGL(factor_diag_kernel, dim3(1), dim3(256), kDiagLdsBytes, stream, N, r0, b, Hw, U, Ut);
         if (r0 == 0) break;
         // panel, transposed: Rt[r0 + c][i] = R[i][r0 + c] = sum_m V[c][m] Hw[r0 + m][i]   (Hw symmetric, V = R_kk^-1)
-        product<kStore>(stream, Ut + (size_t)r0 * N + r0, N, b, Hw + (size_t)r0 * N, N, r0, b, Rt + (size_t)r0 * N, N);
+        launch_product<kStore>(stream, Ut + (size_t)r0 * N + r0, N, b, Hw + (size_t)r0 * N, N, r0, b, Rt + (size_t)r0 * N, N);
         // Hw[i][j] -= sum_c R[i][r0 + c] R[j][r0 + c] for i, j < r0
-        product<kSubtract>(stream, Rt + (size_t)r0 * N, N, r0, Rt + (size_t)r0 * N, N, r0, b, Hw, N);
+        launch_product<kSubtract>(stream, Rt + (size_t)r0 * N, N, r0, Rt + (size_t)r0 * N, N, r0, b, Hw, N);
     }
     // U = R^-1: Hw is free now and holds the intermediate products
     invert_range(stream, N, 0, N, Rt, U, Ut, Hw);
@@ -559,8 +406,8 @@ __global__ void delta_kernel(int M, int Mp, int N, int n_bits, int g, int grid, 
     Dt[(size_t)k * Mp + m] = d;
 }
 
-// err = (sum of the row's tile partials, in tile order) / 2 (H = 2 X X^T); keep the candidate if it
-// is strictly better.
+// err = sum of the row's tile partials, in tile order (each is half of its part of d H d^T: H = 2 X X^T); keep the
+// candidate if it is strictly better.
 __global__ void keep_best_kernel(int M, int Mp, int n_bits, int ntile, int g, int grid, int first, Tying t,
                                  const float *__restrict__ part, const float *__restrict__ wmin,
                                  const float *__restrict__ wmax, float *__restrict__ best, float *__restrict__ S,
@@ -570,7 +417,6 @@ __global__ void keep_best_kernel(int M, int Mp, int n_bits, int ntile, int g, in
     if (m >= M) return;
     float e = 0.0f;
     for (int k = 0; k < ntile; ++k) e += part[(size_t)k * Mp + m];
-    e *= 0.5f;
     if (first || e < best[m]) {
         best[m] = e;
         S[m] = (float)grid_scale(wmin[m], wmax[m], n_bits, g, grid);
@@ -596,10 +442,9 @@ hipError_t launch_quant_search(int M, int N, int n_bits, int q, int grid, const 
         for (const Tying &t : tyings) {
             hipLaunchKernelGGL(delta_kernel, dim3((w.Mp + 255) / 256, N), dim3(256), 0, stream, M, w.Mp, N, n_bits, g,
                                grid, t, w.Wt, w.wmin, w.wmax, w.Dt);
-            // d H d^T row by row: sum_l Dt[l][m] sum_{k <= l} w_kl H[k][l] Dt[k][m], w = 2 off the diagonal
+            // d H d^T / 2 row by row: sum_l Dt[l][m] sum_{k <= l} w_kl H[k][l] Dt[k][m], w = 1/2 on the diagonal
             // (only the upper triangle of H is read), one partial per tile of 128 values of l
-            hipLaunchKernelGGL((mfma_kmajor_kernel<kQuadForm>), dim3((w.Mp + kTile - 1) / kTile, w.ntile), dim3(256), 0,
-                               stream, H, N, N, w.Dt, w.Mp, w.Mp, N, w.part, w.Mp, w.Dt);
+            launch_product<kQuadForm>(stream, w.Dt, w.Mp, w.Mp, H, N, N, N, w.part, w.Mp, w.Dt);
             hipLaunchKernelGGL(keep_best_kernel, dim3((M + 255) / 256), dim3(256), 0, stream, M, w.Mp, n_bits, w.ntile, g,
                                grid, first ? 1 : 0, t, w.part, w.wmin, w.wmax, w.best, S, qbias, labels);
             first = false;
@@ -694,9 +539,8 @@ hipError_t launch_quant_gptq(int M, int N, int n_bits, int q, const float *W, co
         hipLaunchKernelGGL(gptq_block_kernel, dim3((w.Mp + kGptqRows - 1) / kGptqRows), dim3(kGptqRows), 0, stream, M,
                            w.Mp, N, n_bits, q, c0, c1, w.Wt, U, S, qbias, labels, w_int, w.Err);
         if (c1 < N)  // Wt[k][m] -= sum_j U[c0 + j][k] Err[j][m] for the columns k >= c1
-            hipLaunchKernelGGL((mfma_kmajor_kernel<kSubtract>), dim3((w.Mp + kTile - 1) / kTile, (N - c1 + kTile - 1) / kTile),
-                               dim3(256), 0, stream, U + (size_t)c0 * N + c1, N, N - c1, w.Err, w.Mp, w.Mp, c1 - c0,
-                               w.Wt + (size_t)c1 * w.Mp, w.Mp, nullptr);
+            launch_product<kSubtract>(stream, U + (size_t)c0 * N + c1, N, N - c1, w.Err, w.Mp, w.Mp, c1 - c0,
+                                      w.Wt + (size_t)c1 * w.Mp, w.Mp);
     }
     return hipGetLastError();
 }

@@ -206,6 +206,42 @@ def test_hessian(N, T):
     assert np.array_equal(H_g, H_g.T)
 
 
+@pytest.mark.parametrize("N,T", [(4, 1), (132, 31), (124, 32), (516, 33), (260, 65), (1028, 16)])
+def test_hessian_tiles_and_scales(N, T):
+    """The split product at the edges of its tiles (128 columns, 32 samples, blocks of 4 x 4 tiles), with channels of very
+    different size, channels that are zero in the first samples and a channel that grows by 2^20 after them (both make a
+    tile choose its scales again), added to an H that is not symmetric.  Bound per element: three binary32 roundings per
+    16 samples, the dropped product of the two small halves and the final addition, each 2^-24 of sum |x_r x_c|; a value
+    far below its channel's largest is only held to 2^-27 of that one."""
+    rng = np.random.default_rng(N * 7 + T)
+    X = rng.standard_normal((T, N)).astype(np.float32)
+    X *= np.exp2(rng.integers(-40, 41, size=N)).astype(np.float32)
+    X[: (T + 1) // 2, rng.random(N) < 0.2] = 0.0
+    X[:, 1] = 0.0
+    X[:1, 2] *= np.float32(2.0 ** -20)
+    X[-1, 2] = np.float32(2.0 ** 20)
+    H0 = np.zeros((N, N), dtype=np.float32)
+    H0[0, 3] = 5.0
+    H = _dev(H0)
+    bcq.quant_hessian(N, T, _dev(X), H)
+    torch.cuda.synchronize()
+    X64 = X.astype(np.float64)
+    want = H0 + 2.0 * (X64.T @ X64)
+    big = np.abs(X64).max(axis=0)
+    size = 2.0 * (np.abs(X64).T @ np.abs(X64))
+    bound = (3 * ((T + 15) // 16) + 8) * 2.0 ** -24 * (size + np.abs(H0)) + 4.0 * T * 2.0 ** -27 * np.outer(big, big) * (T > 1)
+    got = H.cpu().numpy().astype(np.float64)
+    assert (np.abs(got - want) <= bound + 1e-44).all(), (np.abs(got - want) / (bound + 1e-44)).max()
+    assert np.array_equal(got[4:, 4:], got[4:, 4:].T)
+    # a channel that is not finite leaves every sum with it not finite and the others alone
+    X[T - 1, N - 1] = np.inf
+    H.zero_()
+    bcq.quant_hessian(N, T, _dev(X), H)
+    torch.cuda.synchronize()
+    bad = H.cpu().numpy()
+    assert not np.isfinite(bad[N - 1, N - 1]) and np.isfinite(bad[: N - 1, : N - 1]).all()
+
+
 @pytest.mark.parametrize("N", [64, 160, 384, 1000])
 def test_inverse_hessian_factor(N):
     """U with (H + 0.01 mean(diag H) I)^-1 = U^T U, U upper triangular, against the oracle's binary64 factor;
