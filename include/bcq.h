@@ -243,8 +243,7 @@ bcq_status bcq_gemv_noalloc(const bcq_desc *desc, const void *packed, const uint
  * Y[j][m] = sum_k W_q[m][k] X[j][k],  1 <= batch <= BCQ_MAX_BATCH (64): the fused form of Eq. 11 applied
  * to `batch` activation vectors at once (the paper measures batch 1 only, Sec. III "Speed up of GPTQT", and
  * names larger batches as the method's limitation, Sec. IV).  The weights are read once
- * per call with groups that are multiples of 128 (or N), and once per 16 batch columns with
- * groups of 32/64.
+ * per 16 to 64 batch columns, depending on the number of planes, the groups and the size of the layer.
  *   X   DEVICE, row j starts at X + j*ldx (elements), ldx >= N, ldx % 8 == 0
  *   Y   DEVICE, row j starts at Y + j*ldy (elements), ldy >= M
  *   workspace as for bcq_gemv with bcq_workspace_bytes(desc, batch)
@@ -268,14 +267,13 @@ bcq_status bcq_read_probe(const void *buf, size_t bytes, void *sink, void *strea
  * Launch-shape overrides for tuning runs (HOST state, process-wide, not
  * thread-safe).  Names: "workgroups" (grid size of the GEMV and of the skinny
  * kernel), "waves" (waves per workgroup, 4 or 8: the GEMV, the table kernel of
- * bcq_gemm_skinny up to 16 columns and its 32-column pass), "gemv_early" (1 = the GEMV
+ * bcq_gemm_skinny up to 16 columns; beyond them 8 = the kernel for large layers wherever it exists, 4 = never that one), "gemv_early" (1 = the GEMV
  * builds its tables before its first tile has arrived, 2 = never; automatic: when no wave has
  * more than one tile), "skinny_parts" (K
  * split of bcq_gemm_skinny for batch >= 2), "skinny_version" (1 = the kernel
  * that folds alpha into the matrix-core operand, 2 = the kernel that takes +-1
- * operands from an LDS table, with q = 4 at most 32 columns per pass; groups of
- * 32/64 always use 1; 3 = for batch 2..4 the kernel with sign-sum tables of four
- * vectors wherever it applies, 4 = never that one; 5 = for batch 2 the GEMV's table kernel
+ * operands from an LDS table, 16 columns per pass; groups of
+ * 32/64 always use 1; 3 and 4 = automatic; 5 = for batch 2 the GEMV's table kernel
  * with two vectors per table entry wherever it applies, 6 = never that one, the others chosen
  * automatically), "skinny_lds_steps" (3 or 4, kernel 2 only); 0 =
  * automatic.

@@ -154,7 +154,7 @@ __device__ __forceinline__ float sum_block_owners(float a0, float a1)
     return __uint_as_float(r0) + __uint_as_float(r1);
 }
 
-// Work split of the kernels that walk along K (bcq_skinny.hip, bcq_lut4.hip): `units` work items are cut into one
+// Work split of the kernels that walk along K (bcq_skinny.hip, bcq_wide.hip): `units` work items are cut into one
 // contiguous range per workgroup, of floor or ceil(units / workgroups) items.  Two ways to place the longer ranges:
 //
 // FRONT (kernels that run one workgroup per compute unit): the first `rem` = units mod workgroups of the workgroups
@@ -164,9 +164,7 @@ __device__ __forceinline__ float sum_block_owners(float a0, float a1)
 //
 // Otherwise the longer ranges are spread evenly over the workgroup numbers (range w = [floor(w units / groups),
 // floor((w + 1) units / groups))): with two workgroups per compute unit, numbers w and w + groups / 2 typically
-// share one, and the front placement would give some compute units two long ranges (4.6 us on a 45 us launch).  The
-// kernel of bcq_lut4.hip keeps the even spread too: its long ranges placed at the front lie next to each other in
-// memory and cost 2 to 3 us on layers with five or six items per workgroup.
+// share one, and the front placement would give some compute units two long ranges (4.6 us on a 45 us launch).
 //
 // First item of workgroup w, and the workgroup that owns item u.
 template <bool FRONT>

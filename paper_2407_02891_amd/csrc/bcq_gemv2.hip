@@ -16,8 +16,7 @@
 // makes the 16 lanes of a block read 16 different chunks at every step, so the 32 lanes of a half wave read 32
 // different 8-byte columns of a 256-byte bank row.
 //
-// More vectors do not fit this way (four would need 256 KB, or half slices and twice the atomics): see bcq_lut4.hip
-// and bcq_skinny.hip.
+// More vectors do not fit this way (four would need 256 KB, or half slices and twice the atomics): see bcq_skinny.hip.
 #include <atomic>
 
 #include "bcq_internal.h"

@@ -43,20 +43,16 @@ struct GemvTuning {
     int trace_groups = 0;   // tracing build, skinny kernel: workgroups that buffer has room for (8 waves each)
     int skinny_parts = 0;  // K split of the skinny kernel
     int skinny_version = 0;    // 1 = the first skinny kernel (alpha folded into A) also where the second applies,
-                               // 3 = the table kernel for up to four vectors where it applies, 4 = never that one,
+                               // 2 = the second (table) kernel, 16 columns per pass, 3 and 4 = automatic,
                                // 5 = the two-vector table kernel where it applies, 6 = never that one
     int skinny_lds_steps = 0;  // second skinny kernel: MFMA steps per block whose A operand comes from the
                                // LDS table, 3 or 4 (0 = automatic = 4)
 };
 hipError_t launch_gemv(const Geom &g, const void *packed, const uint16_t *x, uint16_t *y,
                        void *workspace, const GemvTuning &tuning, hipStream_t stream);
-// Single-pass kernel for 2 <= batch <= 16 (matrix cores); parts = K split, 0 = automatic.
+// 2 <= batch <= 64 (matrix cores, two-vector tables).
 hipError_t launch_skinny(const Geom &g, const void *packed, const uint16_t *X, int ldx, uint16_t *Y, int ldy,
                          int batch, void *workspace, const GemvTuning &tuning, hipStream_t stream);
-// Sign-sum tables holding four activation vectors side by side (bcq_lut4.hip): 2 <= batch <= 4.
-bool lut4_applies(const Geom &g, int batch, const void *workspace);
-hipError_t launch_lut4(const Geom &g, const void *packed, const uint16_t *X, int ldx, uint16_t *Y, int ldy, int batch,
-                       void *workspace, const GemvTuning &tuning, hipStream_t stream);
 // The GEMV's tables with both vectors of a two-vector call side by side (bcq_gemv2.hip): batch == 2.
 bool gemv2_applies(const Geom &g, int batch, const void *workspace);
 hipError_t launch_gemv2(const Geom &g, const void *packed, const uint16_t *X, int ldx, uint16_t *Y, int ldy,

@@ -45,25 +45,9 @@
 
 #include "bcq_internal.h"
 #include "bcq_device.h"
+#include "bcq_skinny.h"
 
 namespace bcq {
-
-struct SkinnyParams {
-    const uint8_t *blob;
-    const uint16_t *X;
-    uint16_t *Y;
-    unsigned long long *accum;  // [batch][Mp]
-    int M, N, Mp, batch, ldx, ldy;
-    int ntile, nslice, ntg;  // ntg = ceil(ntile / 4) tile groups (the four row tiles of a workgroup)
-    int units;               // ntg * nslice work units, cut into one contiguous range per workgroup:
-    int unit_base, unit_rem; // units div / mod the number of workgroups (first_unit, owner_of_unit in bcq_device.h)
-    unsigned tile_bytes;
-    int scale_lane_mask;     // 63: one scale record per lane; 15: one per row (group = N)
-#ifdef BCQ_TRACE
-    unsigned *trace;         // [workgroup][wave][kTraceSlots] time stamps (the tracing build only)
-    int trace_groups;        // workgroups the buffer has room for
-#endif
-};
 
 // Per-wave timeline for the tracing build (libbcq_trace.so, see trace_gemv.py): the 100 MHz real-time
 // counter at fixed points and the time spent in each part of a work unit, summed over the wave's units.
@@ -81,8 +65,6 @@ struct SkinnyParams {
 #define BCQ_SK_STAMP(i) ((void)0)
 #define BCQ_SK_PHASE(i) ((void)0)
 #endif
-
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 // Staged X in LDS: one row of 64 chunks (16 B each) per batch column, rows `pitch` bytes apart.  A
 // ds_read_b128 is served 16 lanes at a time -- lanes {0-3, 12-15, 20-23, 24-27}, {4-7, 8-11, 16-19,
@@ -142,47 +124,8 @@ __device__ __forceinline__ void x_slice_store(uint8_t *xs, int tid, const u32x4 
         const int pos = VER == 2 ? ((chunk & 48) | ((chunk & 3) << 2) | ((chunk >> 2) & 3)) : chunk;
         // VER 2: batch column h + 4 j of a group of 16 goes to row 4 h + j, so that the lanes 16 h + r of the (transposed)
         // MFMA result hold the columns h, h + 4, h + 8, h + 12: a flush instruction then covers four neighbouring columns
-        const int row = VER == 2 ? ((c & ~15) | ((c & 3) << 2) | ((c >> 2) & 3)) : c;
+        const int row = VER == 2 ? (((c & 3) << 2) | ((c >> 2) & 3)) : c;
         *reinterpret_cast<u32x4 *>(xs + row * kXPitch<VER> + pos * 16) = o;
-    }
-}
-
-// Undo the per-row byte permutation of the blob (chunk_of_byte): on return byte s of the
-// 128-bit value is chunk s.
-template <int SUB>
-__device__ __forceinline__ void unrotate(u32x4 &w, int r)
-{
-    if (SUB == 1) {
-        // chunk = (byte + r) mod 16: rotate the 128-bit ring left by r bytes, i.e. right by k = (16 - r) mod 16:
-        // byte j of the result is byte j + k of w.  Dword step first (two rounds of selects), then one
-        // v_alignbyte_b32 per dword for the k mod 4 bytes that cross dwords.
-        const int k = (16 - r) & 15;
-        const bool s1 = k & 4, s2 = k & 8;
-        const uint32_t b = k & 3;
-        uint32_t t0 = w.x, t1 = w.y, t2 = w.z, t3 = w.w;
-        const uint32_t u0 = s1 ? t1 : t0, u1 = s1 ? t2 : t1, u2 = s1 ? t3 : t2, u3 = s1 ? t0 : t3;
-        t0 = s2 ? u2 : u0; t1 = s2 ? u3 : u1; t2 = s2 ? u0 : u2; t3 = s2 ? u1 : u3;
-        w.x = __builtin_amdgcn_alignbyte(t1, t0, b);
-        w.y = __builtin_amdgcn_alignbyte(t2, t1, b);
-        w.z = __builtin_amdgcn_alignbyte(t3, t2, b);
-        w.w = __builtin_amdgcn_alignbyte(t0, t3, b);
-    } else if (SUB == 2) {  // rotate each 64-bit half left by r mod 8 bytes, swap the halves if r >= 8
-        unsigned long long lo = ((unsigned long long)w.y << 32) | w.x, hi = ((unsigned long long)w.w << 32) | w.z;
-        lo = __builtin_rotateleft64(lo, 8 * (r & 7));
-        hi = __builtin_rotateleft64(hi, 8 * (r & 7));
-        const unsigned long long a = (r & 8) ? hi : lo, b = (r & 8) ? lo : hi;
-        w.x = (uint32_t)a; w.y = (uint32_t)(a >> 32); w.z = (uint32_t)b; w.w = (uint32_t)(b >> 32);
-    } else {  // rotate each dword left by r mod 4 bytes, dword d goes to d xor (r div 4)
-        const unsigned sh = 8 * (r & 3);
-        uint32_t t0 = __builtin_rotateleft32(w.x, sh), t1 = __builtin_rotateleft32(w.y, sh);
-        uint32_t t2 = __builtin_rotateleft32(w.z, sh), t3 = __builtin_rotateleft32(w.w, sh);
-        // masked exchanges (written without selects so that they stay in registers)
-        const uint32_t m4 = (r & 4) ? 0xffffffffu : 0u, m8 = (r & 8) ? 0xffffffffu : 0u;
-        uint32_t d01 = (t0 ^ t1) & m4, d23 = (t2 ^ t3) & m4;
-        t0 ^= d01; t1 ^= d01; t2 ^= d23; t3 ^= d23;
-        uint32_t d02 = (t0 ^ t2) & m8, d13 = (t1 ^ t3) & m8;
-        t0 ^= d02; t2 ^= d02; t1 ^= d13; t3 ^= d13;
-        w.x = t0; w.y = t1; w.z = t2; w.w = t3;
     }
 }
 
@@ -227,19 +170,16 @@ __device__ __forceinline__ uint32_t scale_bits(const TileRegs<Q, Z, SUB> &t, int
 constexpr int kStagePitch = 33;
 constexpr int kStageFloats = 17 * kStagePitch + 15;  // 576
 
-template <int ROUND, bool TRANSPOSED>
+template <int ROUND>
 __device__ __forceinline__ void skinny_store(const SkinnyParams &p, const f32x4 (&acc)[2], int tile, int lane,
                                              float *stage, int arrivals, int col0)
 {
     const int r = lane & 15, h = lane >> 4;
-    // acc[t][i] is (row 16t + 4h + i, column r) of the tile, or with TRANSPOSED (row 16t + r, column h + 4i)
+    // acc[t][i] is (row 16t + 4h + i, column r) of the tile
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (TRANSPOSED) stage[(h + 4 * i) * kStagePitch + 16 * t + r] = acc[t][i];
-            else stage[r * kStagePitch + 16 * t + 4 * h + i] = acc[t][i];
-        }
+        for (int i = 0; i < 4; ++i) stage[r * kStagePitch + 16 * t + 4 * h + i] = acc[t][i];
     // same wave: its LDS operations complete in order, no barrier needed
     const int row = tile * kTileRows + (lane & 31), half = lane >> 5;
     float v[8];
@@ -279,43 +219,37 @@ __device__ __forceinline__ void skinny_store(const SkinnyParams &p, const f32x4 
     }
 }
 
-// The same for accumulators held transposed (the table kernel): acc[t][j] = (batch column col0 + h + 4j, row 16t + r)
+// The same for accumulators held transposed (the table kernel): acc[t][j] = (batch column h + 4j, row 16t + r)
 // of the tile, lane 16h + r.  No turn through LDS: an instruction's lanes cover 16 consecutive rows of four neighbouring
 // columns, and with few columns the instructions for j beyond them have no active lane.
-template <int ROUND>
 __device__ __forceinline__ void skinny_store_transposed(const SkinnyParams &p, const f32x4 (&acc)[2], int tile, int lane,
-                                                        int arrivals, int col0)
+                                                        int arrivals)
 {
     const int r = lane & 15, h = lane >> 4;
     if (arrivals == 1) {
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            const int col = col0 + h + 4 * (k & 3), row = tile * kTileRows + 16 * (k >> 2) + r;
+            const int col = h + 4 * (k & 3), row = tile * kTileRows + 16 * (k >> 2) + r;
             if (col < p.batch && row < p.M) p.Y[(size_t)col * p.ldy + row] = float_to_half_bits(acc[k >> 2][k & 3]);
         }
         return;
     }
+    unsigned long long mine[8], old[8];
 #pragma unroll
-    for (int k0 = 0; k0 < 8; k0 += ROUND) {
-        unsigned long long mine[ROUND], old[ROUND];
+    for (int k = 0; k < 8; ++k) {
+        const int col = h + 4 * (k & 3), row = tile * kTileRows + 16 * (k >> 2) + r;
+        mine[k] = encode_partial(acc[k >> 2][k & 3]);
+        old[k] = 0;
+        if (col < p.batch)
+            old[k] = __hip_atomic_fetch_add(p.accum + (size_t)col * p.Mp + row, mine[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 #pragma unroll
-        for (int k = 0; k < ROUND; ++k) {
-            const int col = col0 + h + 4 * ((k0 + k) & 3), row = tile * kTileRows + 16 * ((k0 + k) >> 2) + r;
-            mine[k] = encode_partial(acc[(k0 + k) >> 2][(k0 + k) & 3]);
-            old[k] = 0;
-            if (col < p.batch)
-                old[k] = __hip_atomic_fetch_add(p.accum + (size_t)col * p.Mp + row, mine[k], __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT);
-        }
-#pragma unroll
-        for (int k = 0; k < ROUND; ++k) {
-            const int col = col0 + h + 4 * ((k0 + k) & 3), row = tile * kTileRows + 16 * ((k0 + k) >> 2) + r;
-            const unsigned long long total = old[k] + mine[k];
-            if (col < p.batch && arrivals_of(total) == (unsigned)arrivals) {
-                if (row < p.M) p.Y[(size_t)col * p.ldy + row] = float_to_half_bits(decode_total(total));
-                __hip_atomic_store(p.accum + (size_t)col * p.Mp + row, 0ull, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            }
+    for (int k = 0; k < 8; ++k) {
+        const int col = h + 4 * (k & 3), row = tile * kTileRows + 16 * (k >> 2) + r;
+        const unsigned long long total = old[k] + mine[k];
+        if (col < p.batch && arrivals_of(total) == (unsigned)arrivals) {
+            if (row < p.M) p.Y[(size_t)col * p.ldy + row] = float_to_half_bits(decode_total(total));
+            __hip_atomic_store(p.accum + (size_t)col * p.Mp + row, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 }
@@ -407,34 +341,13 @@ __device__ __forceinline__ void compute_folded(TileRegs<Q, Z, SUB> &cur, const u
 // ---------------------------------------------------------------------------------
 // VER 2: lane transpose, +-1.0 operands from the LDS table, alpha applied to the accumulators
 // ---------------------------------------------------------------------------------
-// Sign table: entry b holds 8 binary16 values, pair d = (bit d, bit d + 4) of b, +1.0 for a set bit
-// (the element order the staged X uses); copy c of entry b sits at (TC b + c) * 16 and lane l reads copy
-// l mod TC.  With TC = 16 copies (64 KB) the 16 lanes that a ds_read_b128 serves together always read 16
-// different bank columns whatever their bytes are; with 8 copies (32 KB) two of them share a column and
-// collide unless their bytes are equal, which costs the table reads about half their rate.
-template <int TC> constexpr int kTabBytes = 256 * TC * 16;
-
-template <int NT, int TC>
-__device__ __forceinline__ void build_sign_table(uint8_t *tab, int tid)
-{
-#pragma unroll
-    for (int k = 0; k < 256 * TC / NT; ++k) {
-        const int idx = tid + NT * k, b = idx / TC;
-        u32x4 e;
-#pragma unroll
-        for (int d = 0; d < 4; ++d)
-            e[d] = (((b >> d) & 1) ? 0x3c00u : 0xbc00u) | ((((b >> (d + 4)) & 1) ? 0x3c00u : 0xbc00u) << 16);
-        *reinterpret_cast<u32x4 *>(tab + idx * 16) = e;
-    }
-}
-
 // `issue(g)` is called after the MFMAs of step g = 4 B + s (0..15): the kernel uses it to request the next
 // unit's tile and X slice a piece at a time.  Requested all at once at the top of a unit, the 8 waves of a
 // workgroup queue up behind each other in the CU's vector-memory pipeline (measured: up to 1.4 us per unit
 // for the wave that comes last, and everyone waits for it at the barrier).
-template <int Q, int Z, int LDS_STEPS, int NB, int TC, class Issue>
+template <int Q, int Z, int LDS_STEPS, int TC, class Issue>
 __device__ __forceinline__ void compute_table(const TileRegs<Q, Z, 1> &cur, const uint8_t *xs_buf, const uint8_t *tab,
-                                              uint32_t copy_bits, int r, int h, f32x4 (&acc)[NB][2], unsigned &t_operands,
+                                              uint32_t copy_bits, int r, int h, f32x4 (&acc)[2], unsigned &t_operands,
                                               Issue issue)
 {
     // chunk order, then the 4 x 4 dword transpose across the lanes r, r+16, r+32, r+48:
@@ -471,100 +384,102 @@ __device__ __forceinline__ void compute_table(const TileRegs<Q, Z, 1> &cur, cons
         const auto g23 = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);  // (2,2,2,2), (3,3,3,3)
         sc[0][e] = g01[0]; sc[1][e] = g01[1]; sc[2][e] = g23[0]; sc[3][e] = g23[1];
     }
-    // batch column 16 nb + r of the staged X sits in row 16 nb + r of the buffer
     const uint8_t *xb = xs_buf + r * kXPitch<2> + h * 16;
     const u32x4 ones = {0x3c003c00u, 0x3c003c00u, 0x3c003c00u, 0x3c003c00u};
-#pragma unroll
-    for (int B = 0; B < 4; ++B) {
-        f32x4 C[NB][2][Q];  // first written by the MFMAs of step 0, whose addend is the constant zero
-        f32x4 Cz[NB];
-        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-        // The +-1.0 operands of a step serve every group of 16 batch columns.  With four groups a
-        // wave runs alone on its SIMD (registers, LDS), so nothing else hides the LDS latency: the
-        // operands of step s+1 are requested before the MFMAs of step s are issued (with one or two
-        // groups two waves share a SIMD and the extra registers of that pipelining would cost one).
-        constexpr bool kPipelined = NB == 4;
-        auto fetch = [&](int s, f16x8 (&a)[2][Q], f16x8 (&bx)[NB]) {
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int i = 0; i < Q; ++i) {
-                    const uint32_t w = wb[t][i][B];
-                    if (s < LDS_STEPS) {
-                        if constexpr (TC == 16) {
-                            // 256 bytes per entry: byte s of w becomes byte 1 of the offset, the lane's copy
-                            // (bits 4..7) byte 0 -- one v_perm_b32 per look-up
-                            const uint32_t off = __builtin_amdgcn_perm(w, copy_bits, 0x0c0c0400u | ((uint32_t)s << 8));
-                            a[t][i] = *reinterpret_cast<const f16x8 *>(tab + off);
-                        } else {
-                            const uint32_t byte = (w >> (8 * s)) & 0xffu;
-                            a[t][i] = *reinterpret_cast<const f16x8 *>(tab + copy_bits + byte * (16 * TC));
-                        }
-                    } else {
-                        const uint32_t wn = ~w, wn4 = wn >> 4;
-                        if (s == 0) a[t][i] = expand_byte<0>(wn, wn4, 0x3c003c00u);
-                        if (s == 1) a[t][i] = expand_byte<1>(wn, wn4, 0x3c003c00u);
-                        if (s == 2) a[t][i] = expand_byte<2>(wn, wn4, 0x3c003c00u);
-                        if (s == 3) a[t][i] = expand_byte<3>(wn, wn4, 0x3c003c00u);
-                    }
-                }
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-                bx[nb] = *reinterpret_cast<const f16x8 *>(xb + nb * kXBuf<2> + (16 * B + 4 * s) * 16);
-        };
-        f16x8 abuf[2][2][Q], bbuf[2][NB];
-        fetch(0, abuf[0], bbuf[0]);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int cb = s & 1;
-            if (kPipelined) {
-                if (s + 1 < 4) fetch(s + 1, abuf[cb ^ 1], bbuf[cb ^ 1]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-#pragma unroll
-                for (int t = 0; t < 2; ++t)
-#pragma unroll
-                    for (int i = 0; i < Q; ++i)
-                        C[nb][t][i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bbuf[cb][nb], abuf[cb][t][i],
-                                                                             s == 0 ? zero : C[nb][t][i], 0, 0, 0);
-                if (Z)
-                    Cz[nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bbuf[cb][nb], __builtin_bit_cast(f16x8, ones),
-                                                                    s == 0 ? zero : Cz[nb], 0, 0, 0);
-            }
-            if (kPipelined) __builtin_amdgcn_sched_barrier(0);
-            else if (s + 1 < 4) fetch(s + 1, abuf[cb ^ 1], bbuf[cb ^ 1]);  // left to the compiler's schedule
-            issue(4 * B + s);
-        }
-        // acc[nb][t][j] (batch column 16 nb + h + 4j, row 16t + r) += alpha_i(row, block B) * C[nb][t][i][j]  (+ z * column sums)
+    // The 16 steps of a unit form one pipeline: the
+    // operands of step g + kAhead are requested before the MFMAs of step g are issued (a fence per step keeps the compiler
+    // from moving the requests down to their use, which left one MFMA to cover each LDS access), and the sums of a block
+    // are scaled while the next block's first steps run.  Measured (q = 3, 16 columns): 7168 x 28672 33.7 -> 32.3 us,
+    // 28672 x 8192 37.0 -> 35.5, 2048 x 4096 8.5 -> 8.0.  Where two sets of block sums do not fit the registers (four planes) a
+    // block is scaled at its end and the schedule is the compiler's.
+    auto fetch = [&](int g, f16x8 (&a)[2][Q], f16x8 &bx) {
+        const int B = g >> 2, s = g & 3;
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int c = 0; c < Q + Z; ++c) {
-                const int e = t * (Q + Z) + c;  // half index in the scale record
-                const uint32_t pair = sc[B][e >> 1];
-                const float v = half_bits_to_float((e & 1) ? (pair >> 16) : (pair & 0xffffu));
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-                        acc[nb][t][j] = fmaf(v, c < Q ? C[nb][t][c < Q ? c : 0][j] : Cz[nb][j], acc[nb][t][j]);
+            for (int i = 0; i < Q; ++i) {
+                const uint32_t w = wb[t][i][B];
+                if (s < LDS_STEPS) {
+                    if constexpr (TC == 16) {
+                        // 256 bytes per entry: byte s of w becomes byte 1 of the offset, the lane's copy
+                        // (bits 4..7) byte 0 -- one v_perm_b32 per look-up
+                        const uint32_t off = __builtin_amdgcn_perm(w, copy_bits, 0x0c0c0400u | ((uint32_t)s << 8));
+                        a[t][i] = *reinterpret_cast<const f16x8 *>(tab + off);
+                    } else {
+                        const uint32_t byte = (w >> (8 * s)) & 0xffu;
+                        a[t][i] = *reinterpret_cast<const f16x8 *>(tab + copy_bits + byte * (16 * TC));
+                    }
+                } else {
+                    const uint32_t wn = ~w, wn4 = wn >> 4;
+                    if (s == 0) a[t][i] = expand_byte<0>(wn, wn4, 0x3c003c00u);
+                    if (s == 1) a[t][i] = expand_byte<1>(wn, wn4, 0x3c003c00u);
+                    if (s == 2) a[t][i] = expand_byte<2>(wn, wn4, 0x3c003c00u);
+                    if (s == 3) a[t][i] = expand_byte<3>(wn, wn4, 0x3c003c00u);
+                }
             }
+        bx = *reinterpret_cast<const f16x8 *>(xb + (16 * B + 4 * s) * 16);
+    };
+    constexpr bool kDeferred = Q <= 3;  // registers: two sets of block sums, three of operands
+    constexpr int kAhead = kDeferred && Q + Z <= 3 ? 2 : 1;
+    constexpr int kBufs = kAhead + 1, kSums = kDeferred ? 2 : 1;
+    f16x8 abuf[kBufs][2][Q], bbuf[kBufs];
+    f32x4 C[kSums][2][Q];  // first written by the MFMAs of a block's step 0, whose addend is the constant zero
+    f32x4 Cz[kSums];
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    // acc[t][j] (batch column h + 4j, row 16t + r) += alpha_i(row, block B) * C[t][i][j]  (+ z * column sums)
+    auto apply = [&](int B, int t) {
+#pragma unroll
+        for (int c = 0; c < Q + Z; ++c) {
+            const int e = t * (Q + Z) + c;  // half index in the scale record
+            const uint32_t pair = sc[B][e >> 1];
+            const float v = half_bits_to_float((e & 1) ? (pair >> 16) : (pair & 0xffffu));
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                acc[t][j] = fmaf(v, c < Q ? C[B % kSums][t][c < Q ? c : 0][j] : Cz[B % kSums][j], acc[t][j]);
+        }
+    };
+#pragma unroll
+    for (int g = 0; g < kAhead; ++g) fetch(g, abuf[g], bbuf[g]);
+#pragma unroll
+    for (int g = 0; g < 16; ++g) {
+        const int B = g >> 2, s = g & 3, cb = g % kBufs;
+        if (kDeferred) __builtin_amdgcn_sched_barrier(0);
+        if (g + kAhead < 16) fetch(g + kAhead, abuf[(g + kAhead) % kBufs], bbuf[(g + kAhead) % kBufs]);
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int i = 0; i < Q; ++i)
+                C[B % kSums][t][i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bbuf[cb], abuf[cb][t][i],
+                                                                           s == 0 ? zero : C[B % kSums][t][i], 0, 0, 0);
+        if (Z)
+            Cz[B % kSums] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bbuf[cb], __builtin_bit_cast(f16x8, ones),
+                                                                  s == 0 ? zero : Cz[B % kSums], 0, 0, 0);
+        issue(g);
+        if (kDeferred) {
+            if (B > 0 && s < 2) apply(B - 1, s);
+        } else if (s == 3) {
+            apply(B, 0);
+            apply(B, 1);
+        }
+    }
+    if (kDeferred) {
+        __builtin_amdgcn_sched_barrier(0);
+        apply(3, 0);
+        apply(3, 1);
     }
 }
 
 // ---------------------------------------------------------------------------------
 // the kernel
 // ---------------------------------------------------------------------------------
-// NB = groups of 16 batch columns (1, 2 or 4; with VER 1 or VER 2).  With one group the
+// NB = groups of 16 batch columns (1, 2 or 4 with VER 1, one with VER 2).  With one group the
 // X slice is double-buffered in LDS; with more, the staged slice (16.6 KB per group) is single-
 // buffered: the next slice waits in registers and replaces it between two barriers.
 template <int Q, int Z, int SUB, int VER, int LDS_STEPS, int NB, int NW>
 __global__ __launch_bounds__(64 * NW) void bcq_skinny_kernel(SkinnyParams p)
 {
     constexpr int NT = 64 * NW;
-    static_assert(VER == 1 || SUB == 1, "the table kernel needs one scaling group per block");
+    static_assert(VER == 1 || (SUB == 1 && NB == 1), "the table kernel: one scaling group per block, 16 columns");
     // Eight waves: registers allow one workgroup per CU (two waves per SIMD from q = 2 on), which leaves
     // room for 16 table copies and two X buffers.
     constexpr bool kDouble = NB == 1;
@@ -572,7 +487,7 @@ __global__ __launch_bounds__(64 * NW) void bcq_skinny_kernel(SkinnyParams p)
     constexpr int kBuf = NB * kXBuf<VER>;
     __shared__ __attribute__((aligned(16))) uint8_t xs[(kDouble ? 2 : 1) * kBuf];
     __shared__ __attribute__((aligned(16))) uint8_t tab[VER == 2 ? kTabBytes<TC> : 16];
-    __shared__ float stage[VER == 2 && NB < 4 ? 1 : NW * kStageFloats];  // (the direct flush does not turn its results through LDS)
+    __shared__ float stage[VER == 2 ? 1 : NW * kStageFloats];  // (the direct flush does not turn its results through LDS)
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: tile pointers stay in SGPRs
@@ -661,7 +576,7 @@ __global__ __launch_bounds__(64 * NW) void bcq_skinny_kernel(SkinnyParams p)
                 if constexpr (VER == 1) compute_folded<Q, Z, SUB, NB>(cur, xs + buf * kBuf, r, h, acc);
                 else {
                     unsigned t_operands = 0;
-                    compute_table<Q, Z, LDS_STEPS, NB, TC>(cur, xs + buf * kBuf, tab, copy_bits, r, h, acc, t_operands, issue);
+                    compute_table<Q, Z, LDS_STEPS, TC>(cur, xs + buf * kBuf, tab, copy_bits, r, h, acc[0], t_operands, issue);
 #ifdef BCQ_TRACE
                     ts[8] += t_operands - last;  // next unit's loads issued, this tile arrived, un-rotated and transposed
                     last = t_operands;
@@ -691,11 +606,10 @@ __global__ __launch_bounds__(64 * NW) void bcq_skinny_kernel(SkinnyParams p)
             asm volatile("" : "+v"(flush_lane));
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
-                // (four column groups: the kernel has no scalar registers left for the direct form's column tests)
-                if constexpr (VER == 2 && NB < 4)
-                    skinny_store_transposed<NB == 1 ? 8 : 4>(p, acc[nb], seg_tile, flush_lane, arrivals, 16 * nb);
+                if constexpr (VER == 2)
+                    skinny_store_transposed(p, acc[nb], seg_tile, flush_lane, arrivals);
                 else
-                    skinny_store<NB == 1 ? 8 : 4, VER == 2>(p, acc[nb], seg_tile, flush_lane, stage + wave * kStageFloats, arrivals, 16 * nb);
+                    skinny_store<NB == 1 ? 8 : 4>(p, acc[nb], seg_tile, flush_lane, stage + wave * kStageFloats, arrivals, 16 * nb);
             }
         }
     }
@@ -763,29 +677,15 @@ static hipError_t launch_skinny_qz(const SkinnyParams &p, int nb, int parts, boo
 {
     if (sub == 2) return launch_skinny_one<Q, Z, 2, 1, 0, 1>(p, parts, single_slice, stream);
     if (sub == 4) return launch_skinny_one<Q, Z, 4, 1, 0, 1>(p, parts, single_slice, stream);
-    // Which kernel (measured on 7168 x 28672, q = 3, eager launches): up to 16 columns the table kernel (42 against
-    // 55 us for the kernel that folds alpha into A); 17 to 32 columns the table kernel with two column groups and
-    // eight waves where it exists (60 against 70 us), else the alpha-folding kernel; beyond 32 columns the alpha-folding
-    // kernel (118 against 126 us at 64): its expansion is shared by the column groups like the table kernel's, it
-    // needs no per-block accumulators, and the table kernel with four column groups has four waves and 8 table
-    // copies only.
+    // Up to 16 columns the table kernel (7168 x 28672, q = 3: 42 against 55 us for the kernel that folds alpha into A,
+    // eager launches); more columns come here only on layers too small for bcq_wide.hip and take the alpha-folding kernel,
+    // whose expansion is shared by the column groups and which starts without a 64 KB table.
     const long long tiles = (long long)p.ntile * p.nslice;
-    const bool table2 = nb == 2 && Q <= 3 && (waves == 8 || (waves == 0 && tiles >= 2048));
-    if (version == 1 || (version == 0 && nb > 1 && !table2)) {
+    if (version == 1 || nb > 1) {
         if (nb == 4) return launch_skinny_one<Q, Z, 1, 1, 0, 4>(p, parts, single_slice, stream);
-        // 32 columns: eight waves per workgroup from 4096 tiles on (63 against 73 us on 7168 x 28672)
-        if (nb == 2 && (waves == 8 || (waves == 0 && tiles >= 4096)))
-            return launch_skinny_one<Q, Z, 1, 1, 0, 2, 8>(p, parts, single_slice, stream);
         if (nb == 2) return launch_skinny_one<Q, Z, 1, 1, 0, 2>(p, parts, single_slice, stream);
         return launch_skinny_one<Q, Z, 1, 1, 0, 1>(p, parts, single_slice, stream);
     }
-    if constexpr (Q <= 3) {  // with four planes, four column groups do not fit the table kernel's register budget
-        if (nb == 4) return launch_skinny_one<Q, Z, 1, 2, 4, 4>(p, parts, single_slice, stream);
-    }
-    if constexpr (Q <= 3) {  // four planes exceed 256 registers with two column groups and eight waves
-        if (table2) return launch_skinny_one<Q, Z, 1, 2, 4, 2, 8>(p, parts, single_slice, stream);
-    }
-    if (nb == 2) return launch_skinny_one<Q, Z, 1, 2, 4, 2>(p, parts, single_slice, stream);
     // all four MFMA steps of a block from the LDS table measured fastest; 3 (one step expanded in
     // registers) is kept as the alternative for tuning runs
     // Eight waves per workgroup (eight row tiles share one staged slice of X; one workgroup per CU, which
@@ -802,12 +702,6 @@ static hipError_t launch_skinny_qz(const SkinnyParams &p, int nb, int parts, boo
 hipError_t launch_skinny(const Geom &g, const void *packed, const uint16_t *X, int ldx, uint16_t *Y, int ldy,
                          int batch, void *workspace, const GemvTuning &tuning, hipStream_t stream)
 {
-    // Up to four vectors, three or four planes, large layers: sign-sum tables with the four sums side by side
-    // (bcq_lut4.hip).  Measured against the matrix-core kernel, q = 3, batch 2 / 4: 7168 x 28672 31.2 / 32.8 against
-    // 32.4 / 31.8 us, 28672 x 8192 33.2 / 35.5 against 37.4 / 33.7, 36864 x 9216 42.6 / 44.6 against 49.3 / 46.0,
-    // 9216 x 36864 41.9 / 44.5 against 49.4 / 45.9: with two vectors it wins from about 12000 tiles on, with three or
-    // four only on the largest layers; it loses on smaller ones (9216 x 9216: 21.3 / 24.1 against 18.3 / 18.2) and
-    // with one or two planes (its table builds and barriers do not shrink with q).
     const long long all_tiles = (long long)g.ntile * g.nslice;
     // Two vectors: the GEMV's decomposition with both vectors' sign sums in one table entry (bcq_gemv2.hip).  Measured
     // against the best of the kernels below, q = 3: 7168 x 28672 23.6 against 32.4 us, 28672 x 7168 22.5 / 32.1,
@@ -816,12 +710,8 @@ hipError_t launch_skinny(const Geom &g, const void *packed, const uint16_t *X, i
     if (gemv2_applies(g, batch, workspace) &&
         (tuning.skinny_version == 5 || (tuning.skinny_version == 0 && all_tiles >= 2048)))
         return launch_gemv2(g, packed, X, ldx, Y, ldy, workspace, tuning, stream);
-    // (versions 5 and 6 only switch the two-vector kernel on and off: automatic choice among the others)
-    const int version = tuning.skinny_version >= 5 ? 0 : tuning.skinny_version;
-    if (lut4_applies(g, batch, workspace) &&
-        (version == 3 ||
-         (version == 0 && g.q >= 3 && all_tiles >= (batch == 2 ? 12288 : 18432))))
-        return launch_lut4(g, packed, X, ldx, Y, ldy, batch, workspace, tuning, stream);
+    // (versions 3 to 6 only choose among the kernels for two to four vectors: automatic choice among the others)
+    const int version = tuning.skinny_version >= 3 ? 0 : tuning.skinny_version;
     SkinnyParams p;
     p.blob = static_cast<const uint8_t *>(packed);
     p.M = g.M; p.N = g.N; p.Mp = g.Mp; p.ldx = ldx; p.ldy = ldy;
@@ -836,17 +726,31 @@ hipError_t launch_skinny(const Geom &g, const void *packed, const uint16_t *X, i
     const int parts = tuning.skinny_parts > 0 ? tuning.skinny_parts : -tuning.workgroups;
     const bool single = workspace == nullptr;  // only reachable for a single column slice
     const int sub = g.sub, ver = version, steps = tuning.skinny_lds_steps;
-    // Up to 64 batch columns in one pass over the weights (the expanded operands are shared by the
-    // groups of 16 columns); with several scaling groups per block one pass per 16 columns.
-    const bool wide_ok = sub == 1;
-    const int widest = (g.q <= 3 || ver != 2) ? 64 : 32;
-    const int cols_per_launch = wide_ok ? (batch > 32 ? widest : batch > 16 ? 32 : 16) : 16;
-    for (int col0 = 0; col0 < batch; col0 += cols_per_launch) {
-        const int cols = batch - col0 < cols_per_launch ? batch - col0 : cols_per_launch;
+    // From 17 columns on bcq_wide.hip, in equal passes of at most wide_columns().  Measured against the kernels here (us,
+    // theirs first): 28672 x 8192 q = 3, 64 columns 110 / 80, 32 columns 51 / 46; 7168 x 28672 64 columns 102 / 80; 5000 x
+    // 7232 q = 2 groups of 64, 27 columns 28.9 / 19.8; 2048 x 2048 q = 1, 45 columns 13.6 / 11.1; 512 x 8192, 64 columns
+    // 19.8 / 17.5.  It loses where there is one column slice (half of its waves idle: 8192 x 512, 64 columns 10.4 / 12.9),
+    // on a handful of tiles (512 x 512, 32 columns 7.3 / 8.2: its start-up) and where it needs more passes on a layer
+    // whose weights are not what is waited for (four planes, 64 columns: 4096 x 4096 26.9 / 31.8, 7168 x 28672 131 / 126).
+    const int most = wide_columns(g);
+    const bool one_pass = batch <= most || all_tiles >= 8192 || sub > 1;
+    const bool wide = most > 16 && ver == 0 && (tuning.waves == 8 || (tuning.waves == 0 && g.nslice > 1 && all_tiles >= 128 && one_pass));
+    // The kernels here: up to 64 columns in one pass with alpha folded into A and one scaling group per block, else 16.
+    const int narrow = sub == 1 && ver != 2 ? (batch > 32 ? 64 : batch > 16 ? 32 : 16) : 16;
+    for (int col0 = 0; col0 < batch;) {
+        const int left = batch - col0, passes = (left + most - 1) / (most > 0 ? most : 1);
+        int cols = left < narrow ? left : narrow;
+        if (wide && left > 16) cols = passes == 1 ? left : (left + 16 * passes - 1) / (16 * passes) * 16;
         p.X = X + (size_t)col0 * ldx;
         p.Y = Y + (size_t)col0 * ldy;
         p.accum = static_cast<unsigned long long *>(workspace) + (workspace ? (size_t)col0 * g.Mp : 0);
         p.batch = cols;
+        col0 += cols;
+        if (wide && cols > 16) {
+            const hipError_t e = launch_wide(g, p, tuning, stream);
+            if (e != hipSuccess) return e;
+            continue;
+        }
         const int nb = cols > 32 ? 4 : cols > 16 ? 2 : 1;
         hipError_t e = hipErrorInvalidValue;
         switch (g.q * 2 + g.z) {

@@ -525,6 +525,45 @@ def test_wide_batches(batch, q, offset, group, version):
         bcq.set_option("skinny_version", 0)
 
 
+@pytest.mark.parametrize("workgroups", [0, 1, 5, 50])
+@pytest.mark.parametrize("M,N,q,offset,group,batch", [
+    (128, 1024, 3, False, 128, 64),     # one row group, one pair of slices, four column groups
+    (129, 1536, 3, True, 128, 33),      # a row group with one row, an odd number of slices, three column groups
+    (1, 512, 2, False, 128, 17),        # a single tile and slice: half of the waves have nothing
+    (300, 2592, 3, True, 2592, 50),     # row-wise scales, columns that end inside a block (whose scales are not zero)
+    (127, 4128, 2, True, 32, 48),       # groups of 32, columns that end inside a block
+    (260, 3136, 3, False, 64, 49),      # groups of 64, two passes
+    (70, 1056, 1, True, 32, 64),
+    (203, 2048, 4, True, 128, 40),      # four planes: two passes, the second on the kernel for 16 columns
+    (96, 1152, 4, False, 64, 18),
+    (64, 2048, 4, True, 32, 20),        # does not fit this kernel's registers: the others take it
+])
+def test_wide_kernel_edges(workgroups, M, N, q, offset, group, batch):
+    """17..64 vectors on large layers (bcq_wide.hip), forced on small ones: bit for bit the oracle's result on exact inputs,
+    twice in a row, any split over K and over row groups, padded rows of X and Y, workspace left zero; then the gate on
+    random inputs with outlier channels."""
+    try:
+        bcq.set_option("waves", 8)
+        bcq.set_option("workgroups", workgroups)
+        L = bcq_synth.make_exact_layer(M, N, q, group=group, offset=offset, batch=batch, seed=M + q + batch)
+        pl = U.upload_and_pack(L, max_batch=batch)
+        expect = ref.gemm(L.planes, L.alpha, L.offset, L.x).astype(np.float16).astype(np.float64)
+        X = torch.full((batch, N + 40), 7.0, dtype=torch.float16, device="cuda")
+        X[:, :N] = U.x_dev(L)
+        Y = torch.full((batch, M + 10), 3.0, dtype=torch.float16, device="cuda")
+        for _ in range(2):
+            Y[:, :M] = 0.0
+            bcq.gemm_skinny(pl.desc, pl.packed, X, X.stride(0), Y, Y.stride(0), batch, pl.workspace if pl.workspace_bytes else None)
+            torch.cuda.synchronize()
+            assert np.array_equal(Y[:, :M].cpu().numpy().astype(np.float64), expect)
+            assert torch.all(Y[:, M:] == 3.0)
+            assert not pl.workspace.cpu().numpy().any()
+        _run_case(M, N, q, group, offset, batch=batch, seed=M + workgroups, outlier_frac=0.01)
+    finally:
+        bcq.set_option("workgroups", 0)
+        bcq.set_option("waves", 0)
+
+
 def test_wide_batch_exact_and_strided():
     L = bcq_synth.make_exact_layer(150, 3072, 3, group=128, offset=True, batch=40, seed=77)
     pl = U.upload_and_pack(L, max_batch=40)
