@@ -2,7 +2,7 @@
 // ends with n-bit linear integers W_int, a scale S and a bias qbias per scaling group, and a
 // choice of which linear bit-planes are tied together (Sec. II-B, Eq. 6; Sec. II-D, Eq. 8-11).
 // This turns them into the operands of Eq. 11 -- per-weight plane codes, fused alpha_hat,
-// fused offset -- i.e. exactly what bcq_pack consumes.  Offline step; written for clarity.
+// fused offset -- i.e. exactly what bcq_pack consumes.  Bound: memory.
 //
 //   Eq. 9   W_int = sum_{i=1..n} 2^(i-2) b_i + (2^n - 1)/2,  b_i = +1 iff bit i-1 of W_int is set
 //   Eq. 10  tying the planes of a class c to one sign gives alpha_hat_c = sum_{i in c} 2^(i-2);
@@ -21,13 +21,31 @@ struct ConvertPlan {
     double centre;  // (2^n - 1) / 2
 };
 
-__global__ void from_linear_codes_kernel(ConvertPlan plan, const uint8_t *__restrict__ w_int,
-                                         uint8_t *__restrict__ codes, size_t total)
+// Code of every n-bit integer under one tying (Eq. 6), worked out on the host.
+struct CodeTable {
+    uint8_t code[1 << kMaxBits];
+};
+
+// A thread maps 16 integers (WIDE: both pointers on 16 bytes; the last thread of the array the rest one by one), through a
+// table in LDS: one look-up per weight instead of a scan of the representable set.
+template <bool WIDE>
+__global__ __launch_bounds__(256) void from_linear_codes_kernel(CodeTable table, uint32_t mask, const uint8_t *__restrict__ w_int,
+                                                                uint8_t *__restrict__ codes, size_t total)
 {
-    size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= total) return;
-    const int w = w_int[gid] & ((1 << plan.n_bits) - 1);
-    codes[gid] = code_of(nearest_choice(w, plan.tying.choice, plan.tying.nchoice), plan.tying, plan.q);  // Eq. 6
+    __shared__ uint8_t lut[1 << kMaxBits];
+    lut[threadIdx.x] = table.code[threadIdx.x];
+    __syncthreads();
+    const size_t at = ((size_t)blockIdx.x * 256 + threadIdx.x) * 16;
+    if (at >= total) return;
+    if (WIDE && at + 16 <= total) {
+        const uint4 w = *reinterpret_cast<const uint4 *>(w_int + at);
+        uint4 c;
+        c.x = map_codes(lut, w.x, mask); c.y = map_codes(lut, w.y, mask);
+        c.z = map_codes(lut, w.z, mask); c.w = map_codes(lut, w.w, mask);
+        *reinterpret_cast<uint4 *>(codes + at) = c;
+    } else {
+        for (size_t k = at; k < at + 16 && k < total; ++k) codes[k] = lut[w_int[k] & (mask & 0xffu)];
+    }
 }
 
 __global__ void from_linear_scales_kernel(ConvertPlan plan, const float *__restrict__ S,
@@ -60,8 +78,13 @@ hipError_t launch_from_linear(int M, int N, int group, int n_bits, int q, const 
     ConvertPlan plan;
     if (!make_convert_plan(n_bits, q, class_of_plane, &plan)) return hipErrorInvalidValue;
     const size_t nw = (size_t)M * N, ng = (size_t)M * (N / group);
-    hipLaunchKernelGGL(from_linear_codes_kernel, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, stream, plan,
-                       w_int, codes, nw);
+    CodeTable table = {};
+    for (int w = 0; w < 1 << n_bits; ++w)
+        table.code[w] = code_of(nearest_choice(w, plan.tying.choice, plan.tying.nchoice), plan.tying, q);  // Eq. 6
+    const uint32_t mask = ((1u << n_bits) - 1u) * 0x01010101u;
+    const bool wide = ((reinterpret_cast<uintptr_t>(w_int) | reinterpret_cast<uintptr_t>(codes)) & 15) == 0;
+    hipLaunchKernelGGL((wide ? from_linear_codes_kernel<true> : from_linear_codes_kernel<false>),
+                       dim3((unsigned)((nw + 4095) / 4096)), dim3(256), 0, stream, table, mask, w_int, codes, nw);
     hipLaunchKernelGGL(from_linear_scales_kernel, dim3((unsigned)((ng + 255) / 256)), dim3(256), 0, stream, plan,
                        S, qbias, alpha, offset, ng);
     return hipGetLastError();

@@ -1,6 +1,6 @@
 // bcq_pack / bcq_unpack kernels: canonical operands of Eq. 11 (per-weight codes,
 // alpha[M][G][q], offset[M][G]) <-> the tiled blob described in bcq_layout.h.
-// Offline step; written for clarity, not speed.
+// Packing runs at the rate of memory (see pack_tile_kernel); unpacking is written for clarity.
 #include "bcq_internal.h"
 
 namespace bcq {
@@ -12,65 +12,73 @@ __device__ __forceinline__ bool row_is_mine(const Geom &g, int row, int row0, in
     return row >= row0 && (row < row0 + rows || (row >= g.M && row0 + rows == g.M));
 }
 
-__global__ void pack_planes_kernel(Geom g, int row0, int rows, const uint8_t *__restrict__ codes,
-                                   uint8_t *__restrict__ blob, size_t total_dwords)
+// Eight codes (a byte each) -> the eight bits of plane i, lowest column in bit 0.  Four bytes at a time: the product moves
+// bit 8 b of t to bit 24 + b, and nothing else reaches bits 24..27.
+__device__ __forceinline__ uint32_t plane_byte(uint32_t lo, uint32_t hi, int i)
 {
-    size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= total_dwords) return;
-    const unsigned dwords_per_tile = g.tile_plane_bytes / 4;
-    size_t tile_lin = gid / dwords_per_tile;
-    unsigned rem = (unsigned)(gid % dwords_per_tile);
-    int slice = (int)(tile_lin / g.ntile), tile = (int)(tile_lin % g.ntile);
-    int d = rem & 3, lane = (rem >> 2) & 63, ti = rem >> 8;
-    int t = ti / g.q, i = ti % g.q;
-    int r = lane & 15, h = lane >> 4;
-    int row = kTileRows * tile + 16 * t + r;
-    int kb = 4 * slice + h;
-    if (!row_is_mine(g, row, row0, rows)) return;
-    uint32_t word = 0;
-    if (row < g.M) {
-        for (int n = 0; n < 4; ++n) {
-            int j = 4 * d + n;
-            int c = chunk_of_byte(j, r, g.sub);
-            int col = kBlockCols * kb + kChunkCols * c;
-            if (col < g.N) {
-                const uint8_t *src = codes + (size_t)(row - row0) * g.N + col;
-                for (int b = 0; b < 8; ++b)
-                    word |= (uint32_t)((src[b] >> i) & 1) << (8 * n + b);
-            }
-        }
-    }
-    uint32_t *dst = reinterpret_cast<uint32_t *>(blob + tile_offset(g, slice, tile) +
-                                                 ((size_t)(ti * 64 + lane) * 16 + 4 * d));
-    *dst = word;
+    const uint32_t t = (lo >> i) & 0x01010101u, u = (hi >> i) & 0x01010101u;
+    return ((t * 0x01020408u) >> 24) | (((u * 0x01020408u) >> 20) & 0xf0u);
 }
 
-__global__ void pack_scales_kernel(Geom g, int row0, int rows, const uint16_t *__restrict__ alpha,
-                                   const uint16_t *__restrict__ offset,
-                                   uint8_t *__restrict__ blob, size_t total_entries)
+// One workgroup per tile of 32 rows x 512 columns: a thread owns one dword (four chunks of 8 columns) of a lane in every
+// plane, so the codes are read once whatever the number of planes, in 8-byte loads that cover whole 512-byte row segments
+// (ALIGNED: `codes` on 8 bytes; rows are multiples of 32 bytes), and then one scale entry at a time.  Bound: memory.  28672
+// x 7168, two planes with offset, one group per row: 117 us (a thread per dword and plane with byte loads, and a launch for
+// the scales) -> 76 us, 257 MB.
+template <bool ALIGNED>
+__global__ __launch_bounds__(256) void pack_tile_kernel(Geom g, int row0, int rows, const uint8_t *__restrict__ codes,
+                                                        const uint16_t *__restrict__ alpha,
+                                                        const uint16_t *__restrict__ offset, uint8_t *__restrict__ blob)
 {
-    size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= total_entries) return;
-    const unsigned per_tile = (unsigned)g.scale_lanes * 2u * g.nsc;  // with 16 records per half tile, `lane` below is the row
-    size_t tile_lin = gid / per_tile;
-    unsigned e = (unsigned)(gid % per_tile);
-    int slice = (int)(tile_lin / g.ntile), tile = (int)(tile_lin % g.ntile);
-    int lane = e / (2 * g.nsc), rr = e % (2 * g.nsc);
-    int t = rr / g.nsc, sc = rr % g.nsc;
-    int qz = g.q + g.z;
-    int range = sc / qz, c = sc % qz;
-    int r = lane & 15, h = lane >> 4;
-    int row = kTileRows * tile + 16 * t + r;
-    if (!row_is_mine(g, row, row0, rows)) return;
-    int col = kBlockCols * (4 * slice + h) + subgroup_of_range(range, r, g.sub) * (kBlockCols / g.sub);
-    uint16_t val = 0;
-    if (row < g.M && col < g.N) {
-        size_t G = g.N / g.group, grp = col / g.group, src_row = row - row0;
-        val = c < g.q ? alpha[(src_row * G + grp) * g.q + c] : offset[src_row * G + grp];
+    const int slice = blockIdx.x / (unsigned)g.ntile, tile = blockIdx.x - (unsigned)slice * (unsigned)g.ntile;
+    uint8_t *const out = blob + tile_offset(g, slice, tile);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int idx = threadIdx.x + 256 * k, d = idx & 3, lane = (idx >> 2) & 63, t = idx >> 8;
+        const int r = lane & 15, h = lane >> 4;
+        const int row = kTileRows * tile + 16 * t + r, kb = 4 * slice + h;
+        if (!row_is_mine(g, row, row0, rows)) continue;
+        uint32_t word[kMaxQ] = {0u, 0u, 0u, 0u};
+        if (row < g.M) {
+#pragma unroll
+            for (int n = 0; n < 4; ++n) {
+                const int col = kBlockCols * kb + kChunkCols * chunk_of_byte(4 * d + n, r, g.sub);
+                if (col >= g.N) continue;
+                const uint8_t *src = codes + (size_t)(row - row0) * g.N + col;
+                uint32_t lo, hi;
+                if (ALIGNED) {
+                    const uint2 v = *reinterpret_cast<const uint2 *>(src);
+                    lo = v.x; hi = v.y;
+                } else {
+                    lo = src[0] | src[1] << 8 | src[2] << 16 | (uint32_t)src[3] << 24;
+                    hi = src[4] | src[5] << 8 | src[6] << 16 | (uint32_t)src[7] << 24;
+                }
+#pragma unroll
+                for (int i = 0; i < kMaxQ; ++i)
+                    if (i < g.q) word[i] |= plane_byte(lo, hi, i) << (8 * n);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kMaxQ; ++i)
+            if (i < g.q) *reinterpret_cast<uint32_t *>(out + ((size_t)((t * g.q + i) * 64 + lane) * 16 + 4 * d)) = word[i];
     }
-    uint16_t *dst = reinterpret_cast<uint16_t *>(blob + tile_offset(g, slice, tile) +
-                                                 g.tile_plane_bytes + (size_t)e * 2);
-    *dst = val;
+    const unsigned per_tile = (unsigned)g.scale_lanes * 2u * g.nsc;  // with 16 records per half tile, `lane` below is the row
+    const unsigned qz = g.q + g.z, G = g.N / g.group;
+    for (unsigned e = threadIdx.x; e < per_tile; e += 256) {
+        const unsigned lane = e / (2 * g.nsc), rr = e - lane * (2 * g.nsc);
+        const unsigned t = rr / g.nsc, sc = rr - t * g.nsc;
+        const unsigned range = sc / qz, c = sc - range * qz;
+        const int r = lane & 15, h = lane >> 4;
+        const int row = kTileRows * tile + 16 * t + r;
+        if (!row_is_mine(g, row, row0, rows)) continue;
+        const int col = kBlockCols * (4 * slice + h) + subgroup_of_range(range, r, g.sub) * (kBlockCols / g.sub);
+        uint16_t val = 0;
+        if (row < g.M && col < g.N) {
+            const size_t at = (size_t)(row - row0) * G + (unsigned)col / (unsigned)g.group;
+            val = c < (unsigned)g.q ? alpha[at * g.q + c] : offset[at];
+        }
+        *reinterpret_cast<uint16_t *>(out + g.tile_plane_bytes + (size_t)e * 2) = val;
+    }
 }
 
 __global__ void unpack_codes_kernel(Geom g, const uint8_t *__restrict__ blob,
@@ -128,15 +136,10 @@ static unsigned blocks_for(size_t n, unsigned threads)
 hipError_t launch_pack(const Geom &g, int row0, int rows, const uint8_t *codes, const uint16_t *alpha,
                        const uint16_t *offset, void *packed, hipStream_t stream)
 {
-    size_t tiles = (size_t)g.nslice * g.ntile;
-    size_t nd = tiles * (g.tile_plane_bytes / 4);
-    size_t ne = tiles * (size_t)g.scale_lanes * 2u * g.nsc;
-    hipLaunchKernelGGL(pack_planes_kernel, dim3(blocks_for(nd, 256)), dim3(256), 0, stream, g, row0, rows,
-                       codes, static_cast<uint8_t *>(packed), nd);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(pack_scales_kernel, dim3(blocks_for(ne, 256)), dim3(256), 0, stream, g, row0, rows,
-                       alpha, offset, static_cast<uint8_t *>(packed), ne);
+    const size_t tiles = (size_t)g.nslice * g.ntile;
+    const bool aligned = (reinterpret_cast<uintptr_t>(codes) & 7) == 0;
+    hipLaunchKernelGGL((aligned ? pack_tile_kernel<true> : pack_tile_kernel<false>), dim3((unsigned)tiles), dim3(256), 0, stream, g,
+                       row0, rows, codes, alpha, offset, static_cast<uint8_t *>(packed));
     return hipGetLastError();
 }
 

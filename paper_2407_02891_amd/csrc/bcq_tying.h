@@ -108,6 +108,14 @@ BCQ_HD inline uint8_t code_of(int member, const TyingPlan &plan, int q)
 }
 
 #if defined(__HIPCC__)
+// Four integers (a byte each) through a table of codes in LDS.
+__device__ __forceinline__ uint32_t map_codes(const uint8_t *table, uint32_t w, uint32_t mask)
+{
+    w &= mask;
+    return (uint32_t)table[w & 0xffu] | (uint32_t)table[(w >> 8) & 0xffu] << 8 | (uint32_t)table[(w >> 16) & 0xffu] << 16 |
+           (uint32_t)table[w >> 24] << 24;
+}
+
 // binary64 -> binary16, round to nearest even, with a single rounding: the value is first
 // rounded to binary32 *to odd* (truncate, then set the last bit if anything was lost), which
 // keeps enough information for the final rounding to be the correct one.

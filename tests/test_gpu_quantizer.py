@@ -188,6 +188,54 @@ def test_from_linear_rows(M, N, n, q):
     U.gate(y[None, :], ref.gemm(planes, a16, z16, x), f"from_linear_rows n={n} q={q}")
 
 
+@pytest.mark.parametrize("M,N,n,q", [(5, 1028, 3, 2), (33, 64, 8, 4), (4100, 96, 4, 3)])
+@pytest.mark.parametrize("shift", [0, 1, 4, 8])
+def test_fuse_and_pack_alignment(M, N, n, q, shift):
+    """The widths of the fusion kernels (16, 4 or 1 weights per access, by the alignment of the pointers and of the rows) and
+    of the packing (8-byte or single codes): all give the codes of the oracle, and the same blob."""
+    rng = np.random.default_rng(N + n + shift)
+    parts = fuse.all_partitions(n, q)
+    pick = rng.integers(0, len(parts), size=M)
+    labels = np.stack([_labels_of(parts[i], n) for i in pick])
+    w = rng.integers(0, 256, size=(M, N), dtype=np.uint8)      # (bits beyond n are ignored)
+    S = (0.002 + 0.02 * rng.random(M)).astype(np.float32)
+    qb = (rng.standard_normal(M) * 0.05).astype(np.float32)
+    w_dev = torch.zeros(M * N + 16, dtype=torch.uint8, device="cuda")
+    w_dev[shift: shift + M * N] = _dev(w).reshape(-1)
+    c_dev = torch.full((M * N + 16,), 0xee, dtype=torch.uint8, device="cuda")
+    alpha = torch.empty((M, 1, q), dtype=torch.float16, device="cuda")
+    off = torch.empty((M, 1), dtype=torch.float16, device="cuda")
+    bcq.from_linear_rows(M, N, n, q, _dev(labels), w_dev[shift:], _dev(S), _dev(qb), c_dev[shift:], alpha, off)
+    torch.cuda.synchronize()
+    tables = {}
+    for i in set(pick.tolist()):
+        wq = fuse.nearest_bcchoice(np.arange(2 ** n)[None], fuse.bcchoice(parts[i], n))
+        wq = np.pad(wq, ((0, 0), (0, (-wq.shape[1]) % 32)))
+        pl, _, _ = fuse.fuse(wq, np.ones(1), np.zeros(1), parts[i], n, wq.shape[1])
+        tables[i] = bcq_synth.planes_to_codes(pl)[0][: 2 ** n]
+    want = np.stack([tables[i][w[m] & (2 ** n - 1)] for m, i in enumerate(pick.tolist())])
+    got = c_dev.cpu().numpy()
+    assert np.array_equal(got[shift: shift + M * N].reshape(M, N), want)
+    assert (got[:shift] == 0xee).all() and (got[shift + M * N:] == 0xee).all()
+    # one tying for the whole layer
+    c2 = torch.full((M * N + 16,), 0xee, dtype=torch.uint8, device="cuda")
+    a2 = torch.empty((M, 1, q), dtype=torch.float16, device="cuda")
+    bcq.from_linear(M, N, N, n, q, labels[0].tolist(), w_dev[shift:], _dev(S), _dev(qb), c2[shift:], a2, off)
+    torch.cuda.synchronize()
+    assert np.array_equal(c2.cpu().numpy()[shift: shift + M * N].reshape(M, N), tables[int(pick[0])][w & (2 ** n - 1)])
+    assert (c2.cpu().numpy()[shift + M * N:] == 0xee).all()
+    if N % 32 == 0:
+        blobs = []
+        for codes in (_dev(want).reshape(-1), c_dev[shift: shift + M * N]):
+            layer = bcq.PackedLayer(M, N, q, N, True)
+            layer.packed.fill_(0x5a)
+            blobs.append(layer.pack_from(codes, alpha, off).packed)
+        assert torch.equal(blobs[0], blobs[1])
+        back = torch.empty((M, N), dtype=torch.uint8, device="cuda")
+        bcq.unpack(layer.desc, layer.packed, back, None, None)
+        assert np.array_equal(back.cpu().numpy(), want)
+
+
 @pytest.mark.parametrize("N,T", [(160, 300), (256, 64), (72, 1000)])
 def test_hessian(N, T):
     """H = 2 X X^T (Sec. II-A) accumulated over two batches of inputs, against the oracle in binary64."""
