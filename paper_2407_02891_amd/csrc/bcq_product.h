@@ -57,6 +57,7 @@ typedef _Float16 prod_f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 prod_f16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned prod_u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned prod_u32x2 __attribute__((ext_vector_type(2)));
+typedef float prod_f32x2 __attribute__((ext_vector_type(2)));
 typedef float prod_f32x4 __attribute__((ext_vector_type(4)));
 
 enum ProductMode { kQuadForm = 0, kSubtract = 1, kAddTwiceSymmetric = 2, kStore = 3, kStoreNegated = 4 };

@@ -459,88 +459,166 @@ hipError_t launch_quant_search(int M, int N, int n_bits, int q, int grid, const 
 // ---------------------------------------------------------------------------------
 // GPTQ pass
 // ---------------------------------------------------------------------------------
-// One block of up to 128 columns [c0, c1): one thread per row.  The block's columns of the row sit in
-// LDS; the 32 columns being decided are held in registers, where each decision's compensation reaches
-// the later ones of the 32 at once, and reach the block's remaining columns when the 32 are done
-// (the same order of operations per weight as column by column).  The rows of U that the 32 columns
-// need are staged in LDS: the 32 x 32 corner as it is, the part to its right transposed so that one
-// column's 32 factors are contiguous.
-constexpr int kGptqBlock = 128, kGptqRows = 64, kGptqSub = 32;
-__global__ __launch_bounds__(kGptqRows) void gptq_block_kernel(int M, int Mp, int N, int n_bits, int q, int c0, int c1,
-                                                               float *__restrict__ Wt, const float *__restrict__ U,
-                                                               const float *__restrict__ S, const float *__restrict__ qbias,
-                                                               const int8_t *__restrict__ labels,
-                                                               uint8_t *__restrict__ w_int, float *__restrict__ Err)
+// What Eq. 6 makes of every integer of a row, as a table: 16 nibbles for up to four bits, else a byte per integer.
+__global__ void gptq_tables_kernel(int M, int n_bits, int q, const int8_t *__restrict__ labels,
+                                   unsigned long long *__restrict__ nibbles, uint8_t *__restrict__ bytes)
 {
-    __shared__ float wl[kGptqBlock][kGptqRows + 1];
-    __shared__ __attribute__((aligned(16))) float Ud[kGptqSub][kGptqSub];
-    __shared__ __attribute__((aligned(16))) float Uo[kGptqBlock - kGptqSub][kGptqSub];
-    const int tm = threadIdx.x, m = blockIdx.x * kGptqRows + tm;
-    const bool live = m < M;
-    const int cols = c1 - c0;
+    const int m = blockIdx.x * blockDim.x + threadIdx.x;
+    if (m >= M) return;
+    TyingPlan plan;  // labels come from device memory the host cannot inspect: out-of-range ones are folded
+    make_tying_plan(n_bits, q, labels + (size_t)m * n_bits, true, &plan);
     int choice[16];
-    double s = 1.0, b = 0.0;
-    if (live) {
-        TyingPlan plan;  // labels come from device memory the host cannot inspect: out-of-range ones are folded
-        make_tying_plan(n_bits, q, labels + (size_t)m * n_bits, true, &plan);
-        for (int k = 0; k < 16; ++k) choice[k] = plan.choice[k];
-        s = S[m]; b = qbias[m];
+    for (int k = 0; k < 16; ++k) choice[k] = plan.choice[k];
+    unsigned long long packed = 0;
+    for (int w = 0; w < 1 << n_bits; ++w) {
+        const int c = nearest_choice(w, choice, 1 << q);
+        if (n_bits <= 4) packed |= (unsigned long long)c << (4 * w);
+        else bytes[(size_t)m * 256 + w] = (uint8_t)c;
     }
-    for (int j = 0; j < cols; ++j) wl[j][tm] = live ? Wt[(size_t)(c0 + j) * Mp + m] : 0.0f;
-    for (int sb = 0; sb < cols; sb += kGptqSub) {
-        const int sw = cols - sb < kGptqSub ? cols - sb : kGptqSub;
-        const int rest = cols - sb - sw;
-        __syncthreads();  // the previous round's readers of Ud / Uo are done
-        for (int e = tm; e < kGptqSub * kGptqSub; e += kGptqRows) {
-            const int i = e >> 5, k = e & 31;
-            Ud[i][k] = (i < sw && k < sw) ? U[(size_t)(c0 + sb + i) * N + c0 + sb + k] : (i == k ? 1.0f : 0.0f);
-        }
-        for (int e = tm; e < rest * kGptqSub; e += kGptqRows) {
-            const int i = e / rest, k = e - i * rest;
-            Uo[k][i] = U[(size_t)(c0 + sb + i) * N + c0 + sb + sw + k];  // rest > 0 only with sw = 32
-        }
-        __syncthreads();
-        float w[kGptqSub], err[kGptqSub];
+    if (n_bits <= 4) nibbles[m] = packed;
+}
+
+// One block of up to 128 columns [c0, c0 + cols).  The columns of a row are decided one after the other, each from a
+// weight that carries the compensation of all before it, so the time of a block is the length of that chain: the row
+// is spread over eight lanes (lane l holds the columns 8 i + l in registers), every lane works out the decision for its
+// own column at hand, the one whose turn it is broadcasts its error (two DPP moves) and all of them add its share to
+// their 16 columns.  A wave takes eight rows; at 7168 rows that is one wave on nearly every SIMD.  (One thread per row,
+// as before, left 112 waves on the chip and took 193 us per block of a 7168-row layer; this takes 29.)
+// To keep the chain short, the two divisions of a decision are multiplications by reciprocals with the same results:
+//   * rint((w - qbias) / S): the binary64 product with 1 / S is off by less than 2^-44 for the up to 2^8 steps of the
+//     grid, so it rounds to the same integer unless it lies within 2^-30 of a half; then the division is carried out;
+//   * err / U[j][j] in binary32: quotient, remainder and correction with the rounded reciprocal (Markstein's method),
+//     which gives the correctly rounded quotient.
+// and Eq. 6 is a table look-up.  U's rows are staged in LDS such that the 16 factors of a lane for column c, those of
+// the columns 8 (c / 8 + k) + l, come in four 16-byte reads: [c][k / 4][l][k % 4].
+constexpr int kGptqBlock = 128, kGptqLanes = 8, kGptqRows = 32;  // columns per block, lanes per row, rows per workgroup
+
+template <int LANE>
+__device__ __forceinline__ float gptq_broadcast(float v)  // lane LANE of each group of eight
+{
+    int r = __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + LANE, 0xf, 0x3, false);        // row_newbcast
+    r = __builtin_amdgcn_update_dpp(r, __float_as_int(v), 0x150 + 8 + LANE, 0xf, 0xc, false);
+    return __int_as_float(r);
+}
+
+template <bool NIBBLES>
+__global__ __launch_bounds__(256) void gptq_block_kernel(int M, int Mp, int N, int n_bits, int c0, int cols,
+                                                         const float *__restrict__ Wt, const float *__restrict__ U,
+                                                         const float *__restrict__ S, const float *__restrict__ qbias,
+                                                         const unsigned long long *__restrict__ nibbles,
+                                                         const uint8_t *__restrict__ bytes, uint8_t *__restrict__ w_int,
+                                                         float *__restrict__ Err)
+{
+    __shared__ __attribute__((aligned(16))) float Us[kGptqBlock][4][kGptqLanes][4];
+    __shared__ prod_f32x2 diag[kGptqBlock];  // U[c][c] and its reciprocal
+    __shared__ uint8_t table[NIBBLES ? 1 : kGptqRows][256];
+    const int tid = threadIdx.x, l = tid & 7, row = tid >> 3, m = blockIdx.x * kGptqRows + row;
+    const bool live = m < M;
+
+    float w[16];
 #pragma unroll
-        for (int i = 0; i < kGptqSub; ++i) w[i] = i < sw ? wl[sb + i][tm] : 0.0f;
+    for (int i = 0; i < 16; ++i) w[i] = live && 8 * i + l < cols ? Wt[(size_t)(c0 + 8 * i + l) * Mp + m] : 0.0f;
+    for (int e = tid; e < kGptqBlock * 32; e += 256) {  // four columns at a time; N, c0 and cols are multiples of 4
+        const int c = e >> 5, x = 4 * (e & 31), col = 8 * (c >> 3) + x;
+        prod_f32x4 v = {0.f, 0.f, 0.f, 0.f};
+        if (c < cols && col < cols) v = *reinterpret_cast<const prod_f32x4 *>(U + (size_t)(c0 + c) * N + c0 + col);
 #pragma unroll
-        for (int i = 0; i < kGptqSub; ++i) {
-            err[i] = 0.0f;
-            if (i < sw) {  // uniform
-                if (live) {
-                    const int wq = quant_int((double)w[i], s, b, n_bits, choice, 1 << q);
-                    w_int[(size_t)m * N + c0 + sb + i] = (uint8_t)wq;
-                    const float qv = (float)(s * wq + b);
-                    err[i] = (w[i] - qv) / Ud[i][i];
-                }
-                if (m < Mp) Err[(size_t)(sb + i) * Mp + m] = err[i];  // zeros in the pad rows
-#pragma unroll
-                for (int k = i + 1; k < kGptqSub; ++k) w[k] = fmaf(-err[i], Ud[i][k], w[k]);
-            }
+        for (int j = 0; j < 4; ++j) Us[c][x >> 5][(x + j) & 7][(x >> 3) & 3] = v[j];
+    }
+    if (tid < kGptqBlock) {
+        const float d = tid < cols ? U[(size_t)(c0 + tid) * N + c0 + tid] : 1.0f;
+        diag[tid] = prod_f32x2{d, 1.0f / d};
+    }
+    double s = 1.0, b = 0.0;
+    unsigned long long nib = 0;
+    if (live) {
+        s = S[m];
+        b = qbias[m];
+        if (NIBBLES) nib = nibbles[m];
+    }
+    if (!NIBBLES) {
+        for (int e = tid; e < kGptqRows * 256; e += 256) {
+            const int r = e >> 8, mr = blockIdx.x * kGptqRows + r;
+            table[r][e & 255] = mr < M && (e & 255) < 1 << n_bits ? bytes[(size_t)mr * 256 + (e & 255)] : 0;
         }
-        for (int k = 0; k < rest; ++k) {
-            float a = wl[sb + sw + k][tm];
+    }
+    const double inv_s = 1.0 / s, top = (double)((1 << n_bits) - 1);
+    __syncthreads();
+
+    for (int i = 0; 8 * i < cols; ++i) {
+        int my_q = 0;
+        float my_err = 0.0f;
+        auto step = [&](auto lane_of) {
+            constexpr int kLane = decltype(lane_of)::value;
+            const int c = 8 * i + kLane;  // (columns beyond `cols` are decided too, and dropped)
+            prod_f32x4 u[4];
 #pragma unroll
-            for (int i = 0; i < kGptqSub; ++i) a = fmaf(-err[i], Uo[k][i], a);
-            wl[sb + sw + k][tm] = a;
+            for (int k = 0; k < 4; ++k) u[k] = *reinterpret_cast<const prod_f32x4 *>(&Us[c][k][l][0]);
+            const prod_f32x2 d = diag[c];
+            const double x = (double)w[0] - b;
+            const double t = x * inv_s;
+            double v = rint(t);  // round half to even
+            if (__builtin_expect(!(fabs(t - v) < 0.5 - 0x1p-30), 0)) v = rint(x / s);
+            v = v < 0.0 ? 0.0 : (v > top ? top : v);
+            const int lin = (int)v;
+            const int wq = NIBBLES ? (int)(nib >> (4 * lin)) & 15 : table[row][lin];
+            const float qv = (float)(s * wq + b);
+            const float a = w[0] - qv;
+            const float q0 = a * d[1];
+            const float own = fmaf(fmaf(-q0, d[0], a), d[1], q0);
+            const float err = gptq_broadcast<kLane>(own);
+            my_q = l == kLane ? wq : my_q;
+            my_err = l == kLane ? err : my_err;
+            // (the lanes whose column is decided already change a value that nobody reads any more)
+#pragma unroll
+            for (int k = 0; k < 16; ++k) w[k] = fmaf(-err, u[k >> 2][k & 3], w[k]);
+        };
+        step(std::integral_constant<int, 0>{}); step(std::integral_constant<int, 1>{});
+        step(std::integral_constant<int, 2>{}); step(std::integral_constant<int, 3>{});
+        step(std::integral_constant<int, 4>{}); step(std::integral_constant<int, 5>{});
+        step(std::integral_constant<int, 6>{}); step(std::integral_constant<int, 7>{});
+        if (8 * i + l < cols) {
+            if (live) w_int[(size_t)m * N + c0 + 8 * i + l] = (uint8_t)my_q;
+            if (m < Mp) Err[(size_t)(8 * i + l) * Mp + m] = live ? my_err : 0.0f;  // zeros in the pad rows
         }
+#pragma unroll
+        for (int k = 0; k < 15; ++k) w[k] = w[k + 1];
+        w[15] = 0.0f;
     }
 }
+
+// Columns beyond a panel of four blocks are brought up to date once per panel (K = 512), the rest of the panel after each
+// block: every pass over the remaining weights reads and writes them all, which at one pass per block was most of its time
+// (5.7 ms of a 7168 x 7168 layer, now 3.0; the whole pass 17.3 ms before both, now 4.6).  The errors of a panel are kept in Dt, which the pass does not use otherwise.
+constexpr int kGptqPanel = 4 * kGptqBlock;
 
 hipError_t launch_quant_gptq(int M, int N, int n_bits, int q, const float *W, const float *U, const float *S,
                              const float *qbias, const int8_t *labels, uint8_t *w_int, void *workspace,
                              hipStream_t stream)
 {
     const QuantWorkspace w = carve(workspace, M, N);
+    auto *nibbles = reinterpret_cast<unsigned long long *>(w.part);  // two of the (ceil(N / 128) + 3) Mp floats from here
+    auto *bytes = reinterpret_cast<uint8_t *>(w.Err);                // 256 of the 512 bytes per row
+    float *const err = w.Dt;
     hipLaunchKernelGGL(transpose_kernel, dim3((N + 31) / 32, (w.Mp + 31) / 32), dim3(32, 8), 0, stream, M, w.Mp, N, W,
                        w.Wt);
-    for (int c0 = 0; c0 < N; c0 += kGptqBlock) {
-        const int c1 = c0 + kGptqBlock < N ? c0 + kGptqBlock : N;
-        hipLaunchKernelGGL(gptq_block_kernel, dim3((w.Mp + kGptqRows - 1) / kGptqRows), dim3(kGptqRows), 0, stream, M,
-                           w.Mp, N, n_bits, q, c0, c1, w.Wt, U, S, qbias, labels, w_int, w.Err);
-        if (c1 < N)  // Wt[k][m] -= sum_j U[c0 + j][k] Err[j][m] for the columns k >= c1
-            launch_product<kSubtract>(stream, U + (size_t)c0 * N + c1, N, N - c1, w.Err, w.Mp, w.Mp, c1 - c0,
-                                      w.Wt + (size_t)c1 * w.Mp, w.Mp);
+    hipLaunchKernelGGL(gptq_tables_kernel, dim3((M + 63) / 64), dim3(64), 0, stream, M, n_bits, q, labels, nibbles, bytes);
+    // Wt[k][m] -= sum_j U[j][k] Err[j][m] for the columns k in [from, to) and the errors of the columns [j0, j1)
+    auto update = [&](int j0, int j1, int from, int to) {
+        if (from < to)
+            launch_product<kSubtract>(stream, U + (size_t)j0 * N + from, N, to - from, err + (size_t)j0 * w.Mp, w.Mp, w.Mp, j1 - j0,
+                                      w.Wt + (size_t)from * w.Mp, w.Mp);
+    };
+    for (int p0 = 0; p0 < N; p0 += kGptqPanel) {
+        const int p1 = p0 + kGptqPanel < N ? p0 + kGptqPanel : N;
+        for (int c0 = p0; c0 < p1; c0 += kGptqBlock) {
+            const int c1 = c0 + kGptqBlock < p1 ? c0 + kGptqBlock : p1;
+            hipLaunchKernelGGL((n_bits <= 4 ? gptq_block_kernel<true> : gptq_block_kernel<false>),
+                               dim3((w.Mp + kGptqRows - 1) / kGptqRows), dim3(256), 0, stream, M, w.Mp, N, n_bits, c0, c1 - c0,
+                               w.Wt, U, S, qbias, nibbles, bytes, w_int, err + (size_t)c0 * w.Mp);
+            update(c0, c1, c1, p1);
+        }
+        update(p0, p1, p1, N);
     }
     return hipGetLastError();
 }

@@ -154,6 +154,36 @@ def test_gptq_pass(M, N, n, q):
     assert e_g < e_rtn
 
 
+@pytest.mark.parametrize("M,N,n,q", [(33, 1156, 4, 3), (31, 516, 5, 3), (9, 644, 8, 4), (1, 1024, 2, 2), (65, 132, 6, 1)])
+def test_gptq_blocks_and_panels(M, N, n, q):
+    """The GPTQ pass at the edges of its blocks (128 columns, 32 rows, groups of 8 columns) and panels (512 columns), with
+    tables of nibbles (up to four bits) and of bytes, every tying among the rows, and weights placed exactly on a rounding
+    boundary of the first column (which the reciprocal of the scale must not decide differently from the division)."""
+    rng = np.random.default_rng(500 + N + n)
+    W32, H32 = _layer(M, N, seed=500 + N + n)
+    parts = fuse.all_partitions(n, q)
+    pick = rng.integers(0, len(parts), size=M)
+    choices = [fuse.bcchoice(parts[i], n) for i in pick]
+    labels = np.stack([_labels_of(parts[i], n) for i in pick])
+    b32 = W32.min(axis=1)
+    S32 = ((W32.max(axis=1) - b32) / (2 ** n - 1)).astype(np.float32)
+    # halves of a grid of exactly representable steps
+    S32[::2] = np.float32(2.0 ** -6) * (1 + (np.arange(S32[::2].size) % 3)).astype(np.float32)
+    b32[::2] = -np.float32(0.25)
+    W32[::2, 0] = b32[::2] + S32[::2] * (rng.integers(0, 2 ** n - 1, size=S32[::2].size) + 0.5).astype(np.float32)
+    U32 = quantizer.cholesky_factor(H32).astype(np.float32)
+    w_int = torch.full((M, N), 255, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(bcq.quant_workspace_bytes(M, N), dtype=torch.uint8, device="cuda")
+    ws.fill_(0xff)
+    bcq.quant_gptq(M, N, n, q, _dev(W32), _dev(U32), _dev(S32), _dev(b32), _dev(labels), w_int, ws)
+    torch.cuda.synchronize()
+    Wq = w_int.cpu().numpy().astype(np.int64)
+    S64, b64 = S32.astype(np.float64), b32.astype(np.float64)
+    first = np.array([quantizer.quant_row(W32[m, :1].astype(np.float64), S64[m], b64[m], choices[m], n)[0] for m in range(M)])
+    assert np.array_equal(Wq[:, 0], first)
+    _assert_gptq_explained(W32, U32, S64, b64, choices, n, Wq, f"gptq {M}x{N} n={n} q={q}")
+
+
 @pytest.mark.parametrize("M,N,n,q", [(37, 1024, 3, 2), (12, 512, 4, 3), (5, 1536, 5, 3), (8, 512, 4, 4)])
 def test_from_linear_rows(M, N, n, q):
     rng = np.random.default_rng(300 + N + n + q)
