@@ -7,7 +7,7 @@
 //               E = A.  The k range of a tile stops at its last column.  (out is [tile column][ldo], E has pitch ldo)
 //   kAddTwiceSymmetric   out[r][c] += 2 C[r][c], B = A: only the tiles on and above the diagonal are computed and each
 //               element is added to both out[r][c] and out[c][r]
-//   kSubtract   out[r][c] -= C[r][c]
+//   kSubtract   out[r][c] -= C[r][c];   kSubtractLower   the same for the tiles on and below the diagonal only
 //   kStore      out[r][c] = C[r][c], B[k][c] = 0 for k > c   
 //   kStoreNegated   out[r][c] = -C[r][c], A[k][r] = 0 for k < r
 //
@@ -37,7 +37,7 @@
 // What bounds it: about 200 vector instructions (800 clocks) against 48 matrix instructions (768 clocks) per wave and step,
 // two waves per SIMD: both pipes are half busy.  Measured (binary32 instruction before / now): quadratic form of a 7168 x
 // 7168 layer 3.32 / 1.31 ms per candidate (840 TFLOP/s of binary16 products; a large library product of that type reaches
-// 1230 on this card), 2 X^T X over 4 x 2048 samples of 7168 channels 7.17 / 2.08 ms.
+// 1230 on this card), 2 X^T X over 4 x 2048 samples of 7168 channels 7.17 / 1.85 ms.
 // An octet of column c sits at position c ^ ((c >> 4) & 1): the 16 lanes that a 16-byte LDS access serves together then
 // touch 16 different 16-byte columns both when the pairs of columns are written and when 16 consecutive ones are read.
 //
@@ -60,7 +60,7 @@ typedef unsigned prod_u32x2 __attribute__((ext_vector_type(2)));
 typedef float prod_f32x2 __attribute__((ext_vector_type(2)));
 typedef float prod_f32x4 __attribute__((ext_vector_type(4)));
 
-enum ProductMode { kQuadForm = 0, kSubtract = 1, kAddTwiceSymmetric = 2, kStore = 3, kStoreNegated = 4 };
+enum ProductMode { kQuadForm = 0, kSubtract = 1, kAddTwiceSymmetric = 2, kStore = 3, kStoreNegated = 4, kSubtractLower = 5 };
 
 constexpr int kProdTile = 128, kProdStep = 32, kProdBlock = 4;  // tile edge, k values per step, tiles per block edge
 
@@ -72,7 +72,7 @@ struct ProductArgs {
 };
 
 // Number of workgroups, and the tile of one.  Blocks of 4 x 4 tiles are numbered row by row (only those on and above the
-// diagonal for kAddTwiceSymmetric; column by column from the last one for kQuadForm, whose last columns have the longest k
+// diagonal for kAddTwiceSymmetric, on and below it for kSubtractLower; column by column from the last one for kQuadForm, whose last columns have the longest k
 // range).
 // Each XCD takes a contiguous run of blocks where all tiles cost the same, else every eighth block.
 template <int MODE>
@@ -80,7 +80,7 @@ static inline int product_blocks(int R, int C)
 {
     const int br = (R + kProdTile * kProdBlock - 1) / (kProdTile * kProdBlock);
     const int bc = (C + kProdTile * kProdBlock - 1) / (kProdTile * kProdBlock);
-    return MODE == kAddTwiceSymmetric ? br * (br + 1) / 2 : br * bc;
+    return MODE == kAddTwiceSymmetric || MODE == kSubtractLower ? br * (br + 1) / 2 : br * bc;
 }
 
 template <int MODE>
@@ -92,11 +92,16 @@ __device__ __forceinline__ bool product_tile(int wg, int wgs, int R, int C, int 
     const bool uneven = MODE == kQuadForm || MODE == kStore || MODE == kStoreNegated;
     int s = uneven ? (j / (kProdBlock * kProdBlock)) * 8 + xcd : xcd * per_xcd + j / (kProdBlock * kProdBlock);
     int b_row, b_col;
-    if (MODE == kAddTwiceSymmetric) {
+    if (MODE == kAddTwiceSymmetric || MODE == kSubtractLower) {
         if (s >= br * (br + 1) / 2) return false;
         b_row = 0;
         while (s >= br - b_row) s -= br - b_row++;
         b_col = b_row + s;
+        if (MODE == kSubtractLower) {
+            const int swap = b_row;
+            b_row = b_col;
+            b_col = swap;
+        }
     } else {
         if (s >= br * bc) return false;
         if (MODE == kQuadForm) {
@@ -110,7 +115,8 @@ __device__ __forceinline__ bool product_tile(int wg, int wgs, int R, int C, int 
     }
     *tile_row = b_row * kProdBlock + t / kProdBlock;
     *tile_col = b_col * kProdBlock + t % kProdBlock;
-    return *tile_row < ntr && *tile_col < ntc && (MODE != kAddTwiceSymmetric || *tile_col >= *tile_row);
+    return *tile_row < ntr && *tile_col < ntc && (MODE != kAddTwiceSymmetric || *tile_col >= *tile_row) &&
+           (MODE != kSubtractLower || *tile_col <= *tile_row);
 }
 
 // Exponent of the power of two that puts a magnitude (as float bits) at 2^target .. 2^(target + 1), kept to those a
@@ -330,45 +336,66 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
         if (!__syncthreads_or(bad)) break;
     }
 
-    // element i of a 16 x 16 accumulator: row 4 hi + i, column lo; the scales are taken out again
+    // Element i of a 16 x 16 accumulator: row 4 hi + i, column lo; the scales are taken out again.  Through a descriptor of
+    // the tile, elements that do not exist out of range, so that the 16 old values of a column group are requested together
+    // (one at a time, each behind the store of the one before, they were a third of a short product: K = 128, 384 x 3584 on average, 21.6 -> 12.7 us).
     if constexpr (MODE != kQuadForm) {
+        constexpr unsigned kNone = 0xfffffff0u;
+        constexpr bool kSymmetric = MODE == kAddTwiceSymmetric, kRead = MODE == kSubtract || MODE == kSubtractLower || kSymmetric;
+        const int rows = width[0] < kProdTile ? width[0] : kProdTile, columns = width[1] < kProdTile ? width[1] : kProdTile;
+        const __amdgpu_buffer_rsrc_t tile = __builtin_amdgcn_make_buffer_rsrc(
+            p.out + (size_t)r0 * p.ldo + c0, 0, 4 * ((rows - 1) * p.ldo + columns), kRawBufferFlags);
+        // kAddTwiceSymmetric: element (r, c) with r < c also goes to (c, r)
+        const __amdgpu_buffer_rsrc_t mirror = __builtin_amdgcn_make_buffer_rsrc(
+            p.out + (size_t)c0 * p.ldo + r0, 0, kSymmetric ? 4 * ((columns - 1) * p.ldo + rows) : 0, kRawBufferFlags);
+        const bool diagonal = kSymmetric && r0 == c0;
 #pragma unroll
         for (int tb = 0; tb < 4; ++tb) {
-            const int cl = wc * 64 + tb * 16 + lo, c = c0 + cl;
+            const int cl = wc * 64 + tb * 16 + lo;
             const int shift_c = shift[1][cl];
+            float v[4][4];
+            prod_u32x4 there[4];
+            unsigned old[4][4];
 #pragma unroll
             for (int ta = 0; ta < 4; ++ta) {
-                    const int rl = wr * 64 + ta * 16 + 4 * hi, r = r0 + rl;  // R is a multiple of 4
-                    if (r >= p.R || c >= p.C) continue;
-                    float v[4];
+                const int rl = wr * 64 + ta * 16 + 4 * hi;  // rows and columns are multiples of 4
+                const bool in = rl < rows && cl < columns;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) v[i] = ldexpf(acc[ta][tb][i], -(shift[0][rl + i] + shift_c));
-                    if constexpr (MODE == kAddTwiceSymmetric) {
-                        if (r > c) continue;  // (a group of four rows that crosses the diagonal is handled below)
+                for (int i = 0; i < 4; ++i)
+                    if (kRead)
+                        old[ta][i] = __builtin_amdgcn_raw_buffer_load_b32(
+                            tile, in && !(diagonal && rl + i > cl) ? 4u * (rl * p.ldo + cl) : kNone, 4 * i * p.ldo, 0);
+                if (kSymmetric && !diagonal)
+                    there[ta] = __builtin_amdgcn_raw_buffer_load_b128(mirror, in ? 4u * (cl * p.ldo + rl) : kNone, 0, 0);
+                if (kSymmetric && diagonal) {
 #pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            if (r + i <= c) p.out[(size_t)(r + i) * p.ldo + c] += 2.0f * v[i];
-                        float *o = p.out + (size_t)c * p.ldo + r;
-                        if (r + 3 < c) {
-                            prod_f32x4 w = *reinterpret_cast<prod_f32x4 *>(o);
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) w[i] += 2.0f * v[i];
-                            *reinterpret_cast<prod_f32x4 *>(o) = w;
-                        } else {
-#pragma unroll
-                            for (int i = 0; i < 4; ++i)
-                                if (r + i < c) o[i] += 2.0f * v[i];
-                        }
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            float *o = p.out + (size_t)(r + i) * p.ldo + c;
-                            if (MODE == kSubtract) *o -= v[i];
-                            if (MODE == kStore) *o = v[i];
-                            if (MODE == kStoreNegated) *o = -v[i];
-                        }
-                    }
+                    for (int i = 0; i < 4; ++i)
+                        there[ta][i] = __builtin_amdgcn_raw_buffer_load_b32(
+                            mirror, in && rl + i < cl ? 4u * (cl * p.ldo + rl + i) : kNone, 0, 0);
                 }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[ta][i] = ldexpf(acc[ta][tb][i], -(shift[0][rl + i] + shift_c));
+            }
+#pragma unroll
+            for (int ta = 0; ta < 4; ++ta) {
+                const int rl = wr * 64 + ta * 16 + 4 * hi;
+                const bool in = rl < rows && cl < columns;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float w = v[ta][i];
+                    if (MODE == kStoreNegated) w = -w;
+                    if (MODE == kSubtract || MODE == kSubtractLower) w = __uint_as_float(old[ta][i]) - w;
+                    if (kSymmetric) w = __uint_as_float(old[ta][i]) + 2.0f * w;
+                    __builtin_amdgcn_raw_buffer_store_b32(
+                        __float_as_uint(w), tile, in && !(diagonal && rl + i > cl) ? 4u * (rl * p.ldo + cl) : kNone, 4 * i * p.ldo, 0);
+                    if (kSymmetric) there[ta][i] = __float_as_uint(__uint_as_float(there[ta][i]) + 2.0f * v[ta][i]);
+                    if (kSymmetric && diagonal)
+                        __builtin_amdgcn_raw_buffer_store_b32(there[ta][i], mirror,
+                                                              in && rl + i < cl ? 4u * (cl * p.ldo + rl + i) : kNone, 0, 0);
+                }
+                if (kSymmetric && !diagonal)
+                    __builtin_amdgcn_raw_buffer_store_b128(there[ta], mirror, in ? 4u * (cl * p.ldo + rl) : kNone, 0, 0);
+            }
         }
     } else {
         float *red = reinterpret_cast<float *>(&stage[0][0][0][0][0]);  // [2 column halves][128 rows], free after the loop's last barrier

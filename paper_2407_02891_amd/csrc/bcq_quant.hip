@@ -151,10 +151,10 @@ hipError_t launch_quant_hessian(int N, int T, const float *X, float *H, hipStrea
 // ---------------------------------------------------------------------------------
 // With H_d = H + lambda I = R R^T, R UPPER triangular (a Cholesky factorisation taken from the last
 // row upwards), H_d^-1 = R^-T R^-1, so U = R^-1.  Both steps are blocked by 128 columns; the diagonal
-// blocks are factored and inverted by one workgroup in LDS, everything else is the k-major product
-// of bcq_product.h (K = 128 panels and trailing updates for R; growing K for the off-diagonal blocks of U).
+// blocks are inverted by one workgroup, everything else is the k-major product of bcq_product.h (K = 128
+// panels, trailing updates of K = 128 and 512 for R; growing K for the off-diagonal blocks of U).
 // Working matrices (binary32, pitch N): Hw = H_d (consumed), Rt = R^T, Ut = U^T, T = one panel.
-constexpr int kFactorBlock = 128;
+constexpr int kFactorBlock = 128, kFactorPanel = 512;
 
 __global__ void diag_mean_kernel(int N, const float *__restrict__ H, float damp, float *__restrict__ lambda)
 {
@@ -179,91 +179,78 @@ __global__ void damped_copy_kernel(int N, const float *__restrict__ H, const flo
     Hw[gid] = H[gid] + (i == j ? *lambda : 0.0f);
 }
 
-// Diagonal block [r0, r0 + b): D = R R^T in place (R upper, from the last column to the first), then
-// R^-1 beside it; writes the block of U and of U^T.  One workgroup; both blocks sit in LDS with an
-// odd pitch so that rows and columns are both conflict-free.
-constexpr int kDiagPitch = kFactorBlock + 1;
-constexpr int kDiagLdsBytes = 2 * kFactorBlock * kDiagPitch * 4;  // the block and its inverse, 132096 B: dynamic
-
-// Straight-line (no branch per element, so the LDS reads are issued together): every owned element of
-// the first NM x NM groups is read, changed only where i <= l < j, and written back by its one owner.
-template <int NM>
-__device__ __forceinline__ void corner_update(float *D, int j, int ty, int tx)
-{
-    float ri[NM], rl[NM], v[NM][NM];
-#pragma unroll
-    for (int a = 0; a < NM; ++a) {
-        ri[a] = D[(ty + 16 * a) * kDiagPitch + j];
-        rl[a] = D[(tx + 16 * a) * kDiagPitch + j];
-    }
-#pragma unroll
-    for (int a = 0; a < NM; ++a)
-#pragma unroll
-        for (int c = 0; c < NM; ++c) v[a][c] = D[(ty + 16 * a) * kDiagPitch + tx + 16 * c];
-#pragma unroll
-    for (int a = 0; a < NM; ++a)
-#pragma unroll
-        for (int c = 0; c < NM; ++c) {
-            const int i = ty + 16 * a, l = tx + 16 * c;
-            v[a][c] -= (i <= l && l < j) ? ri[a] * rl[c] : 0.0f;
-        }
-#pragma unroll
-    for (int a = 0; a < NM; ++a)
-#pragma unroll
-        for (int c = 0; c < NM; ++c) D[(ty + 16 * a) * kDiagPitch + tx + 16 * c] = v[a][c];
-}
-
+// Diagonal block [r0, r0 + b): writes the blocks V = R^-1 of U and V^T of Ut, with D = R R^T, R upper triangular.  V is all
+// that is needed of it (the panel is V times the rows of the block), and it comes straight out of an elimination in
+// place, from the last row j upwards: with the pivot d = x[j][j] and f_i = x[i][j] / d,
+//     x[i][l] -= f_i x[j][l]   for i < j and every l but j,      x[i][j] = -f_i.
+// To the left of the pivot that is the Schur complement of D; the columns from j on are done with as parts of D and hold M,
+// unit upper triangular, the product of the row operations, for which M D M^T = diag(d): V = diag(d)^-1/2 M.  D is
+// symmetric, so x[i][j] is x[j][i] and the one thing a step has to hand round is row j: 128 values through LDS, one barrier.
+// One workgroup of 256 threads with the 128 x 128 block in registers, thread (ty, tx) owning the elements (ty + 16 a, tx +
+// 16 c).  What bounds it is that chain, 128 times (write, barrier, read, reciprocal, 8 to 64 multiply-adds): 245 us before
+// (the block and its inverse in LDS, the inverse one column per thread), now 50.
 __global__ __launch_bounds__(256) void factor_diag_kernel(int N, int r0, int b, const float *__restrict__ Hw,
                                                           float *__restrict__ U, float *__restrict__ Ut)
 {
-    extern __shared__ float D[];
+    __shared__ __attribute__((aligned(16))) float row[2][16][8];  // row j: element l at [l % 16][l / 16]
+    __shared__ float pivot[kFactorBlock];
+    __shared__ float V[kFactorBlock][kFactorBlock + 1];
     const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+    float x[8][8];
+#pragma unroll
+    for (int a = 0; a < 8; ++a)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const int i = ty + 16 * a, l = tx + 16 * c;  // beyond b: the identity, which changes nothing
+            x[a][c] = i < b && l < b ? Hw[(size_t)(r0 + i) * N + r0 + l] : (i == l ? 1.0f : 0.0f);
+        }
+    auto eliminate = [&](auto group) {  // the rows j = 16 g + 15 .. 16 g
+        constexpr int g = decltype(group)::value;
+#pragma unroll 1
+        for (int jj = 15; jj >= 0; --jj) {
+            float (&buf)[16][8] = row[jj & 1];
+            if (ty == jj) {
+#pragma unroll
+                for (int c = 0; c < 8; ++c) buf[tx][c] = x[g][c];
+            }
+            __syncthreads();
+            const prod_f32x4 l0 = *reinterpret_cast<const prod_f32x4 *>(&buf[tx][0]), l1 = *reinterpret_cast<const prod_f32x4 *>(&buf[tx][4]);
+            const prod_f32x4 i0 = *reinterpret_cast<const prod_f32x4 *>(&buf[ty][0]), i1 = *reinterpret_cast<const prod_f32x4 *>(&buf[ty][4]);
+            const float d = buf[jj][g];
+            const float inv = d > 0.0f ? 1.0f / d : __builtin_nanf("");  // not positive definite: NaNs from here on
+            if (tid == 0) pivot[16 * g + jj] = d;
+#pragma unroll
+            for (int a = 0; a <= g; ++a) {
+                const float xi = a < 4 ? i0[a & 3] : i1[a & 3];
+                const bool above = a < g || ty < jj;  // i < j
+                const float f = above ? xi * inv : 0.0f;
+                const float at_pivot = above ? -f : x[a][g];
+#pragma unroll
+                for (int c = 0; c < 8; ++c) x[a][c] = fmaf(-f, c < 4 ? l0[c & 3] : l1[c & 3], x[a][c]);
+                if (tx == jj) x[a][g] = at_pivot;
+            }
+        }
+    };
+    eliminate(std::integral_constant<int, 7>{}); eliminate(std::integral_constant<int, 6>{});
+    eliminate(std::integral_constant<int, 5>{}); eliminate(std::integral_constant<int, 4>{});
+    eliminate(std::integral_constant<int, 3>{}); eliminate(std::integral_constant<int, 2>{});
+    eliminate(std::integral_constant<int, 1>{}); eliminate(std::integral_constant<int, 0>{});
+    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < 8; ++a) {
+        const int i = ty + 16 * a;
+        const float rs = 1.0f / sqrtf(pivot[i]);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const int l = tx + 16 * c;
+            V[i][l] = l > i ? x[a][c] * rs : (l == i ? rs : 0.0f);
+        }
+    }
+    __syncthreads();
     for (int e = tid; e < b * b; e += 256) {
         const int i = e / b, l = e - i * b;
-        D[i * kDiagPitch + l] = Hw[(size_t)(r0 + i) * N + r0 + l];
-    }
-    __syncthreads();
-    // column j of R = column j of the remaining block / sqrt(its corner); then the corner's rank-1 update.
-    // D[j][j] keeps the un-rooted corner until the end (nobody reads it after step j).
-    for (int j = b - 1; j >= 0; --j) {
-        const float d = sqrtf(D[j * kDiagPitch + j]);
-        if (tid < j) D[tid * kDiagPitch + j] /= d;  // own element: read and written by this thread only
-        __syncthreads();
-        // D[i][l] -= R[i][j] R[l][j] for i <= l < j; thread (ty, tx) owns i = ty + 16 a, l = tx + 16 c
-        switch ((j + 15) >> 4) {  // uniform: how many 16 x 16 groups reach below j
-            case 1: corner_update<1>(D, j, ty, tx); break;
-            case 2: corner_update<2>(D, j, ty, tx); break;
-            case 3: corner_update<3>(D, j, ty, tx); break;
-            case 4: corner_update<4>(D, j, ty, tx); break;
-            case 5: corner_update<5>(D, j, ty, tx); break;
-            case 6: corner_update<6>(D, j, ty, tx); break;
-            case 7: corner_update<7>(D, j, ty, tx); break;
-            case 8: corner_update<8>(D, j, ty, tx); break;
-            default: break;
-        }
-        __syncthreads();
-    }
-    if (tid < b) D[tid * kDiagPitch + tid] = sqrtf(D[tid * kDiagPitch + tid]);
-    __syncthreads();
-    // V = R^-1 into the second half of the LDS block, one thread per column and no barrier: column j of
-    // R V = I from its diagonal upwards, v[i][j] = -(sum_{i < m <= j} r[i][m] v[m][j]) / r[i][i].  In step i
-    // the threads read the same r[i][m] (broadcast) and their own column of V.
-    float *V = D + kFactorBlock * kDiagPitch;
-    if (tid < b) {
-        const int j = tid;
-        V[j * kDiagPitch + j] = 1.0f / D[j * kDiagPitch + j];
-        for (int i = j - 1; i >= 0; --i) {
-            float acc = 0.0f;
-            for (int m = i + 1; m <= j; ++m) acc = fmaf(D[i * kDiagPitch + m], V[m * kDiagPitch + j], acc);
-            V[i * kDiagPitch + j] = -acc / D[i * kDiagPitch + i];
-        }
-    }
-    __syncthreads();
-    for (int e = tid; e < b * b; e += 256) {
-        const int i = e / b, l = e - i * b;
-        const float v = i <= l ? V[i * kDiagPitch + l] : 0.0f;
-        U[(size_t)(r0 + i) * N + r0 + l] = v;
-        Ut[(size_t)(r0 + l) * N + r0 + i] = v;
+        U[(size_t)(r0 + i) * N + r0 + l] = V[i][l];
+        Ut[(size_t)(r0 + i) * N + r0 + l] = V[l][i];
     }
 }
 
@@ -313,13 +300,6 @@ hipError_t launch_quant_factor(int N, float damp, const float *H, float *U, void
     float *Hw = static_cast<float *>(workspace);
     float *Rt = Hw + (size_t)N * N, *Ut = Rt + (size_t)N * N;
     float *lambda = Ut + (size_t)N * N;
-    static bool lds_set = false;  // per process; the attribute belongs to the function, not to a device
-    if (!lds_set) {
-        hipError_t a = hipFuncSetAttribute(reinterpret_cast<const void *>(factor_diag_kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, kDiagLdsBytes);
-        if (a != hipSuccess) return a;
-        lds_set = true;
-    }
     hipLaunchKernelGGL(diag_mean_kernel, dim3(1), dim3(256), 0, stream, N, H, damp, lambda);
     hipLaunchKernelGGL(damped_copy_kernel, dim3((unsigned)(((size_t)N * N + 255) / 256)), dim3(256), 0, stream, N, H,
                        lambda, Hw);
@@ -327,16 +307,28 @@ hipError_t launch_quant_factor(int N, float damp, const float *H, float *U, void
     if (e != hipSuccess) return e;
     e = launch_fill_zero(Ut, (size_t)N * N * 4, stream);
     if (e != hipSuccess) return e;
-    const int nblk = (N + kFactorBlock - 1) / kFactorBlock;
-    // R, from the last block column to the first
-    for (int k = nblk - 1; k >= 0; --k) {
-        const int r0 = k * kFactorBlock, b = N - r0 < kFactorBlock ? N - r0 : kFactorBlock;
-        hipLaunchKernelGGL(factor_diag_kernel, dim3(1), dim3(256), kDiagLdsBytes, stream, N, r0, b, Hw, U, Ut);
-        if (r0 == 0) break;
-        // panel, transposed: Rt[r0 + c][i] = R[i][r0 + c] = sum_m V[c][m] Hw[r0 + m][i]   (Hw symmetric, V = R_kk^-1)
-        launch_product<kStore>(stream, Ut + (size_t)r0 * N + r0, N, b, Hw + (size_t)r0 * N, N, r0, b, Rt + (size_t)r0 * N, N);
-        // Hw[i][j] -= sum_c R[i][r0 + c] R[j][r0 + c] for i, j < r0
-        launch_product<kSubtract>(stream, Rt + (size_t)r0 * N, N, r0, Rt + (size_t)r0 * N, N, r0, b, Hw, N);
+    // R, from the last block column to the first.  Only the part of Hw on and below its diagonal blocks is kept up to date:
+    // after a block the rows of its panel (four blocks), which the next blocks need, after a panel all rows above it, with
+    // the panel's 512 columns at once (a pass over what remains costs its reading and writing however few columns it adds).
+    for (int p1 = N; p1 > 0;) {
+        const int p0 = (p1 - 1) / kFactorPanel * kFactorPanel;
+        for (int r1 = p1; r1 > p0;) {
+            const int r0 = (r1 - 1) / kFactorBlock * kFactorBlock, b = r1 - r0;
+            hipLaunchKernelGGL(factor_diag_kernel, dim3(1), dim3(256), 0, stream, N, r0, b, Hw, U, Ut);
+            if (r0 > 0) {
+                // panel, transposed: Rt[r0 + c][i] = R[i][r0 + c] = sum_m V[c][m] Hw[r0 + m][i]   (Hw symmetric, V = R_kk^-1)
+                launch_product<kStore>(stream, Ut + (size_t)r0 * N + r0, N, b, Hw + (size_t)r0 * N, N, r0, b, Rt + (size_t)r0 * N, N);
+                // Hw[i][j] -= sum_c R[i][r0 + c] R[j][r0 + c] for p0 <= i < r0, j < r0
+                if (r0 > p0)
+                    launch_product<kSubtract>(stream, Rt + (size_t)r0 * N + p0, N, r0 - p0, Rt + (size_t)r0 * N, N, r0, b,
+                                              Hw + (size_t)p0 * N, N);
+            }
+            r1 = r0;
+        }
+        // Hw[i][j] -= sum_c R[i][p0 + c] R[j][p0 + c] for j <= i < p0 (by tiles)
+        if (p0 > 0)
+            launch_product<kSubtractLower>(stream, Rt + (size_t)p0 * N, N, p0, Rt + (size_t)p0 * N, N, p0, p1 - p0, Hw, N);
+        p1 = p0;
     }
     // U = R^-1: Hw is free now and holds the intermediate products
     invert_range(stream, N, 0, N, Rt, U, Ut, Hw);
@@ -589,7 +581,7 @@ __global__ __launch_bounds__(256) void gptq_block_kernel(int M, int Mp, int N, i
 
 // Columns beyond a panel of four blocks are brought up to date once per panel (K = 512), the rest of the panel after each
 // block: every pass over the remaining weights reads and writes them all, which at one pass per block was most of its time
-// (5.7 ms of a 7168 x 7168 layer, now 3.0; the whole pass 17.3 ms before both, now 4.6).  The errors of a panel are kept in Dt, which the pass does not use otherwise.
+// (5.7 ms of a 7168 x 7168 layer, now 2.3; the whole pass 17.3 ms before, now 3.8).  The errors of a panel are kept in Dt, which the pass does not use otherwise.
 constexpr int kGptqPanel = 4 * kGptqBlock;
 
 hipError_t launch_quant_gptq(int M, int N, int n_bits, int q, const float *W, const float *U, const float *S,
