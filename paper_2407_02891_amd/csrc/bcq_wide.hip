@@ -297,7 +297,8 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void bcq_wide_kernel(WideParams
                 // the next stage's X has arrived (what was requested after it may still be under way); everyone is done with
                 // this stage
                 if (B < 2) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(Q) : "memory");
-                else if (B == 2) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kRec) : "memory");
+                // (the compiler may join the scale loads, four dwords to an instruction at most)
+                else if (B == 2) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((kRec + 3) / 4) : "memory");
                 else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
                 __builtin_amdgcn_sched_barrier(0);
             }
