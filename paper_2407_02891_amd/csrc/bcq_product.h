@@ -5,6 +5,7 @@
 //   kQuadForm   part[tile column][r] = sum over the tile's columns c of C'[r][c] * E[c][r], where C' takes B[k][c] with the
 //               weight 1 for k < c, 1/2 for k = c and 0 for k > c: half of the quadratic form of a symmetric B if
 //               E = A.  The k range of a tile stops at its last column.  (out is [tile column][ldo], E has pitch ldo)
+//   kQuadFormSplit   kQuadForm with A split beforehand (see ProductArgs)
 //   kAddTwiceSymmetric   out[r][c] += 2 C[r][c], B = A: only the tiles on and above the diagonal are computed and each
 //               element is added to both out[r][c] and out[c][r]
 //   kSubtract   out[r][c] -= C[r][c];   kSubtractLower   the same for the tiles on and below the diagonal only
@@ -36,8 +37,8 @@
 // matrix instructions: with branches the same loop was 25 % slower.
 // What bounds it: about 200 vector instructions (800 clocks) against 48 matrix instructions (768 clocks) per wave and step,
 // two waves per SIMD: both pipes are half busy.  Measured (binary32 instruction before / now): quadratic form of a 7168 x
-// 7168 layer 3.32 / 1.31 ms per candidate (840 TFLOP/s of binary16 products; a large library product of that type reaches
-// 1230 on this card), 2 X^T X over 4 x 2048 samples of 7168 channels 7.17 / 1.85 ms.
+// 7168 layer 3.32 / 1.38 ms per candidate, 1.19 with A split beforehand (kQuadFormSplit: 930 TFLOP/s of binary16 products; a
+// large library product of that type reaches 1230 on this card), 2 X^T X over 4 x 2048 samples of 7168 channels 7.17 / 1.85 ms.
 // An octet of column c sits at position c ^ ((c >> 4) & 1): the 16 lanes that a 16-byte LDS access serves together then
 // touch 16 different 16-byte columns both when the pairs of columns are written and when 16 consecutive ones are read.
 //
@@ -60,7 +61,9 @@ typedef unsigned prod_u32x2 __attribute__((ext_vector_type(2)));
 typedef float prod_f32x2 __attribute__((ext_vector_type(2)));
 typedef float prod_f32x4 __attribute__((ext_vector_type(4)));
 
-enum ProductMode { kQuadForm = 0, kSubtract = 1, kAddTwiceSymmetric = 2, kStore = 3, kStoreNegated = 4, kSubtractLower = 5 };
+#define PROD_INLINE __attribute__((always_inline))
+
+enum ProductMode { kQuadForm = 0, kSubtract = 1, kAddTwiceSymmetric = 2, kStore = 3, kStoreNegated = 4, kSubtractLower = 5, kQuadFormSplit = 6 };
 
 constexpr int kProdTile = 128, kProdStep = 32, kProdBlock = 4;  // tile edge, k values per step, tiles per block edge
 
@@ -69,11 +72,14 @@ struct ProductArgs {
     float *out;
     int lda, R, ldb, C, K, ldo;
     int triangular_b;  // kStore: B[k][c] = 0 for k > c
+    const uint16_t *split;  // kQuadFormSplit: A in two halves, [hi, lo][k / 8][row (pitch ldo)][8 values of k]; K a multiple of 8
+    size_t split_plane;     // values per half
+    const int *split_shift; // exponent of each row's scale
 };
 
 // Number of workgroups, and the tile of one.  Blocks of 4 x 4 tiles are numbered row by row (only those on and above the
-// diagonal for kAddTwiceSymmetric, on and below it for kSubtractLower; column by column from the last one for kQuadForm, whose last columns have the longest k
-// range).
+// diagonal for kAddTwiceSymmetric, on and below it for kSubtractLower; column by column from the last one for the quadratic
+// forms, whose last columns have the longest k range).
 // Each XCD takes a contiguous run of blocks where all tiles cost the same, else every eighth block.
 template <int MODE>
 static inline int product_blocks(int R, int C)
@@ -89,7 +95,7 @@ __device__ __forceinline__ bool product_tile(int wg, int wgs, int R, int C, int 
     const int ntr = (R + kProdTile - 1) / kProdTile, ntc = (C + kProdTile - 1) / kProdTile;
     const int br = (ntr + kProdBlock - 1) / kProdBlock, bc = (ntc + kProdBlock - 1) / kProdBlock;
     const int xcd = wg & 7, j = wg >> 3, t = j & (kProdBlock * kProdBlock - 1), per_xcd = wgs / (8 * kProdBlock * kProdBlock);
-    const bool uneven = MODE == kQuadForm || MODE == kStore || MODE == kStoreNegated;
+    const bool uneven = MODE == kQuadForm || MODE == kQuadFormSplit || MODE == kStore || MODE == kStoreNegated;
     int s = uneven ? (j / (kProdBlock * kProdBlock)) * 8 + xcd : xcd * per_xcd + j / (kProdBlock * kProdBlock);
     int b_row, b_col;
     if (MODE == kAddTwiceSymmetric || MODE == kSubtractLower) {
@@ -104,7 +110,7 @@ __device__ __forceinline__ bool product_tile(int wg, int wgs, int R, int C, int 
         }
     } else {
         if (s >= br * bc) return false;
-        if (MODE == kQuadForm) {
+        if (MODE == kQuadForm || MODE == kQuadFormSplit) {
             b_col = s / br;
             b_row = s - b_col * br;
             b_col = bc - 1 - b_col;
@@ -130,7 +136,13 @@ __device__ __forceinline__ int product_shift(unsigned magnitude, int target)
 template <int MODE>
 __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
 {
-    __shared__ __attribute__((aligned(16))) uint8_t stage[2][2][2][4][kProdTile * 16];  // [stage][A, B][hi, lo][octet][column]
+    constexpr bool kQuad = MODE == kQuadForm || MODE == kQuadFormSplit, kSplitA = MODE == kQuadFormSplit;
+    constexpr int kFirst = kSplitA ? 1 : 0;  // first operand that comes in binary32
+    // the two stages of both operands, [hi, lo][octet][column]; A's are two objects so that the compiler can tell the copies
+    // into one (kQuadFormSplit) from the reads of the other
+    __shared__ __attribute__((aligned(16))) uint8_t stage_a0[2][4][kProdTile * 16];
+    __shared__ __attribute__((aligned(16))) uint8_t stage_a1[2][4][kProdTile * 16];
+    __shared__ __attribute__((aligned(16))) uint8_t stage_b[2][2][4][kProdTile * 16];
     __shared__ unsigned largest[2][kProdTile];  // largest magnitude per row of A's tile, column of B's tile (float bits)
     __shared__ unsigned largest_of_tile[2];
     __shared__ int shift[2][kProdTile];  // exponents of the scales
@@ -143,7 +155,7 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
 
     // k range of the tile: what a triangular operand leaves
     int k_begin = 0, k_end = p.K;
-    if (MODE == kQuadForm && k_end > c0 + kProdTile) k_end = c0 + kProdTile;
+    if (kQuad && k_end > c0 + kProdTile) k_end = c0 + kProdTile;
     if (MODE == kStore && p.triangular_b && k_end > c0 + kProdTile) k_end = c0 + kProdTile;
     if (MODE == kStoreNegated) k_begin = r0;
     const int steps = (k_end - k_begin + kProdStep - 1) / kProdStep;
@@ -154,11 +166,11 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
     const float *const panel[2] = {p.A + r0, p.B + c0};
     const int pitch[2] = {p.lda, p.ldb}, width[2] = {p.R - r0, p.C - c0};
     prod_u32x2 raw[2][8];
-    auto load = [&](int step) {
+    auto load = [&](int step) PROD_INLINE {
         const int k = k_begin + step * kProdStep + 8 * wave;
         const int rows = k_end - k < 0 ? 0 : (k_end - k < 8 ? k_end - k : 8);
 #pragma unroll
-        for (int o = 0; o < 2; ++o) {
+        for (int o = kFirst; o < 2; ++o) {
             const unsigned bytes = rows ? 4u * ((unsigned)(rows - 1) * (unsigned)pitch[o] + (unsigned)width[o]) : 0u;
             const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
                 const_cast<float *>(panel[o] + (size_t)(rows ? k : k_begin) * pitch[o]), 0, (int)bytes, kRawBufferFlags);
@@ -167,7 +179,7 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
                 raw[o][j] = __builtin_amdgcn_raw_buffer_load_b64(rsrc, 8 * lane, 4 * j * pitch[o], 0);
         }
     };
-    auto weigh = [&](int step) {  // kQuadForm: B on and beyond its diagonal
+    auto weigh = [&](int step) PROD_INLINE {  // kQuadForm: B on and beyond its diagonal
         const int k0 = k_begin + step * kProdStep + 8 * wave;
 #pragma unroll
         for (int j = 0; j < 8; ++j)
@@ -179,25 +191,26 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
             }
     };
     float top[2][2] = {{0.f, 0.f}, {0.f, 0.f}};  // largest magnitudes seen by this lane
-    auto track = [&]() {
+    auto track = [&]() PROD_INLINE {
 #pragma unroll
-        for (int o = 0; o < 2; ++o)
+        for (int o = kFirst; o < 2; ++o)
 #pragma unroll
             for (int j = 0; j < 8; ++j)
 #pragma unroll
                 for (int e = 0; e < 2; ++e) top[o][e] = fmaxf(top[o][e], fabsf(__uint_as_float(raw[o][j][e])));
     };
-    auto publish = [&]() {  // the lanes' maxima into `largest`
+    auto publish = [&]() PROD_INLINE {  // the lanes' maxima into `largest`
 #pragma unroll
-        for (int o = 0; o < 2; ++o)
+        for (int o = kFirst; o < 2; ++o)
 #pragma unroll
             for (int e = 0; e < 2; ++e) atomicMax(&largest[o][2 * lane + e], __float_as_uint(top[o][e]));
     };
     float s[2][2];
     const int at = (2 * lane) ^ ((lane >> 3) & 1);  // position of the lane's first column; the second one's is at ^ 1
-    auto split_store = [&](int buf) {
+    auto split_store = [&](auto buf) PROD_INLINE {
+        const int b = buf;
 #pragma unroll
-        for (int o = 0; o < 2; ++o)
+        for (int o = kFirst; o < 2; ++o)
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 prod_u32x4 h, l;
@@ -211,26 +224,61 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
                     l[j] = __builtin_bit_cast(unsigned, prod_f16x2{(_Float16)fmaf(v0, s[o][e], -(float)hp[0]),
                                                                   (_Float16)fmaf(v1, s[o][e], -(float)hp[1])});
                 }
-                *reinterpret_cast<prod_u32x4 *>(&stage[buf][o][0][wave][(at ^ e) * 16]) = h;
-                *reinterpret_cast<prod_u32x4 *>(&stage[buf][o][1][wave][(at ^ e) * 16]) = l;
+                auto &st = o ? stage_b[b] : (b ? stage_a1 : stage_a0);
+                *reinterpret_cast<prod_u32x4 *>(&st[0][wave][(at ^ e) * 16]) = h;
+                *reinterpret_cast<prod_u32x4 *>(&st[1][wave][(at ^ e) * 16]) = l;
             }
     };
 
     prod_f32x4 acc[4][4];
-    auto clear = [&]() {
+    auto clear = [&]() PROD_INLINE {
 #pragma unroll
         for (int a = 0; a < 4; ++a)
 #pragma unroll
             for (int b = 0; b < 4; ++b) acc[a][b] = prod_f32x4{0.f, 0.f, 0.f, 0.f};
     };
-    auto multiply = [&](int buf) {
+    // kQuadFormSplit: A's halves are in the operand layout already and are copied by buffer loads with an LDS destination;
+    // wave w brings the octets 2 (w % 2) and 2 (w % 2) + 1 of half w / 2.
+    auto copy_a = [&](auto buf, int step) PROD_INLINE {
+        const int b = buf;
+        auto &st = b ? stage_a1 : stage_a0;
+        const int rows = width[0] < kProdTile ? width[0] : kProdTile, half = wave >> 1;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int octet = 2 * (wave & 1) + q, k8 = 4 * step + octet;
+            const bool in = 8 * k8 < k_end;
+            const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<uint16_t *>(p.split + half * p.split_plane + ((size_t)(in ? k8 : 0) * p.ldo + r0) * 8), 0,
+                in ? 16 * rows : 0, kRawBufferFlags);
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    rsrc, (__attribute__((address_space(3))) void *)&st[half][octet][64 * x * 16], 16,
+                    16 * (64 * x + (lane ^ ((lane >> 4) & 1))), 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);  // (the waits count the loads that follow)
+    };
+    constexpr int kLoads = 8 * (2 - kFirst);  // per wave and step
+    auto barrier = [&]() PROD_INLINE {
+        if (kSplitA) {
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kLoads) : "memory");
+            __builtin_amdgcn_sched_barrier(0);
+        } else {
+            __syncthreads();
+        }
+    };
+    auto multiply = [&](auto buf) PROD_INLINE {
+        const int bf = buf;
+        auto &sa = bf ? stage_a1 : stage_a0;
+        auto &sb = stage_b[bf];
         prod_f16x8 a[2][4], b[2][4];  // [hi, lo][tile]
 #pragma unroll
         for (int x = 0; x < 2; ++x)
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                a[x][t] = *reinterpret_cast<const prod_f16x8 *>(&stage[buf][0][x][hi][(wr * 64 + t * 16 + (lo ^ (t & 1))) * 16]);
-                b[x][t] = *reinterpret_cast<const prod_f16x8 *>(&stage[buf][1][x][hi][(wc * 64 + t * 16 + (lo ^ (t & 1))) * 16]);
+                a[x][t] = *reinterpret_cast<const prod_f16x8 *>(&sa[x][hi][(wr * 64 + t * 16 + (lo ^ (t & 1))) * 16]);
+                b[x][t] = *reinterpret_cast<const prod_f16x8 *>(&sb[x][hi][(wc * 64 + t * 16 + (lo ^ (t & 1))) * 16]);
             }
 #pragma unroll
         for (int x = 0; x < 3; ++x)  // lo hi', hi lo', hi hi'
@@ -242,20 +290,33 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
     };
     // Steps [from, to): while a step is multiplied, the next one is split and stored to the other stage and the one
     // after it is requested.
-    auto run = [&](int from, int to, auto weighed) {
-        for (int step = from; step < to; ++step) {
-            multiply(step & 1);
-            if (decltype(weighed)::value) weigh(step + 1);
-            track();
-            split_store((step & 1) ^ 1);
-            load(step + 2);
-            __syncthreads();  // the other stage is complete, and everyone is done reading this one
+    auto one = [&](auto buf, auto other, int step, auto weighed) PROD_INLINE {
+        if (kSplitA) copy_a(other, step + 1);
+        multiply(buf);
+        if (decltype(weighed)::value) weigh(step + 1);
+        track();
+        split_store(other);
+        load(step + 2);
+        barrier();  // the other stage is complete, and everyone is done reading this one
+    };
+    constexpr std::integral_constant<int, 0> even{};
+    constexpr std::integral_constant<int, 1> odd{};
+    auto run = [&](int from, int to, auto weighed) PROD_INLINE {  // kSplitA: `from` is even, and the stages are constants
+        if constexpr (kSplitA) {
+            int step = from;
+            for (; step + 1 < to; step += 2) {
+                one(even, odd, step, weighed);
+                one(odd, even, step + 1, weighed);
+            }
+            if (step < to) one(even, odd, step, weighed);  // the last of all
+        } else {
+            for (int step = from; step < to; ++step) one(step & 1, (step & 1) ^ 1, step, weighed);
         }
     };
     // kQuadForm: the accumulators' contribution to the quadratic form, and a fresh start.  Once per 1024 values of k: the
     // shorter sums lose less to rounding.
     prod_f32x4 sum[4];
-    auto contract = [&]() {
+    auto contract = [&]() PROD_INLINE {
         const int columns = width[1] < kProdTile ? width[1] : kProdTile;
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<float *>(p.E + (size_t)c0 * p.ldo + r0), 0, 4 * ((columns - 1) * p.ldo + width[0]), kRawBufferFlags);
@@ -278,8 +339,9 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
         clear();
     };
     for (int attempt = 0;; ++attempt) {
+        if (kSplitA) copy_a(even, 0);
         load(0);
-        if (MODE == kQuadForm && c0 < kProdStep) weigh(0);
+        if (kQuad && c0 < kProdStep) weigh(0);
         track();
         if (attempt == 0) {
             largest[tid >> 7][tid & 127] = 0u;
@@ -287,7 +349,7 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
             __syncthreads();
             publish();
 #pragma unroll
-            for (int o = 0; o < 2; ++o) {
+            for (int o = kFirst; o < 2; ++o) {
                 float m = fmaxf(top[o][0], top[o][1]);
 #pragma unroll
                 for (int d = 32; d > 0; d >>= 1) m = fmaxf(m, __shfl_xor(m, d));
@@ -301,18 +363,21 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
             const int o = tid >> 7;
             const unsigned m = largest[o][tid & 127];
             shift[o][tid & 127] = attempt ? product_shift(m, 14) : product_shift(m ? m : largest_of_tile[o], 4);
+            if (kSplitA && o == 0) shift[0][tid & 127] = (tid & 127) < width[0] ? p.split_shift[r0 + (tid & 127)] : 0;
         }
         __syncthreads();
 #pragma unroll
-        for (int o = 0; o < 2; ++o)
+        for (int o = kFirst; o < 2; ++o)
 #pragma unroll
             for (int e = 0; e < 2; ++e) s[o][e] = ldexpf(1.0f, shift[o][2 * lane + e]);
         clear();
-        split_store(0);
+        split_store(even);
         load(1);
-        __syncthreads();
-        if constexpr (MODE == kQuadForm) {
-            const int plain = c0 / kProdStep - 1;  // the last steps, which reach the diagonal, are weighed one step ahead
+        barrier();
+        if constexpr (kQuad) {
+            // the last steps, which reach the diagonal, are weighed one step ahead (and, to keep the number of the others even,
+            // the one before them, which changes nothing in it)
+            const int plain = c0 / kProdStep - 2;
             constexpr int kChunk = 1024 / kProdStep;
 #pragma unroll
             for (int ta = 0; ta < 4; ++ta) sum[ta] = prod_f32x4{0.f, 0.f, 0.f, 0.f};
@@ -332,14 +397,15 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
         __syncthreads();
         const int o = tid >> 7;
         const float most = ldexpf(__uint_as_float(largest[o][tid & 127]), shift[o][tid & 127]);
-        const bool bad = (tid & 127) < width[o] && (!(most <= 60000.0f) || (most < 4.0f && most > 0.0f));
+        const bool bad = o >= kFirst && (tid & 127) < width[o] && (!(most <= 60000.0f) || (most < 4.0f && most > 0.0f));
         if (!__syncthreads_or(bad)) break;
     }
 
     // Element i of a 16 x 16 accumulator: row 4 hi + i, column lo; the scales are taken out again.  Through a descriptor of
     // the tile, elements that do not exist out of range, so that the 16 old values of a column group are requested together
-    // (one at a time, each behind the store of the one before, they were a third of a short product: K = 128, 384 x 3584 on average, 21.6 -> 12.7 us).
-    if constexpr (MODE != kQuadForm) {
+    // (one at a time, each behind the store of the one before, they were a third of a short product: K = 128, 384 x 3584
+    // on average, 21.6 -> 12.7 us).
+    if constexpr (!kQuad) {
         constexpr unsigned kNone = 0xfffffff0u;
         constexpr bool kSymmetric = MODE == kAddTwiceSymmetric, kRead = MODE == kSubtract || MODE == kSubtractLower || kSymmetric;
         const int rows = width[0] < kProdTile ? width[0] : kProdTile, columns = width[1] < kProdTile ? width[1] : kProdTile;
@@ -398,7 +464,7 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
             }
         }
     } else {
-        float *red = reinterpret_cast<float *>(&stage[0][0][0][0][0]);  // [2 column halves][128 rows], free after the loop's last barrier
+        float *red = reinterpret_cast<float *>(&stage_b[0][0][0][0]);  // [2 column halves][128 rows], free after the loop's last barrier
         contract();
 #pragma unroll
         for (int ta = 0; ta < 4; ++ta)
@@ -419,9 +485,18 @@ template <int MODE>
 static void launch_product(hipStream_t stream, const float *A, int lda, int R, const float *B, int ldb, int C, int K, float *out,
                            int ldo, const float *E = nullptr, bool triangular_b = false)
 {
-    ProductArgs p = {A, B, E, out, lda, R, ldb, C, K, ldo, triangular_b ? 1 : 0};
+    ProductArgs p = {A, B, E, out, lda, R, ldb, C, K, ldo, triangular_b ? 1 : 0, nullptr, 0, nullptr};
     const int blocks = (product_blocks<MODE>(R, C) + 7) / 8 * 8;
     hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)(blocks * kProdBlock * kProdBlock)), dim3(256), 0, stream, p);
+}
+
+// kQuadFormSplit: A comes as `split` (see ProductArgs), E holds the same values in binary32.
+static void launch_quad_form_split(hipStream_t stream, const uint16_t *split, size_t plane, const int *shift, int R, const float *B,
+                                   int ldb, int C, int K, float *out, int ldo, const float *E)
+{
+    ProductArgs p = {E, B, E, out, ldo, R, ldb, C, K, ldo, 0, split, plane, shift};
+    const int blocks = (product_blocks<kQuadFormSplit>(R, C) + 7) / 8 * 8;
+    hipLaunchKernelGGL((product_kernel<kQuadFormSplit>), dim3((unsigned)(blocks * kProdBlock * kProdBlock)), dim3(256), 0, stream, p);
 }
 
 }  // namespace bcq

@@ -31,6 +31,7 @@ struct Tying {
     int8_t label[kMaxBits];
     int nchoice;
     int choice[16];
+    unsigned long long nibbles;  // up to four bits: nearest choice of every integer
 };
 
 // All partitions of the planes 1..n into q non-empty classes; classes ordered by their smallest
@@ -70,18 +71,22 @@ static std::vector<Tying> all_tyings(int n, int q)
         make_tying_plan(n, q, t.label, false, &plan);
         t.nchoice = plan.nchoice;
         std::copy(plan.choice, plan.choice + plan.nchoice, t.choice);
+        for (int w = 0; n <= 4 && w < 1 << n; ++w) t.nibbles |= (unsigned long long)nearest_choice(w, t.choice, t.nchoice) << (4 * w);
         out.push_back(t);
     }
     return out;
 }
 
-// Eq. 5 step 1 and Eq. 6 for one weight, in binary64.
-__device__ __forceinline__ int quant_int(double w, double S, double qbias, int n_bits, const int *choice, int nchoice)
+// Eq. 5 step 1 for one weight, in binary64: clamp(rne(x / S)), x = w - qbias.  The product with inv_s = 1 / S is off by less
+// than 2^-44 for the up to 2^8 steps of the grid, so it rounds to the same integer as the quotient unless it lies within
+// 2^-30 of a half; then the division is carried out.
+__device__ __forceinline__ int linear_int(double x, double S, double inv_s, double top)
 {
-    double v = rint((w - qbias) / S);  // round half to even
-    const double top = (double)((1 << n_bits) - 1);
+    const double t = x * inv_s;
+    double v = rint(t);  // round half to even
+    if (__builtin_expect(!(fabs(t - v) < 0.5 - 0x1p-30), 0)) v = rint(x / S);
     v = v < 0.0 ? 0.0 : (v > top ? top : v);
-    return nearest_choice((int)v, choice, nchoice);
+    return (int)v;
 }
 
 // ---------------------------------------------------------------------------------
@@ -380,22 +385,64 @@ __device__ __forceinline__ double grid_scale(double wmin, double wmax, int n_bit
     return lo + (hi - lo) * ((double)(g + 1) / ((double)grid + 1.0));
 }
 
-// Dt[k][m] = S' W_q + qbias - w for one candidate (grid point g, tying t); zeros in the pad rows.
-__global__ void delta_kernel(int M, int Mp, int N, int n_bits, int g, int grid, Tying t,
-                             const float *__restrict__ Wt, const float *__restrict__ wmin,
-                             const float *__restrict__ wmax, float *__restrict__ Dt)
+// Exponent of the power of two by which a row's d are scaled before they are split: |d| stays below twice the row's range,
+// which goes to at most 2^15.
+__global__ void split_shift_kernel(int M, int Mp, const float *__restrict__ wmin, const float *__restrict__ wmax,
+                                   int *__restrict__ shift)
 {
     const int m = blockIdx.x * blockDim.x + threadIdx.x;
-    const int k = blockIdx.y;
-    if (m >= Mp) return;
-    float d = 0.0f;
-    if (m < M) {
-        const double lo = wmin[m], S = grid_scale(lo, wmax[m], n_bits, g, grid);
-        const double w = Wt[(size_t)k * Mp + m];
-        const int wq = quant_int(w, S, lo, n_bits, t.choice, t.nchoice);
-        d = (float)(S * wq + lo - w);
+    if (m < Mp) shift[m] = m < M ? product_shift(__float_as_uint(wmax[m] - wmin[m]), 13) : 0;
+}
+
+// Dt[k][m] = S' W_q + qbias - w for one candidate (grid point g, tying t), from Wt (SPLIT = false) or from W; zeros in the
+// pad rows.  With SPLIT the same values also go to `split` as two binary16 halves in the operand layout of the matrix
+// instructions, [hi, lo][k / 8][m][k % 8], so that the product does not have to convert them once per column tile.  A
+// workgroup takes 64 rows by 32 columns, a thread eight columns of a row.  Bound: memory.  7168 x 7168: 218 us per
+// candidate (a division and a scan of the representable set per weight, nothing split) -> 111 us with the split, 617 MB.
+template <bool SPLIT>
+__global__ __launch_bounds__(256) void delta_kernel(int M, int Mp, int N, int n_bits, int g, int grid, Tying t,
+                                                    const float *__restrict__ W, const float *__restrict__ wmin,
+                                                    const float *__restrict__ wmax, float *__restrict__ Dt,
+                                                    const int *__restrict__ shift, uint16_t *__restrict__ split, size_t plane)
+{
+    const int m = blockIdx.x * 64 + (threadIdx.x & 63), k0 = 8 * (blockIdx.y * 4 + (threadIdx.x >> 6));
+    if (m >= Mp || k0 >= N) return;
+    float w[8], d[8];
+    if (SPLIT) {  // N is a multiple of 8, W on 16 bytes
+        const prod_f32x4 *src = reinterpret_cast<const prod_f32x4 *>(W + (size_t)(m < M ? m : 0) * N + k0);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) w[j] = src[j >> 2][j & 3];
+    } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) w[j] = k0 + j < N ? W[(size_t)(k0 + j) * Mp + m] : 0.0f;
     }
-    Dt[(size_t)k * Mp + m] = d;
+    if (m < M) {
+        const double lo = wmin[m], S = grid_scale(lo, wmax[m], n_bits, g, grid), inv_s = 1.0 / S, top = (double)((1 << n_bits) - 1);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int lin = linear_int((double)w[j] - lo, S, inv_s, top);
+            const int wq = n_bits <= 4 ? (int)(t.nibbles >> (4 * lin)) & 15 : nearest_choice(lin, t.choice, t.nchoice);
+            d[j] = (float)(S * wq + lo - (double)w[j]);
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) d[j] = 0.0f;
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        if (k0 + j < N) Dt[(size_t)(k0 + j) * Mp + m] = d[j];
+    if (SPLIT) {
+        const float s = ldexpf(1.0f, shift[m]);
+        prod_f16x8 hi, lo;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            hi[j] = (_Float16)(d[j] * s);
+            lo[j] = (_Float16)fmaf(d[j], s, -(float)hi[j]);
+        }
+        uint16_t *const at = split + ((size_t)(k0 >> 3) * Mp + m) * 8;
+        *reinterpret_cast<prod_f16x8 *>(at) = hi;
+        *reinterpret_cast<prod_f16x8 *>(at + plane) = lo;
+    }
 }
 
 // err = sum of the row's tile partials, in tile order (each is half of its part of d H d^T: H = 2 X X^T); keep the
@@ -428,15 +475,25 @@ hipError_t launch_quant_search(int M, int N, int n_bits, int q, int grid, const 
                        w.Wt, w.Dt);
     hipLaunchKernelGGL(row_range_final_kernel, dim3((M + 63) / 64), dim3(64), 0, stream, M, w.Mp, chunks, w.Dt, w.wmin,
                        w.wmax);
+    // Split beforehand (in place of Wt, which the row ranges were the last to read) where rows can be read eight weights at a
+    // time; else the product splits what it reads.
+    const bool split = N % 8 == 0 && (reinterpret_cast<uintptr_t>(W) & 15) == 0;
+    auto *halves = reinterpret_cast<uint16_t *>(w.Wt);
+    auto *shift = reinterpret_cast<int *>(w.Err);
+    const size_t plane = (size_t)N * w.Mp;
+    if (split) hipLaunchKernelGGL(split_shift_kernel, dim3((w.Mp + 255) / 256), dim3(256), 0, stream, M, w.Mp, w.wmin, w.wmax, shift);
     const std::vector<Tying> tyings = all_tyings(n_bits, q);
     bool first = true;
     for (int g = 0; g < grid; ++g)
         for (const Tying &t : tyings) {
-            hipLaunchKernelGGL(delta_kernel, dim3((w.Mp + 255) / 256, N), dim3(256), 0, stream, M, w.Mp, N, n_bits, g,
-                               grid, t, w.Wt, w.wmin, w.wmax, w.Dt);
+            hipLaunchKernelGGL((split ? delta_kernel<true> : delta_kernel<false>), dim3((w.Mp + 63) / 64, (N + 31) / 32), dim3(256), 0,
+                               stream, M, w.Mp, N, n_bits, g, grid, t, split ? W : w.Wt, w.wmin, w.wmax, w.Dt, shift, halves, plane);
             // d H d^T / 2 row by row: sum_l Dt[l][m] sum_{k <= l} w_kl H[k][l] Dt[k][m], w = 1/2 on the diagonal
             // (only the upper triangle of H is read), one partial per tile of 128 values of l
-            launch_product<kQuadForm>(stream, w.Dt, w.Mp, w.Mp, H, N, N, N, w.part, w.Mp, w.Dt);
+            if (split)
+                launch_quad_form_split(stream, halves, plane, shift, w.Mp, H, N, N, N, w.part, w.Mp, w.Dt);
+            else
+                launch_product<kQuadForm>(stream, w.Dt, w.Mp, w.Mp, H, N, N, N, w.part, w.Mp, w.Dt);
             hipLaunchKernelGGL(keep_best_kernel, dim3((M + 255) / 256), dim3(256), 0, stream, M, w.Mp, n_bits, w.ntile, g,
                                grid, first ? 1 : 0, t, w.part, w.wmin, w.wmax, w.best, S, qbias, labels);
             first = false;
@@ -477,8 +534,7 @@ __global__ void gptq_tables_kernel(int M, int n_bits, int q, const int8_t *__res
 // their 16 columns.  A wave takes eight rows; at 7168 rows that is one wave on nearly every SIMD.  (One thread per row,
 // as before, left 112 waves on the chip and took 193 us per block of a 7168-row layer; this takes 29.)
 // To keep the chain short, the two divisions of a decision are multiplications by reciprocals with the same results:
-//   * rint((w - qbias) / S): the binary64 product with 1 / S is off by less than 2^-44 for the up to 2^8 steps of the
-//     grid, so it rounds to the same integer unless it lies within 2^-30 of a half; then the division is carried out;
+//   * rint((w - qbias) / S): see linear_int;
 //   * err / U[j][j] in binary32: quotient, remainder and correction with the rounded reciprocal (Markstein's method),
 //     which gives the correctly rounded quotient.
 // and Eq. 6 is a table look-up.  U's rows are staged in LDS such that the 16 factors of a lane for column c, those of
@@ -548,11 +604,7 @@ __global__ __launch_bounds__(256) void gptq_block_kernel(int M, int Mp, int N, i
             for (int k = 0; k < 4; ++k) u[k] = *reinterpret_cast<const prod_f32x4 *>(&Us[c][k][l][0]);
             const prod_f32x2 d = diag[c];
             const double x = (double)w[0] - b;
-            const double t = x * inv_s;
-            double v = rint(t);  // round half to even
-            if (__builtin_expect(!(fabs(t - v) < 0.5 - 0x1p-30), 0)) v = rint(x / s);
-            v = v < 0.0 ? 0.0 : (v > top ? top : v);
-            const int lin = (int)v;
+            const int lin = linear_int(x, s, inv_s, top);
             const int wq = NIBBLES ? (int)(nib >> (4 * lin)) & 15 : table[row][lin];
             const float qv = (float)(s * wq + b);
             const float a = w[0] - qv;

@@ -126,6 +126,38 @@ def test_search(M, N, n, q, grid):
     assert np.allclose(e_g, e_o, rtol=1e-4, atol=0), np.abs(e_g / e_o - 1).max()
 
 
+@pytest.mark.parametrize("M,N,n,q,grid,shift", [(5, 132, 3, 2, 3, 0), (130, 136, 3, 2, 2, 0), (33, 136, 4, 3, 2, 1),
+                                                (3, 1288, 3, 3, 2, 0), (129, 40, 6, 2, 2, 0), (4, 8, 2, 1, 4, 0)])
+def test_search_paths(M, N, n, q, grid, shift):
+    """Both ways of feeding the quadratic form: split into halves beforehand (columns a multiple of 8, weights on 16 bytes) and
+    split by the product, at the edges of tiles, chunks (1024 columns) and octets, against the oracle; a constant row (no
+    range to scale by) and a row of the smallest weights; the lower triangle of H is not read."""
+    W32, H32 = _layer(M, N, seed=700 + N + n)
+    W32[0] = np.float32(0.02)
+    if M > 1:
+        W32[1] *= np.float32(2.0 ** -60)
+    S_o, b_o, p_o, e_o = quantizer.search(W32, H32, n, q, grid)
+    flat = torch.zeros(M * N + 4, dtype=torch.float32, device="cuda")
+    flat[shift: shift + M * N] = _dev(W32).reshape(-1)
+    H_up = _dev(H32)
+    H_up[_dev(np.tril(np.ones((N, N), dtype=bool), -1))] = float("nan")
+    S = torch.empty(M, dtype=torch.float32, device="cuda")
+    b = torch.empty(M, dtype=torch.float32, device="cuda")
+    lab = torch.empty((M, n), dtype=torch.int8, device="cuda")
+    err = torch.empty(M, dtype=torch.float32, device="cuda")
+    ws = torch.empty(bcq.quant_workspace_bytes(M, N), dtype=torch.uint8, device="cuda")
+    ws.fill_(0xff)
+    bcq.quant_search(M, N, n, q, grid, flat[shift:], H_up, S, b, lab, err, ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(b.cpu().numpy(), b_o.astype(np.float32))
+    e_g = err.cpu().numpy()
+    assert e_g[0] == 0.0 and np.allclose(e_g, e_o, rtol=1e-4, atol=0), np.abs(e_g / e_o - 1).max()
+    parts = fuse.all_partitions(n, q)
+    S_g, lab_g = S.cpu().numpy(), lab.cpu().numpy()
+    same = sum(_partition_of(lab_g[m]) == parts[p_o[m]] and S_g[m] == np.float32(S_o[m]) for m in range(M))
+    assert same >= 0.9 * M
+
+
 @pytest.mark.parametrize("M,N,n,q", [(70, 320, 3, 2), (40, 256, 4, 3), (9, 96, 3, 3)])
 def test_gptq_pass(M, N, n, q):
     W32, H32 = _layer(M, N, seed=200 + N + n)
