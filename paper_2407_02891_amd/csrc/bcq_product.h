@@ -75,6 +75,10 @@ struct ProductArgs {
     const uint16_t *split;  // kQuadFormSplit: A in two halves, [hi, lo][k / 8][row (pitch ldo)][8 values of k]; K a multiple of 8
     size_t split_plane;     // values per half
     const int *split_shift; // exponent of each row's scale
+    // several products of one shape in a launch (blockIdx.y): operands and result of product y lie y * stride floats on; the
+    // last one may have fewer columns, columns_end - y * columns_step of them, and with k_is_columns as many values of k
+    size_t stride;
+    int columns_end, columns_step, k_is_columns;
 };
 
 // Number of workgroups, and the tile of one.  Blocks of 4 x 4 tiles are numbered row by row (only those on and above the
@@ -149,6 +153,14 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lo = lane & 15, hi = lane >> 4, wr = wave >> 1, wc = wave & 1;
+    if (MODE == kStore || MODE == kStoreNegated) {
+        p.A += blockIdx.y * p.stride;
+        p.B += blockIdx.y * p.stride;
+        p.out += blockIdx.y * p.stride;
+        const int left = p.columns_end - (int)blockIdx.y * p.columns_step;
+        if (left < p.C) p.C = left;
+        if (p.k_is_columns) p.K = p.C;
+    }
     int tile_row, tile_col;
     if (!product_tile<MODE>(blockIdx.x, gridDim.x, p.R, p.C, &tile_row, &tile_col)) return;
     const int r0 = tile_row * kProdTile, c0 = tile_col * kProdTile;
@@ -483,18 +495,29 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
 
 template <int MODE>
 static void launch_product(hipStream_t stream, const float *A, int lda, int R, const float *B, int ldb, int C, int K, float *out,
-                           int ldo, const float *E = nullptr, bool triangular_b = false)
+                           int ldo, const float *E = nullptr)
 {
-    ProductArgs p = {A, B, E, out, lda, R, ldb, C, K, ldo, triangular_b ? 1 : 0, nullptr, 0, nullptr};
+    ProductArgs p = {A, B, E, out, lda, R, ldb, C, K, ldo, 0, nullptr, 0, nullptr, 0, C, 0, 0};
     const int blocks = (product_blocks<MODE>(R, C) + 7) / 8 * 8;
     hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)(blocks * kProdBlock * kProdBlock)), dim3(256), 0, stream, p);
+}
+
+// `count` products kStore (with B[k][c] = 0 for k > c) or kStoreNegated of size x size x size, see ProductArgs.
+template <int MODE>
+static void launch_products(hipStream_t stream, int count, size_t stride, int columns_end, const float *A, const float *B, float *out,
+                            int pitch, int size)
+{
+    ProductArgs p = {A, B, nullptr, out, pitch, size, pitch, size, size, pitch, MODE == kStore ? 1 : 0, nullptr, 0, nullptr,
+                     stride, columns_end, 2 * size, MODE == kStore ? 1 : 0};
+    const int blocks = (product_blocks<MODE>(size, size) + 7) / 8 * 8;
+    hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)(blocks * kProdBlock * kProdBlock), (unsigned)count), dim3(256), 0, stream, p);
 }
 
 // kQuadFormSplit: A comes as `split` (see ProductArgs), E holds the same values in binary32.
 static void launch_quad_form_split(hipStream_t stream, const uint16_t *split, size_t plane, const int *shift, int R, const float *B,
                                    int ldb, int C, int K, float *out, int ldo, const float *E)
 {
-    ProductArgs p = {E, B, E, out, ldo, R, ldb, C, K, ldo, 0, split, plane, shift};
+    ProductArgs p = {E, B, E, out, ldo, R, ldb, C, K, ldo, 0, split, plane, shift, 0, C, 0, 0};
     const int blocks = (product_blocks<kQuadFormSplit>(R, C) + 7) / 8 * 8;
     hipLaunchKernelGGL((product_kernel<kQuadFormSplit>), dim3((unsigned)(blocks * kProdBlock * kProdBlock)), dim3(256), 0, stream, p);
 }

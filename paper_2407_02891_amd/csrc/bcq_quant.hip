@@ -178,10 +178,13 @@ __global__ void diag_mean_kernel(int N, const float *__restrict__ H, float damp,
 __global__ void damped_copy_kernel(int N, const float *__restrict__ H, const float *__restrict__ lambda,
                                    float *__restrict__ Hw)
 {
-    const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= (size_t)N * N) return;
-    const int i = (int)(gid / N), j = (int)(gid - (size_t)i * N);
-    Hw[gid] = H[gid] + (i == j ? *lambda : 0.0f);
+    const int i = blockIdx.y, j = 4 * (blockIdx.x * blockDim.x + threadIdx.x);  // N is a multiple of 4
+    if (j >= N) return;
+    prod_f32x4 v = *reinterpret_cast<const prod_f32x4 *>(H + (size_t)i * N + j);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (i == j + k) v[k] += *lambda;
+    *reinterpret_cast<prod_f32x4 *>(Hw + (size_t)i * N + j) = v;
 }
 
 // Diagonal block [r0, r0 + b): writes the blocks V = R^-1 of U and V^T of Ut, with D = R R^T, R upper triangular.  V is all
@@ -259,20 +262,24 @@ __global__ __launch_bounds__(256) void factor_diag_kernel(int N, int r0, int b, 
     }
 }
 
-// dst[c][r] = src[r][c] for a rows x cols block.
-__global__ void transpose_block_kernel(int rows, int cols, const float *__restrict__ src, int lds, float *__restrict__ dst,
-                                       int ldd)
+// dst[c][r] = src[r][c] for size x size blocks of a matrix of pitch N, block z of them z * stride floats on, the last one
+// with columns_end - 2 size z columns.
+__global__ void transpose_blocks_kernel(int size, int N, size_t stride, int columns_end, const float *__restrict__ src,
+                                        float *__restrict__ dst)
 {
     __shared__ float tile[32][33];
+    src += blockIdx.z * stride;
+    dst += blockIdx.z * stride;
+    const int left = columns_end - 2 * size * (int)blockIdx.z, cols = left < size ? left : size;
     const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
     for (int i = threadIdx.y; i < 32; i += blockDim.y) {
         const int r = r0 + i, c = c0 + threadIdx.x;
-        tile[i][threadIdx.x] = (r < rows && c < cols) ? src[(size_t)r * lds + c] : 0.0f;
+        tile[i][threadIdx.x] = c < cols ? src[(size_t)r * N + c] : 0.0f;  // size is a multiple of 32
     }
     __syncthreads();
     for (int i = threadIdx.y; i < 32; i += blockDim.y) {
         const int c = c0 + i, r = r0 + threadIdx.x;
-        if (r < rows && c < cols) dst[(size_t)c * ldd + r] = tile[threadIdx.x][i];
+        if (c < cols) dst[(size_t)c * N + r] = tile[threadIdx.x][i];
     }
 }
 
@@ -282,22 +289,23 @@ size_t quant_factor_workspace_bytes(int N)
     return (floats * 4 + 255) / 256 * 256;
 }
 
-// Off-diagonal blocks of U = R^-1 for the rows / columns [lo, hi) (the diagonal blocks are in place):
-// with the range cut at a block boundary, U12 = -U11 (R12 U22), both factors from the two halves.
-static void invert_range(hipStream_t stream, int N, int lo, int hi, const float *Rt, float *U, float *Ut, float *T)
+// Off-diagonal blocks of U = R^-1 (the diagonal blocks are in place), in neighbouring pairs of 1, 2, 4, ... blocks: with
+// the rows / columns [lo, mid) and [mid, hi) of a pair done, U12 = -U11 (R12 U22).  All pairs of one size are one launch
+// per product (28 of the 128-column ones at 7168, at 11 us each they were most of the inverse: 2.4 -> 1.1 ms).  T = R12 U22
+// takes the place of the same block of a matrix that is free.
+static void invert_blocks(hipStream_t stream, int N, const float *Rt, float *U, float *Ut, float *T)
 {
-    const int nblk = (hi - lo + kFactorBlock - 1) / kFactorBlock;
-    if (nblk <= 1) return;
-    const int mid = lo + (nblk / 2) * kFactorBlock;
-    invert_range(stream, N, lo, mid, Rt, U, Ut, T);
-    invert_range(stream, N, mid, hi, Rt, U, Ut, T);
-    const int rows = mid - lo, cols = hi - mid;
-    // T[i][c] = sum_m R[lo + i][mid + m] U[mid + m][mid + c]
-    launch_product<kStore>(stream, Rt + (size_t)mid * N + lo, N, rows, U + (size_t)mid * N + mid, N, cols, cols, T, cols, nullptr, true);
-    // U[lo + r][mid + c] = -sum_j U[lo + r][lo + j] T[j][c]
-    launch_product<kStoreNegated>(stream, Ut + (size_t)lo * N + lo, N, rows, T, cols, cols, rows, U + (size_t)lo * N + mid, N);
-    hipLaunchKernelGGL(transpose_block_kernel, dim3((cols + 31) / 32, (rows + 31) / 32), dim3(32, 8), 0, stream, rows, cols,
-                       U + (size_t)lo * N + mid, N, Ut + (size_t)mid * N + lo, N);
+    for (int size = kFactorBlock; size < N; size *= 2) {
+        const int count = (N - size + 2 * size - 1) / (2 * size);  // pairs whose second half is not empty
+        const size_t stride = (size_t)2 * size * ((size_t)N + 1);
+        const size_t above = size, below = (size_t)size * N;  // block (lo, mid), block (mid, lo) of the first pair
+        // T[i][c] = sum_m R[lo + i][mid + m] U[mid + m][mid + c]
+        launch_products<kStore>(stream, count, stride, N - size, Rt + below, U + below + above, T + above, N, size);
+        // U[lo + r][mid + c] = -sum_j U[lo + r][lo + j] T[j][c]
+        launch_products<kStoreNegated>(stream, count, stride, N - size, Ut, T + above, U + above, N, size);
+        hipLaunchKernelGGL(transpose_blocks_kernel, dim3(size / 32, size / 32, count), dim3(32, 8), 0, stream, size, N, stride,
+                           N - size, U + above, Ut + below);
+    }
 }
 
 hipError_t launch_quant_factor(int N, float damp, const float *H, float *U, void *workspace, hipStream_t stream)
@@ -306,8 +314,7 @@ hipError_t launch_quant_factor(int N, float damp, const float *H, float *U, void
     float *Rt = Hw + (size_t)N * N, *Ut = Rt + (size_t)N * N;
     float *lambda = Ut + (size_t)N * N;
     hipLaunchKernelGGL(diag_mean_kernel, dim3(1), dim3(256), 0, stream, N, H, damp, lambda);
-    hipLaunchKernelGGL(damped_copy_kernel, dim3((unsigned)(((size_t)N * N + 255) / 256)), dim3(256), 0, stream, N, H,
-                       lambda, Hw);
+    hipLaunchKernelGGL(damped_copy_kernel, dim3((N / 4 + 255) / 256, N), dim3(256), 0, stream, N, H, lambda, Hw);
     hipError_t e = launch_fill_zero(U, (size_t)N * N * 4, stream);
     if (e != hipSuccess) return e;
     e = launch_fill_zero(Ut, (size_t)N * N * 4, stream);
@@ -336,7 +343,7 @@ hipError_t launch_quant_factor(int N, float damp, const float *H, float *U, void
         p1 = p0;
     }
     // U = R^-1: Hw is free now and holds the intermediate products
-    invert_range(stream, N, 0, N, Rt, U, Ut, Hw);
+    invert_blocks(stream, N, Rt, U, Ut, Hw);
     return hipGetLastError();
 }
 
