@@ -95,8 +95,14 @@ def _ptr(t):
 
 
 def _stream(stream):
+    """hipStream_t of `stream`, of torch's current stream if it is None.  The current one is asked for as a number:
+    torch.cuda.current_stream() builds an object around it, 2.8 us of the 7.1 us a small GEMV call took from Python
+    (0.3 us this way; the call is then as long as its kernel, 4.5 us on 1024 x 8192)."""
     if stream is None:
         import torch
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:
+            return raw(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
