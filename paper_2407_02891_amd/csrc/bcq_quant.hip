@@ -195,12 +195,15 @@ __global__ void damped_copy_kernel(int N, const float *__restrict__ H, const flo
 // unit upper triangular, the product of the row operations, for which M D M^T = diag(d): V = diag(d)^-1/2 M.  D is
 // symmetric, so x[i][j] is x[j][i] and the one thing a step has to hand round is row j: 128 values through LDS, one barrier.
 // One workgroup of 256 threads with the 128 x 128 block in registers, thread (ty, tx) owning the elements (ty + 16 a, tx +
-// 16 c).  What bounds it is that chain, 128 times (write, barrier, read, reciprocal, 8 to 64 multiply-adds): 245 us before
-// (the block and its inverse in LDS, the inverse one column per thread), now 50.
+// 16 c).  What bounds it is that chain (write, barrier, read, reciprocal, 8 to 64 multiply-adds), so two rows j, j - 1 are
+// handed round at a time: every thread brings the second one up to date for itself, and the next two are written before the
+// multiply-adds of the other rows.  A column that becomes -f starts from 0 with a 1 in the row for it.  The same operations
+// in the same order as with one row: the results are the same bits.  A block takes 39 us; with one row
+// at a time 50, with the block and its inverse in LDS and the inverse one column per thread 245.
 __global__ __launch_bounds__(256) void factor_diag_kernel(int N, int r0, int b, const float *__restrict__ Hw,
                                                           float *__restrict__ U, float *__restrict__ Ut)
 {
-    __shared__ __attribute__((aligned(16))) float row[2][16][8];  // row j: element l at [l % 16][l / 16]
+    __shared__ __attribute__((aligned(16))) float rows[2][2][16][8];  // [buffer][j odd, even]: element l at [l % 16][l / 16]
     __shared__ float pivot[kFactorBlock];
     __shared__ float V[kFactorBlock][kFactorBlock + 1];
     const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
@@ -212,33 +215,56 @@ __global__ __launch_bounds__(256) void factor_diag_kernel(int N, int r0, int b, 
             const int i = ty + 16 * a, l = tx + 16 * c;  // beyond b: the identity, which changes nothing
             x[a][c] = i < b && l < b ? Hw[(size_t)(r0 + i) * N + r0 + l] : (i == l ? 1.0f : 0.0f);
         }
+    auto hand_round = [&](const float (&v)[8], int jj) {  // rows jj and jj - 1 (jj odd) of a group of 16
+        if (ty >> 1 == jj >> 1) {
+            float (&to)[16][8] = rows[(jj >> 1) & 1][~ty & 1];
+            *reinterpret_cast<prod_f32x4 *>(&to[tx][0]) = prod_f32x4{v[0], v[1], v[2], v[3]};
+            *reinterpret_cast<prod_f32x4 *>(&to[tx][4]) = prod_f32x4{v[4], v[5], v[6], v[7]};
+        }
+    };
+    auto reciprocal = [](float d) { return d > 0.0f ? 1.0f / d : __builtin_nanf(""); };  // not positive definite: NaNs from here on
     auto eliminate = [&](auto group) {  // the rows j = 16 g + 15 .. 16 g
         constexpr int g = decltype(group)::value;
 #pragma unroll 1
-        for (int jj = 15; jj >= 0; --jj) {
-            float (&buf)[16][8] = row[jj & 1];
-            if (ty == jj) {
-#pragma unroll
-                for (int c = 0; c < 8; ++c) buf[tx][c] = x[g][c];
-            }
+        for (int jj = 15; jj > 0; jj -= 2) {
+            const float (&p)[16][8] = rows[(jj >> 1) & 1][0], (&q)[16][8] = rows[(jj >> 1) & 1][1];
             __syncthreads();
-            const prod_f32x4 l0 = *reinterpret_cast<const prod_f32x4 *>(&buf[tx][0]), l1 = *reinterpret_cast<const prod_f32x4 *>(&buf[tx][4]);
-            const prod_f32x4 i0 = *reinterpret_cast<const prod_f32x4 *>(&buf[ty][0]), i1 = *reinterpret_cast<const prod_f32x4 *>(&buf[ty][4]);
-            const float d = buf[jj][g];
-            const float inv = d > 0.0f ? 1.0f / d : __builtin_nanf("");  // not positive definite: NaNs from here on
-            if (tid == 0) pivot[16 * g + jj] = d;
+            float pl[8], ql[8], pi[8], qi[8];
 #pragma unroll
-            for (int a = 0; a <= g; ++a) {
-                const float xi = a < 4 ? i0[a & 3] : i1[a & 3];
-                const bool above = a < g || ty < jj;  // i < j
-                const float f = above ? xi * inv : 0.0f;
-                const float at_pivot = above ? -f : x[a][g];
+            for (int k = 0; k < 8; k += 4) {
+                const prod_f32x4 v0 = *reinterpret_cast<const prod_f32x4 *>(&p[tx][k]), v1 = *reinterpret_cast<const prod_f32x4 *>(&q[tx][k]);
+                const prod_f32x4 v2 = *reinterpret_cast<const prod_f32x4 *>(&p[ty][k]), v3 = *reinterpret_cast<const prod_f32x4 *>(&q[ty][k]);
 #pragma unroll
-                for (int c = 0; c < 8; ++c) x[a][c] = fmaf(-f, c < 4 ? l0[c & 3] : l1[c & 3], x[a][c]);
-                if (tx == jj) x[a][g] = at_pivot;
+                for (int e = 0; e < 4; ++e) { pl[k + e] = v0[e]; ql[k + e] = v1[e]; pi[k + e] = v2[e]; qi[k + e] = v3[e]; }
             }
+            const float d1 = p[jj][g], cross = p[jj - 1][g];
+            const float inv1 = reciprocal(d1), f = cross * inv1;
+            const float d2 = fmaf(-f, cross, q[jj - 1][g]), inv2 = reciprocal(d2);
+            if (tid == 0) { pivot[16 * g + jj] = d1; pivot[16 * g + jj - 1] = d2; }
+            const bool at1 = tx == jj, at2 = tx == jj - 1;  // (in column group g)
+            pl[g] = at1 ? 1.0f : at2 ? 0.0f : pl[g];
+            ql[g] = at1 ? 0.0f : ql[g];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) ql[c] = fmaf(-f, pl[c], ql[c]);
+            ql[g] = at2 ? 1.0f : ql[g];
+            auto update = [&](int a) {
+                float f1 = pi[a] * inv1, f2 = fmaf(-f, pi[a], qi[a]) * inv2;
+                if (a == g) {
+                    f1 = ty < jj ? f1 : 0.0f;  // i < j
+                    f2 = ty < jj - 1 ? f2 : 0.0f;
+                }
+                x[a][g] = at1 || at2 ? 0.0f : x[a][g];  // (in the rows from j on nobody reads it any more)
+#pragma unroll
+                for (int c = 0; c < 8; ++c) x[a][c] = fmaf(-f2, ql[c], fmaf(-f1, pl[c], x[a][c]));
+            };
+            update(g);
+            if (jj > 1) hand_round(x[g], jj - 2);
+#pragma unroll
+            for (int a = g - 1; a >= 0; --a) update(a);
         }
+        if (g > 0) hand_round(x[g > 0 ? g - 1 : 0], 15);
     };
+    hand_round(x[7], 15);
     eliminate(std::integral_constant<int, 7>{}); eliminate(std::integral_constant<int, 6>{});
     eliminate(std::integral_constant<int, 5>{}); eliminate(std::integral_constant<int, 4>{});
     eliminate(std::integral_constant<int, 3>{}); eliminate(std::integral_constant<int, 2>{});
@@ -255,11 +281,12 @@ __global__ __launch_bounds__(256) void factor_diag_kernel(int N, int r0, int b, 
         }
     }
     __syncthreads();
-    for (int e = tid; e < b * b; e += 256) {
-        const int i = e / b, l = e - i * b;
-        U[(size_t)(r0 + i) * N + r0 + l] = V[i][l];
-        Ut[(size_t)(r0 + i) * N + r0 + l] = V[l][i];
-    }
+    const int l = tid & (kFactorBlock - 1);
+    for (int i = tid / kFactorBlock; i < b; i += 256 / kFactorBlock)
+        if (l < b) {
+            U[(size_t)(r0 + i) * N + r0 + l] = V[i][l];
+            Ut[(size_t)(r0 + i) * N + r0 + l] = V[l][i];
+        }
 }
 
 // dst[c][r] = src[r][c] for size x size blocks of a matrix of pitch N, block z of them z * stride floats on, the last one
