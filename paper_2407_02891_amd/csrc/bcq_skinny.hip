@@ -733,8 +733,10 @@ hipError_t launch_skinny(const Geom &g, const void *packed, const uint16_t *X, i
     // on a handful of tiles (512 x 512, 32 columns 7.3 / 8.2: its start-up) and where it needs more passes on a layer
     // whose weights are not what is waited for (four planes, 64 columns: 4096 x 4096 26.9 / 31.8, 7168 x 28672 131 / 126).
     const int most = wide_columns(g);
+    // Its byte offsets into X are 32 bits for the whole batch; the kernels here need that per pass only.
+    const bool in_reach = (unsigned long long)batch * (unsigned)ldx < 0x7ffffff0ull;
     const bool one_pass = batch <= most || all_tiles >= 8192 || sub > 1;
-    const bool wide = most > 16 && ver == 0 && (tuning.waves == 8 || (tuning.waves == 0 && g.nslice > 1 && all_tiles >= 128 && one_pass));
+    const bool wide = most > 16 && ver == 0 && in_reach && (tuning.waves == 8 || (tuning.waves == 0 && g.nslice > 1 && all_tiles >= 128 && one_pass));
     // The kernels here: up to 64 columns in one pass with alpha folded into A and one scaling group per block, else 16.
     const int narrow = sub == 1 && ver != 2 ? (batch > 32 ? 64 : batch > 16 ? 32 : 16) : 16;
     for (int col0 = 0; col0 < batch;) {

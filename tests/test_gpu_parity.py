@@ -564,6 +564,20 @@ def test_wide_kernel_edges(workgroups, M, N, q, offset, group, batch):
         bcq.set_option("waves", 0)
 
 
+def test_far_apart_rows_of_many_vectors():
+    """17 vectors so far apart that only 16 of them fit 32-bit byte offsets: taken in passes of 16."""
+    M, N, ldx, batch = 2048, 1024, 2 ** 27 - 8, 17
+    L = bcq_synth.make_exact_layer(M, N, 2, group=64, offset=False, batch=batch, seed=5)
+    pl = U.upload_and_pack(L, max_batch=batch)
+    expect = ref.gemm(L.planes, L.alpha, L.offset, L.x).astype(np.float16).astype(np.float64)
+    X = torch.empty((batch - 1) * ldx + N, dtype=torch.float16, device="cuda")
+    X.as_strided((batch, N), (ldx, 1)).copy_(U.x_dev(L))
+    Y = torch.zeros((batch, M), dtype=torch.float16, device="cuda")
+    bcq.gemm_skinny(pl.desc, pl.packed, X, ldx, Y, M, batch, pl.workspace)
+    torch.cuda.synchronize()
+    assert np.array_equal(Y.cpu().numpy().astype(np.float64), expect)
+
+
 def test_wide_batch_exact_and_strided():
     L = bcq_synth.make_exact_layer(150, 3072, 3, group=128, offset=True, batch=40, seed=77)
     pl = U.upload_and_pack(L, max_batch=40)
