@@ -6,7 +6,7 @@
 // kernel (one table set per activation vector) no longer fit in LDS.  Here every sign becomes
 // a binary16 operand of the matrix cores (v_mfma_f32_16x16x32_f16, fp32 accumulate); the cost
 // is the same for every batch up to 16; wider batches (up to 64) reuse the expanded operands for
-// every group of 16 columns.
+// every group of 16 columns (here only on small layers, see launch_skinny; else in bcq_wide.hip).
 //
 // Common skeleton (bcq_skinny_kernel<Q, Z, SUB, VER, LDS_STEPS, NB, NW>):
 //  * Same packed blob as the GEMV (bcq_layout.h).  A work unit is (tile group, column slice): the
@@ -33,11 +33,11 @@
 //    one row exchange dwords (4 x 4 transpose, v_permlane16_swap / v_permlane32_swap), after
 //    which lane (h, r) holds, for EVERY block B of row r, the chunks 4h..4h+3, and one MFMA step
 //    contracts 32 columns of a single block.  A is then just +-1.0, independent of the row: it
-//    comes from a 256-entry table in LDS (one ds_read_b128 per 8 signs; 8 interleaved copies so
-//    that neighbouring lanes read different banks); LDS_STEPS of the 4 steps of a block use the
+//    comes from a 256-entry table in LDS (one ds_read_b128 per 8 signs; 16 interleaved copies, 8 with
+//    four waves, so that lanes served together read different banks); LDS_STEPS of the 4 steps of a block use the
 //    table, the others expand in registers.  The products of one block are collected in a
 //    temporary accumulator and scaled by alpha (fp32) when the block is done; the scales are
-//    fetched into the accumulator's row layout with ds_bpermute.  The offset term uses A = all
+//    copied to all lane groups with lane swaps.  The offset term uses A = all
 //    ones: the block's column sums of X, scaled by z.  Bound: LDS read bandwidth.
 //  In both, the pairing inside an octet (elements 2d, 2d+1 <-> columns d, d+4) is arbitrary as
 //  long as A and B agree; X is stored in LDS in that order.
