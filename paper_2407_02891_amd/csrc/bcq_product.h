@@ -402,7 +402,8 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
             }
             run(step, steps, std::true_type{});
         } else {
-            run(0, steps, std::false_type{});
+            run(0, steps - 1, std::false_type{});
+            multiply((steps - 1) & 1);  // nothing follows it that had to be split
         }
         if (attempt) break;
         publish();
