@@ -417,7 +417,7 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
     // Element i of a 16 x 16 accumulator: row 4 hi + i, column lo; the scales are taken out again.  Through a descriptor of
     // the tile, elements that do not exist out of range, so that the 16 old values of a column group are requested together
     // (one at a time, each behind the store of the one before, they were a third of a short product: K = 128, 384 x 3584
-    // on average, 21.6 -> 12.7 us).
+    // on average, 21.6 -> 12.7 us, 12.1 since the last step no longer splits a step that does not exist).
     if constexpr (!kQuad) {
         constexpr unsigned kNone = 0xfffffff0u;
         constexpr bool kSymmetric = MODE == kAddTwiceSymmetric, kRead = MODE == kSubtract || MODE == kSubtractLower || kSymmetric;

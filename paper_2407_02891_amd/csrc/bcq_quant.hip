@@ -667,7 +667,8 @@ __global__ __launch_bounds__(256) void gptq_block_kernel(int M, int Mp, int N, i
 
 // Columns beyond a panel of four blocks are brought up to date once per panel (K = 512), the rest of the panel after each
 // block: every pass over the remaining weights reads and writes them all, which at one pass per block was most of its time
-// (5.7 ms of a 7168 x 7168 layer, now 2.3; the whole pass 17.3 ms before, now 3.8).  The errors of a panel are kept in Dt, which the pass does not use otherwise.
+// (5.7 ms of a 7168 x 7168 layer, now 2.2; the whole pass 17.3 ms before, now 3.8).  The errors of a panel are kept in Dt,
+// which the pass does not use otherwise.
 constexpr int kGptqPanel = 4 * kGptqBlock;
 
 hipError_t launch_quant_gptq(int M, int N, int n_bits, int q, const float *W, const float *U, const float *S,
@@ -705,8 +706,8 @@ hipError_t launch_quant_gptq(int M, int N, int n_bits, int q, const float *W, co
 // fusion with one tying per row (row-wise parameters: one scaling group per row)
 // ---------------------------------------------------------------------------------
 // A workgroup takes up to 16 rows (fewer where that would leave the chip idle): one thread per row works out its tying, all
-// at the same time (a sort each), all threads fill one table of codes per row, and the rows are then mapped WIDTH weights (1, 4 or 16, by the alignment) at a time.  Bound:
-// memory.  28672 x 7168: 441 us (a workgroup per row whose first thread worked out the tying, a scan of the representable
+// at the same time (a sort each), all threads fill one table of codes per row, and the rows are then mapped WIDTH weights
+// (1, 4 or 16, by the alignment) at a time.  Bound: memory.  28672 x 7168: 441 us (a workgroup per row whose first thread worked out the tying, a scan of the representable
 // set per weight) -> 78 us, 411 MB: 5.3 TB/s.
 constexpr int kFuseRows = 16;
 template <int WIDTH>
