@@ -94,11 +94,12 @@ __device__ __forceinline__ void x_slice_load(const SkinnyParams &p, __amdgpu_buf
     }
 }
 
-// Descriptor of the activations: rows 0 .. batch-1 of X (batch * ldx binary16 values).
+// Descriptor of the activations: rows 0 .. batch-1 of X, up to the last value of the last one.  Offsets into it are 32 bits;
+// launch_skinny makes passes of rows that they reach.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t x_descriptor(const SkinnyParams &p)
 {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.X), 0, (int)(2u * (uint32_t)p.batch * (uint32_t)p.ldx),
-                                             kRawBufferFlags);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.X), 0,
+                                             (int)(2u * ((uint32_t)(p.batch - 1) * (uint32_t)p.ldx + (uint32_t)p.N)), kRawBufferFlags);
 }
 
 // Descriptor of one tile, or an empty one.
@@ -733,12 +734,14 @@ hipError_t launch_skinny(const Geom &g, const void *packed, const uint16_t *X, i
     // on a handful of tiles (512 x 512, 32 columns 7.3 / 8.2: its start-up) and where it needs more passes on a layer
     // whose weights are not what is waited for (four planes, 64 columns: 4096 x 4096 26.9 / 31.8, 7168 x 28672 131 / 126).
     const int most = wide_columns(g);
-    // Its byte offsets into X are 32 bits for the whole batch; the kernels here need that per pass only.
-    const bool in_reach = (unsigned long long)batch * (unsigned)ldx < 0x7ffffff0ull;
+    // Byte offsets into the rows of X of a pass are 32 bits, in all kernels: no pass has more rows than they reach.
+    const long long reach = 1 + (0x7ffffff0ll - g.N) / ldx;
+    const bool in_reach = reach >= (batch < most ? batch : most);
     const bool one_pass = batch <= most || all_tiles >= 8192 || sub > 1;
     const bool wide = most > 16 && ver == 0 && in_reach && (tuning.waves == 8 || (tuning.waves == 0 && g.nslice > 1 && all_tiles >= 128 && one_pass));
     // The kernels here: up to 64 columns in one pass with alpha folded into A and one scaling group per block, else 16.
-    const int narrow = sub == 1 && ver != 2 ? (batch > 32 ? 64 : batch > 16 ? 32 : 16) : 16;
+    int narrow = sub == 1 && ver != 2 ? (batch > 32 ? 64 : batch > 16 ? 32 : 16) : 16;
+    if (narrow > reach) narrow = (int)reach;
     for (int col0 = 0; col0 < batch;) {
         const int left = batch - col0, passes = (left + most - 1) / (most > 0 ? most : 1);
         int cols = left < narrow ? left : narrow;

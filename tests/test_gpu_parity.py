@@ -564,10 +564,16 @@ def test_wide_kernel_edges(workgroups, M, N, q, offset, group, batch):
         bcq.set_option("waves", 0)
 
 
-def test_far_apart_rows_of_many_vectors():
-    """17 vectors so far apart that only 16 of them fit 32-bit byte offsets: taken in passes of 16."""
-    M, N, ldx, batch = 2048, 1024, 2 ** 27 - 8, 17
-    L = bcq_synth.make_exact_layer(M, N, 2, group=64, offset=False, batch=batch, seed=5)
+@pytest.mark.parametrize("group,batch,ldx", [
+    (64, 17, 2 ** 27 - 8), (128, 17, 2 ** 27 - 8), (1024, 17, 2 ** 27 - 8),   # 16 rows fit 32-bit byte offsets, 17 do not
+    (128, 16, 2 ** 28), (64, 9, 2 ** 28),                                     # 8 fit
+    (128, 3, 2 ** 30 + 8), (128, 2, 2 ** 31 - 8), (64, 2, 2 ** 31 - 8),       # 2, and 1
+])
+def test_far_apart_rows_of_many_vectors(group, batch, ldx):
+    """Vectors so far apart that 32-bit byte offsets reach only some of them: taken in passes of those that they reach, with one
+    scaling group per block, row-wise scales and several groups per block."""
+    M, N = 2048, 1024
+    L = bcq_synth.make_exact_layer(M, N, 2, group=group, offset=False, batch=batch, seed=5)
     pl = U.upload_and_pack(L, max_batch=batch)
     expect = ref.gemm(L.planes, L.alpha, L.offset, L.x).astype(np.float16).astype(np.float64)
     X = torch.empty((batch - 1) * ldx + N, dtype=torch.float16, device="cuda")
