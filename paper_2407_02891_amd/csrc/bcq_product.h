@@ -9,23 +9,32 @@
 //   kAddTwiceSymmetric   out[r][c] += 2 C[r][c], B = A: only the tiles on and above the diagonal are computed and each
 //               element is added to both out[r][c] and out[c][r]
 //   kSubtract   out[r][c] -= C[r][c];   kSubtractLower   the same for the tiles on and below the diagonal only
-//   kStore      out[r][c] = C[r][c], B[k][c] = 0 for k > c   
+//   kStore      out[r][c] = C[r][c]; with triangular_b B[k][c] = 0 for k > c
 //   kStoreNegated   out[r][c] = -C[r][c], A[k][r] = 0 for k < r
 //
 // Arithmetic.  The binary32 matrix instruction (v_mfma_f32_32x32x2_f32) runs at 1/16 of the rate of the binary16 ones
 // (v_mfma_f32_16x16x32_f16).  So every operand value x is split, after scaling by a power of two s that belongs to its
-// row or column of the product, into two binary16 numbers,
-//     hi = rne16(s x),   lo = rne16(s x - hi),      |s x - hi - lo| <= 2^-24 |s x|  (or 2^-25, see below),
-// and the product is lo hi' + hi lo' + hi hi', three instructions that accumulate in binary32; the dropped lo lo' is
-// below 2^-24 of the term.  The accumulator is rounded three times per 16 values of k (measured: the instruction over 32
-// values rounds twice) instead of 16 times, so the result is closer to the binary64 one: 2-norm error of 2 X^T X with
-// standard normal X against binary64, binary32 instruction / this, 256 samples 2.9e-7 / 1.9e-7, 2048 samples
-// 8.2e-7 / 5.0e-7 (up to 32 samples the representation shows: 7.3e-8 / 8.6e-8 at 16).
-// The scales: binary16 reaches from 2^-24 to 2^16, so s is chosen from the largest magnitude in the first 32 values of
-// the row or column, which it puts at 2^4..2^5: later values may be 2^11 times larger, and the smallest step, 2^-25, is
-// 2^-29 of that largest value.  The largest magnitude of all values is tracked on the way; a tile with a row or column
-// outside 4 <= s max |x| <= 60000 at the end (none in a usual layer) is computed once more with s from the true maximum.
-// A value that is not finite makes every sum it enters not finite.
+// row or column of the product, into two binary16 numbers, hi = rne16(s x) and lo = rne16(s x - hi), and the product is
+// lo hi' + hi lo' + hi hi', three instructions that accumulate in binary32.  Where |s x| >= 1/4, |s x - hi - lo| is at most
+// 2^-23 |s x| (three significands in four are exact); below that it is at most 2^-25, half the smallest step of a binary16
+// number.  The dropped lo lo' is at most 2^-22 of the term.  The accumulator is rounded three times per 16 values of k
+// (measured: the instruction over 32 values rounds twice) instead of 16 times, which outweighs that: 2-norm error of
+// 2 X^T X with standard normal X against binary64, binary32 instruction / this, 33 samples 1.04e-7 / 0.96e-7, 256 samples
+// 2.8e-7 / 1.8e-7, 2048 samples 6.6e-7 / 4.1e-7.
+// The scales: 2^-24 to 2^16 is what binary16 reaches, and values far below the largest of their row or column must keep
+// their bits, because what they are multiplied by may be as much larger (the inverse of a diagonal block times entries of a
+// loud channel).  s puts the largest magnitude of the row or column so far at 2^10..2^11: full precision down to 2^-13 of
+// it, and later values may be 29 times larger.  A larger one ends the stretch of steps: all scales that it does not fit
+// are chosen again, the accumulators move to them (powers of two: exact) and the steps go on from there, which costs about
+// two steps.  A quadratic form knows better: |d| is bounded by the row's range, and the values of a positive semidefinite B
+// by its diagonal, which together with the largest of all puts them at most at 2^15.  A row or column that is zero in the
+// first step takes its tile's largest, or the diagonal of a triangular operand; if that turns out more than 2^6 too large,
+// or a bound too small, the tile is computed once more with all magnitudes known.
+// Inverse-Hessian factor, error per column of U against binary64, binary32 instruction / this, four channels 2^10 (2^12) times as
+// loud at the start of every block of 128 channels: 2.0e-7 / 1.9e-7 (5.1e-7 / 4.8e-7); with scales from the first step at 2^4 and
+// no changes on the way it was 9e-7 (1.4e-5).  Search with four of 7168 channels 2^13 times as loud: 59.0 ms when the
+// tiles of H had to be computed twice, now 31.7 as with any other.
+// A value that is not finite makes every sum it enters not finite and has no say in the scales.
 //
 // Work split.  A workgroup of four waves owns a 128 x 128 tile of C, a wave a 64 x 64 quarter as 4 x 4 accumulators of
 // 16 x 16; a step takes 32 values of k.  Wave w brings the eight rows 8 w .. 8 w + 7 of the step, lane l the columns 2 l
@@ -34,11 +43,12 @@
 // matrix instruction takes its operands.  Two stages in LDS (64 KB) with one barrier per step; two workgroups per
 // compute unit, so that one's loads and splits run under the other's matrix instructions.  The loop has no branch around
 // its loads (buffer descriptors end at the k range), so that the compiler interleaves the vector instructions with the
-// matrix instructions: with branches the same loop was 25 % slower.
+// matrix instructions: with branches the same loop was 25 % slower.  Whether the next step fits the scales is known once per
+// step, by a flag in LDS beside its barrier.
 // What bounds it: about 200 vector instructions (800 clocks) against 48 matrix instructions (768 clocks) per wave and step,
 // two waves per SIMD: both pipes are half busy.  Measured (binary32 instruction before / now): quadratic form of a 7168 x
 // 7168 layer 3.32 / 1.38 ms per candidate, 1.19 with A split beforehand (kQuadFormSplit: 930 TFLOP/s of binary16 products; a
-// large library product of that type reaches 1230 on this card), 2 X^T X over 4 x 2048 samples of 7168 channels 7.17 / 1.85 ms.
+// large library product of that type reaches 1230 on this card), 2 X^T X over 4 x 2048 samples of 7168 channels 7.17 / 1.80 ms.
 // An octet of column c sits at position c ^ ((c >> 4) & 1): the 16 lanes that a 16-byte LDS access serves together then
 // touch 16 different 16-byte columns both when the pairs of columns are written and when 16 consecutive ones are read.
 //
@@ -66,6 +76,8 @@ typedef float prod_f32x4 __attribute__((ext_vector_type(4)));
 enum ProductMode { kQuadForm = 0, kSubtract = 1, kAddTwiceSymmetric = 2, kStore = 3, kStoreNegated = 4, kSubtractLower = 5, kQuadFormSplit = 6 };
 
 constexpr int kProdTile = 128, kProdStep = 32, kProdBlock = 4;  // tile edge, k values per step, tiles per block edge
+constexpr int kProdTarget = 10;                                 // a first guess puts its magnitude at 2^10 .. 2^11
+constexpr float kProdMost = 60000.0f, kProdLeast = 16.0f;       // where scaled maxima have to lie, see above
 
 struct ProductArgs {
     const float *A, *B, *E;
@@ -74,7 +86,8 @@ struct ProductArgs {
     int triangular_b;  // kStore: B[k][c] = 0 for k > c
     const uint16_t *split;  // kQuadFormSplit: A in two halves, [hi, lo][k / 8][row (pitch ldo)][8 values of k]; K a multiple of 8
     size_t split_plane;     // values per half
-    const int *split_shift; // exponent of each row's scale
+    const int *split_shift; // quadratic forms: exponent of each row's scale
+    const float *diag_max;  // quadratic forms: largest value on B's diagonal
     // several products of one shape in a launch (blockIdx.y): operands and result of product y lie y * stride floats on; the
     // last one may have fewer columns, columns_end - y * columns_step of them, and with k_is_columns as many values of k
     size_t stride;
@@ -142,6 +155,7 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
 {
     constexpr bool kQuad = MODE == kQuadForm || MODE == kQuadFormSplit, kSplitA = MODE == kQuadFormSplit;
     constexpr int kFirst = kSplitA ? 1 : 0;  // first operand that comes in binary32
+    constexpr bool kStops = !kQuad;          // scales may change on the way
     // the two stages of both operands, [hi, lo][octet][column]; A's are two objects so that the compiler can tell the copies
     // into one (kQuadFormSplit) from the reads of the other
     __shared__ __attribute__((aligned(16))) uint8_t stage_a0[2][4][kProdTile * 16];
@@ -150,6 +164,8 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
     __shared__ unsigned largest[2][kProdTile];  // largest magnitude per row of A's tile, column of B's tile (float bits)
     __shared__ unsigned largest_of_tile[2];
     __shared__ int shift[2][kProdTile];  // exponents of the scales
+    __shared__ int change[2][kProdTile]; // what they change by
+    __shared__ unsigned stop[2];         // the next step does not fit the scales (by stage)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lo = lane & 15, hi = lane >> 4, wr = wave >> 1, wc = wave & 1;
@@ -302,32 +318,54 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
     };
     // Steps [from, to): while a step is multiplied, the next one is split and stored to the other stage and the one
     // after it is requested.
+    // True if the next step does not fit the scales, which all four waves see alike: `stop` of a stage is written before the
+    // barrier, read after it and written again two barriers later.
     auto one = [&](auto buf, auto other, int step, auto weighed) PROD_INLINE {
+        const int b = buf;
         if (kSplitA) copy_a(other, step + 1);
         multiply(buf);
         if (decltype(weighed)::value) weigh(step + 1);
         track();
         split_store(other);
         load(step + 2);
+        if constexpr (kStops) {
+            float most = 0.0f;
+#pragma unroll
+            for (int o = 0; o < 2; ++o)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) most = fmaxf(most, top[o][e] * s[o][e]);
+            if (most > kProdMost) stop[b] = 1u;
+        }
         barrier();  // the other stage is complete, and everyone is done reading this one
+        return kStops && __builtin_amdgcn_readfirstlane((int)*(volatile __attribute__((address_space(3))) unsigned *)&stop[b]) != 0;
     };
     constexpr std::integral_constant<int, 0> even{};
     constexpr std::integral_constant<int, 1> odd{};
+    int begin = 0;         // first step under the present scales: steps of its parity use the first stage
+    bool stopped = false;  // the step that run() returns does not fit them
     auto run = [&](int from, int to, auto weighed) PROD_INLINE {  // kSplitA: `from` is even, and the stages are constants
+        int step = from;
         if constexpr (kSplitA) {
-            int step = from;
             for (; step + 1 < to; step += 2) {
                 one(even, odd, step, weighed);
                 one(odd, even, step + 1, weighed);
             }
             if (step < to) one(even, odd, step, weighed);  // the last of all
+            step = to;
         } else {
-            for (int step = from; step < to; ++step) one(step & 1, (step & 1) ^ 1, step, weighed);
+            if (step < to) {
+                bool on;
+                do {
+                    stopped = one((step - begin) & 1, (step - begin + 1) & 1, step, weighed);
+                    on = (++step < to) & !stopped;
+                } while (on);
+            }
         }
+        return step;
     };
     // kQuadForm: the accumulators' contribution to the quadratic form, and a fresh start.  Once per 1024 values of k: the
     // shorter sums lose less to rounding.
-    prod_f32x4 sum[4];
+    prod_f32x4 sum[4] = {};
     auto contract = [&]() PROD_INLINE {
         const int columns = width[1] < kProdTile ? width[1] : kProdTile;
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
@@ -350,50 +388,88 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
         }
         clear();
     };
-    for (int attempt = 0;; ++attempt) {
-        if (kSplitA) copy_a(even, 0);
-        load(0);
-        if (kQuad && c0 < kProdStep) weigh(0);
+    // A stretch of steps under one set of scales: from step 0, or (begin > 0) from the one that did not fit the last set; once more
+    // from step 0, with all magnitudes known, if a guess was too low.
+    bool known = false;
+    largest[tid >> 7][tid & 127] = 0u;
+    if (tid < 2) largest_of_tile[tid] = stop[tid] = 0u;
+    clear();
+    __syncthreads();
+    for (;;) {
+        const int o = tid >> 7, i = tid & 127;  // this thread's row of A's tile, column of B's
+        // A magnitude that the first step need not show.  Quadratic form: with a positive semidefinite B no value of column c is
+        // above sqrt(max_k B[k][k] B[c][c]); twice that, and no more than 2^12 B[c][c], is taken for the largest.  Else the
+        // diagonal of a triangular operand.
+        float hint = 0.0f;
+        if (begin == 0 && !known) {
+            if (kQuad && o == 1 && c0 + i < p.C) {
+                const float d = fabsf(p.B[(size_t)(c0 + i) * p.ldb + c0 + i]);
+                hint = d * fminf(sqrtf(*p.diag_max / d), 0x1p12f);
+            }
+            if ((MODE == kStore || MODE == kStoreNegated) && o == 0 && r0 + i < p.R && r0 + i < p.K)
+                hint = fabsf(p.A[(size_t)(r0 + i) * p.lda + r0 + i]);
+        }
+        if (kSplitA) copy_a(even, begin);
+        load(begin);
+        if (kQuad && c0 < (begin + 1) * kProdStep) weigh(begin);
         track();
-        if (attempt == 0) {
-            largest[tid >> 7][tid & 127] = 0u;
-            if (tid < 2) largest_of_tile[tid] = 0u;
-            __syncthreads();
-            publish();
 #pragma unroll
-            for (int o = kFirst; o < 2; ++o) {
-                float m = fmaxf(top[o][0], top[o][1]);
+        for (int x = kFirst; x < 2; ++x)  // what is not finite has no say in the scales
+#pragma unroll
+            for (int e = 0; e < 2; ++e) top[x][e] = top[x][e] < INFINITY ? top[x][e] : 0.0f;
+        publish();
+        if (begin == 0 && !known) {
+#pragma unroll
+            for (int x = kFirst; x < 2; ++x) {
+                float m = fmaxf(top[x][0], top[x][1]);
 #pragma unroll
                 for (int d = 32; d > 0; d >>= 1) m = fmaxf(m, __shfl_xor(m, d));
-                if (lane == 0) atomicMax(&largest_of_tile[o], __float_as_uint(m));
+                if (lane == 0) atomicMax(&largest_of_tile[x], __float_as_uint(m));
             }
-            __syncthreads();
         }
+        __syncthreads();
         {
-            // first pass: the first step's largest value goes to 2^4 (a row or column that is zero there takes the
-            // tile's); second pass: the largest of all values goes to 2^14
-            const int o = tid >> 7;
-            const unsigned m = largest[o][tid & 127];
-            shift[o][tid & 127] = attempt ? product_shift(m, 14) : product_shift(m ? m : largest_of_tile[o], 4);
-            if (kSplitA && o == 0) shift[0][tid & 127] = (tid & 127) < width[0] ? p.split_shift[r0 + (tid & 127)] : 0;
+            unsigned m = largest[o][i];
+            const int old = shift[o][i];
+            int now;
+            if (begin == 0 && !known) {  // (a row or column without any guess takes the tile's)
+                if (hint < INFINITY) m = __float_as_uint(fmaxf(hint, __uint_as_float(m)));
+                now = product_shift(m ? m : largest_of_tile[o], kQuad ? 14 : kProdTarget);
+            } else if (begin == 0) {
+                now = product_shift(m, 14);
+            } else {
+                now = ldexpf(__uint_as_float(m), old) > kProdMost ? product_shift(m, kProdTarget) : old;
+            }
+            if (kQuad && o == 0) now = i < width[0] ? p.split_shift[r0 + i] : 0;
+            shift[o][i] = now;
+            change[o][i] = now - old;
+            if (tid < 2) stop[tid] = 0u;
         }
         __syncthreads();
 #pragma unroll
-        for (int o = kFirst; o < 2; ++o)
+        for (int x = kFirst; x < 2; ++x)
 #pragma unroll
-            for (int e = 0; e < 2; ++e) s[o][e] = ldexpf(1.0f, shift[o][2 * lane + e]);
-        clear();
+            for (int e = 0; e < 2; ++e) s[x][e] = ldexpf(1.0f, shift[x][2 * lane + e]);
+        if (kStops && begin > 0) {  // the sums so far under the new scales
+#pragma unroll
+            for (int ta = 0; ta < 4; ++ta)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int change_r = change[0][wr * 64 + ta * 16 + 4 * hi + j];
+#pragma unroll
+                    for (int tb = 0; tb < 4; ++tb) acc[ta][tb][j] = ldexpf(acc[ta][tb][j], change_r + change[1][wc * 64 + tb * 16 + lo]);
+                }
+        }
         split_store(even);
-        load(1);
+        load(begin + 1);
         barrier();
+        stopped = false;
+        int step = begin;
         if constexpr (kQuad) {
             // the last steps, which reach the diagonal, are weighed one step ahead (and, to keep the number of the others even,
             // the one before them, which changes nothing in it)
             const int plain = c0 / kProdStep - 2;
             constexpr int kChunk = 1024 / kProdStep;
-#pragma unroll
-            for (int ta = 0; ta < 4; ++ta) sum[ta] = prod_f32x4{0.f, 0.f, 0.f, 0.f};
-            int step = 0;
             while (step < plain) {
                 const int to = plain - step < kChunk ? plain : step + kChunk;
                 run(step, to, std::false_type{});
@@ -402,16 +478,26 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
             }
             run(step, steps, std::true_type{});
         } else {
-            run(0, steps - 1, std::false_type{});
-            multiply((steps - 1) & 1);  // nothing follows it that had to be split
+            step = run(begin, steps - 1, std::false_type{});
+            if (!stopped) multiply((steps - 1 - begin) & 1);  // nothing follows it that had to be split
         }
-        if (attempt) break;
+        if (kStops && stopped && step < steps) {
+            begin = step;
+            continue;
+        }
+        if (known) break;
         publish();
         __syncthreads();
-        const int o = tid >> 7;
-        const float most = ldexpf(__uint_as_float(largest[o][tid & 127]), shift[o][tid & 127]);
-        const bool bad = o >= kFirst && (tid & 127) < width[o] && (!(most <= 60000.0f) || (most < 4.0f && most > 0.0f));
-        if (!__syncthreads_or(bad)) break;
+        const float most = ldexpf(__uint_as_float(largest[o][i]), shift[o][i]);
+        const bool off = o >= (kQuad ? 1 : 0) && i < width[o] && ((most < (kQuad ? 1.0f : kProdLeast) && most > 0.0f) || (kQuad && most > kProdMost));
+        if (!__syncthreads_or(off)) break;
+        known = true;
+        begin = 0;
+        clear();
+        if constexpr (kQuad) {
+#pragma unroll
+            for (int ta = 0; ta < 4; ++ta) sum[ta] = prod_f32x4{0.f, 0.f, 0.f, 0.f};
+        }
     }
 
     // Element i of a 16 x 16 accumulator: row 4 hi + i, column lo; the scales are taken out again.  Through a descriptor of
@@ -496,9 +582,9 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
 
 template <int MODE>
 static void launch_product(hipStream_t stream, const float *A, int lda, int R, const float *B, int ldb, int C, int K, float *out,
-                           int ldo, const float *E = nullptr)
+                           int ldo)
 {
-    ProductArgs p = {A, B, E, out, lda, R, ldb, C, K, ldo, 0, nullptr, 0, nullptr, 0, C, 0, 0};
+    ProductArgs p = {A, B, nullptr, out, lda, R, ldb, C, K, ldo, 0, nullptr, 0, nullptr, nullptr, 0, C, 0, 0};
     const int blocks = (product_blocks<MODE>(R, C) + 7) / 8 * 8;
     hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)(blocks * kProdBlock * kProdBlock)), dim3(256), 0, stream, p);
 }
@@ -508,19 +594,21 @@ template <int MODE>
 static void launch_products(hipStream_t stream, int count, size_t stride, int columns_end, const float *A, const float *B, float *out,
                             int pitch, int size)
 {
-    ProductArgs p = {A, B, nullptr, out, pitch, size, pitch, size, size, pitch, MODE == kStore ? 1 : 0, nullptr, 0, nullptr,
+    ProductArgs p = {A, B, nullptr, out, pitch, size, pitch, size, size, pitch, MODE == kStore ? 1 : 0, nullptr, 0, nullptr, nullptr,
                      stride, columns_end, 2 * size, MODE == kStore ? 1 : 0};
     const int blocks = (product_blocks<MODE>(size, size) + 7) / 8 * 8;
     hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)(blocks * kProdBlock * kProdBlock), (unsigned)count), dim3(256), 0, stream, p);
 }
 
-// kQuadFormSplit: A comes as `split` (see ProductArgs), E holds the same values in binary32.
-static void launch_quad_form_split(hipStream_t stream, const uint16_t *split, size_t plane, const int *shift, int R, const float *B,
-                                   int ldb, int C, int K, float *out, int ldo, const float *E)
+// The quadratic forms of the rows of D: kQuadForm splits them as it reads them, for kQuadFormSplit they come as `split` too
+// (see ProductArgs).
+template <int MODE>
+static void launch_quad_form(hipStream_t stream, const uint16_t *split, size_t plane, const int *shift, const float *D, int R, const float *B,
+                             int ldb, const float *diag_max, int C, float *out, int ldo)
 {
-    ProductArgs p = {E, B, E, out, ldo, R, ldb, C, K, ldo, 0, split, plane, shift, 0, C, 0, 0};
-    const int blocks = (product_blocks<kQuadFormSplit>(R, C) + 7) / 8 * 8;
-    hipLaunchKernelGGL((product_kernel<kQuadFormSplit>), dim3((unsigned)(blocks * kProdBlock * kProdBlock)), dim3(256), 0, stream, p);
+    ProductArgs p = {D, B, D, out, ldo, R, ldb, C, C, ldo, 0, split, plane, shift, diag_max, 0, C, 0, 0};
+    const int blocks = (product_blocks<MODE>(R, C) + 7) / 8 * 8;
+    hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)(blocks * kProdBlock * kProdBlock)), dim3(256), 0, stream, p);
 }
 
 }  // namespace bcq

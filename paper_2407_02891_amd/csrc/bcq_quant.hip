@@ -428,6 +428,25 @@ __global__ void split_shift_kernel(int M, int Mp, const float *__restrict__ wmin
     if (m < Mp) shift[m] = m < M ? product_shift(__float_as_uint(wmax[m] - wmin[m]), 13) : 0;
 }
 
+// Largest finite value on the diagonal of H, from which the quadratic forms take the scales of its columns.
+__global__ __launch_bounds__(1024) void diag_max_kernel(int N, const float *__restrict__ H, float *__restrict__ most)
+{
+    __shared__ float part[16];
+    float m = 0.0f;
+    for (int i = threadIdx.x; i < N; i += 1024) {
+        const float d = H[(size_t)i * N + i];
+        if (d < INFINITY) m = fmaxf(m, d);
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) m = fmaxf(m, __shfl_xor(m, d));
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 16; ++w) m = fmaxf(m, part[w]);
+        *most = m;
+    }
+}
+
 // Dt[k][m] = S' W_q + qbias - w for one candidate (grid point g, tying t), from Wt (SPLIT = false) or from W; zeros in the
 // pad rows.  With SPLIT the same values also go to `split` as two binary16 halves in the operand layout of the matrix
 // instructions, [hi, lo][k / 8][m][k % 8], so that the product does not have to convert them once per column tile.  A
@@ -515,7 +534,9 @@ hipError_t launch_quant_search(int M, int N, int n_bits, int q, int grid, const 
     auto *halves = reinterpret_cast<uint16_t *>(w.Wt);
     auto *shift = reinterpret_cast<int *>(w.Err);
     const size_t plane = (size_t)N * w.Mp;
-    if (split) hipLaunchKernelGGL(split_shift_kernel, dim3((w.Mp + 255) / 256), dim3(256), 0, stream, M, w.Mp, w.wmin, w.wmax, shift);
+    auto *diag_max = reinterpret_cast<float *>(shift + w.Mp);
+    hipLaunchKernelGGL(split_shift_kernel, dim3((w.Mp + 255) / 256), dim3(256), 0, stream, M, w.Mp, w.wmin, w.wmax, shift);
+    hipLaunchKernelGGL(diag_max_kernel, dim3(1), dim3(1024), 0, stream, N, H, diag_max);
     const std::vector<Tying> tyings = all_tyings(n_bits, q);
     bool first = true;
     for (int g = 0; g < grid; ++g)
@@ -524,10 +545,8 @@ hipError_t launch_quant_search(int M, int N, int n_bits, int q, int grid, const 
                                stream, M, w.Mp, N, n_bits, g, grid, t, split ? W : w.Wt, w.wmin, w.wmax, w.Dt, shift, halves, plane);
             // d H d^T / 2 row by row: sum_l Dt[l][m] sum_{k <= l} w_kl H[k][l] Dt[k][m], w = 1/2 on the diagonal
             // (only the upper triangle of H is read), one partial per tile of 128 values of l
-            if (split)
-                launch_quad_form_split(stream, halves, plane, shift, w.Mp, H, N, N, N, w.part, w.Mp, w.Dt);
-            else
-                launch_product<kQuadForm>(stream, w.Dt, w.Mp, w.Mp, H, N, N, N, w.part, w.Mp, w.Dt);
+            (split ? launch_quad_form<kQuadFormSplit> : launch_quad_form<kQuadForm>)(stream, halves, plane, shift, w.Dt, w.Mp, H, N,
+                                                                                     diag_max, N, w.part, w.Mp);
             hipLaunchKernelGGL(keep_best_kernel, dim3((M + 255) / 256), dim3(256), 0, stream, M, w.Mp, n_bits, w.ntile, g,
                                grid, first ? 1 : 0, t, w.part, w.wmin, w.wmax, w.best, S, qbias, labels);
             first = false;

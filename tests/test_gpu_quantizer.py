@@ -320,9 +320,11 @@ def test_hessian(N, T):
 def test_hessian_tiles_and_scales(N, T):
     """The split product at the edges of its tiles (128 columns, 32 samples, blocks of 4 x 4 tiles), with channels of very
     different size, channels that are zero in the first samples and a channel that grows by 2^20 after them (both make a
-    tile choose its scales again), added to an H that is not symmetric.  Bound per element: three binary32 roundings per
-    16 samples, the dropped product of the two small halves and the final addition, each 2^-24 of sum |x_r x_c|; a value
-    far below its channel's largest is only held to 2^-27 of that one."""
+    tile choose its scales again), added to an H that is not symmetric.  Bound per element, in units of 2^-24 of sum |x_r x_c|:
+    three binary32 roundings per 16 samples; the halves of an operand leave at most 2^-23 of it (2 units each), the dropped
+    product of the two small halves is at most 2^-22 (4); the final addition 1: 9, of which 8 are allowed (the worst cases of
+    the halves exclude each other).  A value far below its channel's largest is only held to 2^-31 of that one: the smallest
+    step of a half is 2^-24 (rounded to nearest: 2^-25) and the scaled largest is at least 2^4, or 2^6 on average."""
     rng = np.random.default_rng(N * 7 + T)
     X = rng.standard_normal((T, N)).astype(np.float32)
     X *= np.exp2(rng.integers(-40, 41, size=N)).astype(np.float32)
@@ -350,6 +352,74 @@ def test_hessian_tiles_and_scales(N, T):
     torch.cuda.synchronize()
     bad = H.cpu().numpy()
     assert not np.isfinite(bad[N - 1, N - 1]) and np.isfinite(bad[: N - 1, : N - 1]).all()
+
+
+@pytest.mark.parametrize("N,T", [(132, 300), (260, 97), (516, 640)])
+def test_hessian_scales_that_change_on_the_way(N, T):
+    """Channels that grow by 2^9 or 2^14 at one sample, or again and again, at every position of a step and of the two stages,
+    one that starts late and small, and one with an infinity on the way: the tiles choose new scales from the step at which
+    the old ones no longer do and go on.  Bound as in test_hessian_tiles_and_scales, but for values far below the largest of
+    their channel up to their own step (later ones do not touch them)."""
+    rng = np.random.default_rng(N + T)
+    X = rng.standard_normal((T, N)).astype(np.float32)
+    for c in range(0, 100, 3):
+        X[rng.integers(1, T):, c] *= np.float32(2.0 ** rng.choice([9, 14]))
+    for t in range(40, min(T, 240), 33):
+        X[t:, 101] *= np.float32(2.0 ** 7)
+    X[: T // 2, 102] = 0.0
+    X[T // 2:, 102] *= np.float32(2.0 ** -9)
+    X *= np.float32(2.0) ** rng.integers(-20, 1, size=N).astype(np.float32)
+    H = torch.zeros((N, N), dtype=torch.float32, device="cuda")
+    bcq.quant_hessian(N, T, _dev(X), H)
+    torch.cuda.synchronize()
+    X64 = X.astype(np.float64)
+    want, size = 2.0 * (X64.T @ X64), 2.0 * (np.abs(X64).T @ np.abs(X64))
+    step = (np.arange(T) // 32 * 32 + 31).clip(max=T - 1)
+    big = np.maximum.accumulate(np.abs(X64), axis=0)[step]       # the largest of its channel up to the end of its step
+    low = 2.0 * 2.0 ** -31 * (big.T @ np.abs(X64) + np.abs(X64).T @ big)
+    bound = (3 * ((T + 15) // 16) + 8) * 2.0 ** -24 * size + low
+    got = H.cpu().numpy().astype(np.float64)
+    assert (np.abs(got - want) <= bound).all(), (np.abs(got - want) / bound).max()
+    assert np.array_equal(got, got.T)
+    X[T // 3, 103] = np.inf
+    X[T // 2, 104] = np.nan
+    H.zero_()
+    bcq.quant_hessian(N, T, _dev(X), H)
+    torch.cuda.synchronize()
+    bad = H.cpu().numpy()
+    assert not np.isfinite(bad[[103, 104]]).any()
+    keep = np.setdiff1d(np.arange(N), [103, 104])
+    assert (np.abs(bad[np.ix_(keep, keep)] - want[np.ix_(keep, keep)]) <= bound[np.ix_(keep, keep)]).all()
+
+
+@pytest.mark.parametrize("N,loud,damp", [(384, 2.0 ** 10, 1e-4), (520, 2.0 ** 12, 1e-6)])
+def test_factor_with_loud_channels(N, loud, damp):
+    """Four channels 2^10 or 2^12 times as loud as the others at the start of every diagonal block: their entries are the largest
+    of the columns that the panels multiply by a block's inverse, which scales them down again, so the ordinary entries must
+    not be held to a step of the large ones.  Error per column of U against binary64, over that of a binary32 factorisation
+    (LAPACK): at most 8, where binary32 matrix instructions give 2.3 and 4."""
+    from scipy.linalg import solve_triangular
+    rng = np.random.default_rng(1)
+    X = rng.standard_normal((2 * N, N)) + 0.5 * rng.standard_normal((2 * N, 8)) @ rng.standard_normal((8, N))
+    for b in range(0, N, 128):
+        X[:, b + 3: b + 7] *= loud
+    H32 = (2 * X.T @ X).astype(np.float32)
+    H32 = ((H32 + H32.T) / 2).astype(np.float32)
+
+    def factor(dtype):
+        Hd = H32.astype(dtype) + dtype(damp * np.mean(np.diag(H32.astype(np.float64)))) * np.eye(N, dtype=dtype)
+        inv = solve_triangular(np.linalg.cholesky(Hd[::-1, ::-1]), np.eye(N, dtype=dtype), lower=True)
+        return inv[::-1, ::-1].astype(np.float64)
+
+    U_o, U_32 = factor(np.float64), factor(np.float32)
+    U = torch.empty((N, N), dtype=torch.float32, device="cuda")
+    ws = torch.empty(bcq.quant_factor_workspace_bytes(N), dtype=torch.uint8, device="cuda")
+    bcq.quant_factor(N, damp, _dev(H32), U, ws)
+    torch.cuda.synchronize()
+    size = np.linalg.norm(U_o, axis=0)
+    err, err32 = (np.linalg.norm((u - U_o) / size) for u in (U.cpu().numpy().astype(np.float64), U_32))
+    print(f"N={N}: {err / N ** 0.5:.2e}, binary32 {err32 / N ** 0.5:.2e}")
+    assert err <= 8 * err32
 
 
 @pytest.mark.parametrize("N", [64, 160, 384, 1000])
