@@ -354,6 +354,26 @@ def test_hessian_tiles_and_scales(N, T):
     assert not np.isfinite(bad[N - 1, N - 1]) and np.isfinite(bad[: N - 1, : N - 1]).all()
 
 
+@pytest.mark.parametrize("T", [1, 2, 7, 16, 24, 32, 33])
+def test_hessian_of_few_samples(T):
+    """With few samples the roundings of the operands do not average out: the result is as close to the binary64 one as a chain
+    of binary32 multiply-adds is (both round every sum; 5 % for their different order)."""
+    N = 260
+    rng = np.random.default_rng(T)
+    X = rng.standard_normal((T, N)).astype(np.float32)
+    H = torch.zeros((N, N), dtype=torch.float32, device="cuda")
+    bcq.quant_hessian(N, T, _dev(X), H)
+    torch.cuda.synchronize()
+    X64 = X.astype(np.float64)
+    want = 2.0 * (X64.T @ X64)
+    chain = np.zeros((N, N), dtype=np.float32)
+    for t in range(T):
+        chain = (chain + np.outer(X64[t], X64[t])).astype(np.float32)
+    err, err32 = np.linalg.norm(H.cpu().numpy() - want), np.linalg.norm(2.0 * chain.astype(np.float64) - want)
+    print(f"T={T}: {err / np.linalg.norm(want):.2e}, binary32 chain {err32 / np.linalg.norm(want):.2e}")
+    assert err <= 1.05 * err32
+
+
 @pytest.mark.parametrize("N,T", [(132, 300), (260, 97), (516, 640)])
 def test_hessian_scales_that_change_on_the_way(N, T):
     """Channels that grow by 2^9 or 2^14 at one sample, or again and again, at every position of a step and of the two stages,
