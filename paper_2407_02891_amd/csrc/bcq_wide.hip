@@ -18,8 +18,8 @@
 //    slice of a pair, waves 4-7 the odd one (K groups), and the two partial sums of a row tile meet in LDS when the
 //    workgroup leaves it.  Half the rows per workgroup means half the split-K atomics of eight row tiles for the same number
 //    of workgroups, and they are what the kernel before this one paid most for besides the matrix instructions.
-//  * Workgroups per row group: a whole number where that keeps the chip busy (plan_wide), so that no workgroup holds parts
-//    of two row groups; a single one writes its outputs without atomics.
+//  * Workgroups per row group: a whole number unless that leaves too much of the chip idle (plan_wide), so that no workgroup
+//    holds parts of two row groups; a single one writes its outputs without atomics.
 #include <atomic>
 
 #include "bcq_internal.h"
@@ -359,18 +359,26 @@ static int compute_units()
     return cus;
 }
 
-// Workgroups: `parts` per row group where all row groups fit the chip at once, else one contiguous range of units each.
+// Workgroups: a whole number (`parts`) per row group, or one contiguous range of units each.  A range may end inside a row
+// group, and then two row groups are added to the outputs, which costs about as much as half a unit; against a single
+// workgroup per row group, which adds nothing but stores, about two units.  So ranges are taken if they have that much less
+// for the workgroup with the most units (us, whole / ranges; units in parentheses).  One per row group, 8192 columns, 64
+// vectors: 16512 rows 73.9 / 66.6 (8 / 5), 23040 rows 76.6 / 75.8 (8 / 6), 25600 rows 79.9 / 85.5 (8 / 7), 16512 x 4096 39.3 /
+// 46.6 (4 / 3).  Several: 11008 x 8192 49.9 / 45.2 (4 / 3), 11008 x 28672, 32 vectors 85.2 / 71.2 (14 / 10), 8960 x 8192 41.7 / 48.1
+// (3 / 3), 7168 x 28672 83.3 / 82.5 (7 / 7).
 static void plan_wide(WideParams &wp, bool single_slice, int forced, int *groups)
 {
     const int cus = compute_units(), rgs = wp.s.ntg;
     const long long units = (long long)rgs * wp.pairs;
     wp.s.units = (int)units;
     wp.parts = 0;
+    const int parts = single_slice || rgs > cus ? 1 : (cus / rgs < wp.pairs ? cus / rgs : wp.pairs);
+    const long long most_whole = (wp.pairs + parts - 1) / parts, most_ranges = (units + cus - 1) / cus;
     if (forced > 0) {
         *groups = (int)(forced < units ? forced : units);
-    } else if (single_slice || rgs <= cus) {
-        wp.parts = single_slice ? 1 : (cus / rgs < wp.pairs ? cus / rgs : wp.pairs);
-        *groups = rgs * wp.parts;
+    } else if (single_slice || (rgs <= cus && most_ranges + (parts == 1 ? 2 : 1) > most_whole)) {
+        wp.parts = parts;
+        *groups = rgs * parts;
     } else {
         *groups = (int)(cus < units ? cus : units);
     }
