@@ -125,7 +125,7 @@ __device__ __forceinline__ void x_slice_store(uint8_t *xs, int tid, const u32x4 
         const int pos = VER == 2 ? ((chunk & 48) | ((chunk & 3) << 2) | ((chunk >> 2) & 3)) : chunk;
         // VER 2: batch column h + 4 j of a group of 16 goes to row 4 h + j, so that the lanes 16 h + r of the (transposed)
         // MFMA result hold the columns h, h + 4, h + 8, h + 12: a flush instruction then covers four neighbouring columns
-        const int row = VER == 2 ? (((c & 3) << 2) | ((c >> 2) & 3)) : c;
+        const int row = VER == 2 ? ((c & ~15) | ((c & 3) << 2) | ((c >> 2) & 3)) : c;
         *reinterpret_cast<u32x4 *>(xs + row * kXPitch<VER> + pos * 16) = o;
     }
 }
@@ -220,17 +220,17 @@ __device__ __forceinline__ void skinny_store(const SkinnyParams &p, const f32x4 
     }
 }
 
-// The same for accumulators held transposed (the table kernel): acc[t][j] = (batch column h + 4j, row 16t + r)
+// The same for accumulators held transposed (the table kernel): acc[t][j] = (batch column col0 + h + 4j, row 16t + r)
 // of the tile, lane 16h + r.  No turn through LDS: an instruction's lanes cover 16 consecutive rows of four neighbouring
 // columns, and with few columns the instructions for j beyond them have no active lane.
 __device__ __forceinline__ void skinny_store_transposed(const SkinnyParams &p, const f32x4 (&acc)[2], int tile, int lane,
-                                                        int arrivals)
+                                                        int arrivals, int col0)
 {
     const int r = lane & 15, h = lane >> 4;
     if (arrivals == 1) {
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            const int col = h + 4 * (k & 3), row = tile * kTileRows + 16 * (k >> 2) + r;
+            const int col = col0 + h + 4 * (k & 3), row = tile * kTileRows + 16 * (k >> 2) + r;
             if (col < p.batch && row < p.M) p.Y[(size_t)col * p.ldy + row] = float_to_half_bits(acc[k >> 2][k & 3]);
         }
         return;
@@ -238,7 +238,7 @@ __device__ __forceinline__ void skinny_store_transposed(const SkinnyParams &p, c
     unsigned long long mine[8], old[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-        const int col = h + 4 * (k & 3), row = tile * kTileRows + 16 * (k >> 2) + r;
+        const int col = col0 + h + 4 * (k & 3), row = tile * kTileRows + 16 * (k >> 2) + r;
         mine[k] = encode_partial(acc[k >> 2][k & 3]);
         old[k] = 0;
         if (col < p.batch)
@@ -246,7 +246,7 @@ __device__ __forceinline__ void skinny_store_transposed(const SkinnyParams &p, c
     }
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-        const int col = h + 4 * (k & 3), row = tile * kTileRows + 16 * (k >> 2) + r;
+        const int col = col0 + h + 4 * (k & 3), row = tile * kTileRows + 16 * (k >> 2) + r;
         const unsigned long long total = old[k] + mine[k];
         if (col < p.batch && arrivals_of(total) == (unsigned)arrivals) {
             if (row < p.M) p.Y[(size_t)col * p.ldy + row] = float_to_half_bits(decode_total(total));
@@ -346,9 +346,9 @@ __device__ __forceinline__ void compute_folded(TileRegs<Q, Z, SUB> &cur, const u
 // unit's tile and X slice a piece at a time.  Requested all at once at the top of a unit, the 8 waves of a
 // workgroup queue up behind each other in the CU's vector-memory pipeline (measured: up to 1.4 us per unit
 // for the wave that comes last, and everyone waits for it at the barrier).
-template <int Q, int Z, int LDS_STEPS, int TC, class Issue>
+template <int Q, int Z, int LDS_STEPS, int NB, int TC, class Issue>
 __device__ __forceinline__ void compute_table(const TileRegs<Q, Z, 1> &cur, const uint8_t *xs_buf, const uint8_t *tab,
-                                              uint32_t copy_bits, int r, int h, f32x4 (&acc)[2], unsigned &t_operands,
+                                              uint32_t copy_bits, int r, int h, f32x4 (&acc)[NB][2], unsigned &t_operands,
                                               Issue issue)
 {
     // chunk order, then the 4 x 4 dword transpose across the lanes r, r+16, r+32, r+48:
@@ -391,9 +391,9 @@ __device__ __forceinline__ void compute_table(const TileRegs<Q, Z, 1> &cur, cons
     // operands of step g + kAhead are requested before the MFMAs of step g are issued (a fence per step keeps the compiler
     // from moving the requests down to their use, which left one MFMA to cover each LDS access), and the sums of a block
     // are scaled while the next block's first steps run.  Measured (q = 3, 16 columns): 7168 x 28672 33.7 -> 32.3 us,
-    // 28672 x 8192 37.0 -> 35.5, 2048 x 4096 8.5 -> 8.0.  Where two sets of block sums do not fit the registers (four planes) a
-    // block is scaled at its end and the schedule is the compiler's.
-    auto fetch = [&](int g, f16x8 (&a)[2][Q], f16x8 &bx) {
+    // 28672 x 8192 37.0 -> 35.5, 2048 x 4096 8.5 -> 8.0.  Where two sets of block sums do not fit the registers (four planes, two
+    // groups of columns) a block is scaled at its end and the schedule is the compiler's.
+    auto fetch = [&](int g, f16x8 (&a)[2][Q], f16x8 (&bx)[NB]) {
         const int B = g >> 2, s = g & 3;
 #pragma unroll
         for (int t = 0; t < 2; ++t)
@@ -418,16 +418,18 @@ __device__ __forceinline__ void compute_table(const TileRegs<Q, Z, 1> &cur, cons
                     if (s == 3) a[t][i] = expand_byte<3>(wn, wn4, 0x3c003c00u);
                 }
             }
-        bx = *reinterpret_cast<const f16x8 *>(xb + (16 * B + 4 * s) * 16);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) bx[nb] = *reinterpret_cast<const f16x8 *>(xb + nb * kXBuf<2> + (16 * B + 4 * s) * 16);
     };
-    constexpr bool kDeferred = Q <= 3;  // registers: two sets of block sums, three of operands
+    constexpr bool kDeferred = Q <= 3 && NB == 1;  // registers: two sets of block sums, three of operands
+    constexpr bool kByBlock = NB > 1;  // registers: no operands from one block to the next
     constexpr int kAhead = kDeferred && Q + Z <= 3 ? 2 : 1;
     constexpr int kBufs = kAhead + 1, kSums = kDeferred ? 2 : 1;
-    f16x8 abuf[kBufs][2][Q], bbuf[kBufs];
-    f32x4 C[kSums][2][Q];  // first written by the MFMAs of a block's step 0, whose addend is the constant zero
-    f32x4 Cz[kSums];
+    f16x8 abuf[kBufs][2][Q], bbuf[kBufs][NB];
+    f32x4 C[kSums][NB][2][Q];  // first written by the MFMAs of a block's step 0, whose addend is the constant zero
+    f32x4 Cz[kSums][NB];
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    // acc[t][j] (batch column h + 4j, row 16t + r) += alpha_i(row, block B) * C[t][i][j]  (+ z * column sums)
+    // acc[nb][t][j] (batch column 16 nb + h + 4j, row 16t + r) += alpha_i(row, block B) * C[nb][t][i][j]  (+ z * column sums)
     auto apply = [&](int B, int t) {
 #pragma unroll
         for (int c = 0; c < Q + Z; ++c) {
@@ -436,25 +438,35 @@ __device__ __forceinline__ void compute_table(const TileRegs<Q, Z, 1> &cur, cons
             const float v = half_bits_to_float((e & 1) ? (pair >> 16) : (pair & 0xffffu));
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                acc[t][j] = fmaf(v, c < Q ? C[B % kSums][t][c < Q ? c : 0][j] : Cz[B % kSums][j], acc[t][j]);
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+                    acc[nb][t][j] = fmaf(v, c < Q ? C[B % kSums][nb][t][c < Q ? c : 0][j] : Cz[B % kSums][nb][j], acc[nb][t][j]);
         }
     };
 #pragma unroll
-    for (int g = 0; g < kAhead; ++g) fetch(g, abuf[g], bbuf[g]);
+    for (int g = 0; g < kAhead; ++g)
+        if (!kByBlock) fetch(g, abuf[g], bbuf[g]);
 #pragma unroll
     for (int g = 0; g < 16; ++g) {
         const int B = g >> 2, s = g & 3, cb = g % kBufs;
         if (kDeferred) __builtin_amdgcn_sched_barrier(0);
-        if (g + kAhead < 16) fetch(g + kAhead, abuf[(g + kAhead) % kBufs], bbuf[(g + kAhead) % kBufs]);
+        if (kByBlock ? s == 0 : g + kAhead < 16) {
+            const int f = kByBlock ? g : g + kAhead;
+            fetch(f, abuf[f % kBufs], bbuf[f % kBufs]);
+        }
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int nb = 0; nb < NB; ++nb) {
 #pragma unroll
-            for (int i = 0; i < Q; ++i)
-                C[B % kSums][t][i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bbuf[cb], abuf[cb][t][i],
-                                                                           s == 0 ? zero : C[B % kSums][t][i], 0, 0, 0);
-        if (Z)
-            Cz[B % kSums] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bbuf[cb], __builtin_bit_cast(f16x8, ones),
-                                                                  s == 0 ? zero : Cz[B % kSums], 0, 0, 0);
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int i = 0; i < Q; ++i)
+                    C[B % kSums][nb][t][i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bbuf[cb][nb], abuf[cb][t][i],
+                                                                                   s == 0 ? zero : C[B % kSums][nb][t][i], 0, 0, 0);
+            if (Z)
+                Cz[B % kSums][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bbuf[cb][nb], __builtin_bit_cast(f16x8, ones),
+                                                                          s == 0 ? zero : Cz[B % kSums][nb], 0, 0, 0);
+        }
+        if (kByBlock && s < 3) fetch(g + 1, abuf[(g + 1) % kBufs], bbuf[(g + 1) % kBufs]);
         issue(g);
         if (kDeferred) {
             if (B > 0 && s < 2) apply(B - 1, s);
@@ -473,14 +485,14 @@ __device__ __forceinline__ void compute_table(const TileRegs<Q, Z, 1> &cur, cons
 // ---------------------------------------------------------------------------------
 // the kernel
 // ---------------------------------------------------------------------------------
-// NB = groups of 16 batch columns (1, 2 or 4 with VER 1, one with VER 2).  With one group the
+// NB = groups of 16 batch columns (1, 2 or 4 with VER 1, 1 or 2 with VER 2).  With one group the
 // X slice is double-buffered in LDS; with more, the staged slice (16.6 KB per group) is single-
 // buffered: the next slice waits in registers and replaces it between two barriers.
 template <int Q, int Z, int SUB, int VER, int LDS_STEPS, int NB, int NW>
 __global__ __launch_bounds__(64 * NW) void bcq_skinny_kernel(SkinnyParams p)
 {
     constexpr int NT = 64 * NW;
-    static_assert(VER == 1 || (SUB == 1 && NB == 1), "the table kernel: one scaling group per block, 16 columns");
+    static_assert(VER == 1 || (SUB == 1 && NB <= 2), "the table kernel: one scaling group per block, up to 32 columns");
     // Eight waves: registers allow one workgroup per CU (two waves per SIMD from q = 2 on), which leaves
     // room for 16 table copies and two X buffers.
     constexpr bool kDouble = NB == 1;
@@ -577,7 +589,7 @@ __global__ __launch_bounds__(64 * NW) void bcq_skinny_kernel(SkinnyParams p)
                 if constexpr (VER == 1) compute_folded<Q, Z, SUB, NB>(cur, xs + buf * kBuf, r, h, acc);
                 else {
                     unsigned t_operands = 0;
-                    compute_table<Q, Z, LDS_STEPS, TC>(cur, xs + buf * kBuf, tab, copy_bits, r, h, acc[0], t_operands, issue);
+                    compute_table<Q, Z, LDS_STEPS, NB, TC>(cur, xs + buf * kBuf, tab, copy_bits, r, h, acc, t_operands, issue);
 #ifdef BCQ_TRACE
                     ts[8] += t_operands - last;  // next unit's loads issued, this tile arrived, un-rotated and transposed
                     last = t_operands;
@@ -608,7 +620,7 @@ __global__ __launch_bounds__(64 * NW) void bcq_skinny_kernel(SkinnyParams p)
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
                 if constexpr (VER == 2)
-                    skinny_store_transposed(p, acc[nb], seg_tile, flush_lane, arrivals);
+                    skinny_store_transposed(p, acc[nb], seg_tile, flush_lane, arrivals, 16 * nb);
                 else
                     skinny_store<NB == 1 ? 8 : 4>(p, acc[nb], seg_tile, flush_lane, stage + wave * kStageFloats, arrivals, 16 * nb);
             }
@@ -679,9 +691,16 @@ static hipError_t launch_skinny_qz(const SkinnyParams &p, int nb, int parts, boo
     if (sub == 2) return launch_skinny_one<Q, Z, 2, 1, 0, 1>(p, parts, single_slice, stream);
     if (sub == 4) return launch_skinny_one<Q, Z, 4, 1, 0, 1>(p, parts, single_slice, stream);
     // Up to 16 columns the table kernel (7168 x 28672, q = 3: 42 against 55 us for the kernel that folds alpha into A,
-    // eager launches); more columns come here only on layers too small for bcq_wide.hip and take the alpha-folding kernel,
-    // whose expansion is shared by the column groups and which starts without a 64 KB table.
+    // eager launches); more columns come here only on layers too small for bcq_wide.hip, or with one column slice, and take the
+    // alpha-folding kernel, whose expansion is shared by the column groups and which starts without a 64 KB table.  With one
+    // slice and enough tiles for eight waves per workgroup the table kernel serves 32 columns too (up to three planes: registers):
+    // 65536 x 512, q = 3 10.0 against 11.7 us, 131072 x 512 18.5 / 19.9, q = 2 with offset 15.3 / 17.0 (bcq_wide.hip, whose
+    // second K group then has nothing: 33.8, 29.7).
     const long long tiles = (long long)p.ntile * p.nslice;
+    if constexpr (Q <= 3) {
+        if (version == 0 && nb == 2 && p.nslice == 1 && waves == 0 && tiles >= 2048)
+            return launch_skinny_one<Q, Z, 1, 2, 4, 2, 8>(p, parts, single_slice, stream);
+    }
     if (version == 1 || nb > 1) {
         if (nb == 4) return launch_skinny_one<Q, Z, 1, 1, 0, 4>(p, parts, single_slice, stream);
         if (nb == 2) return launch_skinny_one<Q, Z, 1, 1, 0, 2>(p, parts, single_slice, stream);

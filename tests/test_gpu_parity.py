@@ -584,6 +584,26 @@ def test_far_apart_rows_of_many_vectors(group, batch, ldx):
     assert np.array_equal(Y.cpu().numpy().astype(np.float64), expect)
 
 
+@pytest.mark.parametrize("M,N,q,offset,group,batch", [
+    (65536, 512, 3, False, 128, 17), (65536 + 37, 480, 3, True, 480, 32), (65505, 256, 2, True, 128, 29), (70001, 96, 1, False, 96, 18)])
+def test_one_slice_of_many_tiles(M, N, q, offset, group, batch):
+    """17..32 vectors on layers of one column slice and at least 2048 row tiles, which take the table kernel with two groups of 16
+    columns: bit for bit the oracle's result on exact inputs, padded rows of X and Y, with and without a workspace."""
+    L = bcq_synth.make_exact_layer(M, N, q, group=group, offset=offset, batch=batch, seed=M + q)
+    pl = U.upload_and_pack(L, max_batch=batch)
+    expect = ref.gemm(L.planes, L.alpha, L.offset, L.x).astype(np.float16).astype(np.float64)
+    X = torch.full((batch, N + 40), 7.0, dtype=torch.float16, device="cuda")
+    X[:, :N] = U.x_dev(L)
+    Y = torch.full((batch, M + 10), 3.0, dtype=torch.float16, device="cuda")
+    workspace = torch.zeros(batch * (M + 31) // 32 * 32 * 8 + 256, dtype=torch.uint8, device="cuda")
+    for ws in (None, workspace):
+        Y[:, :M] = 0.0
+        bcq.gemm_skinny(pl.desc, pl.packed, X, X.stride(0), Y, Y.stride(0), batch, ws)
+        torch.cuda.synchronize()
+        assert np.array_equal(Y[:, :M].cpu().numpy().astype(np.float64), expect)
+        assert torch.all(Y[:, M:] == 3.0)
+
+
 def test_wide_batch_exact_and_strided():
     L = bcq_synth.make_exact_layer(150, 3072, 3, group=128, offset=True, batch=40, seed=77)
     pl = U.upload_and_pack(L, max_batch=40)
