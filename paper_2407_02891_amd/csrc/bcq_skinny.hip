@@ -756,8 +756,16 @@ hipError_t launch_skinny(const Geom &g, const void *packed, const uint16_t *X, i
     // Byte offsets into the rows of X of a pass are 32 bits, in all kernels: no pass has more rows than they reach.
     const long long reach = 1 + (0x7ffffff0ll - g.N) / ldx;
     const bool in_reach = reach >= (batch < most ? batch : most);
+    // Fewest tiles from which its start-up and its steps one after the other on a row tile are paid for (us, kernels here / it): most
+    // layers 128; the more operands a step has, the later.  Groups of 32: q = 3 with offset 512 tiles 18.3 / 19.8, 1024 tiles
+    // 20.4 / 20.9 (20 columns) and 44.5 / 44.2 (64); q = 3, or 2 with offset, 128 tiles 15.7 / 16.8, 512 tiles 18.5 / 18.1.  Four planes,
+    // one group per block, 512 tiles 12.0 / 12.8, 1024 tiles 13.4 / 13.9 (20 columns) and 15.7 / 15.5 (32), 1398 tiles 19.5 / 17.0 (32).  With offset and few
+    // columns in the second group (20) 512 tiles 10.1 / 10.4, 1024 tiles 11.5 / 11.2.
+    const int terms = g.q + g.z;
+    const int least = sub == 4 && terms == 4 ? 1024 : sub == 4 && terms == 3 ? 512 : sub == 1 && g.q == 4 ? 1280
+                      : sub == 1 && g.z && batch <= 24 ? 1024 : 128;
     const bool one_pass = batch <= most || all_tiles >= 8192 || sub > 1;
-    const bool wide = most > 16 && ver == 0 && in_reach && (tuning.waves == 8 || (tuning.waves == 0 && g.nslice > 1 && all_tiles >= 128 && one_pass));
+    const bool wide = most > 16 && ver == 0 && in_reach && (tuning.waves == 8 || (tuning.waves == 0 && g.nslice > 1 && all_tiles >= least && one_pass));
     // The kernels here: up to 64 columns in one pass with alpha folded into A and one scaling group per block, else 16.
     int narrow = sub == 1 && ver != 2 ? (batch > 32 ? 64 : batch > 16 ? 32 : 16) : 16;
     if (narrow > reach) narrow = (int)reach;
