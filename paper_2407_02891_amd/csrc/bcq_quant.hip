@@ -589,7 +589,9 @@ __global__ void gptq_tables_kernel(int M, int n_bits, int q, const int8_t *__res
 // To keep the chain short, the two divisions of a decision are multiplications by reciprocals with the same results:
 //   * rint((w - qbias) / S): see linear_int;
 //   * err / U[j][j] in binary32: quotient, remainder and correction with the rounded reciprocal (Markstein's method),
-//     which gives the correctly rounded quotient.
+//     which gives the correctly rounded quotient unless something on the way leaves the normal range (a zero, infinite or
+//     very large or small diagonal or error); a group of eight columns with such an error is gone through again, with divisions
+//     (a test per column, on the chain, took 8 % of the pass).
 // and Eq. 6 is a table look-up.  U's rows are staged in LDS such that the 16 factors of a lane for column c, those of
 // the columns 8 (c / 8 + k) + l, come in four 16-byte reads: [c][k / 4][l][k % 4].
 constexpr int kGptqBlock = 128, kGptqLanes = 8, kGptqRows = 32;  // columns per block, lanes per row, rows per workgroup
@@ -611,7 +613,7 @@ __global__ __launch_bounds__(256) void gptq_block_kernel(int M, int Mp, int N, i
                                                          float *__restrict__ Err)
 {
     __shared__ __attribute__((aligned(16))) float Us[kGptqBlock][4][kGptqLanes][4];
-    __shared__ prod_f32x2 diag[kGptqBlock];  // U[c][c] and its reciprocal
+    __shared__ prod_f32x2 diag[kGptqBlock];  // U[c][c] and its reciprocal, no number unless that stands for the division
     __shared__ uint8_t table[NIBBLES ? 1 : kGptqRows][256];
     const int tid = threadIdx.x, l = tid & 7, row = tid >> 3, m = blockIdx.x * kGptqRows + row;
     const bool live = m < M;
@@ -628,7 +630,7 @@ __global__ __launch_bounds__(256) void gptq_block_kernel(int M, int Mp, int N, i
     }
     if (tid < kGptqBlock) {
         const float d = tid < cols ? U[(size_t)(c0 + tid) * N + c0 + tid] : 1.0f;
-        diag[tid] = prod_f32x2{d, 1.0f / d};
+        diag[tid] = prod_f32x2{d, fabsf(d) >= 0x1p-40f && fabsf(d) <= 0x1p40f ? 1.0f / d : __builtin_nanf("")};
     }
     double s = 1.0, b = 0.0;
     unsigned long long nib = 0;
@@ -649,8 +651,9 @@ __global__ __launch_bounds__(256) void gptq_block_kernel(int M, int Mp, int N, i
     for (int i = 0; 8 * i < cols; ++i) {
         int my_q = 0;
         float my_err = 0.0f;
-        auto step = [&](auto lane_of) {
+        auto step = [&](auto lane_of, auto divide) PROD_INLINE {
             constexpr int kLane = decltype(lane_of)::value;
+            constexpr bool kDivide = decltype(divide)::value;
             const int c = 8 * i + kLane;  // (columns beyond `cols` are decided too, and dropped)
             prod_f32x4 u[4];
 #pragma unroll
@@ -662,7 +665,7 @@ __global__ __launch_bounds__(256) void gptq_block_kernel(int M, int Mp, int N, i
             const float qv = (float)(s * wq + b);
             const float a = w[0] - qv;
             const float q0 = a * d[1];
-            const float own = fmaf(fmaf(-q0, d[0], a), d[1], q0);
+            const float own = kDivide ? a / d[0] : fmaf(fmaf(-q0, d[0], a), d[1], q0);
             const float err = gptq_broadcast<kLane>(own);
             my_q = l == kLane ? wq : my_q;
             my_err = l == kLane ? err : my_err;
@@ -670,10 +673,22 @@ __global__ __launch_bounds__(256) void gptq_block_kernel(int M, int Mp, int N, i
 #pragma unroll
             for (int k = 0; k < 16; ++k) w[k] = fmaf(-err, u[k >> 2][k & 3], w[k]);
         };
-        step(std::integral_constant<int, 0>{}); step(std::integral_constant<int, 1>{});
-        step(std::integral_constant<int, 2>{}); step(std::integral_constant<int, 3>{});
-        step(std::integral_constant<int, 4>{}); step(std::integral_constant<int, 5>{});
-        step(std::integral_constant<int, 6>{}); step(std::integral_constant<int, 7>{});
+        auto group = [&](auto divide) PROD_INLINE {
+            step(std::integral_constant<int, 0>{}, divide); step(std::integral_constant<int, 1>{}, divide);
+            step(std::integral_constant<int, 2>{}, divide); step(std::integral_constant<int, 3>{}, divide);
+            step(std::integral_constant<int, 4>{}, divide); step(std::integral_constant<int, 5>{}, divide);
+            step(std::integral_constant<int, 6>{}, divide); step(std::integral_constant<int, 7>{}, divide);
+        };
+        float before[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) before[k] = w[k];
+        group(std::false_type{});
+        // (every lane has the error of its column: zero, or 2^-60 .. 2^60)
+        if (__builtin_expect(__any((__builtin_amdgcn_ubfe(__float_as_uint(my_err), 23, 8) - 67u > 120u) & (my_err != 0.0f)), 0)) {
+#pragma unroll
+            for (int k = 0; k < 16; ++k) w[k] = before[k];
+            group(std::true_type{});
+        }
         if (8 * i + l < cols) {
             if (live) w_int[(size_t)m * N + c0 + 8 * i + l] = (uint8_t)my_q;
             if (m < Mp) Err[(size_t)(8 * i + l) * Mp + m] = live ? my_err : 0.0f;  // zeros in the pad rows

@@ -216,6 +216,46 @@ def test_gptq_blocks_and_panels(M, N, n, q):
     _assert_gptq_explained(W32, U32, S64, b64, choices, n, Wq, f"gptq {M}x{N} n={n} q={q}")
 
 
+def test_gptq_unusual_diagonals():
+    """Diagonal entries of U at which a reciprocal does not stand for the division: infinite, zero, subnormal and with a subnormal or
+    infinite reciprocal, and errors that are zero or leave the normal range.  Integers of a column-by-column replay in
+    binary32 with divisions, bit for bit (one block; a weight that is not a number gives 0)."""
+    M, N, n, q = 37, 96, 4, 3
+    rng = np.random.default_rng(3)
+    W32 = (rng.standard_normal((M, N)) * 0.02).astype(np.float32)
+    W32[1] = np.float32(0.01)                                              # errors of zero
+    W32[2] *= np.float32(2.0 ** -110)
+    W32[3] *= np.float32(2.0 ** 100)
+    U32 = (np.triu(rng.standard_normal((N, N)) * 0.3, 1) + np.diag(0.5 + rng.random(N))).astype(np.float32)
+    for j, d in ((5, np.inf), (11, 2.0 ** 127), (17, 2.0 ** 125), (23, 2.0 ** -20), (31, -np.inf), (40, 2.0 ** 60), (70, 1e-41),
+                 (80, 0.0)):
+        U32[j, j] = d
+        if abs(d) < 1e-3:
+            U32[j, j + 1:] *= np.float32(2.0 ** -20)
+    b32 = W32.min(axis=1)
+    span = W32.max(axis=1) - b32
+    S32 = np.where(span > 0, span / 15, 1.0).astype(np.float32)
+    parts = fuse.all_partitions(n, q)
+    pick = rng.integers(0, len(parts), size=M)
+    labels = np.stack([_labels_of(parts[i], n) for i in pick])
+    nearest = np.stack([fuse.nearest_bcchoice(np.arange(16), fuse.bcchoice(parts[i], n)) for i in pick])
+    s, b, w = S32.astype(np.float64), b32.astype(np.float64), W32.copy()
+    want = np.empty((M, N), dtype=np.uint8)
+    with np.errstate(all="ignore"):
+        for j in range(N):
+            t = np.rint((w[:, j].astype(np.float64) - b) / s)
+            wq = nearest[np.arange(M), np.nan_to_num(np.clip(t, 0, 15), nan=0.0).astype(np.int64)]
+            want[:, j] = wq
+            err = (w[:, j] - (s * wq + b).astype(np.float32)) / U32[j, j]
+            w[:, j + 1:] = (w[:, j + 1:].astype(np.float64) - err[:, None].astype(np.float64) * U32[j, j + 1:]).astype(np.float32)
+    w_int = torch.full((M, N), 255, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(bcq.quant_workspace_bytes(M, N), dtype=torch.uint8, device="cuda")
+    bcq.quant_gptq(M, N, n, q, _dev(W32), _dev(U32), _dev(S32), _dev(b32), _dev(labels), w_int, ws)
+    torch.cuda.synchronize()
+    got = w_int.cpu().numpy()
+    assert np.array_equal(got, want), np.argwhere(got != want)[:10]
+
+
 @pytest.mark.parametrize("M,N,n,q", [(37, 1024, 3, 2), (12, 512, 4, 3), (5, 1536, 5, 3), (8, 512, 4, 4)])
 def test_from_linear_rows(M, N, n, q):
     rng = np.random.default_rng(300 + N + n + q)
