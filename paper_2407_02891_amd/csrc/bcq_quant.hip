@@ -517,8 +517,8 @@ __global__ void keep_best_kernel(int M, int Mp, int n_bits, int ntile, int g, in
     }
 }
 
-hipError_t launch_quant_search(int M, int N, int n_bits, int q, int grid, const float *W, const float *H, float *S,
-                               float *qbias, int8_t *labels, float *err_out, void *workspace, hipStream_t stream)
+static hipError_t search_rows(int M, int N, int n_bits, int q, int grid, const float *W, const float *H, float *S, float *qbias,
+                              int8_t *labels, float *err_out, void *workspace, hipStream_t stream)
 {
     const QuantWorkspace w = carve(workspace, M, N);
     hipLaunchKernelGGL(transpose_kernel, dim3((N + 31) / 32, (w.Mp + 31) / 32), dim3(32, 8), 0, stream, M, w.Mp, N, W,
@@ -556,6 +556,27 @@ hipError_t launch_quant_search(int M, int N, int n_bits, int q, int grid, const 
         if (e != hipSuccess) return e;
     }
     return hipGetLastError();
+}
+
+// Rows are independent in the search and in the GPTQ pass, and both take at most this many at a time (in the same workspace): the
+// products address a tile of [column][row] matrices by 32-bit byte offsets, which reach 2^23 rows, and the grids of the
+// row-wise kernels have 2^16 blocks of 32 rows in their second dimension.
+constexpr int kMaxRows = 1 << 20;
+
+hipError_t launch_quant_search(int M, int N, int n_bits, int q, int grid, const float *W, const float *H, float *S,
+                               float *qbias, int8_t *labels, float *err_out, void *workspace, hipStream_t stream)
+{
+    hipError_t e = hipSuccess;
+    for (int rows; M > 0 && e == hipSuccess; M -= rows) {
+        rows = M < kMaxRows ? M : kMaxRows;
+        e = search_rows(rows, N, n_bits, q, grid, W, H, S, qbias, labels, err_out, workspace, stream);
+        W += (size_t)rows * N;
+        S += rows;
+        qbias += rows;
+        labels += (size_t)rows * n_bits;
+        if (err_out) err_out += rows;
+    }
+    return e;
 }
 
 // ---------------------------------------------------------------------------------
@@ -705,9 +726,8 @@ __global__ __launch_bounds__(256) void gptq_block_kernel(int M, int Mp, int N, i
 // which the pass does not use otherwise.
 constexpr int kGptqPanel = 4 * kGptqBlock;
 
-hipError_t launch_quant_gptq(int M, int N, int n_bits, int q, const float *W, const float *U, const float *S,
-                             const float *qbias, const int8_t *labels, uint8_t *w_int, void *workspace,
-                             hipStream_t stream)
+static hipError_t gptq_rows(int M, int N, int n_bits, int q, const float *W, const float *U, const float *S, const float *qbias,
+                            const int8_t *labels, uint8_t *w_int, void *workspace, hipStream_t stream)
 {
     const QuantWorkspace w = carve(workspace, M, N);
     auto *nibbles = reinterpret_cast<unsigned long long *>(w.part);  // two of the (ceil(N / 128) + 3) Mp floats from here
@@ -734,6 +754,23 @@ hipError_t launch_quant_gptq(int M, int N, int n_bits, int q, const float *W, co
         update(p0, p1, p1, N);
     }
     return hipGetLastError();
+}
+
+hipError_t launch_quant_gptq(int M, int N, int n_bits, int q, const float *W, const float *U, const float *S,
+                             const float *qbias, const int8_t *labels, uint8_t *w_int, void *workspace,
+                             hipStream_t stream)
+{
+    hipError_t e = hipSuccess;
+    for (int rows; M > 0 && e == hipSuccess; M -= rows) {
+        rows = M < kMaxRows ? M : kMaxRows;
+        e = gptq_rows(rows, N, n_bits, q, W, U, S, qbias, labels, w_int, workspace, stream);
+        W += (size_t)rows * N;
+        S += rows;
+        qbias += rows;
+        labels += (size_t)rows * n_bits;
+        w_int += (size_t)rows * N;
+    }
+    return e;
 }
 
 // ---------------------------------------------------------------------------------

@@ -216,6 +216,41 @@ def test_gptq_blocks_and_panels(M, N, n, q):
     _assert_gptq_explained(W32, U32, S64, b64, choices, n, Wq, f"gptq {M}x{N} n={n} q={q}")
 
 
+@pytest.mark.parametrize("M,N", [(2 ** 23 + 2 ** 20 + 165, 132), (2 ** 20 + 37, 8)])
+def test_many_rows(M, N):
+    """More rows than the byte offsets of a tile reach (2^23, from 128 columns on) or than are taken at a time: the search and the GPTQ
+    pass give sampled rows what they give them alone."""
+    n, q, grid = 2, 1, 1
+    free, _ = torch.cuda.mem_get_info()
+    if free < 10 * 4 * M * max(N, 64):
+        pytest.skip("not enough device memory")
+    g = torch.Generator(device="cuda").manual_seed(5)
+    W = torch.randn((M, N), device="cuda", generator=g) * 0.02
+    _, H32 = _layer(4, N, seed=N)
+    H, Uf = _dev(H32), _dev(quantizer.cholesky_factor(H32).astype(np.float32))
+
+    def both(W):
+        rows = W.shape[0]
+        S, b, err = (torch.empty(rows, device="cuda") for _ in range(3))
+        lab = torch.full((rows, n), 7, dtype=torch.int8, device="cuda")
+        w_int = torch.full((rows, N), 255, dtype=torch.uint8, device="cuda")
+        ws = torch.empty(bcq.quant_workspace_bytes(rows, N), dtype=torch.uint8, device="cuda")
+        bcq.quant_search(rows, N, n, q, grid, W, H, S, b, lab, err, ws)
+        bcq.quant_gptq(rows, N, n, q, W, Uf, S, b, lab, w_int, ws)
+        torch.cuda.synchronize()
+        return S, b, lab, err, w_int
+
+    whole = both(W)
+    for lo in (0, 2 ** 20 - 128, M // 2 // 128 * 128, (M - 200) // 128 * 128):
+        hi = min(M, lo + 300)
+        for a, part in zip(whole, both(W[lo:hi].contiguous())):
+            a = a[lo:hi]
+            if a.dtype == torch.float32:
+                assert torch.allclose(a, part, rtol=1e-5, atol=0)
+            else:
+                assert (a != part).float().mean() <= 1e-4   # (other rows of a tile may move the rounding of a sum)
+
+
 def test_gptq_unusual_diagonals():
     """Diagonal entries of U at which a reciprocal does not stand for the division: infinite, zero, subnormal and with a subnormal or
     infinite reciprocal, and errors that are zero or leave the normal range.  Integers of a column-by-column replay in
