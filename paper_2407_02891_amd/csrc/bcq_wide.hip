@@ -105,15 +105,15 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void bcq_wide_kernel(WideParams
     // ---- copying X: instruction c of this wave fills the four rows 4 (wave kCopies + c) .. + 3 of the stage ----
     const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t *>(p.X), 0, (int)(2u * ((uint32_t)(p.batch - 1) * (uint32_t)p.ldx + (uint32_t)p.N)), kRawBufferFlags);
-    uint32_t src[kCopies];   // byte offset of the lane's chunk in block 0 of slice 0, or out of range
-    int chunk8[kCopies];     // first column of that chunk inside a block
+    uint32_t src[kCopies];   // byte offset of the lane's chunk in block 0 of slice 0
+    int chunk8[kCopies];     // first column of that chunk inside a block; beyond all columns for a row without a vector
 #pragma unroll
     for (int c = 0; c < kCopies; ++c) {
         const int row = (4 * (wave * kCopies + c) + (lane >> 4)) % kRows;  // the same rows for both K groups
         const int rho = row & 15, g = rho ^ ((rho & 4) << 1);
         const int col = (row & ~15) + (rho >> 2) + 4 * (rho & 3);  // staged row 4 h + j holds column h + 4 j (see wide_store)
-        chunk8[c] = 8 * ((lane & 15) ^ g);
-        src[c] = col < p.batch ? 2u * ((uint32_t)col * (uint32_t)p.ldx + (uint32_t)chunk8[c]) : 0xfffffff0u;
+        chunk8[c] = col < p.batch ? 8 * ((lane & 15) ^ g) : p.N;
+        src[c] = 2u * ((uint32_t)col * (uint32_t)p.ldx + (uint32_t)chunk8[c]);
     }
     auto copy_stage = [&](uint8_t *stage, int pair, int B) {
         int first = wave * kCopies;
