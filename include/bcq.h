@@ -168,9 +168,10 @@ bcq_status bcq_from_linear(int32_t M, int32_t N, int32_t group, int32_t n_bits, 
  * N a multiple of 4, 2 <= n_bits <= 8, q <= n_bits, 1 <= grid <= 4096; q > 4 or N > 32768 is
  * BCQ_ERR_UNSUPPORTED (all three calls).
  * Integer decisions are taken in binary64; the error sums and the compensation accumulate in
- * binary32 on the matrix cores, their operands split into pairs of binary16 numbers.  Against binary64 that
- * measured no larger errors than binary32 matrix instructions, on Gaussian data with channels up to 2^12 times as
- * loud as the others; an operand keeps 22 to 24 bits where it is not below 2^-13 of its row's or column's largest value.
+ * binary32 on the matrix cores, their operands split into pairs of binary16 numbers (sums
+ * of up to 20 terms in binary32 throughout).  Against binary64 that measured no larger errors than binary32 matrix
+ * instructions, on Gaussian data with channels up to 2^12 times as loud as the others.  An operand keeps 22 to 24 bits where
+ * it is not below 2^-10 of the largest of the first 32 values of its row or column; quantities of the GPTQ pass 2^-7.
  */
 size_t bcq_quant_workspace_bytes(int32_t M, int32_t N);
 bcq_status bcq_quant_hessian(int32_t N, int32_t T, const float *X, float *H, void *stream);

@@ -19,22 +19,26 @@
 // 2^-23 |s x| (three significands in four are exact); below that it is at most 2^-25, half the smallest step of a binary16
 // number.  The dropped lo lo' is at most 2^-22 of the term.  The accumulator is rounded three times per 16 values of k
 // (measured: the instruction over 32 values rounds twice) instead of 16 times, which outweighs that: 2-norm error of
-// 2 X^T X with standard normal X against binary64, binary32 instruction / this, 33 samples 1.04e-7 / 0.96e-7, 256 samples
-// 2.8e-7 / 1.8e-7, 2048 samples 6.6e-7 / 4.1e-7.
-// The scales: 2^-24 to 2^16 is what binary16 reaches, and values far below the largest of their row or column must keep
-// their bits, because what they are multiplied by may be as much larger (the inverse of a diagonal block times entries of a
-// loud channel).  s puts the largest magnitude of the row or column so far at 2^10..2^11: full precision down to 2^-13 of
-// it, and later values may be 29 times larger.  A larger one ends the stretch of steps: all scales that it does not fit
-// are chosen again, the accumulators move to them (powers of two: exact) and the steps go on from there, which costs about
-// two steps.  A quadratic form knows better: |d| is bounded by the row's range, and the values of a positive semidefinite B
-// by its diagonal, which together with the largest of all puts them at most at 2^15.  A row or column that is zero in the
-// first step takes its tile's largest, or the diagonal of a triangular operand; if that turns out more than 2^6 too large,
-// or a bound too small, the tile is computed once more with all magnitudes known.
+// 2 X^T X with standard normal X against binary64, binary32 instruction / this, 16 samples 7.4e-8 / 8.4e-8, 24 samples 8.9e-8 /
+// 8.6e-8, 256 samples 2.8e-7 / 1.8e-7, 2048 samples 6.6e-7 / 4.1e-7.  Up to 20 values of k the binary32 instruction is used.
+// The scales: binary16 reaches from 2^-24 to 2^16, and values far below the largest of their row or column should keep their
+// bits, because what they are multiplied by may be as much larger.  So s is chosen from the largest magnitude in the first 32
+// values of the row or column, which it puts at 2^8..2^9: full precision down to 2^-10 of it, and later values may be 117
+// times larger.  Where more is known, more is used:
+//   quadratic forms   d is bounded by its row's range, and the values of a positive semidefinite B by its diagonal, which
+//                 together with the largest of all puts them at most at 2^15;
+//   triangular operands, zero in the first 32 values   the diagonal;
+//   errors of the GPTQ pass   they have been divided by the diagonal of U, whose smallest value in reach is known (ProductArgs::least).
+//                 They and the rows of U grow more on the way than data do and start at 2^5, which leaves a factor of 1875;
+//   the factor    its matrix is scaled so that all channels are of one size (bcq_quant.hip).
+// The largest magnitude of all values is tracked on the way; a tile with a guess that was too low, or more than 2^6 too high, is
+// computed once more with s from the true maximum, at 2^14.  (Scales that change on the way, by a flag in LDS per step that
+// all waves look at, cost 11 % of a large Hessian and 24 % of a small one.)
 // Inverse-Hessian factor, error per column of U against binary64, binary32 instruction / this, four channels 2^10 (2^12) times as
-// loud at the start of every block of 128 channels: 2.0e-7 / 1.9e-7 (5.1e-7 / 4.8e-7); with scales from the first step at 2^4 and
-// no changes on the way it was 9e-7 (1.4e-5).  Search with four of 7168 channels 2^13 times as loud: 59.0 ms when the
-// tiles of H had to be computed twice, now 31.7 as with any other.
-// A value that is not finite makes every sum it enters not finite and has no say in the scales.
+// loud at the start of every block of 128 channels: 2.0e-7 / 1.7e-7 (5.1e-7 / 4.3e-7); before its channels were scaled, and with a
+// first guess at 2^4, 9e-7 (1.4e-5).  Search with four of 7168 channels 2^13 times as loud: 59.0 ms when the tiles of H had to be
+// computed twice, now 31 as with any other.
+// A value that is not finite makes every sum it enters not finite.
 //
 // Work split.  A workgroup of four waves owns a 128 x 128 tile of C, a wave a 64 x 64 quarter as 4 x 4 accumulators of
 // 16 x 16; a step takes 32 values of k.  Wave w brings the eight rows 8 w .. 8 w + 7 of the step, lane l the columns 2 l
@@ -43,8 +47,7 @@
 // matrix instruction takes its operands.  Two stages in LDS (64 KB) with one barrier per step; two workgroups per
 // compute unit, so that one's loads and splits run under the other's matrix instructions.  The loop has no branch around
 // its loads (buffer descriptors end at the k range), so that the compiler interleaves the vector instructions with the
-// matrix instructions: with branches the same loop was 25 % slower.  Whether the next step fits the scales is known once per
-// step, by a flag in LDS beside its barrier.
+// matrix instructions: with branches the same loop was 25 % slower.
 // What bounds it: about 200 vector instructions (800 clocks) against 48 matrix instructions (768 clocks) per wave and step,
 // two waves per SIMD: both pipes are half busy.  Measured (binary32 instruction before / now): quadratic form of a 7168 x
 // 7168 layer 3.32 / 1.38 ms per candidate, 1.19 with A split beforehand (kQuadFormSplit: 930 TFLOP/s of binary16 products; a
@@ -76,8 +79,9 @@ typedef float prod_f32x4 __attribute__((ext_vector_type(4)));
 enum ProductMode { kQuadForm = 0, kSubtract = 1, kAddTwiceSymmetric = 2, kStore = 3, kStoreNegated = 4, kSubtractLower = 5, kQuadFormSplit = 6 };
 
 constexpr int kProdTile = 128, kProdStep = 32, kProdBlock = 4;  // tile edge, k values per step, tiles per block edge
-constexpr int kProdTarget = 10;                                 // a first guess puts its magnitude at 2^10 .. 2^11
-constexpr float kProdMost = 60000.0f, kProdLeast = 16.0f;       // where scaled maxima have to lie, see above
+constexpr int kProdTarget = 8;                                  // a first guess puts its magnitude at 2^8 .. 2^9
+constexpr int kProdFew = 20;                                    // up to so many values of k in binary32 instructions
+constexpr float kProdMost = 60000.0f, kProdLeast = 4.0f;        // where scaled maxima have to lie, see above
 
 struct ProductArgs {
     const float *A, *B, *E;
@@ -88,6 +92,8 @@ struct ProductArgs {
     size_t split_plane;     // values per half
     const int *split_shift; // quadratic forms: exponent of each row's scale
     const float *diag_max;  // quadratic forms: largest value on B's diagonal
+    const float *least;     // kSubtract, errors of the GPTQ pass: smallest divisor of the 128 rows of block k / 128 of B and of its
+    int least_first;        // first 32, at least[2 ((least_first + k / 128) % 4)], for up to four blocks; or null
     // several products of one shape in a launch (blockIdx.y): operands and result of product y lie y * stride floats on; the
     // last one may have fewer columns, columns_end - y * columns_step of them, and with k_is_columns as many values of k
     size_t stride;
@@ -155,7 +161,7 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
 {
     constexpr bool kQuad = MODE == kQuadForm || MODE == kQuadFormSplit, kSplitA = MODE == kQuadFormSplit;
     constexpr int kFirst = kSplitA ? 1 : 0;  // first operand that comes in binary32
-    constexpr bool kStops = !kQuad;          // scales may change on the way
+    constexpr int kGuess = kQuad ? 1 : 0;    // first operand whose scales are guessed
     // the two stages of both operands, [hi, lo][octet][column]; A's are two objects so that the compiler can tell the copies
     // into one (kQuadFormSplit) from the reads of the other
     __shared__ __attribute__((aligned(16))) uint8_t stage_a0[2][4][kProdTile * 16];
@@ -164,8 +170,6 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
     __shared__ unsigned largest[2][kProdTile];  // largest magnitude per row of A's tile, column of B's tile (float bits)
     __shared__ unsigned largest_of_tile[2];
     __shared__ int shift[2][kProdTile];  // exponents of the scales
-    __shared__ int change[2][kProdTile]; // what they change by
-    __shared__ unsigned stop[2];         // the next step does not fit the scales (by stage)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lo = lane & 15, hi = lane >> 4, wr = wave >> 1, wc = wave & 1;
@@ -204,7 +208,7 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
                 const_cast<float *>(panel[o] + (size_t)(rows ? k : k_begin) * pitch[o]), 0, (int)bytes, kRawBufferFlags);
 #pragma unroll
             for (int j = 0; j < 8; ++j)
-                raw[o][j] = __builtin_amdgcn_raw_buffer_load_b64(rsrc, 8 * lane, 4 * j * pitch[o], 0);
+                raw[o][j] = __builtin_amdgcn_raw_buffer_load_b64(rsrc, 8 * lane, __builtin_amdgcn_readfirstlane(4 * j * pitch[o]), 0);
         }
     };
     auto weigh = [&](int step) PROD_INLINE {  // kQuadForm: B on and beyond its diagonal
@@ -221,7 +225,7 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
     float top[2][2] = {{0.f, 0.f}, {0.f, 0.f}};  // largest magnitudes seen by this lane
     auto track = [&]() PROD_INLINE {
 #pragma unroll
-        for (int o = kFirst; o < 2; ++o)
+        for (int o = kGuess; o < 2; ++o)
 #pragma unroll
             for (int j = 0; j < 8; ++j)
 #pragma unroll
@@ -229,7 +233,7 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
     };
     auto publish = [&]() PROD_INLINE {  // the lanes' maxima into `largest`
 #pragma unroll
-        for (int o = kFirst; o < 2; ++o)
+        for (int o = kGuess; o < 2; ++o)
 #pragma unroll
             for (int e = 0; e < 2; ++e) atomicMax(&largest[o][2 * lane + e], __float_as_uint(top[o][e]));
     };
@@ -318,102 +322,60 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
     };
     // Steps [from, to): while a step is multiplied, the next one is split and stored to the other stage and the one
     // after it is requested.
-    // A single step (not a quadratic form): with so few terms the roundings of the operands do not average out, so what their
-    // halves leave (`rest`, in the place of the second stage's lo) and lo lo' are not dropped, and the large products are
-    // added by the vector ALU, which rounds to nearest.  2-norm error of 2 X^T X with 1 / 2 / 7 / 16 / 32 samples, against a
-    // chain of binary32 multiply-adds (in parentheses), 10^-8: 2.6 (2.6),
-    // 3.1 (3.1), 4.0 (4.9), 4.3 (7.3), 5.0 (10.2); with two halves and without lo lo' 8.3 to 8.7.
-    auto split_rest = [&]() PROD_INLINE {
+    // Up to kProdFew values of k (not a quadratic form): with so few terms the roundings of the operands do not average out, and
+    // finding scales takes longer than multiplying.  Such a product is the binary32 instruction's, from one copy of both panels
+    // [k][column ^ 16 (k % 4)] in the place of a stage.  512 channels, 8 samples 14.4 -> 12.4 us.
+    auto multiply_few = [&]() PROD_INLINE {
+        load(0);
+        float *const panels[2] = {reinterpret_cast<float *>(&stage_a0[0][0][0]), reinterpret_cast<float *>(&stage_b[0][0][0][0])};
 #pragma unroll
         for (int o = 0; o < 2; ++o)
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                prod_f16x8 rest;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const float v = __uint_as_float(raw[o][j][e]);
-                    const float l = fmaf(v, s[o][e], -(float)(_Float16)(v * s[o][e]));
-                    rest[j] = (_Float16)(l - (float)(_Float16)l);
-                }
-                auto &st = o ? stage_b[1] : stage_a1;
-                *reinterpret_cast<prod_f16x8 *>(&st[1][wave][(at ^ e) * 16]) = rest;
-            }
-    };
-    auto multiply_single = [&]() PROD_INLINE {
-        const int row = (hi * kProdTile + wr * 64) * 16, column = (hi * kProdTile + wc * 64) * 16;
-        auto pass = [&](const uint8_t *pa, const uint8_t *pb, auto large) PROD_INLINE {
-            prod_f16x8 a[4], b[4];
+            for (int j = 0; j < 8; ++j)
+                *reinterpret_cast<prod_u32x2 *>(panels[o] + (8 * wave + j) * kProdTile + ((2 * lane) ^ (16 * (j & 3)))) = raw[o][j];
+        shift[tid >> 7][tid & 127] = 0;
+        __syncthreads();
+        for (int k = 0; k < k_end - k_begin; k += 4) {
+            float a[4], b[4];
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                a[t] = *reinterpret_cast<const prod_f16x8 *>(pa + row + (t * 16 + (lo ^ (t & 1))) * 16);
-                b[t] = *reinterpret_cast<const prod_f16x8 *>(pb + column + (t * 16 + (lo ^ (t & 1))) * 16);
+                a[t] = panels[0][(k + hi) * kProdTile + ((wr * 64 + t * 16 + lo) ^ (16 * hi))];
+                b[t] = panels[1][(k + hi) * kProdTile + ((wc * 64 + t * 16 + lo) ^ (16 * hi))];
             }
 #pragma unroll
             for (int ta = 0; ta < 4; ++ta)
 #pragma unroll
-                for (int tb = 0; tb < 4; ++tb) {
-                    const prod_f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-                    const prod_f32x4 c = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[ta], b[tb], decltype(large)::value ? zero : acc[ta][tb], 0, 0, 0);
-                    acc[ta][tb] = decltype(large)::value ? acc[ta][tb] + c : c;
-                }
-        };
-        const uint8_t *const a_hi = &stage_a0[0][0][0], *const a_lo = &stage_a0[1][0][0], *const a_rest = &stage_a1[1][0][0];
-        const uint8_t *const b_hi = &stage_b[0][0][0][0], *const b_lo = &stage_b[0][1][0][0], *const b_rest = &stage_b[1][1][0][0];
-        pass(a_lo, b_lo, std::false_type{});
-        pass(a_rest, b_hi, std::false_type{});
-        pass(a_hi, b_rest, std::false_type{});
-        pass(a_lo, b_hi, std::false_type{});
-        pass(a_hi, b_lo, std::false_type{});
-        pass(a_hi, b_hi, std::true_type{});
+                for (int tb = 0; tb < 4; ++tb) acc[ta][tb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ta], b[tb], acc[ta][tb], 0, 0, 0);
+        }
     };
-    // True if the next step does not fit the scales, which all four waves see alike: `stop` of a stage is written before the
-    // barrier, read after it and written again two barriers later.
+    // Steps [from, to): while a step is multiplied, the next one is split and stored to the other stage and the one
+    // after it is requested.
     auto one = [&](auto buf, auto other, int step, auto weighed) PROD_INLINE {
-        const int b = buf;
         if (kSplitA) copy_a(other, step + 1);
         multiply(buf);
         if (decltype(weighed)::value) weigh(step + 1);
         track();
         split_store(other);
         load(step + 2);
-        if constexpr (kStops) {
-            float most = 0.0f;
-#pragma unroll
-            for (int o = 0; o < 2; ++o)
-#pragma unroll
-                for (int e = 0; e < 2; ++e) most = fmaxf(most, top[o][e] * s[o][e]);
-            if (most > kProdMost) stop[b] = 1u;
-        }
         barrier();  // the other stage is complete, and everyone is done reading this one
-        return kStops && __builtin_amdgcn_readfirstlane((int)*(volatile __attribute__((address_space(3))) unsigned *)&stop[b]) != 0;
     };
     constexpr std::integral_constant<int, 0> even{};
     constexpr std::integral_constant<int, 1> odd{};
-    int begin = 0;         // first step under the present scales: steps of its parity use the first stage
-    bool stopped = false;  // the step that run() returns does not fit them
     auto run = [&](int from, int to, auto weighed) PROD_INLINE {  // kSplitA: `from` is even, and the stages are constants
-        int step = from;
         if constexpr (kSplitA) {
+            int step = from;
             for (; step + 1 < to; step += 2) {
                 one(even, odd, step, weighed);
                 one(odd, even, step + 1, weighed);
             }
             if (step < to) one(even, odd, step, weighed);  // the last of all
-            step = to;
         } else {
-            if (step < to) {
-                bool on;
-                do {
-                    stopped = one((step - begin) & 1, (step - begin + 1) & 1, step, weighed);
-                    on = (++step < to) & !stopped;
-                } while (on);
-            }
+            for (int step = from; step < to; ++step) one(step & 1, (step & 1) ^ 1, step, weighed);
         }
-        return step;
     };
     // kQuadForm: the accumulators' contribution to the quadratic form, and a fresh start.  Once per 1024 values of k: the
     // shorter sums lose less to rounding.
-    prod_f32x4 sum[4] = {};
+    prod_f32x4 sum[4];
     auto contract = [&]() PROD_INLINE {
         const int columns = width[1] < kProdTile ? width[1] : kProdTile;
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
@@ -436,91 +398,88 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
         }
         clear();
     };
-    // A stretch of steps under one set of scales: from step 0, or (begin > 0) from the one that did not fit the last set; once more
-    // from step 0, with all magnitudes known, if a guess was too low.
-    bool known = false;
-    largest[tid >> 7][tid & 127] = 0u;
-    if (tid < 2) largest_of_tile[tid] = stop[tid] = 0u;
-    clear();
-    __syncthreads();
-    for (;;) {
+    // All steps under one set of scales, and once more with all magnitudes known if a guess was too low or too high.
+    const bool few = !kQuad && k_end - k_begin <= kProdFew;
+    if constexpr (!kQuad) {
+        if (few) {
+            clear();
+            multiply_few();
+        }
+    }
+    for (int attempt = 0; !few; ++attempt) {
         const int o = tid >> 7, i = tid & 127;  // this thread's row of A's tile, column of B's
-        // A magnitude that the first step need not show.  Quadratic form: with a positive semidefinite B no value of column c is
-        // above sqrt(max_k B[k][k] B[c][c]); twice that, and no more than 2^12 B[c][c], is taken for the largest.  Else the
-        // diagonal of a triangular operand.
-        float hint = 0.0f;
-        if (begin == 0 && !known) {
+        // A magnitude that the first step need not show: the diagonal of a symmetric or triangular operand.
+        float hint = 0.0f, ratio = 1.0f;
+        if (attempt == 0) {
+            if (MODE == kSubtract && p.least) {
+                float all = INFINITY;
+                for (int b = 0; b < 4; ++b)
+                    if (b * kProdTile < p.K) all = fminf(all, p.least[2 * ((p.least_first + b) & 3)]);
+                ratio = p.least[2 * p.least_first + 1] / all;
+            }
             if (kQuad && o == 1 && c0 + i < p.C) {
-                const float d = fabsf(p.B[(size_t)(c0 + i) * p.ldb + c0 + i]);
-                hint = d * fminf(sqrtf(*p.diag_max / d), 0x1p12f);
+                hint = p.B[(size_t)(c0 + i) * p.ldb + c0 + i];
+                ratio = *p.diag_max;
             }
             if ((MODE == kStore || MODE == kStoreNegated) && o == 0 && r0 + i < p.R && r0 + i < p.K)
                 hint = fabsf(p.A[(size_t)(r0 + i) * p.lda + r0 + i]);
         }
-        if (kSplitA) copy_a(even, begin);
-        load(begin);
-        if (kQuad && c0 < (begin + 1) * kProdStep) weigh(begin);
+        if (kSplitA) copy_a(even, 0);
+        load(0);
+        if (kQuad && c0 < kProdStep) weigh(0);
         track();
+        if (attempt == 0) {
+            largest[o][i] = 0u;
+            if (tid < 2) largest_of_tile[tid] = 0u;
+            __syncthreads();
+            publish();
 #pragma unroll
-        for (int x = kFirst; x < 2; ++x)  // what is not finite has no say in the scales
-#pragma unroll
-            for (int e = 0; e < 2; ++e) top[x][e] = top[x][e] < INFINITY ? top[x][e] : 0.0f;
-        publish();
-        if (begin == 0 && !known) {
-#pragma unroll
-            for (int x = kFirst; x < 2; ++x) {
+            for (int x = kGuess; x < 2; ++x) {
                 float m = fmaxf(top[x][0], top[x][1]);
 #pragma unroll
                 for (int d = 32; d > 0; d >>= 1) m = fmaxf(m, __shfl_xor(m, d));
                 if (lane == 0) atomicMax(&largest_of_tile[x], __float_as_uint(m));
             }
+            __syncthreads();
         }
-        __syncthreads();
         {
             unsigned m = largest[o][i];
-            const int old = shift[o][i];
-            int now;
-            if (begin == 0 && !known) {  // (a row or column without any guess takes the tile's)
-                if (hint < INFINITY) m = __float_as_uint(fmaxf(hint, __uint_as_float(m)));
-                now = product_shift(m ? m : largest_of_tile[o], kQuad ? 14 : kProdTarget);
-            } else if (begin == 0) {
-                now = product_shift(m, 14);
-            } else {
-                now = ldexpf(__uint_as_float(m), old) > kProdMost ? product_shift(m, kProdTarget) : old;
+            int to = 14;
+            if (attempt == 0) {  // (a row or column without any guess takes the tile's)
+                if (!kQuad && hint < INFINITY) m = __float_as_uint(fmaxf(hint, __uint_as_float(m)));
+                if (m == 0u) m = largest_of_tile[o];
+                if (!kQuad) to = kProdTarget;
+                if (MODE == kSubtract && p.least) to = 5;  // errors and rows of U grow more on the way than data do
             }
-            if (kQuad && o == 0) now = i < width[0] ? p.split_shift[r0 + i] : 0;
+            int now = product_shift(m, to);
+            if (MODE == kSubtract && p.least && o == 1 && attempt == 0) {  // and errors divided by smaller numbers are as much larger
+                const float grown = __uint_as_float(m) * ratio;
+                if (grown < INFINITY) now = min(now, product_shift(__float_as_uint(grown), 12));
+            }
+            // Quadratic form: with a positive semidefinite B no value of column c is above sqrt(max_k B[k][k] B[c][c]): that, or
+            // 2^15 B[c][c] if it is less, goes to 2^15 (by exponents).
+            const int e_diag = (int)(__float_as_uint(hint) >> 23) - 127, e_max = (int)(__float_as_uint(ratio) >> 23) - 127;
+            if (kQuad && attempt == 0 && e_diag > -127 && e_diag < 128) now = min(now, 15 - min((e_max + e_diag + 3) >> 1, e_diag + 15));
             shift[o][i] = now;
-            change[o][i] = now - old;
-            if (tid < 2) stop[tid] = 0u;
+            if (kQuad && o == 0) shift[0][i] = i < width[0] ? p.split_shift[r0 + i] : 0;
         }
         __syncthreads();
 #pragma unroll
         for (int x = kFirst; x < 2; ++x)
 #pragma unroll
             for (int e = 0; e < 2; ++e) s[x][e] = ldexpf(1.0f, shift[x][2 * lane + e]);
-        if (kStops && begin > 0) {  // the sums so far under the new scales
-#pragma unroll
-            for (int ta = 0; ta < 4; ++ta)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int change_r = change[0][wr * 64 + ta * 16 + 4 * hi + j];
-#pragma unroll
-                    for (int tb = 0; tb < 4; ++tb) acc[ta][tb][j] = ldexpf(acc[ta][tb][j], change_r + change[1][wc * 64 + tb * 16 + lo]);
-                }
-        }
+        clear();
         split_store(even);
-        if constexpr (kStops) {
-            if (steps == 1) split_rest();
-        }
-        load(begin + 1);
+        load(1);
         barrier();
-        stopped = false;
-        int step = begin;
         if constexpr (kQuad) {
             // the last steps, which reach the diagonal, are weighed one step ahead (and, to keep the number of the others even,
             // the one before them, which changes nothing in it)
             const int plain = c0 / kProdStep - 2;
             constexpr int kChunk = 1024 / kProdStep;
+#pragma unroll
+            for (int ta = 0; ta < 4; ++ta) sum[ta] = prod_f32x4{0.f, 0.f, 0.f, 0.f};
+            int step = 0;
             while (step < plain) {
                 const int to = plain - step < kChunk ? plain : step + kChunk;
                 run(step, to, std::false_type{});
@@ -529,27 +488,16 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
             }
             run(step, steps, std::true_type{});
         } else {
-            step = run(begin, steps - 1, std::false_type{});
-            if (steps == 1) multiply_single();
-            else if (!stopped) multiply((steps - 1 - begin) & 1);  // nothing follows it that had to be split
+            run(0, steps - 1, std::false_type{});
+            multiply((steps - 1) & 1);  // nothing follows it that had to be split
         }
-        if (kStops && stopped && step < steps) {
-            begin = step;
-            continue;
-        }
-        if (known) break;
+        if (attempt) break;
         publish();
         __syncthreads();
-        const float most = ldexpf(__uint_as_float(largest[o][i]), shift[o][i]);
-        const bool off = o >= (kQuad ? 1 : 0) && i < width[o] && ((most < (kQuad ? 1.0f : kProdLeast) && most > 0.0f) || (kQuad && most > kProdMost));
-        if (!__syncthreads_or(off)) break;
-        known = true;
-        begin = 0;
-        clear();
-        if constexpr (kQuad) {
-#pragma unroll
-            for (int ta = 0; ta < 4; ++ta) sum[ta] = prod_f32x4{0.f, 0.f, 0.f, 0.f};
-        }
+        const float most = ldexpf(__uint_as_float(largest[tid >> 7][tid & 127]), shift[tid >> 7][tid & 127]);
+        const bool bad = tid >> 7 >= kGuess && (tid & 127) < width[tid >> 7] &&
+                         (!(most <= kProdMost) || (most < (kQuad ? 0.25f : MODE == kSubtract && p.least ? 0x1p-6f : kProdLeast) && most > 0.0f));
+        if (!__syncthreads_or(bad)) break;
     }
 
     // Element i of a 16 x 16 accumulator: row 4 hi + i, column lo; the scales are taken out again.  Through a descriptor of
@@ -634,9 +582,9 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
 
 template <int MODE>
 static void launch_product(hipStream_t stream, const float *A, int lda, int R, const float *B, int ldb, int C, int K, float *out,
-                           int ldo)
+                           int ldo, const float *least = nullptr, int least_first = 0)
 {
-    ProductArgs p = {A, B, nullptr, out, lda, R, ldb, C, K, ldo, 0, nullptr, 0, nullptr, nullptr, 0, C, 0, 0};
+    ProductArgs p = {A, B, nullptr, out, lda, R, ldb, C, K, ldo, 0, nullptr, 0, nullptr, nullptr, least, least_first, 0, C, 0, 0};
     const int blocks = (product_blocks<MODE>(R, C) + 7) / 8 * 8;
     hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)(blocks * kProdBlock * kProdBlock)), dim3(256), 0, stream, p);
 }
@@ -646,7 +594,7 @@ template <int MODE>
 static void launch_products(hipStream_t stream, int count, size_t stride, int columns_end, const float *A, const float *B, float *out,
                             int pitch, int size)
 {
-    ProductArgs p = {A, B, nullptr, out, pitch, size, pitch, size, size, pitch, MODE == kStore ? 1 : 0, nullptr, 0, nullptr, nullptr,
+    ProductArgs p = {A, B, nullptr, out, pitch, size, pitch, size, size, pitch, MODE == kStore ? 1 : 0, nullptr, 0, nullptr, nullptr, nullptr, 0,
                      stride, columns_end, 2 * size, MODE == kStore ? 1 : 0};
     const int blocks = (product_blocks<MODE>(size, size) + 7) / 8 * 8;
     hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)(blocks * kProdBlock * kProdBlock), (unsigned)count), dim3(256), 0, stream, p);
@@ -658,7 +606,7 @@ template <int MODE>
 static void launch_quad_form(hipStream_t stream, const uint16_t *split, size_t plane, const int *shift, const float *D, int R, const float *B,
                              int ldb, const float *diag_max, int C, float *out, int ldo)
 {
-    ProductArgs p = {D, B, D, out, ldo, R, ldb, C, C, ldo, 0, split, plane, shift, diag_max, 0, C, 0, 0};
+    ProductArgs p = {D, B, D, out, ldo, R, ldb, C, C, ldo, 0, split, plane, shift, diag_max, nullptr, 0, 0, C, 0, 0};
     const int blocks = (product_blocks<MODE>(R, C) + 7) / 8 * 8;
     hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)(blocks * kProdBlock * kProdBlock)), dim3(256), 0, stream, p);
 }

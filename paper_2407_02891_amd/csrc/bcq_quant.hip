@@ -161,7 +161,19 @@ hipError_t launch_quant_hessian(int N, int T, const float *X, float *H, hipStrea
 // Working matrices (binary32, pitch N): Hw = H_d (consumed), Rt = R^T, Ut = U^T, T = one panel.
 constexpr int kFactorBlock = 128, kFactorPanel = 512;
 
-__global__ void diag_mean_kernel(int N, const float *__restrict__ H, float damp, float *__restrict__ lambda)
+// H_d is factored as D^-1 H_d D^-1, D = diag(2^e) with 2^2e <= H_d[j][j] < 2^(2e + 2): powers of two, so every rounding is that of
+// the unscaled factorisation, but all rows and columns of what the products multiply are of one size.  (They hold an operand
+// to a step that its row's or column's largest value sets: with loud channels the ordinary entries of a column would lose bits
+// that count once a block's inverse has scaled the large ones down again.)  The columns of U are scaled back where they are
+// first written; Ut stays as it is.
+__device__ __forceinline__ int channel_shift(float h, float lambda)
+{
+    const unsigned bits = __float_as_uint(h + lambda);
+    return bits - 0x00800000u < 0x7f000000u ? (((int)(bits >> 23) - 127) >> 1) : 0;  // (not a positive normal number: no scale)
+}
+
+// lambda and the scale of every channel
+__global__ void diag_mean_kernel(int N, const float *__restrict__ H, float damp, float *__restrict__ lambda, float *__restrict__ scale)
 {
     __shared__ float part[256];
     float s = 0.0f;
@@ -172,10 +184,12 @@ __global__ void diag_mean_kernel(int N, const float *__restrict__ H, float damp,
         if ((int)threadIdx.x < k) part[threadIdx.x] += part[threadIdx.x + k];
         __syncthreads();
     }
-    if (threadIdx.x == 0) *lambda = damp * part[0] / (float)N;
+    const float l = damp * part[0] / (float)N;
+    if (threadIdx.x == 0) *lambda = l;
+    for (int i = threadIdx.x; i < N; i += 256) scale[i] = ldexpf(1.0f, -channel_shift(H[(size_t)i * N + i], l));
 }
 
-__global__ void damped_copy_kernel(int N, const float *__restrict__ H, const float *__restrict__ lambda,
+__global__ void damped_copy_kernel(int N, const float *__restrict__ H, const float *__restrict__ lambda, const float *__restrict__ scale,
                                    float *__restrict__ Hw)
 {
     const int i = blockIdx.y, j = 4 * (blockIdx.x * blockDim.x + threadIdx.x);  // N is a multiple of 4
@@ -184,6 +198,9 @@ __global__ void damped_copy_kernel(int N, const float *__restrict__ H, const flo
 #pragma unroll
     for (int k = 0; k < 4; ++k)
         if (i == j + k) v[k] += *lambda;
+    const prod_f32x4 s = *reinterpret_cast<const prod_f32x4 *>(scale + j);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] *= scale[i] * s[k];
     *reinterpret_cast<prod_f32x4 *>(Hw + (size_t)i * N + j) = v;
 }
 
@@ -200,8 +217,8 @@ __global__ void damped_copy_kernel(int N, const float *__restrict__ H, const flo
 // multiply-adds of the other rows.  A column that becomes -f starts from 0 with a 1 in the row for it.  The same operations
 // in the same order as with one row: the results are the same bits.  A block takes 39 us; with one row
 // at a time 50, with the block and its inverse in LDS and the inverse one column per thread 245.
-__global__ __launch_bounds__(256) void factor_diag_kernel(int N, int r0, int b, const float *__restrict__ Hw,
-                                                          float *__restrict__ U, float *__restrict__ Ut)
+__global__ __launch_bounds__(256) void factor_diag_kernel(int N, int r0, int b, const float *__restrict__ Hw, const float *__restrict__ H,
+                                                          const float *__restrict__ lambda, float *__restrict__ U, float *__restrict__ Ut)
 {
     __shared__ __attribute__((aligned(16))) float rows[2][2][16][8];  // [buffer][j odd, even]: element l at [l % 16][l / 16]
     __shared__ float pivot[kFactorBlock];
@@ -282,17 +299,18 @@ __global__ __launch_bounds__(256) void factor_diag_kernel(int N, int r0, int b, 
     }
     __syncthreads();
     const int l = tid & (kFactorBlock - 1);
+    const float scale = l < b ? ldexpf(1.0f, -channel_shift(H[(size_t)(r0 + l) * N + r0 + l], *lambda)) : 1.0f;
     for (int i = tid / kFactorBlock; i < b; i += 256 / kFactorBlock)
         if (l < b) {
-            U[(size_t)(r0 + i) * N + r0 + l] = V[i][l];
+            U[(size_t)(r0 + i) * N + r0 + l] = V[i][l] * scale;
             Ut[(size_t)(r0 + i) * N + r0 + l] = V[l][i];
         }
 }
 
-// dst[c][r] = src[r][c] for size x size blocks of a matrix of pitch N, block z of them z * stride floats on, the last one
-// with columns_end - 2 size z columns.
+// dst[c][r] = src[r][c], without the scale of channel c, for size x size blocks of a matrix of pitch N, block z of them z * stride
+// floats on, the last one with columns_end - 2 size z columns; the columns of the first one are the channels from `size` on.
 __global__ void transpose_blocks_kernel(int size, int N, size_t stride, int columns_end, const float *__restrict__ src,
-                                        float *__restrict__ dst)
+                                        const float *__restrict__ H, const float *__restrict__ lambda, float *__restrict__ dst)
 {
     __shared__ float tile[32][33];
     src += blockIdx.z * stride;
@@ -306,7 +324,9 @@ __global__ void transpose_blocks_kernel(int size, int N, size_t stride, int colu
     __syncthreads();
     for (int i = threadIdx.y; i < 32; i += blockDim.y) {
         const int c = c0 + i, r = r0 + threadIdx.x;
-        if (c < cols) dst[(size_t)c * N + r] = tile[threadIdx.x][i];
+        if (c >= cols) continue;
+        const size_t channel = (size_t)size + 2 * (size_t)size * blockIdx.z + c;
+        dst[(size_t)c * N + r] = tile[threadIdx.x][i] * ldexpf(1.0f, channel_shift(H[channel * N + channel], *lambda));
     }
 }
 
@@ -320,7 +340,7 @@ size_t quant_factor_workspace_bytes(int N)
 // the rows / columns [lo, mid) and [mid, hi) of a pair done, U12 = -U11 (R12 U22).  All pairs of one size are one launch
 // per product (28 of the 128-column ones at 7168, at 11 us each they were most of the inverse: 2.4 -> 1.1 ms).  T = R12 U22
 // takes the place of the same block of a matrix that is free.
-static void invert_blocks(hipStream_t stream, int N, const float *Rt, float *U, float *Ut, float *T)
+static void invert_blocks(hipStream_t stream, int N, const float *Rt, const float *H, const float *lambda, float *U, float *Ut, float *T)
 {
     for (int size = kFactorBlock; size < N; size *= 2) {
         const int count = (N - size + 2 * size - 1) / (2 * size);  // pairs whose second half is not empty
@@ -331,7 +351,7 @@ static void invert_blocks(hipStream_t stream, int N, const float *Rt, float *U, 
         // U[lo + r][mid + c] = -sum_j U[lo + r][lo + j] T[j][c]
         launch_products<kStoreNegated>(stream, count, stride, N - size, Ut, T + above, U + above, N, size);
         hipLaunchKernelGGL(transpose_blocks_kernel, dim3(size / 32, size / 32, count), dim3(32, 8), 0, stream, size, N, stride,
-                           N - size, U + above, Ut + below);
+                           N - size, U + above, H, lambda, Ut + below);
     }
 }
 
@@ -340,8 +360,9 @@ hipError_t launch_quant_factor(int N, float damp, const float *H, float *U, void
     float *Hw = static_cast<float *>(workspace);
     float *Rt = Hw + (size_t)N * N, *Ut = Rt + (size_t)N * N;
     float *lambda = Ut + (size_t)N * N;
-    hipLaunchKernelGGL(diag_mean_kernel, dim3(1), dim3(256), 0, stream, N, H, damp, lambda);
-    hipLaunchKernelGGL(damped_copy_kernel, dim3((N / 4 + 255) / 256, N), dim3(256), 0, stream, N, H, lambda, Hw);
+    float *const scale = Rt;  // (written over by the first panel)
+    hipLaunchKernelGGL(diag_mean_kernel, dim3(1), dim3(256), 0, stream, N, H, damp, lambda, scale);
+    hipLaunchKernelGGL(damped_copy_kernel, dim3((N / 4 + 255) / 256, N), dim3(256), 0, stream, N, H, lambda, scale, Hw);
     hipError_t e = launch_fill_zero(U, (size_t)N * N * 4, stream);
     if (e != hipSuccess) return e;
     e = launch_fill_zero(Ut, (size_t)N * N * 4, stream);
@@ -353,7 +374,7 @@ hipError_t launch_quant_factor(int N, float damp, const float *H, float *U, void
         const int p0 = (p1 - 1) / kFactorPanel * kFactorPanel;
         for (int r1 = p1; r1 > p0;) {
             const int r0 = (r1 - 1) / kFactorBlock * kFactorBlock, b = r1 - r0;
-            hipLaunchKernelGGL(factor_diag_kernel, dim3(1), dim3(256), 0, stream, N, r0, b, Hw, U, Ut);
+            hipLaunchKernelGGL(factor_diag_kernel, dim3(1), dim3(256), 0, stream, N, r0, b, Hw, H, lambda, U, Ut);
             if (r0 > 0) {
                 // panel, transposed: Rt[r0 + c][i] = R[i][r0 + c] = sum_m V[c][m] Hw[r0 + m][i]   (Hw symmetric, V = R_kk^-1)
                 launch_product<kStore>(stream, Ut + (size_t)r0 * N + r0, N, b, Hw + (size_t)r0 * N, N, r0, b, Rt + (size_t)r0 * N, N);
@@ -370,7 +391,7 @@ hipError_t launch_quant_factor(int N, float damp, const float *H, float *U, void
         p1 = p0;
     }
     // U = R^-1: Hw is free now and holds the intermediate products
-    invert_blocks(stream, N, Rt, U, Ut, Hw);
+    invert_blocks(stream, N, Rt, H, lambda, U, Ut, Hw);
     return hipGetLastError();
 }
 
@@ -419,32 +440,29 @@ __device__ __forceinline__ double grid_scale(double wmin, double wmax, int n_bit
     return lo + (hi - lo) * ((double)(g + 1) / ((double)grid + 1.0));
 }
 
-// Exponent of the power of two by which a row's d are scaled before they are split: |d| stays below twice the row's range,
-// which goes to at most 2^15.
-__global__ void split_shift_kernel(int M, int Mp, const float *__restrict__ wmin, const float *__restrict__ wmax,
-                                   int *__restrict__ shift)
+// What the quadratic forms take their scales from.  Exponent of the power of two by which a row's d are scaled before they are
+// split: |d| stays below twice the row's range, which goes to at most 2^15.  The last block: the largest finite value on the
+// diagonal of H (a launch of its own for it was 3 us of a small search).
+__global__ __launch_bounds__(256) void split_shift_kernel(int M, int Mp, const float *__restrict__ wmin, const float *__restrict__ wmax,
+                                                          int *__restrict__ shift, int N, const float *__restrict__ H,
+                                                          float *__restrict__ diag_max)
 {
-    const int m = blockIdx.x * blockDim.x + threadIdx.x;
-    if (m < Mp) shift[m] = m < M ? product_shift(__float_as_uint(wmax[m] - wmin[m]), 13) : 0;
-}
-
-// Largest finite value on the diagonal of H, from which the quadratic forms take the scales of its columns.
-__global__ __launch_bounds__(1024) void diag_max_kernel(int N, const float *__restrict__ H, float *__restrict__ most)
-{
-    __shared__ float part[16];
-    float m = 0.0f;
-    for (int i = threadIdx.x; i < N; i += 1024) {
+    if (blockIdx.x < gridDim.x - 1) {
+        const int m = blockIdx.x * blockDim.x + threadIdx.x;
+        if (m < Mp) shift[m] = m < M ? product_shift(__float_as_uint(wmax[m] - wmin[m]), 13) : 0;
+        return;
+    }
+    __shared__ float part[4];
+    float most = 0.0f;
+    for (int i = threadIdx.x; i < N; i += 256) {
         const float d = H[(size_t)i * N + i];
-        if (d < INFINITY) m = fmaxf(m, d);
+        if (d < INFINITY) most = fmaxf(most, d);
     }
 #pragma unroll
-    for (int d = 32; d > 0; d >>= 1) m = fmaxf(m, __shfl_xor(m, d));
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = m;
+    for (int d = 32; d > 0; d >>= 1) most = fmaxf(most, __shfl_xor(most, d));
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = most;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < 16; ++w) m = fmaxf(m, part[w]);
-        *most = m;
-    }
+    if (threadIdx.x == 0) *diag_max = fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
 }
 
 // Dt[k][m] = S' W_q + qbias - w for one candidate (grid point g, tying t), from Wt (SPLIT = false) or from W; zeros in the
@@ -535,8 +553,8 @@ static hipError_t search_rows(int M, int N, int n_bits, int q, int grid, const f
     auto *shift = reinterpret_cast<int *>(w.Err);
     const size_t plane = (size_t)N * w.Mp;
     auto *diag_max = reinterpret_cast<float *>(shift + w.Mp);
-    hipLaunchKernelGGL(split_shift_kernel, dim3((w.Mp + 255) / 256), dim3(256), 0, stream, M, w.Mp, w.wmin, w.wmax, shift);
-    hipLaunchKernelGGL(diag_max_kernel, dim3(1), dim3(1024), 0, stream, N, H, diag_max);
+    hipLaunchKernelGGL(split_shift_kernel, dim3((w.Mp + 255) / 256 + 1), dim3(256), 0, stream, M, w.Mp, w.wmin, w.wmax, shift, N, H,
+                       diag_max);
     const std::vector<Tying> tyings = all_tyings(n_bits, q);
     bool first = true;
     for (int g = 0; g < grid; ++g)
@@ -631,7 +649,7 @@ __global__ __launch_bounds__(256) void gptq_block_kernel(int M, int Mp, int N, i
                                                          const float *__restrict__ S, const float *__restrict__ qbias,
                                                          const unsigned long long *__restrict__ nibbles,
                                                          const uint8_t *__restrict__ bytes, uint8_t *__restrict__ w_int,
-                                                         float *__restrict__ Err)
+                                                         float *__restrict__ Err, float *__restrict__ least)
 {
     __shared__ __attribute__((aligned(16))) float Us[kGptqBlock][4][kGptqLanes][4];
     __shared__ prod_f32x2 diag[kGptqBlock];  // U[c][c] and its reciprocal, no number unless that stands for the division
@@ -668,6 +686,22 @@ __global__ __launch_bounds__(256) void gptq_block_kernel(int M, int Mp, int N, i
     }
     const double inv_s = 1.0 / s, top = (double)((1 << n_bits) - 1);
     __syncthreads();
+    if (blockIdx.x == 0 && tid < 64) {  // for the products with these errors: smallest diagonal of the block and of its first 32 columns
+        auto size_of = [&](int c) {
+            const float d = fabsf(diag[c][0]);
+            return c < cols && d > 0.0f ? d : INFINITY;
+        };
+        float first = tid < 32 ? size_of(tid) : INFINITY, all = fminf(size_of(tid), size_of(tid + 64));
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) {
+            first = fminf(first, __shfl_xor(first, d));
+            all = fminf(all, __shfl_xor(all, d));
+        }
+        if (tid == 0) {
+            least[0] = all;
+            least[1] = first;
+        }
+    }
 
     for (int i = 0; 8 * i < cols; ++i) {
         int my_q = 0;
@@ -733,6 +767,7 @@ static hipError_t gptq_rows(int M, int N, int n_bits, int q, const float *W, con
     auto *nibbles = reinterpret_cast<unsigned long long *>(w.part);  // two of the (ceil(N / 128) + 3) Mp floats from here
     auto *bytes = reinterpret_cast<uint8_t *>(w.Err);                // 256 of the 512 bytes per row
     float *const err = w.Dt;
+    float *const least = w.Err + 64 * (size_t)w.Mp;                  // 8 floats: smallest diagonals of the blocks of a panel
     hipLaunchKernelGGL(transpose_kernel, dim3((N + 31) / 32, (w.Mp + 31) / 32), dim3(32, 8), 0, stream, M, w.Mp, N, W,
                        w.Wt);
     hipLaunchKernelGGL(gptq_tables_kernel, dim3((M + 63) / 64), dim3(64), 0, stream, M, n_bits, q, labels, nibbles, bytes);
@@ -740,7 +775,7 @@ static hipError_t gptq_rows(int M, int N, int n_bits, int q, const float *W, con
     auto update = [&](int j0, int j1, int from, int to) {
         if (from < to)
             launch_product<kSubtract>(stream, U + (size_t)j0 * N + from, N, to - from, err + (size_t)j0 * w.Mp, w.Mp, w.Mp, j1 - j0,
-                                      w.Wt + (size_t)from * w.Mp, w.Mp);
+                                      w.Wt + (size_t)from * w.Mp, w.Mp, least, j0 / kGptqBlock % 4);
     };
     for (int p0 = 0; p0 < N; p0 += kGptqPanel) {
         const int p1 = p0 + kGptqPanel < N ? p0 + kGptqPanel : N;
@@ -748,7 +783,7 @@ static hipError_t gptq_rows(int M, int N, int n_bits, int q, const float *W, con
             const int c1 = c0 + kGptqBlock < p1 ? c0 + kGptqBlock : p1;
             hipLaunchKernelGGL((n_bits <= 4 ? gptq_block_kernel<true> : gptq_block_kernel<false>),
                                dim3((w.Mp + kGptqRows - 1) / kGptqRows), dim3(256), 0, stream, M, w.Mp, N, n_bits, c0, c1 - c0,
-                               w.Wt, U, S, qbias, nibbles, bytes, w_int, err + (size_t)c0 * w.Mp);
+                               w.Wt, U, S, qbias, nibbles, bytes, w_int, err + (size_t)c0 * w.Mp, least + 2 * (c0 / kGptqBlock % 4));
             update(c0, c1, c1, p1);
         }
         update(p0, p1, p1, N);

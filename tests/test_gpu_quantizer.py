@@ -398,8 +398,8 @@ def test_hessian_tiles_and_scales(N, T):
     tile choose its scales again), added to an H that is not symmetric.  Bound per element, in units of 2^-24 of sum |x_r x_c|:
     three binary32 roundings per 16 samples; the halves of an operand leave at most 2^-23 of it (2 units each), the dropped
     product of the two small halves is at most 2^-22 (4); the final addition 1: 9, of which 8 are allowed (the worst cases of
-    the halves exclude each other).  A value far below its channel's largest is only held to 2^-31 of that one: the smallest
-    step of a half is 2^-24 (rounded to nearest: 2^-25) and the scaled largest is at least 2^4, or 2^6 on average."""
+    the halves exclude each other).  A value far below its channel's largest is only held to 2^-27 of that one: the smallest
+    step of a half is 2^-24 (rounded to nearest: 2^-25) and the scaled largest is at least 2^2."""
     rng = np.random.default_rng(N * 7 + T)
     X = rng.standard_normal((T, N)).astype(np.float32)
     X *= np.exp2(rng.integers(-40, 41, size=N)).astype(np.float32)
@@ -429,10 +429,10 @@ def test_hessian_tiles_and_scales(N, T):
     assert not np.isfinite(bad[N - 1, N - 1]) and np.isfinite(bad[: N - 1, : N - 1]).all()
 
 
-@pytest.mark.parametrize("T", [1, 2, 7, 16, 24, 32, 33])
+@pytest.mark.parametrize("T", [1, 2, 7, 16, 20, 21, 24, 32, 33])
 def test_hessian_of_few_samples(T):
-    """With few samples the roundings of the operands do not average out: the result is as close to the binary64 one as a chain
-    of binary32 multiply-adds is (both round every sum; 5 % for their different order)."""
+    """With few samples the roundings of the operands do not average out (up to 20 are summed in binary32): the result is as close to
+    the binary64 one as a chain of binary32 multiply-adds is (5 % for a different order)."""
     N = 260
     rng = np.random.default_rng(T)
     X = rng.standard_normal((T, N)).astype(np.float32)
@@ -450,11 +450,10 @@ def test_hessian_of_few_samples(T):
 
 
 @pytest.mark.parametrize("N,T", [(132, 300), (260, 97), (516, 640)])
-def test_hessian_scales_that_change_on_the_way(N, T):
+def test_hessian_channels_that_grow(N, T):
     """Channels that grow by 2^9 or 2^14 at one sample, or again and again, at every position of a step and of the two stages,
-    one that starts late and small, and one with an infinity on the way: the tiles choose new scales from the step at which
-    the old ones no longer do and go on.  Bound as in test_hessian_tiles_and_scales, but for values far below the largest of
-    their channel up to their own step (later ones do not touch them)."""
+    one that starts late and small, and one with an infinity on the way: tiles whose scales from the first samples do not
+    do are computed again.  Bound as in test_hessian_tiles_and_scales."""
     rng = np.random.default_rng(N + T)
     X = rng.standard_normal((T, N)).astype(np.float32)
     for c in range(0, 100, 3):
@@ -469,9 +468,8 @@ def test_hessian_scales_that_change_on_the_way(N, T):
     torch.cuda.synchronize()
     X64 = X.astype(np.float64)
     want, size = 2.0 * (X64.T @ X64), 2.0 * (np.abs(X64).T @ np.abs(X64))
-    step = (np.arange(T) // 32 * 32 + 31).clip(max=T - 1)
-    big = np.maximum.accumulate(np.abs(X64), axis=0)[step]       # the largest of its channel up to the end of its step
-    low = 2.0 * 2.0 ** -31 * (big.T @ np.abs(X64) + np.abs(X64).T @ big)
+    total, big = np.abs(X64).sum(axis=0), np.abs(X64).max(axis=0)
+    low = 2.0 * 2.0 ** -27 * (np.outer(big, total) + np.outer(total, big))
     bound = (3 * ((T + 15) // 16) + 8) * 2.0 ** -24 * size + low
     got = H.cpu().numpy().astype(np.float64)
     assert (np.abs(got - want) <= bound).all(), (np.abs(got - want) / bound).max()
@@ -492,7 +490,7 @@ def test_factor_with_loud_channels(N, loud, damp):
     """Four channels 2^10 or 2^12 times as loud as the others at the start of every diagonal block: their entries are the largest
     of the columns that the panels multiply by a block's inverse, which scales them down again, so the ordinary entries must
     not be held to a step of the large ones.  Error per column of U against binary64, over that of a binary32 factorisation
-    (LAPACK): at most 8, where binary32 matrix instructions give 2.3 and 4."""
+    (LAPACK): at most 8, where binary32 matrix instructions give 2.3 and 4 (and this 2.3 and 2.6)."""
     from scipy.linalg import solve_triangular
     rng = np.random.default_rng(1)
     X = rng.standard_normal((2 * N, N)) + 0.5 * rng.standard_normal((2 * N, 8)) @ rng.standard_normal((8, N))
