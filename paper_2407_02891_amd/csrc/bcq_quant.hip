@@ -828,9 +828,13 @@ __global__ __launch_bounds__(256) void from_linear_rows_kernel(int M, int N, int
     __shared__ __attribute__((aligned(4))) uint8_t table[kFuseRows][1 << kMaxBits];
     if (tid < rows) {
         const int m = m0 + tid;
-        make_tying_plan(n_bits, q, labels + (size_t)m * n_bits, true, &plan[tid]);
+        TyingPlan mine;
+        make_tying_plan(n_bits, q, labels + (size_t)m * n_bits, true, &mine);
+        plan[tid] = mine;
         const double s = S[m];
-        for (int o = 0; o < q; ++o) alpha[(size_t)m * q + o] = double_to_half_bits(s * plan[tid].alpha_hat[o]);
+#pragma unroll
+        for (int o = 0; o < kMaxQ; ++o)
+            if (o < q) alpha[(size_t)m * q + o] = double_to_half_bits(s * mine.alpha_hat[o]);
         offset[m] = double_to_half_bits(((1 << n_bits) - 1) / 2.0 * s + (double)qbias[m]);
     }
     __syncthreads();
