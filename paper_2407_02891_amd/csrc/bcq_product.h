@@ -48,12 +48,14 @@
 // compute unit, so that one's loads and splits run under the other's matrix instructions.  The loop has no branch around
 // its loads (buffer descriptors end at the k range), so that the compiler interleaves the vector instructions with the
 // matrix instructions: with branches the same loop was 25 % slower.
-// What bounds it: about 200 vector instructions (800 clocks) against 48 matrix instructions (768 clocks) per wave and step,
-// two waves per SIMD: both pipes are half busy.  Measured (binary32 instruction before / now): quadratic form of a 7168 x
+// What bounds it: 110 vector instructions (440 clocks) and 48 matrix instructions (768 clocks) per wave and step, two waves per
+// SIMD.  Counters: 2 X^T X over 14336 samples of 7168 channels matrix pipe busy 36 % of the time, vector ALU 30 %, LDS 36 %
+// (a third of it bank conflicts of the 16-byte stores), waves at a wait 42 % of their cycles; the quadratic form with A split
+// beforehand 47 %, 27 %, 32 % (a quarter conflicts), 36 %.  Measured (binary32 instruction before / now): quadratic form of a 7168 x
 // 7168 layer 3.32 / 1.38 ms per candidate, 1.19 with A split beforehand (kQuadFormSplit: 930 TFLOP/s of binary16 products; a
 // large library product of that type reaches 1230 on this card), 2 X^T X over 4 x 2048 samples of 7168 channels 7.17 / 1.80 ms.
-// An octet of column c sits at position c ^ ((c >> 4) & 1): the 16 lanes that a 16-byte LDS access serves together then
-// touch 16 different 16-byte columns both when the pairs of columns are written and when 16 consecutive ones are read.
+// An octet of column c sits at position c ^ ((c >> 4) & 1): the 16 lanes that a 16-byte LDS read serves together then
+// touch 16 different 16-byte columns.
 //
 // Tiles are taken in blocks of 4 x 4 per XCD (workgroup numbers go round the eight XCDs), so that the workgroups that
 // share an L2 at a time share their operand panels.
@@ -412,10 +414,16 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
         float hint = 0.0f, ratio = 1.0f;
         if (attempt == 0) {
             if (MODE == kSubtract && p.least) {
-                float all = INFINITY;
-                for (int b = 0; b < 4; ++b)
-                    if (b * kProdTile < p.K) all = fminf(all, p.least[2 * ((p.least_first + b) & 3)]);
-                ratio = p.least[2 * p.least_first + 1] / all;
+                float all = INFINITY, first = 1.0f, of_block[8];
+#pragma unroll
+                for (int b = 0; b < 8; ++b) of_block[b] = p.least[b];  // (all requested together)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const int k = ((b - p.least_first) & 3) * kProdTile;  // first row of the block that has slot b
+                    if (k < p.K) all = fminf(all, of_block[2 * b]);
+                    if (k == 0) first = of_block[2 * b + 1];
+                }
+                ratio = first / all;
             }
             if (kQuad && o == 1 && c0 + i < p.C) {
                 hint = p.B[(size_t)(c0 + i) * p.ldb + c0 + i];
