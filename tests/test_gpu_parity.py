@@ -345,7 +345,7 @@ def test_skinny_eight_waves_per_workgroup(workgroups, q, offset):
         assert not pl.workspace.cpu().numpy().any()
         _run_case(203, 3200, q, 128, offset, batch=13, seed=q + workgroups)
         _run_case(70, 1536, q, 256, offset, batch=2, seed=q + workgroups + 1)
-        _run_case(203, 3200, q, 128, offset, batch=29, seed=q + workgroups + 2)   # 32 columns per pass, eight waves
+        _run_case(203, 3200, q, 128, offset, batch=29, seed=q + workgroups + 2)   # (more than 16 columns: bcq_wide.hip)
     finally:
         bcq.set_option("workgroups", 0)
         bcq.set_option("waves", 0)
@@ -353,11 +353,10 @@ def test_skinny_eight_waves_per_workgroup(workgroups, q, offset):
 
 @pytest.mark.parametrize("workgroups", [0, 3, 10])
 @pytest.mark.parametrize("q,offset", [(3, False), (2, True), (1, True), (2, False), (3, True), (4, False)])
-def test_skinny_table_kernel_two_column_groups_eight_waves(workgroups, q, offset):
-    """17..32 columns on large layers: the table kernel with two groups of 16 columns and eight waves per
-    workgroup (16 table copies, one X buffer of two groups; up to three planes, four planes take the four-wave
-    kernel).  Forced here on small ragged shapes: bit-exact on exact inputs for any work split, workspace left
-    zero, gated on random inputs with ragged batch and rows."""
+def test_wide_kernel_two_column_groups(workgroups, q, offset):
+    """17..32 columns on large layers (bcq_wide.hip, two groups of 16 columns), one to four planes.  Forced here on small ragged
+    shapes: bit-exact on exact inputs for any work split, workspace left zero, gated on random inputs with ragged
+    batch and rows.  (The table kernel with two groups: test_one_slice_of_many_tiles.)"""
     try:
         bcq.set_option("waves", 8)
         bcq.set_option("workgroups", workgroups)
@@ -374,16 +373,18 @@ def test_skinny_table_kernel_two_column_groups_eight_waves(workgroups, q, offset
         bcq.set_option("waves", 0)
 
 
+@pytest.mark.parametrize("waves", [4, 8])
 @pytest.mark.parametrize("workgroups", [0, 1, 3, 7])
 @pytest.mark.parametrize("batch", [2, 3, 4])
-def test_table_kernel_for_up_to_four_vectors(workgroups, batch):
-    """2..4 activation vectors on large layers: sign-sum tables with the four sums side by side, rebuilt along K
-    (bcq_lut4.hip).  Forced here on small shapes: ragged rows and columns (a last half slice that is empty or
-    partial), fewer tiles than a row group has, one to four planes with and without offset, row-wise scales, any
+def test_table_kernel_for_up_to_four_vectors(workgroups, batch, waves):
+    """2..4 activation vectors in the table kernel for up to 16 (bcq_skinny.hip; two vectors take bcq_gemv2.hip on their own), with
+    four and with eight waves.  Forced here on small shapes: ragged rows and columns (a last slice that is
+    partial), fewer tiles than a workgroup has waves, one to four planes with and without offset, row-wise scales, any
     work split; bit for bit the oracle's result (one binary16 rounding) on exact inputs, workspace left zero;
     gate on random inputs with outlier channels; padded rows of X and Y."""
     try:
-        bcq.set_option("skinny_version", 3)
+        bcq.set_option("skinny_version", 2)
+        bcq.set_option("waves", waves)
         bcq.set_option("workgroups", workgroups)
         for (M, N, q, off, group) in [(96, 2048, 3, False, 128), (300, 5120, 3, True, 128), (70, 1536, 2, True, 128),
                                       (1000, 2560, 1, False, 128), (203, 3200, 4, False, 128), (96, 2048, 3, True, 2048),
@@ -406,6 +407,7 @@ def test_table_kernel_for_up_to_four_vectors(workgroups, batch):
         assert torch.all(Y[:, L.M:] == 3.0)
     finally:
         bcq.set_option("workgroups", 0)
+        bcq.set_option("waves", 0)
         bcq.set_option("skinny_version", 0)
 
 
@@ -515,9 +517,9 @@ def test_graph_replay_matches_eager():
 @pytest.mark.parametrize("batch", [17, 24, 32, 33, 50, 64])
 @pytest.mark.parametrize("q,offset,group", [(3, False, 128), (2, True, 128), (4, True, 256), (3, True, 64)])
 def test_wide_batches(batch, q, offset, group, version):
-    """17..64 activation vectors: the expanded operands are shared between groups of 16 columns, up to 64
-    per pass (default: the kernel that folds alpha into A; version 2: the table kernel, q = 4: 32 per
-    pass); groups of 64 columns take one pass per 16."""
+    """17..64 activation vectors on a layer of 35 tiles: by default the kernel that folds alpha into A, whose expanded operands
+    are shared between groups of 16 columns, up to 64 per pass; version 2: the table kernel, 16 per pass; groups of 64
+    columns take one pass per 16 either way."""
     try:
         bcq.set_option("skinny_version", version)
         _run_case(203, 2560, q, group, offset, batch=batch, seed=batch + q)
