@@ -96,8 +96,8 @@ def _ptr(t):
 
 def _stream(stream):
     """hipStream_t of `stream`, of torch's current stream if it is None.  The current one is asked for as a number:
-    torch.cuda.current_stream() builds an object around it, 2.8 us of the 7.1 us a small GEMV call took from Python
-    (0.3 us this way; the call is then as long as its kernel, 4.5 us on 1024 x 8192)."""
+    torch.cuda.current_stream() builds an object around it, 2.8 us of the 7.1 to 7.5 us an eager GEMV call on 1024 x 8192
+    took from Python (0.3 us this way: 4.6 to 5.1 us on different cards; in a graph or from C nothing changes)."""
     if stream is None:
         import torch
         raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)

@@ -49,9 +49,9 @@
 // its loads (buffer descriptors end at the k range), so that the compiler interleaves the vector instructions with the
 // matrix instructions: with branches the same loop was 25 % slower.
 // What bounds it: 110 vector instructions (440 clocks) and 48 matrix instructions (768 clocks) per wave and step, two waves per
-// SIMD.  Counters: 2 X^T X over 14336 samples of 7168 channels matrix pipe busy 36 % of the time, vector ALU 30 %, LDS 36 %
-// (a third of it bank conflicts of the 16-byte stores), waves at a wait 42 % of their cycles; the quadratic form with A split
-// beforehand 47 %, 27 %, 32 % (a quarter conflicts), 36 %.  Measured (binary32 instruction before / now): quadratic form of a 7168 x
+// SIMD.  Counters: 2 X^T X over 14336 samples of 7168 channels matrix pipe busy 36 % of the time, vector ALU 21 %, LDS 36 %
+// (a third of it bank conflicts: not the reads, so the 16-byte stores), waves at a wait 42 % of their cycles; the quadratic form
+// with A split beforehand 47 %, 16 %, 32 % (a quarter conflicts), 36 %.  Measured (binary32 instruction before / now): quadratic form of a 7168 x
 // 7168 layer 3.32 / 1.38 ms per candidate, 1.19 with A split beforehand (kQuadFormSplit: 930 TFLOP/s of binary16 products; a
 // large library product of that type reaches 1230 on this card), 2 X^T X over 4 x 2048 samples of 7168 channels 7.17 / 1.80 ms.
 // An octet of column c sits at position c ^ ((c >> 4) & 1): the 16 lanes that a 16-byte LDS read serves together then

@@ -1,7 +1,6 @@
 // The GPTQT quantiser for one linear layer with row-wise parameters (paper Sec. II-A Eq. 1-2,
 // Sec. II-B Eq. 5-6, Sec. II-C Eq. 7 and the algorithm that closes Sec. II-D), the step that
-// produces what bcq_from_linear_rows / bcq_pack consume.  Offline tooling: written for clarity
-// and determinism (fixed reduction orders), not tuned.
+// produces what bcq_from_linear_rows / bcq_pack consume.  All reduction orders are fixed: the same inputs give the same bits.
 //
 //   search   per row m: qbias = min w, range = max w - min w; for S' on `grid` equidistant points
 //            inside (range / (2^(n+1) - 1), range / (2^(n-1) - 1))  (Eq. 7), for every way of tying
@@ -95,10 +94,12 @@ __device__ __forceinline__ int linear_int(double x, double S, double inv_s, doub
 // Both steps work on transposed binary32 copies, [column k][row m] with the row index fastest and a
 // pitch Mp = M rounded up to 4: one thread per row then reads and writes coalesced, and both dense
 // products (bcq_product.h) take their operands "k-major" (the summation index is the slow one).  Workspace, in floats:
-//   Wt [N][Mp] | Dt [N][Mp] | part [ceil(N/128)][Mp] | wmin, wmax, best [3][Mp] | Err [128][Mp]
+//   Wt [N][Mp] | Dt [N][Mp] | part [ceil(N/128)][Mp] | wmin, wmax, best [3][Mp] | small [128][Mp]
+// (search: Wt becomes the halves of d, Dt holds d, small the exponents of its scales; GPTQ pass: Dt holds the errors of a panel, part
+// or small the tables, small the smallest diagonals of a panel)
 struct QuantWorkspace {
     int Mp, ntile;
-    float *Wt, *Dt, *part, *wmin, *wmax, *best, *Err;
+    float *Wt, *Dt, *part, *wmin, *wmax, *best, *small;
 };
 
 static int pitch_of(int M) { return (M + 3) / 4 * 4; }
@@ -114,7 +115,7 @@ static QuantWorkspace carve(void *workspace, int M, int N)
     w.wmin = w.part + (size_t)w.ntile * w.Mp;
     w.wmax = w.wmin + w.Mp;
     w.best = w.wmax + w.Mp;
-    w.Err = w.best + w.Mp;
+    w.small = w.best + w.Mp;
     return w;
 }
 
@@ -215,7 +216,7 @@ __global__ void damped_copy_kernel(int N, const float *__restrict__ H, const flo
 // 16 c).  What bounds it is that chain (write, barrier, read, reciprocal, 8 to 64 multiply-adds), so two rows j, j - 1 are
 // handed round at a time: every thread brings the second one up to date for itself, and the next two are written before the
 // multiply-adds of the other rows.  A column that becomes -f starts from 0 with a 1 in the row for it.  The same operations
-// in the same order as with one row: the results are the same bits.  A block takes 39 us; with one row
+// in the same order as with one row: the results are the same bits.  A block takes 39 to 40 us; with one row
 // at a time 50, with the block and its inverse in LDS and the inverse one column per thread 245.
 __global__ __launch_bounds__(256) void factor_diag_kernel(int N, int r0, int b, const float *__restrict__ Hw, const float *__restrict__ H,
                                                           const float *__restrict__ lambda, float *__restrict__ U, float *__restrict__ Ut)
@@ -550,7 +551,7 @@ static hipError_t search_rows(int M, int N, int n_bits, int q, int grid, const f
     // time; else the product splits what it reads.
     const bool split = N % 8 == 0 && (reinterpret_cast<uintptr_t>(W) & 15) == 0;
     auto *halves = reinterpret_cast<uint16_t *>(w.Wt);
-    auto *shift = reinterpret_cast<int *>(w.Err);
+    auto *shift = reinterpret_cast<int *>(w.small);
     const size_t plane = (size_t)N * w.Mp;
     auto *diag_max = reinterpret_cast<float *>(shift + w.Mp);
     hipLaunchKernelGGL(split_shift_kernel, dim3((w.Mp + 255) / 256 + 1), dim3(256), 0, stream, M, w.Mp, w.wmin, w.wmax, shift, N, H,
@@ -765,9 +766,9 @@ static hipError_t gptq_rows(int M, int N, int n_bits, int q, const float *W, con
 {
     const QuantWorkspace w = carve(workspace, M, N);
     auto *nibbles = reinterpret_cast<unsigned long long *>(w.part);  // two of the (ceil(N / 128) + 3) Mp floats from here
-    auto *bytes = reinterpret_cast<uint8_t *>(w.Err);                // 256 of the 512 bytes per row
+    auto *bytes = reinterpret_cast<uint8_t *>(w.small);              // 256 of the 512 bytes per row
     float *const err = w.Dt;
-    float *const least = w.Err + 64 * (size_t)w.Mp;                  // 8 floats: smallest diagonals of the blocks of a panel
+    float *const least = w.small + 64 * (size_t)w.Mp;                // 8 floats: smallest diagonals of the blocks of a panel
     hipLaunchKernelGGL(transpose_kernel, dim3((N + 31) / 32, (w.Mp + 31) / 32), dim3(32, 8), 0, stream, M, w.Mp, N, W,
                        w.Wt);
     hipLaunchKernelGGL(gptq_tables_kernel, dim3((M + 63) / 64), dim3(64), 0, stream, M, n_bits, q, labels, nibbles, bytes);
@@ -814,7 +815,7 @@ hipError_t launch_quant_gptq(int M, int N, int n_bits, int q, const float *W, co
 // A workgroup takes up to 16 rows (fewer where that would leave the chip idle): one thread per row works out its tying, all
 // at the same time (a sort each), all threads fill one table of codes per row, and the rows are then mapped WIDTH weights
 // (1, 4 or 16, by the alignment) at a time.  Bound: memory.  28672 x 7168: 441 us (a workgroup per row whose first thread worked out the tying, a scan of the representable
-// set per weight) -> 78 us, 411 MB: 5.3 TB/s.
+// set per weight) -> 78 us with the plan worked out in LDS, 74 in registers, 411 MB: 5.5 TB/s; 512 x 64: 8.3 -> 10.8 -> 7.0 us.
 constexpr int kFuseRows = 16;
 template <int WIDTH>
 __global__ __launch_bounds__(256) void from_linear_rows_kernel(int M, int N, int per_group, int n_bits, int q,

@@ -1,5 +1,6 @@
 // Skinny binary-coding GEMM for gfx950: Y[j][m] = sum_k W_q[m][k] X[j][k] for 2 <= batch <= 64
-// (paper Eq. 11 applied to a few activation vectors at once), reading the packed weights ONCE.
+// (paper Eq. 11 applied to a few activation vectors at once), reading the packed weights once per 16 columns, or
+// once per 32 or 64 where the expanded operands are shared (see launch_skinny).
 //
 // With several activation vectors the work per weight bit grows with the batch while the
 // bytes do not, so the path stops being HBM-bound and the sign-sum tables of the batch-1
@@ -751,7 +752,9 @@ hipError_t launch_skinny(const Geom &g, const void *packed, const uint16_t *X, i
     // 7232 q = 2 groups of 64, 27 columns 28.9 / 19.8; 2048 x 2048 q = 1, 45 columns 13.6 / 11.1; 512 x 8192, 64 columns
     // 19.8 / 17.5.  It loses where there is one column slice (half of its waves idle: 8192 x 512, 64 columns 10.4 / 12.9),
     // on a handful of tiles (512 x 512, 32 columns 7.3 / 8.2: its start-up) and where it needs more passes on a layer
-    // whose weights are not what is waited for (four planes, 64 columns: 4096 x 4096 26.9 / 31.8, 7168 x 28672 131 / 126).
+    // whose weights are not what is waited for (64 columns, four planes: 4096 x 4096 26.4 / 31, 8192 x 8192 50.0 / 54.6, 8192 x 16384
+    // 83.4 / 81.5, 12288 x 12288 92.3 / 91.1, 7168 x 28672 125 / 116; three with offset: 8192 x 8192 45.5 / 49.9, 8192 x 16384 74.4 /
+    // 73.2, 12288 x 12288 84.8 / 81.3).
     const int most = wide_columns(g);
     // Byte offsets into the rows of X of a pass are 32 bits, in all kernels: no pass has more rows than they reach.
     const long long reach = 1 + (0x7ffffff0ll - g.N) / ldx;

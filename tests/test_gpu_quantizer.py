@@ -515,7 +515,7 @@ def test_factor_with_loud_channels(N, loud, damp):
     assert err <= 8 * err32
 
 
-@pytest.mark.parametrize("N", [64, 160, 384, 1000])
+@pytest.mark.parametrize("N", [64, 132, 160, 384, 404, 408, 1000])   # (a last block of 4, 20 and 24 columns: products of as many terms)
 def test_inverse_hessian_factor(N):
     """U with (H + 0.01 mean(diag H) I)^-1 = U^T U, U upper triangular, against the oracle's binary64 factor;
     the device works in binary32, so the comparison is relative to the size of the entries of U and the
