@@ -23,13 +23,13 @@
 // 8.6e-8, 256 samples 2.8e-7 / 1.8e-7, 2048 samples 6.6e-7 / 4.1e-7.  Up to 20 values of k the binary32 instruction is used.
 // The scales: binary16 reaches from 2^-24 to 2^16, and values far below the largest of their row or column should keep their
 // bits, because what they are multiplied by may be as much larger.  So s is chosen from the largest magnitude in the first 32
-// values of the row or column, which it puts at 2^8..2^9: full precision down to 2^-10 of it, and later values may be 117
-// times larger.  Where more is known, more is used:
+// values of the row or column, which it puts at 2^8..2^9: full precision down to 2^-10 of it, and later values may be at
+// least 117 times larger.  Where more is known, more is used:
 //   quadratic forms   d is bounded by its row's range, and the values of a positive semidefinite B by its diagonal, which
 //                 together with the largest of all puts them at most at 2^15;
 //   triangular operands, zero in the first 32 values   the diagonal;
 //   errors of the GPTQ pass   they have been divided by the diagonal of U, whose smallest value in reach is known (ProductArgs::least).
-//                 They and the rows of U grow more on the way than data do and start at 2^5, which leaves a factor of 1875;
+//                 They and the rows of U grow more on the way than data do and start at 2^5, which leaves a factor of at least 937;
 //   the factor    its matrix is scaled so that all channels are of one size (bcq_quant.hip).
 // The largest magnitude of all values is tracked on the way; a tile with a guess that was too low, or more than 2^6 too high, is
 // computed once more with s from the true maximum, at 2^14.  (Scales that change on the way, by a flag in LDS per step that
