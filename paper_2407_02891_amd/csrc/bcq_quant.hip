@@ -620,147 +620,394 @@ __global__ void gptq_tables_kernel(int M, int n_bits, int q, const int8_t *__res
     if (n_bits <= 4) nibbles[m] = packed;
 }
 
-// One block of up to 128 columns [c0, c0 + cols).  The columns of a row are decided one after the other, each from a
-// weight that carries the compensation of all before it, so the time of a block is the length of that chain: the row
-// is spread over eight lanes (lane l holds the columns 8 i + l in registers), every lane works out the decision for its
-// own column at hand, the one whose turn it is broadcasts its error (two DPP moves) and all of them add its share to
-// their 16 columns.  A wave takes eight rows; at 7168 rows that is one wave on nearly every SIMD.  (One thread per row,
-// as before, left 112 waves on the chip and took 193 us per block of a 7168-row layer; this takes 29.)
-// To keep the chain short, the two divisions of a decision are multiplications by reciprocals with the same results:
-//   * rint((w - qbias) / S): see linear_int;
-//   * err / U[j][j] in binary32: quotient, remainder and correction with the rounded reciprocal (Markstein's method),
-//     which gives the correctly rounded quotient unless something on the way leaves the normal range (a zero, infinite or
-//     very large or small diagonal or error); a group of eight columns with such an error is gone through again, with divisions
-//     (a test per column, on the chain, took 8 % of the pass).
-// and Eq. 6 is a table look-up.  U's rows are staged in LDS such that the 16 factors of a lane for column c, those of
-// the columns 8 (c / 8 + k) + l, come in four 16-byte reads: [c][k / 4][l][k % 4].
+// A panel of up to four blocks of up to 128 columns, [p0, p1).  The columns of a row are decided one after the other, each from
+// a weight that carries the compensation of all before it, so the time of a panel is the length of that chain.  Rows do not
+// depend on each other: a workgroup takes 32 rows through all blocks of the panel.
+// Within a block a row is spread over eight lanes (lane l holds the columns 8 i + l in registers), every lane works out the
+// decision for its own column at hand, the one whose turn it is hands its deviation a = w - quant(w) to the others and all of them
+// add its share -U[c][k] / U[c][c] a to their columns.  A wave takes eight rows; at 7168 rows that is one wave on nearly every
+// SIMD.  Measured on such a wave: an instruction that needs the one before takes 8.5 clocks, one that does not 5.4, a DPP move
+// with its wait states 17, a read of LDS 68.  So what counts is the number of dependent instructions from one decision to the
+// next, nine here (eleven at four bits), and the rest goes between them:
+//   * the integer, clamp(rint((w - qbias) / S)), is rounded from w / S - qbias / S with both terms off by few 2^-24: the quotient
+//     lies less than 2^-22 (2^n + |qbias / S|) from the exact one, so the integer is the same unless that is so close to a half;
+//   * Eq. 6 is a look-up in a table that the lane holds (a byte permutation), for more than four bits in LDS;
+//   * S W_q + qbias is one multiply-add;
+//   * U's rows are divided by their diagonal when they are staged: a division less on the way, and as many roundings as with
+//     err = a / U[c][c] rounded.  The errors themselves, for the columns beyond the block, are divisions afterwards;
+//   * the share of the column that is decided next is added straight from the lanes (a DPP operand per half of a row of 16
+//     lanes), those of the others by the multiply-adds that fill the next step;
+//   * a step's factors are requested from LDS a step ahead.
+// The factors are zero up to the diagonal, so a weight stays as it was when its column was decided, and after the eighth step of a
+// group of eight columns every lane holds the decision of its own: a group with one that is too close to a half, or with a diagonal
+// beyond 2^-40 .. 2^40, is gone through again by the definition: decisions from binary64, errors by division.
+// Before a block the errors of the panel's earlier ones are applied to its columns by binary32 matrix instructions.
+// The factors are staged in LDS such that the 16 of a lane for column c, those of the columns 8 (c / 8 + k) + l, come in
+// up to four 16-byte reads: [c][k / 4][l][k % 4], of which columns from 32 g on need 4 - g.
 constexpr int kGptqBlock = 128, kGptqLanes = 8, kGptqRows = 32;  // columns per block, lanes per row, rows per workgroup
+constexpr int kGptqPanel = 4 * kGptqBlock;
 
-template <int LANE>
-__device__ __forceinline__ float gptq_broadcast(float v)  // lane LANE of each group of eight
+// Single instructions, in this order (the compiler leaves the order of volatile ones alone): d = a b + c; w += x u with x
+// from lane LANE of each group of eight (at least two instructions after x was written, or WAIT); x from that lane.
+#define GPTQ_FMA(d, a, b, c) asm volatile("v_fma_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c))
+template <int LANE, bool WAIT>
+__device__ __forceinline__ void gptq_add_from(float &w, float x, float u)
 {
-    int r = __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + LANE, 0xf, 0x3, false);        // row_newbcast
-    r = __builtin_amdgcn_update_dpp(r, __float_as_int(v), 0x150 + 8 + LANE, 0xf, 0xc, false);
-    return __int_as_float(r);
+    if (WAIT) asm volatile("s_nop 1");
+    asm volatile("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0x3" : "+v"(w) : "v"(x), "v"(u), "n"(LANE));
+    asm volatile("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xc" : "+v"(w) : "v"(x), "v"(u), "n"(LANE + 8));
+}
+template <int LANE>
+__device__ __forceinline__ float gptq_from(float x)
+{
+    float y;
+    asm volatile("v_mov_b32_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0x3\n\t"
+                 "v_mov_b32_dpp %0, %1 row_newbcast:%3 row_mask:0xf bank_mask:0xc" : "=&v"(y) : "v"(x), "n"(LANE), "n"(LANE + 8));
+    return y;
 }
 
-template <bool NIBBLES>
-__global__ __launch_bounds__(256) void gptq_block_kernel(int M, int Mp, int N, int n_bits, int c0, int cols,
-                                                         const float *__restrict__ Wt, const float *__restrict__ U,
-                                                         const float *__restrict__ S, const float *__restrict__ qbias,
-                                                         const unsigned long long *__restrict__ nibbles,
-                                                         const uint8_t *__restrict__ bytes, uint8_t *__restrict__ w_int,
-                                                         float *__restrict__ Err, float *__restrict__ least)
-{
-    __shared__ __attribute__((aligned(16))) float Us[kGptqBlock][4][kGptqLanes][4];
-    __shared__ prod_f32x2 diag[kGptqBlock];  // U[c][c] and its reciprocal, no number unless that stands for the division
-    __shared__ uint8_t table[NIBBLES ? 1 : kGptqRows][256];
-    const int tid = threadIdx.x, l = tid & 7, row = tid >> 3, m = blockIdx.x * kGptqRows + row;
-    const bool live = m < M;
+constexpr int kGptqUs = 32 * 32 * (4 + 3 + 2 + 1);  // staged factors of a block
 
-    float w[16];
+__device__ __forceinline__ bool ordinary(float d) { return fabsf(d) >= 0x1p-40f && fabsf(d) <= 0x1p40f; }
+
+enum GptqTable { kEight = 0, kSixteen = 1, kBytes = 2 };  // integers a row can hold: up to 8, up to 16, a byte each in LDS
+
+template <int TABLE>
+__global__ __launch_bounds__(256, 2) void gptq_panel_kernel(int M, int Mp, int N, int n_bits, int p0, int p1,
+                                                            const float *__restrict__ Wt, const float *__restrict__ U,
+                                                            const float *__restrict__ S, const float *__restrict__ qbias,
+                                                            const unsigned long long *__restrict__ nibbles,
+                                                            const uint8_t *__restrict__ bytes, uint8_t *__restrict__ w_int,
+                                                            float *Err, float *__restrict__ least)
+{
+    constexpr int kPitch = kGptqBlock + 4;
+    __shared__ __attribute__((aligned(16))) float Us[kGptqUs + 32];
+    __shared__ __attribute__((aligned(16))) float Ws[kGptqRows][kPitch];
+    __shared__ float diag[kGptqBlock];
+    __shared__ __attribute__((aligned(4))) uint8_t Qs[kGptqRows][kGptqBlock + 4];
+    __shared__ uint8_t table[TABLE == kBytes ? kGptqRows : 1][256];
+    const int tid = threadIdx.x, l = tid & 7, row = tid >> 3, m0 = blockIdx.x * kGptqRows, m = m0 + row;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool live = m < M, aligned = (reinterpret_cast<uintptr_t>(w_int) & 3) == 0;
+
+    // U's block at c0, requested before the block before it is decided: a thread brings ten of the 16-byte pieces of Us, pieces tid +
+    // 256 n (n = 0..3: columns from 0, 4..6 from 32, 7 and 8 from 64, 9 from 96), and each piece's diagonal.  Columns that do not exist
+    // read others.
+    float next_u[10][4], next_d[10];
+    auto piece = [&](int n, int t, int *c, int *x) PROD_INLINE {  // of column c, the columns 8 (c / 8) + x + 8 j
+        const int g = n < 4 ? 0 : n < 7 ? 1 : n < 9 ? 2 : 3, from = g == 0 ? 0 : g == 1 ? 4 : g == 2 ? 7 : 9;
+        const int chunk = (t >> 3) + 32 * (n - from);
+        *c = 32 * g + chunk / (4 - g);
+        *x = 32 * (chunk % (4 - g)) + (t & 7);
+    };
+    auto request_u = [&](int c0, int cols) PROD_INLINE {
+        int t = tid;
+        asm volatile("" : "+v"(t));  // (no addresses kept in registers from block to block)
+        const float *const from = U + (size_t)c0 * (N + 1);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) w[i] = live && 8 * i + l < cols ? Wt[(size_t)(c0 + 8 * i + l) * Mp + m] : 0.0f;
-    for (int e = tid; e < kGptqBlock * 32; e += 256) {  // four columns at a time; N, c0 and cols are multiples of 4
-        const int c = e >> 5, x = 4 * (e & 31), col = 8 * (c >> 3) + x;
-        prod_f32x4 v = {0.f, 0.f, 0.f, 0.f};
-        if (c < cols && col < cols) v = *reinterpret_cast<const prod_f32x4 *>(U + (size_t)(c0 + c) * N + c0 + col);
+        for (int n = 0; n < 10; ++n) {
+            int c, x;
+            piece(n, t, &c, &x);
+            const unsigned row = c < cols ? (unsigned)c * (unsigned)N : 0u;  // (N is at most 2^15)
+            next_d[n] = from[row + (c < cols ? c : 0)];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) Us[c][x >> 5][(x + j) & 7][(x >> 3) & 3] = v[j];
-    }
-    if (tid < kGptqBlock) {
-        const float d = tid < cols ? U[(size_t)(c0 + tid) * N + c0 + tid] : 1.0f;
-        diag[tid] = prod_f32x2{d, fabsf(d) >= 0x1p-40f && fabsf(d) <= 0x1p40f ? 1.0f / d : __builtin_nanf("")};
-    }
-    double s = 1.0, b = 0.0;
-    unsigned long long nib = 0;
+            for (int j = 0; j < 4; ++j) {
+                const int col = (c & ~7) + x + 8 * j;
+                next_u[n][j] = from[row + (col < cols ? col : 0)];
+            }
+        }
+    };
+    auto stage_u = [&](int cols) PROD_INLINE {
+        int t = tid;
+        asm volatile("" : "+v"(t));
+#pragma unroll
+        for (int n = 0; n < 10; ++n) {
+            int c, x;
+            piece(n, t, &c, &x);
+            const float d = c < cols ? next_d[n] : 1.0f;
+            if (x == 0) diag[c] = d;
+            prod_f32x4 f;
+            const float inv = -1.0f / d;  // quotient, remainder and correction: correctly rounded where nothing underflows
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float q = next_u[n][j] * inv;
+                f[j] = fmaf(fmaf(q, d, next_u[n][j]), inv, q);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (!(x + 8 * j > (c & 7) && (c & ~7) + x + 8 * j < cols) || !ordinary(d)) f[j] = 0.0f;
+            *reinterpret_cast<prod_f32x4 *>(&Us[4 * (t + 256 * n)]) = f;
+        }
+    };
+    request_u(p0, min(kGptqBlock, p1 - p0));
+
+    float sf = 1.0f, bf = 0.0f;
+    uint32_t tab0 = 0, tab1 = 0, tab2 = 0, tab3 = 0;  // a byte per integer
     if (live) {
-        s = S[m];
-        b = qbias[m];
-        if (NIBBLES) nib = nibbles[m];
+        sf = S[m];
+        bf = qbias[m];
+        if (TABLE != kBytes) {
+            const unsigned long long nib = nibbles[m];
+            auto spread = [&](int k) {
+                const uint32_t four = (uint32_t)(nib >> (16 * k)) & 0xffffu, two = (four | (four << 8)) & 0x00ff00ffu;
+                return (two | (two << 4)) & 0x0f0f0f0fu;
+            };
+            tab0 = spread(0); tab1 = spread(1); tab2 = spread(2); tab3 = spread(3);
+        }
     }
-    if (!NIBBLES) {
+    if (TABLE == kBytes) {
         for (int e = tid; e < kGptqRows * 256; e += 256) {
-            const int r = e >> 8, mr = blockIdx.x * kGptqRows + r;
+            const int r = e >> 8, mr = m0 + r;
             table[r][e & 255] = mr < M && (e & 255) < 1 << n_bits ? bytes[(size_t)mr * 256 + (e & 255)] : 0;
         }
     }
-    const double inv_s = 1.0 / s, top = (double)((1 << n_bits) - 1);
-    __syncthreads();
-    if (blockIdx.x == 0 && tid < 64) {  // for the products with these errors: smallest diagonal of the block and of its first 32 columns
-        auto size_of = [&](int c) {
-            const float d = fabsf(diag[c][0]);
-            return c < cols && d > 0.0f ? d : INFINITY;
-        };
-        float first = tid < 32 ? size_of(tid) : INFINITY, all = fminf(size_of(tid), size_of(tid + 64));
-#pragma unroll
-        for (int d = 32; d > 0; d >>= 1) {
-            first = fminf(first, __shfl_xor(first, d));
-            all = fminf(all, __shfl_xor(all, d));
-        }
-        if (tid == 0) {
-            least[0] = all;
-            least[1] = first;
-        }
-    }
+    const float topf = (float)((1 << n_bits) - 1), inv_f = 1.0f / sf, shift_f = -bf * inv_f;
+    // how far a quotient may be from its integer without doubt; scales out of the ordinary leave none
+    const float steps = ldexpf(1.0f, n_bits) + fabsf(shift_f);
+    const float sure = fabsf(sf) >= 0x1p-60f && fabsf(sf) <= 0x1p60f ? fmaf(steps, -0x1p-22f, 0.5f) : -1.0f;
+    constexpr float kRound = 0x1.8p23f;
 
-    for (int i = 0; 8 * i < cols; ++i) {
-        int my_q = 0;
-        float my_err = 0.0f;
-        auto step = [&](auto lane_of, auto divide) PROD_INLINE {
-            constexpr int kLane = decltype(lane_of)::value;
-            constexpr bool kDivide = decltype(divide)::value;
-            const int c = 8 * i + kLane;  // (columns beyond `cols` are decided too, and dropped)
-            prod_f32x4 u[4];
+    for (int c0 = p0; c0 < p1; c0 += kGptqBlock) {
+        const int cols = min(kGptqBlock, p1 - c0);
+        // Ws[row][column] = Wt - what the errors of the panel's earlier columns leave: wave w the columns 32 w .. 32 w + 31, 2 x 2
+        // tiles of 16; element i of a tile: column 4 hi + i, row lo
+        {
+            prod_f32x4 acc[2][2];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) u[k] = *reinterpret_cast<const prod_f32x4 *>(&Us[c][k][l][0]);
-            const prod_f32x2 d = diag[c];
-            const double x = (double)w[0] - b;
-            const int lin = linear_int(x, s, inv_s, top);
-            const int wq = NIBBLES ? (int)(nib >> (4 * lin)) & 15 : table[row][lin];
-            const float qv = (float)(s * wq + b);
-            const float a = w[0] - qv;
-            const float q0 = a * d[1];
-            const float own = kDivide ? a / d[0] : fmaf(fmaf(-q0, d[0], a), d[1], q0);
-            const float err = gptq_broadcast<kLane>(own);
-            my_q = l == kLane ? wq : my_q;
-            my_err = l == kLane ? err : my_err;
-            // (the lanes whose column is decided already change a value that nobody reads any more)
+            for (int a = 0; a < 4; ++a) acc[a >> 1][a & 1] = prod_f32x4{0.f, 0.f, 0.f, 0.f};
+            // (rows and columns that do not exist read others, and nobody reads what they give)
+            int col[2], mm[2], at = lane;
+            asm volatile("" : "+v"(at));
+            const int lo = at & 15, hi = at >> 4;
 #pragma unroll
-            for (int k = 0; k < 16; ++k) w[k] = fmaf(-err, u[k >> 2][k & 3], w[k]);
-        };
-        auto group = [&](auto divide) PROD_INLINE {
-            step(std::integral_constant<int, 0>{}, divide); step(std::integral_constant<int, 1>{}, divide);
-            step(std::integral_constant<int, 2>{}, divide); step(std::integral_constant<int, 3>{}, divide);
-            step(std::integral_constant<int, 4>{}, divide); step(std::integral_constant<int, 5>{}, divide);
-            step(std::integral_constant<int, 6>{}, divide); step(std::integral_constant<int, 7>{}, divide);
-        };
-        float before[16];
+            for (int t = 0; t < 2; ++t) {
+                col[t] = 32 * wave + 16 * t + lo;
+                col[t] = c0 + (col[t] < cols ? col[t] : 0);
+                mm[t] = m0 + 16 * t + lo;
+                mm[t] = mm[t] < Mp ? mm[t] : 0;
+            }
+            // 32 of them at a time (there are whole blocks of 128), the next ones requested before these are multiplied
+            float u[2][8][2], e[2][8][2];
+            auto request = [&](int k, float (&uu)[8][2], float (&ee)[8][2]) PROD_INLINE {
+                const float *const from_u = U + (size_t)k * N, *const from_e = Err + (size_t)(k - p0) * Mp;
 #pragma unroll
-        for (int k = 0; k < 16; ++k) before[k] = w[k];
-        group(std::false_type{});
-        // (every lane has the error of its column: zero, or 2^-60 .. 2^60)
-        if (__builtin_expect(__any((__builtin_amdgcn_ubfe(__float_as_uint(my_err), 23, 8) - 67u > 120u) & (my_err != 0.0f)), 0)) {
+                for (int x = 0; x < 8; ++x)
 #pragma unroll
-            for (int k = 0; k < 16; ++k) w[k] = before[k];
-            group(std::true_type{});
+                    for (int t = 0; t < 2; ++t) {
+                        uu[x][t] = from_u[(unsigned)(4 * x + hi) * (unsigned)N + col[t]];
+                        ee[x][t] = from_e[(unsigned)(4 * x + hi) * (unsigned)Mp + mm[t]];
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            auto multiply = [&](const float (&uu)[8][2], const float (&ee)[8][2]) PROD_INLINE {
+#pragma unroll
+                for (int x = 0; x < 8; ++x)
+#pragma unroll
+                    for (int a = 0; a < 4; ++a)
+                        acc[a >> 1][a & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(uu[x][a >> 1], ee[x][a & 1], acc[a >> 1][a & 1], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            if (c0 > p0) request(p0, u[0], e[0]);
+            for (int k = p0; k < c0; k += 64) {
+                request(k + 32, u[1], e[1]);
+                multiply(u[0], e[0]);
+                request(k + 64 < c0 ? k + 64 : p0, u[0], e[0]);  // (behind the last ones, others that nobody uses)
+                multiply(u[1], e[1]);
+            }
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                const int first = 32 * wave + 16 * (a >> 1) + 4 * hi;  // (a multiple of 4, as cols is)
+                prod_f32x4 v = {0.f, 0.f, 0.f, 0.f};
+                if (first < cols) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[i] = Wt[(size_t)(c0 + first + i) * Mp + mm[a & 1]] - acc[a >> 1][a & 1][i];
+                }
+                *reinterpret_cast<prod_f32x4 *>(&Ws[16 * (a & 1) + lo][first]) = v;
+            }
         }
-        if (8 * i + l < cols) {
-            if (live) w_int[(size_t)m * N + c0 + 8 * i + l] = (uint8_t)my_q;
-            if (m < Mp) Err[(size_t)(8 * i + l) * Mp + m] = live ? my_err : 0.0f;  // zeros in the pad rows
-        }
+        stage_u(cols);
+        __syncthreads();
+        if (c0 + kGptqBlock < p1) request_u(c0 + kGptqBlock, min(kGptqBlock, p1 - c0 - kGptqBlock));
+        if (blockIdx.x == 0 && tid < 64) {  // for the products with these errors: smallest diagonal of the block and of its first 32 columns
+            auto size_of = [&](int c) {
+                const float d = fabsf(diag[c]);
+                return c < cols && d > 0.0f ? d : INFINITY;
+            };
+            float first = tid < 32 ? size_of(tid) : INFINITY, all = fminf(size_of(tid), size_of(tid + 64));
 #pragma unroll
-        for (int k = 0; k < 15; ++k) w[k] = w[k + 1];
-        w[15] = 0.0f;
+            for (int d = 32; d > 0; d >>= 1) {
+                first = fminf(first, __shfl_xor(first, d));
+                all = fminf(all, __shfl_xor(all, d));
+            }
+            if (tid == 0) {
+                least[2 * ((c0 - p0) / kGptqBlock)] = all;
+                least[2 * ((c0 - p0) / kGptqBlock) + 1] = first;
+            }
+        }
+        float w[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) w[i] = live ? Ws[row][8 * i + l] : 0.0f;
+        int odd = 0;  // groups with a diagonal out of the ordinary: by the definition, step by step
+        for (int i = 0; i < 16; ++i) odd |= (int)!ordinary(diag[8 * i + l]) << i;
+        odd |= __shfl_xor(odd, 1); odd |= __shfl_xor(odd, 2); odd |= __shfl_xor(odd, 4);
+
+        // groups of eight columns, with the 4 kChunks columns of a lane that are still to come
+        auto groups = [&](auto chunks_of, int i_begin) PROD_INLINE {
+            constexpr int kChunks = decltype(chunks_of)::value, g = 4 - kChunks, kSlots = 4 * kChunks;
+            // factors of the step before, this step and the next (behind the last one, others that nobody uses)
+            prod_f32x4 u[4][kChunks];
+            auto fetch = [&](int c, prod_f32x4 (&to)[kChunks]) PROD_INLINE {
+                const float *const from = Us + 32 * (32 * (4 * g - g * (g - 1) / 2) + (c - 32 * g) * kChunks) + 4 * l;
+#pragma unroll
+                for (int k = 0; k < kChunks; ++k) to[k] = *reinterpret_cast<const prod_f32x4 *>(from + 32 * k);
+            };
+            fetch(32 * g, u[0]);
+#pragma unroll 1
+            for (int i = i_begin; i < i_begin + 4 && 8 * i < cols; ++i) {  // (columns beyond `cols` are decided too, and dropped)
+                float v[kSlots];  // the weights on the way; `w` keeps what they were before the group
+                float a = 0.0f, e = 0.0f, t = 0.0f, r = 0.0f, wqf = 0.0f;
+                v[0] = w[0];
+                auto decide = [&](auto lane_of) PROD_INLINE {
+                    constexpr int kLane = decltype(lane_of)::value;
+                    __builtin_amdgcn_sched_barrier(0);
+                    fetch(8 * i + kLane + 1, u[(kLane + 1) & 3]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    int slot = 1;  // the shares of the step before, between the instructions that wait for each other
+                    auto fill = [&](int count) PROD_INLINE {
+#pragma unroll
+                        for (int n = 0; n < count; ++n)
+                            if (kLane > 0 && slot < kSlots) {
+                                GPTQ_FMA(v[slot], e, u[(kLane + 3) & 3][slot >> 2][slot & 3], kLane == 1 ? w[slot] : v[slot]);
+                                ++slot;
+                            }
+                    };
+                    constexpr int kEach = kSlots >= 16 ? 2 : kSlots >= 8 ? 1 : 0;
+                    GPTQ_FMA(t, v[0], inv_f, shift_f);
+                    fill(kEach);
+                    asm volatile("v_med3_f32 %0, %1, 0, %2" : "=v"(t) : "v"(t), "v"(topf));
+                    fill(kEach);
+                    asm volatile("v_add_f32 %0, 0x4b400000, %1" : "=v"(r) : "v"(t));  // the integer in the low byte
+                    if (TABLE == kBytes) {
+                        wqf = (float)table[row][__float_as_uint(r) & 0xffu];
+                        fill(2 * kEach);
+                    } else {
+                        uint32_t q;
+                        if (TABLE == kSixteen) {
+                            float r8;  // the integer less 8
+                            uint32_t q8;
+                            unsigned long long upper;
+                            asm volatile("v_add_f32 %0, 0x4b3ffff8, %1" : "=v"(r8) : "v"(t));
+                            asm volatile("v_cmp_lt_f32 %0, %1, %2" : "=s"(upper) : "v"(7.5f), "v"(t));
+                            fill(1);
+                            asm volatile("v_perm_b32 %0, %1, %2, %3" : "=v"(q) : "v"(tab1), "v"(tab0), "v"(r));
+                            asm volatile("v_perm_b32 %0, %1, %2, %3" : "=v"(q8) : "v"(tab3), "v"(tab2), "v"(r8));
+                            fill(1);
+                            asm volatile("v_cndmask_b32 %0, %1, %2, %3" : "=v"(q) : "v"(q), "v"(q8), "s"(upper));
+                        } else {
+                            fill(kEach);
+                            asm volatile("v_perm_b32 %0, %1, %2, %3" : "=v"(q) : "v"(tab1), "v"(tab0), "v"(r));
+                        }
+                        fill(kEach);
+                        asm volatile("v_cvt_f32_ubyte0 %0, %1" : "=v"(wqf) : "v"(q));
+                    }
+                    fill(kEach);
+                    float qv;
+                    GPTQ_FMA(qv, sf, wqf, bf);
+                    fill(kSlots - 1 - slot - 2);
+                    asm volatile("v_sub_f32 %0, %1, %2" : "=v"(a) : "v"(v[0]), "v"(qv));
+                    fill(kSlots);
+                };
+                auto step = [&](auto lane_of) PROD_INLINE {
+                    constexpr int kLane = decltype(lane_of)::value;
+                    decide(lane_of);
+                    gptq_add_from<kLane, kLane == 0>(v[0], a, u[kLane & 3][0][0]);
+                    e = gptq_from<kLane>(a);
+                };
+                step(std::integral_constant<int, 0>{}); step(std::integral_constant<int, 1>{});
+                step(std::integral_constant<int, 2>{}); step(std::integral_constant<int, 3>{});
+                step(std::integral_constant<int, 4>{}); step(std::integral_constant<int, 5>{});
+                step(std::integral_constant<int, 6>{});
+                decide(std::integral_constant<int, 7>{});
+                int my_q = (int)wqf;
+                float last = a;
+                // (a deviation without end has made the weights decided before it no numbers)
+                if (__builtin_expect(__any(!(fabsf(t - (r - kRound)) < sure) | !(fabsf(a) < INFINITY) | ((odd >> i) & 1)), 0)) {
+#pragma unroll
+                    for (int k = 0; k < kSlots; ++k) v[k] = w[k];
+#pragma unroll 1
+                    for (int turn = 0; turn < 8; ++turn) {
+                        const double s = sf, b = bf;
+                        const int lin = linear_int((double)v[0] - b, s, 1.0 / s, topf);
+                        int wq;
+                        if (TABLE == kBytes) wq = table[row][lin];
+                        else wq = (int)((lin & 8 ? (lin & 4 ? tab3 : tab2) : (lin & 4 ? tab1 : tab0)) >> (8 * (lin & 3))) & 0xff;
+                        const float now = v[0] - (float)(s * wq + b);
+                        my_q = l == turn ? wq : my_q;
+                        a = l == turn ? now : a;
+                        last = a;
+                        if (turn == 7) break;
+                        const int c = 8 * i + turn;
+                        const float err = __shfl(now, turn, 8) / diag[c];
+                        const float *const of_u = U + (size_t)(c0 + c) * N + c0 + 8 * i + l;
+#pragma unroll
+                        for (int k = 0; k < kSlots; ++k)
+                            if (8 * k + l > turn && 8 * (i + k) + l < cols) v[k] = fmaf(-err, of_u[8 * k], v[k]);
+                    }
+                    if ((odd >> i) & 1) {  // the last column's share too
+                        last = 0.0f;
+                        const float err = __shfl(a, 7, 8) / diag[8 * i + 7];
+                        const float *const of_u = U + (size_t)(c0 + 8 * i + 7) * N + c0 + 8 * i + l;
+#pragma unroll
+                        for (int k = 1; k < kSlots; ++k)
+                            if (8 * (i + k) + l < cols) v[k] = fmaf(-err, of_u[8 * k], v[k]);
+                    }
+                }
+                // the last column's share, and every lane goes on to its next column
+                gptq_add_from<7, true>(v[1], last, u[3][0][1]);
+                e = gptq_from<7>(last);
+                w[0] = v[1];
+#pragma unroll
+                for (int k = 2; k < kSlots; ++k) GPTQ_FMA(w[k - 1], e, u[3][k >> 2][k & 3], v[k]);
+                Ws[row][8 * i + l] = a;
+                Qs[row][8 * i + l] = (uint8_t)my_q;
+            }
+        };
+        groups(std::integral_constant<int, 4>{}, 0);
+        groups(std::integral_constant<int, 3>{}, 4);
+        groups(std::integral_constant<int, 2>{}, 8);
+        groups(std::integral_constant<int, 1>{}, 12);
+        __syncthreads();
+        // the block's errors and integers, each division beside others
+        {
+            int t = tid;
+            asm volatile("" : "+v"(t));
+            const int r = t & 31, first = t >> 5, mr = m0 + r;
+#pragma unroll
+            for (int k = 0; k < kGptqBlock / 8; ++k) {
+                const int c = first + 8 * k;
+                const float err = Ws[r][c] / diag[c];
+                if (c < cols && mr < Mp) Err[(size_t)(c0 - p0 + c) * Mp + mr] = mr < M ? err : 0.0f;  // zeros in the pad rows
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int c = 4 * (8 * k + l);  // (cols, N and c0 are multiples of 4)
+                const uint32_t four = *reinterpret_cast<const uint32_t *>(&Qs[row][c]);
+                if (live && c < cols) {
+                    uint8_t *const to = w_int + (size_t)m * N + c0 + c;
+                    if (aligned) *reinterpret_cast<uint32_t *>(to) = four;
+                    else for (int j = 0; j < 4; ++j) to[j] = (uint8_t)(four >> (8 * j));
+                }
+            }
+        }
+        __syncthreads();  // the errors are in memory, and everyone is done with U's block and Ws
     }
 }
 
-// Columns beyond a panel of four blocks are brought up to date once per panel (K = 512), the rest of the panel after each
-// block: every pass over the remaining weights reads and writes them all, which at one pass per block was most of its time
-// (5.7 ms of a 7168 x 7168 layer, now 2.2; the whole pass 17.3 ms before, now 3.8).  The errors of a panel are kept in Dt,
-// which the pass does not use otherwise.
-constexpr int kGptqPanel = 4 * kGptqBlock;
-
+// Columns beyond a panel of four blocks are brought up to date once per panel (K = 512): every pass over the remaining weights
+// reads and writes them all, which at one pass per block was most of its time (5.7 ms of a 7168 x 7168 layer, now 1.7).  The panel's own
+// columns are its kernel's: with a launch per block and a product for the rest of the panel after each, 38 us a block, now 22 (a panel of
+// 7168 rows, four bits: updates 25 us, chains 42, staging, errors and integers 20).  The errors of a panel are kept in Dt,
+// which the pass does not use otherwise.  Whole pass 3.78 -> 3.04 ms.
 static hipError_t gptq_rows(int M, int N, int n_bits, int q, const float *W, const float *U, const float *S, const float *qbias,
                             const int8_t *labels, uint8_t *w_int, void *workspace, hipStream_t stream)
 {
@@ -772,22 +1019,15 @@ static hipError_t gptq_rows(int M, int N, int n_bits, int q, const float *W, con
     hipLaunchKernelGGL(transpose_kernel, dim3((N + 31) / 32, (w.Mp + 31) / 32), dim3(32, 8), 0, stream, M, w.Mp, N, W,
                        w.Wt);
     hipLaunchKernelGGL(gptq_tables_kernel, dim3((M + 63) / 64), dim3(64), 0, stream, M, n_bits, q, labels, nibbles, bytes);
-    // Wt[k][m] -= sum_j U[j][k] Err[j][m] for the columns k in [from, to) and the errors of the columns [j0, j1)
-    auto update = [&](int j0, int j1, int from, int to) {
-        if (from < to)
-            launch_product<kSubtract>(stream, U + (size_t)j0 * N + from, N, to - from, err + (size_t)j0 * w.Mp, w.Mp, w.Mp, j1 - j0,
-                                      w.Wt + (size_t)from * w.Mp, w.Mp, least, j0 / kGptqBlock % 4);
-    };
+    const auto panel = n_bits <= 3 ? gptq_panel_kernel<kEight> : n_bits == 4 ? gptq_panel_kernel<kSixteen> : gptq_panel_kernel<kBytes>;
     for (int p0 = 0; p0 < N; p0 += kGptqPanel) {
         const int p1 = p0 + kGptqPanel < N ? p0 + kGptqPanel : N;
-        for (int c0 = p0; c0 < p1; c0 += kGptqBlock) {
-            const int c1 = c0 + kGptqBlock < p1 ? c0 + kGptqBlock : p1;
-            hipLaunchKernelGGL((n_bits <= 4 ? gptq_block_kernel<true> : gptq_block_kernel<false>),
-                               dim3((w.Mp + kGptqRows - 1) / kGptqRows), dim3(256), 0, stream, M, w.Mp, N, n_bits, c0, c1 - c0,
-                               w.Wt, U, S, qbias, nibbles, bytes, w_int, err + (size_t)c0 * w.Mp, least + 2 * (c0 / kGptqBlock % 4));
-            update(c0, c1, c1, p1);
-        }
-        update(p0, p1, p1, N);
+        hipLaunchKernelGGL(panel, dim3((w.Mp + kGptqRows - 1) / kGptqRows), dim3(256), 0, stream, M, w.Mp, N, n_bits, p0, p1, w.Wt, U, S,
+                           qbias, nibbles, bytes, w_int, err, least);
+        // Wt[k][m] -= sum_j U[j][k] Err[j][m] for the columns k beyond the panel and its errors j
+        if (p1 < N)
+            launch_product<kSubtract>(stream, U + (size_t)p0 * N + p1, N, N - p1, err, w.Mp, w.Mp, p1 - p0, w.Wt + (size_t)p1 * w.Mp,
+                                      w.Mp, least, 0);
     }
     return hipGetLastError();
 }

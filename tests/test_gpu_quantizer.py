@@ -291,6 +291,37 @@ def test_gptq_unusual_diagonals():
     assert np.array_equal(got, want), np.argwhere(got != want)[:10]
 
 
+@pytest.mark.parametrize("n,q", [(2, 2), (3, 2), (4, 3), (5, 3), (8, 4)])
+def test_gptq_decisions_where_binary32_does_not_tell(n, q):
+    """The GPTQ pass decides from a binary32 quotient unless that is close to a half or the scale is out of the ordinary: weights on
+    and next to the halves, offsets 2^20 steps away, scales of 2^-70 and 2^70, weights beyond the grid.  Without compensation
+    (U diagonal) the integers are those of the definition in binary64, all of them."""
+    M, N = 24, 136
+    rng = np.random.default_rng(40 + n)
+    S32 = (0.01 + 0.02 * rng.random(M)).astype(np.float32)
+    S32[3] *= np.float32(2.0 ** -64)
+    S32[4] *= np.float32(2.0 ** 76)
+    S32[5] *= np.float32(-1.0)
+    b32 = (-S32 * (2 ** (n - 1)) * rng.random(M)).astype(np.float32)
+    b32[1] = S32[1] * np.float32(2.0 ** 20)
+    b32[2] = -S32[2] * np.float32(2.0 ** 10)
+    steps = rng.integers(-2, 2 ** n + 2, size=(M, N)) + rng.choice([0.0, 0.25, 0.5, 0.5 - 2.0 ** -20, 0.5 + 2.0 ** -22], size=(M, N))
+    W32 = (b32[:, None] + steps * S32[:, None].astype(np.float64)).astype(np.float32)
+    parts = fuse.all_partitions(n, q)
+    pick = rng.integers(0, len(parts), size=M)
+    labels = np.stack([_labels_of(parts[i], n) for i in pick])
+    nearest = np.stack([fuse.nearest_bcchoice(np.arange(2 ** n), fuse.bcchoice(parts[i], n)) for i in pick])
+    t = np.rint((W32.astype(np.float64) - b32[:, None]) / S32[:, None].astype(np.float64))
+    want = np.take_along_axis(nearest, np.clip(t, 0, 2 ** n - 1).astype(np.int64), axis=1)
+    w_int = torch.full((M, N), 255, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(bcq.quant_workspace_bytes(M, N), dtype=torch.uint8, device="cuda")
+    U = torch.diag(torch.linspace(0.5, 2.0, N)).cuda()
+    bcq.quant_gptq(M, N, n, q, _dev(W32), U, _dev(S32), _dev(b32), _dev(labels), w_int, ws)
+    torch.cuda.synchronize()
+    got = w_int.cpu().numpy()
+    assert np.array_equal(got, want), np.argwhere(got != want)[:10]
+
+
 @pytest.mark.parametrize("M,N,n,q", [(37, 1024, 3, 2), (12, 512, 4, 3), (5, 1536, 5, 3), (8, 512, 4, 4)])
 def test_from_linear_rows(M, N, n, q):
     rng = np.random.default_rng(300 + N + n + q)
