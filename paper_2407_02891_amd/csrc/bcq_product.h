@@ -100,6 +100,7 @@ struct ProductArgs {
     // last one may have fewer columns, columns_end - y * columns_step of them, and with k_is_columns as many values of k
     size_t stride;
     int columns_end, columns_step, k_is_columns;
+    const int *rows;  // kQuadFormSplit: number of rows that are there, in device memory, or null: R
 };
 
 // Number of workgroups, and the tile of one.  Blocks of 4 x 4 tiles are numbered row by row (only those on and above the
@@ -186,6 +187,7 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
     int tile_row, tile_col;
     if (!product_tile<MODE>(blockIdx.x, gridDim.x, p.R, p.C, &tile_row, &tile_col)) return;
     const int r0 = tile_row * kProdTile, c0 = tile_col * kProdTile;
+    if (kSplitA && p.rows && r0 >= *p.rows) return;
 
     // k range of the tile: what a triangular operand leaves
     int k_begin = 0, k_end = p.K;
@@ -592,7 +594,7 @@ template <int MODE>
 static void launch_product(hipStream_t stream, const float *A, int lda, int R, const float *B, int ldb, int C, int K, float *out,
                            int ldo, const float *least = nullptr, int least_first = 0)
 {
-    ProductArgs p = {A, B, nullptr, out, lda, R, ldb, C, K, ldo, 0, nullptr, 0, nullptr, nullptr, least, least_first, 0, C, 0, 0};
+    ProductArgs p = {A, B, nullptr, out, lda, R, ldb, C, K, ldo, 0, nullptr, 0, nullptr, nullptr, least, least_first, 0, C, 0, 0, nullptr};
     const int blocks = (product_blocks<MODE>(R, C) + 7) / 8 * 8;
     hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)(blocks * kProdBlock * kProdBlock)), dim3(256), 0, stream, p);
 }
@@ -603,7 +605,7 @@ static void launch_products(hipStream_t stream, int count, size_t stride, int co
                             int pitch, int size)
 {
     ProductArgs p = {A, B, nullptr, out, pitch, size, pitch, size, size, pitch, MODE == kStore ? 1 : 0, nullptr, 0, nullptr, nullptr, nullptr, 0,
-                     stride, columns_end, 2 * size, MODE == kStore ? 1 : 0};
+                     stride, columns_end, 2 * size, MODE == kStore ? 1 : 0, nullptr};
     const int blocks = (product_blocks<MODE>(size, size) + 7) / 8 * 8;
     hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)(blocks * kProdBlock * kProdBlock), (unsigned)count), dim3(256), 0, stream, p);
 }
@@ -612,9 +614,9 @@ static void launch_products(hipStream_t stream, int count, size_t stride, int co
 // (see ProductArgs).
 template <int MODE>
 static void launch_quad_form(hipStream_t stream, const uint16_t *split, size_t plane, const int *shift, const float *D, int R, const float *B,
-                             int ldb, const float *diag_max, int C, float *out, int ldo)
+                             int ldb, const float *diag_max, int C, float *out, int ldo, const int *rows = nullptr)
 {
-    ProductArgs p = {D, B, D, out, ldo, R, ldb, C, C, ldo, 0, split, plane, shift, diag_max, nullptr, 0, 0, C, 0, 0};
+    ProductArgs p = {D, B, D, out, ldo, R, ldb, C, C, ldo, 0, split, plane, shift, diag_max, nullptr, 0, 0, C, 0, 0, rows};
     const int blocks = (product_blocks<MODE>(R, C) + 7) / 8 * 8;
     hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)(blocks * kProdBlock * kProdBlock)), dim3(256), 0, stream, p);
 }

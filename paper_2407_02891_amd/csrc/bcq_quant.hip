@@ -21,6 +21,7 @@
 #include "bcq_internal.h"
 #include "bcq_device.h"
 #include "bcq_product.h"
+#include "bcq_screen.h"
 #include "bcq_tying.h"
 
 namespace bcq {
@@ -432,6 +433,33 @@ __global__ void row_range_final_kernel(int M, int Mp, int chunks, const float *_
     wmax[m] = hi;
 }
 
+// The same from W itself, a wave per row, where its rows can be read four weights at a time.
+__global__ __launch_bounds__(256) void row_range_kernel(int M, int N, const float *__restrict__ W, float *__restrict__ wmin,
+                                                        float *__restrict__ wmax)
+{
+    const int m = 4 * blockIdx.x + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (m >= M) return;
+    const prod_f32x4 *const row = reinterpret_cast<const prod_f32x4 *>(W + (size_t)m * N);
+    float lo = INFINITY, hi = -INFINITY;
+    for (int k = lane; k < N / 4; k += 64) {
+        const prod_f32x4 v = row[k];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            lo = fminf(lo, v[j]);
+            hi = fmaxf(hi, v[j]);
+        }
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        lo = fminf(lo, __shfl_xor(lo, d));
+        hi = fmaxf(hi, __shfl_xor(hi, d));
+    }
+    if (lane == 0) {
+        wmin[m] = lo;
+        wmax[m] = hi;
+    }
+}
+
 // Scale of grid point g (0-based) of a row, Eq. 7, in binary64.
 __device__ __forceinline__ double grid_scale(double wmin, double wmax, int n_bits, int g, int grid)
 {
@@ -466,55 +494,139 @@ __global__ __launch_bounds__(256) void split_shift_kernel(int M, int Mp, const f
     if (threadIdx.x == 0) *diag_max = fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
 }
 
-// Dt[k][m] = S' W_q + qbias - w for one candidate (grid point g, tying t), from Wt (SPLIT = false) or from W; zeros in the
-// pad rows.  With SPLIT the same values also go to `split` as two binary16 halves in the operand layout of the matrix
-// instructions, [hi, lo][k / 8][m][k % 8], so that the product does not have to convert them once per column tile.  A
-// workgroup takes 64 rows by 32 columns, a thread eight columns of a row.  Bound: memory.  7168 x 7168: 218 us per
-// candidate (a division and a scan of the representable set per weight, nothing split) -> 111 us with the split, 617 MB.
-template <bool SPLIT>
+// What the search keeps of a candidate of a chunk: the nearest representable integer of every integer, as nibbles (up to four
+// bits) and bytes, and the class of every plane.
+struct CandidateTable {
+    unsigned long long nibbles;
+    int8_t label[kMaxBits];
+    uint8_t nearest[1 << kMaxBits];
+};
+
+// Rows to evaluate and with which candidate of the chunk each.
+struct SearchList {
+    const int *count, *row, *candidate;
+    const CandidateTable *tables;
+    int first_candidate, tyings;
+};
+
+// d = S' W_q + qbias - w of one candidate (grid point g, tying t), in three forms:
+//   kPlain    Dt[k][m] from Wt; zeros in the pad rows
+//   kSplit    Dt[k][m] from W, and the same values as two binary16 halves in the operand layout of the matrix instructions, [hi,
+//             lo][k / 8][m][k % 8], so that the product does not have to convert them once per column tile
+//   kListed   kSplit of the rows and candidates of a list
+// A workgroup takes 64 rows by 32 columns, a thread eight columns of a row.  Bound: memory.  7168 x 7168: 218 us per candidate (a
+// division and a scan of the representable set per weight, nothing split) -> 111 us with the split, 617 MB.
+enum DeltaForm { kPlain = 0, kSplit = 1, kListed = 2 };
+template <int FORM>
 __global__ __launch_bounds__(256) void delta_kernel(int M, int Mp, int N, int n_bits, int g, int grid, Tying t,
                                                     const float *__restrict__ W, const float *__restrict__ wmin,
                                                     const float *__restrict__ wmax, float *__restrict__ Dt,
-                                                    const int *__restrict__ shift, uint16_t *__restrict__ split, size_t plane)
+                                                    const int *__restrict__ shift, uint16_t *__restrict__ split, size_t plane,
+                                                    SearchList list, int *__restrict__ slot_shift)
+{
+    const int slot = blockIdx.x * 64 + (threadIdx.x & 63);
+    if (FORM == kListed && blockIdx.x * 64 >= (unsigned)*list.count) return;
+    if (slot >= Mp) return;
+    int k0 = 8 * (blockIdx.y * 4 + (threadIdx.x >> 6));
+    bool live = slot < M;
+    int m = live ? slot : 0;
+    const CandidateTable *of = nullptr;
+    unsigned long long nibbles = t.nibbles;
+    if (FORM == kListed) {
+        live = slot < *list.count;
+        m = live ? list.row[slot] : 0;
+        const int c = live ? list.candidate[slot] : 0;
+        of = list.tables + c;
+        nibbles = of->nibbles;
+        g = (list.first_candidate + c) / list.tyings;
+        if (k0 == 0) slot_shift[slot] = live ? shift[m] : 0;
+    }
+    for (; k0 < N; k0 += FORM == kListed ? 32 * (int)gridDim.y : N) {
+        float w[8], d[8];
+        if (FORM != kPlain) {  // N is a multiple of 8, W on 16 bytes
+            const prod_f32x4 *src = reinterpret_cast<const prod_f32x4 *>(W + (size_t)m * N + k0);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) w[j] = src[j >> 2][j & 3];
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) w[j] = k0 + j < N ? W[(size_t)(k0 + j) * Mp + slot] : 0.0f;
+        }
+        if (live) {
+            const double lo = wmin[m], S = grid_scale(lo, wmax[m], n_bits, g, grid), inv_s = 1.0 / S, top = (double)((1 << n_bits) - 1);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int lin = linear_int((double)w[j] - lo, S, inv_s, top);
+                const int wq = n_bits <= 4 ? (int)(nibbles >> (4 * lin)) & 15
+                               : FORM == kListed ? of->nearest[lin] : nearest_choice(lin, t.choice, t.nchoice);
+                d[j] = (float)(S * wq + lo - (double)w[j]);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) d[j] = 0.0f;
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (k0 + j < N) Dt[(size_t)(k0 + j) * Mp + slot] = d[j];
+        if (FORM != kPlain) {
+            const float s = ldexpf(1.0f, live ? shift[m] : 0);
+            prod_f16x8 hi, lo;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                hi[j] = (_Float16)(d[j] * s);
+                lo[j] = (_Float16)fmaf(d[j], s, -(float)hi[j]);
+            }
+            uint16_t *const at = split + ((size_t)(k0 >> 3) * Mp + slot) * 8;
+            *reinterpret_cast<prod_f16x8 *>(at) = hi;
+            *reinterpret_cast<prod_f16x8 *>(at + plane) = lo;
+        }
+    }
+}
+
+// The same d for the screened search: of up to kPlanes tyings of one grid point, each a binary16 number rounded to nearest, in planes
+// of the operand layout; also fills the candidates' tables.  Bound: memory.  7168 x 7168, three tyings: 68 us each one by one, W
+// being read each time.
+constexpr int kPlanes = 4;
+struct TyingSet { Tying t[kPlanes]; };
+template <int PLANES>
+__global__ __launch_bounds__(256) void delta_single_kernel(int M, int Mp, int N, int n_bits, int g, int grid, TyingSet set,
+                                                           const float *__restrict__ W, const float *__restrict__ wmin,
+                                                           const float *__restrict__ wmax, const int *__restrict__ shift,
+                                                           uint16_t *__restrict__ out, CandidateTable *__restrict__ tables)
 {
     const int m = blockIdx.x * 64 + (threadIdx.x & 63), k0 = 8 * (blockIdx.y * 4 + (threadIdx.x >> 6));
+    if (blockIdx.x == 0 && blockIdx.y == 0) {
+        const int w = threadIdx.x;
+#pragma unroll
+        for (int p = 0; p < PLANES; ++p) {
+            const Tying &t = set.t[p];
+            if (w == 0) tables[p].nibbles = t.nibbles;
+            if (w < kMaxBits) tables[p].label[w] = t.label[w];
+            if (w < 1 << n_bits) tables[p].nearest[w] = (uint8_t)nearest_choice(w, t.choice, t.nchoice);
+        }
+    }
     if (m >= Mp || k0 >= N) return;
-    float w[8], d[8];
-    if (SPLIT) {  // N is a multiple of 8, W on 16 bytes
-        const prod_f32x4 *src = reinterpret_cast<const prod_f32x4 *>(W + (size_t)(m < M ? m : 0) * N + k0);
+    prod_f16x8 d[PLANES];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) w[j] = src[j >> 2][j & 3];
-    } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) w[j] = k0 + j < N ? W[(size_t)(k0 + j) * Mp + m] : 0.0f;
-    }
+    for (int p = 0; p < PLANES; ++p) d[p] = prod_f16x8{0, 0, 0, 0, 0, 0, 0, 0};
     if (m < M) {
+        const prod_f32x4 *src = reinterpret_cast<const prod_f32x4 *>(W + (size_t)m * N + k0);
+        const prod_f32x4 w0 = src[0], w1 = src[1];
         const double lo = wmin[m], S = grid_scale(lo, wmax[m], n_bits, g, grid), inv_s = 1.0 / S, top = (double)((1 << n_bits) - 1);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int lin = linear_int((double)w[j] - lo, S, inv_s, top);
-            const int wq = n_bits <= 4 ? (int)(t.nibbles >> (4 * lin)) & 15 : nearest_choice(lin, t.choice, t.nchoice);
-            d[j] = (float)(S * wq + lo - (double)w[j]);
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) d[j] = 0.0f;
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-        if (k0 + j < N) Dt[(size_t)(k0 + j) * Mp + m] = d[j];
-    if (SPLIT) {
         const float s = ldexpf(1.0f, shift[m]);
-        prod_f16x8 hi, lo;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            hi[j] = (_Float16)(d[j] * s);
-            lo[j] = (_Float16)fmaf(d[j], s, -(float)hi[j]);
+            const double w = j < 4 ? w0[j & 3] : w1[j & 3];
+            const int lin = linear_int(w - lo, S, inv_s, top);
+#pragma unroll
+            for (int p = 0; p < PLANES; ++p) {
+                const int wq = n_bits <= 4 ? (int)(set.t[p].nibbles >> (4 * lin)) & 15 : nearest_choice(lin, set.t[p].choice, set.t[p].nchoice);
+                d[p][j] = (_Float16)((float)(S * wq + lo - w) * s);
+            }
         }
-        uint16_t *const at = split + ((size_t)(k0 >> 3) * Mp + m) * 8;
-        *reinterpret_cast<prod_f16x8 *>(at) = hi;
-        *reinterpret_cast<prod_f16x8 *>(at + plane) = lo;
     }
+    const size_t at = ((size_t)(k0 >> 3) * Mp + m) * 8, plane = (size_t)N * Mp;
+#pragma unroll
+    for (int p = 0; p < PLANES; ++p) *reinterpret_cast<prod_f16x8 *>(out + p * plane + at) = d[p];
 }
 
 // err = sum of the row's tile partials, in tile order (each is half of its part of d H d^T: H = 2 X X^T); keep the
@@ -536,20 +648,196 @@ __global__ void keep_best_kernel(int M, int Mp, int n_bits, int ntile, int g, in
     }
 }
 
+// A round of the screened search, per row: takes the errors of the round before (entries of the row's range in the list), and lists
+// what is to be evaluated next: in a chunk's first round the candidate with the lowest bound, then all whose bound does not exclude
+// that they are better than the best so far, or as good and earlier.  As much as fits; the rest comes in the next round.
+struct SearchRound {
+    float *bound;             // [candidate of the chunk][Mp]; infinite: done with
+    int candidates, first_candidate, tyings;
+    int *total;               // entries of this round, zero before
+    const int *last_total;    // and of the one before: none means that nothing is left
+    int *row, *candidate;     // its list, up to Mp entries
+    const int *last_candidate; // the list of the round before
+    int *begin, *count;       // [Mp] range of a row's entries
+    int *index;               // [Mp] candidate that is best (-1: decided, first candidate without a number)
+    const CandidateTable *tables;
+    int fresh, start, end;    // nothing evaluated yet; first round of a chunk; no further round
+};
+__global__ __launch_bounds__(256) void search_round_kernel(int M, int Mp, int n_bits, int grid, int ntile, SearchRound r,
+                                                           const float *__restrict__ part, const float *__restrict__ wmin,
+                                                           const float *__restrict__ wmax, float *__restrict__ best_out,
+                                                           float *__restrict__ S, float *__restrict__ qbias, int8_t *__restrict__ labels)
+{
+    const int m = blockIdx.x * blockDim.x + threadIdx.x;
+    if (m >= M || (!r.start && *r.last_total == 0)) return;
+    float best = r.fresh ? INFINITY : best_out[m];
+    int index = r.fresh ? 0x7fffffff : r.index[m];
+    if (!r.start) {
+        const int before = index, begin = r.begin[m], count = r.count[m];
+        int won = 0;
+        for (int e = begin; e < begin + count; ++e) {
+            const int c = r.last_candidate[e], j = r.first_candidate + c;
+            float err = 0.0f;
+            for (int k = 0; k < ntile; ++k) err += part[(size_t)k * Mp + e];
+            if (j == 0 && err != err) {
+                best = err;
+                index = -1;
+                won = c;
+            } else if (index >= 0 && (err < best || (err == best && j < index))) {
+                best = err;
+                index = j;
+                won = c;
+            }
+        }
+        if (index != before) {
+            S[m] = (float)grid_scale(wmin[m], wmax[m], n_bits, (r.first_candidate + won) / r.tyings, grid);
+            qbias[m] = wmin[m];
+            for (int i = 0; i < n_bits; ++i) labels[(size_t)m * n_bits + i] = r.tables[won].label[i];
+        }
+    }
+    best_out[m] = best;
+    r.index[m] = index;
+    if (r.end) return;
+    int n = 0, lowest = 0;
+    float low = INFINITY;
+    if (index >= 0)
+        for (int c = 0; c < r.candidates; ++c) {
+            const float b = r.bound[(size_t)c * Mp + m];
+            if (!(b < INFINITY) || b > best || (b == best && r.first_candidate + c > index)) continue;
+            ++n;
+            if (b < low) {
+                low = b;
+                lowest = c;
+            }
+        }
+    if (r.start && n > 1) n = 1;
+    int at = n ? atomicAdd(r.total, n) : 0;
+    if (at >= Mp) n = 0;  // (the total may run beyond the list; who reads it takes no more than fits)
+    else if (at + n > Mp) n = Mp - at;
+    r.begin[m] = at;
+    r.count[m] = n;
+    for (int c = r.start ? lowest : 0; n > 0 && c < r.candidates; ++c) {
+        float &b = r.bound[(size_t)c * Mp + m];
+        if (!(b < INFINITY) || b > best || (b == best && r.first_candidate + c > index)) continue;
+        r.row[at] = m;
+        r.candidate[at++] = c;
+        b = INFINITY;
+        --n;
+    }
+}
+
+// The screened search (bcq_screen.h) keeps its matrices in the place of Wt and Dt, where the listed rows' d come afterwards:
+//   Dh binary16 [planes][N / 8][Mp][8] | Hh binary16 [N / 8][N][8]
+// and in `small`: shift [Mp] | diag_max, frobenius | bound [kChunk][Mp] | sums [kPlanes][4][Mp] | slot_shift, row and candidate of two
+// lists, begin, count, index [8][Mp] | unscale, norms [2][N] | totals [kChunk] | tables [kChunk].
+constexpr int kChunk = 48;
+static int screen_planes(int M, int N, int tyings)  // 0: there is no room
+{
+    const long long Mp = pitch_of(M);
+    if ((kChunk + 4 * kPlanes + 9) * Mp + 16 + 2LL * N + kChunk * (1 + (long long)sizeof(CandidateTable) / 4) + 64 > 128 * Mp) return 0;
+    const long long planes = (8 * Mp * N - 2LL * N * N) / (2 * Mp * N);
+    return (int)(planes < 0 ? 0 : planes < tyings ? (planes < kPlanes ? planes : kPlanes) : (tyings < kPlanes ? tyings : kPlanes));
+}
+
+// Two rounds of three products each and a product per candidate instead of three per candidate: pays from a few candidates on, down
+// to where launches are what counts (three per grid point and three per candidate for rounds that find nothing, instead of three
+// per candidate).  us, all candidates / screened: 7168 x 7168, three bits, two planes, grid 8 32000 / 10360 (1.17 candidates a row
+// evaluated of 24; a form 309 of 1300), 2500 x 7168 11700 / 5030, 2048 x 2048 2140 / 757, 512 x 512 790 / 365, 256 x 512 (grid 4) 385 / 284.
+static bool screen_pays(int M, int N, int candidates) { return M >= 256 && N >= 256 && candidates >= 4; }
+
+static hipError_t search_screened(int M, int N, int n_bits, int grid, const std::vector<Tying> &tyings, int most_planes, const float *W,
+                                  const float *H, float *S, float *qbias, int8_t *labels, const QuantWorkspace &w, hipStream_t stream)
+{
+    const int Mp = w.Mp, T = (int)tyings.size(), all = grid * T;
+    auto *Dh = reinterpret_cast<uint16_t *>(w.Wt);
+    uint16_t *const Hh = Dh + (size_t)most_planes * N * Mp;
+    auto *shift = reinterpret_cast<int *>(w.small);
+    float *diag_max = w.small + Mp, *frobenius = diag_max + 4, *bound = diag_max + 16, *sums = bound + (size_t)kChunk * Mp;
+    auto *slot_shift = reinterpret_cast<int *>(sums + 4 * (size_t)kPlanes * Mp);
+    int *list[2] = {slot_shift + Mp, slot_shift + 3 * (size_t)Mp};
+    int *begin = slot_shift + 5 * (size_t)Mp, *count = begin + Mp, *index = count + Mp;
+    float *unscale = reinterpret_cast<float *>(index + Mp), *norms = unscale + N;
+    int *totals = reinterpret_cast<int *>(norms + N);
+    auto *tables = reinterpret_cast<CandidateTable *>((reinterpret_cast<uintptr_t>(totals + kChunk) + 15) & ~(uintptr_t)15);
+    const dim3 delta_grid((Mp + 63) / 64, (N + 31) / 32), rows((M + 63) / 64);
+    const size_t plane = (size_t)N * Mp;
+    SearchRound round = {};
+    round.bound = bound;
+    round.tyings = T;
+    round.begin = begin;
+    round.count = count;
+    round.index = index;
+    round.tables = tables;
+    SearchList listed = {nullptr, nullptr, nullptr, tables, 0, T};
+    hipError_t e = launch_fill_zero(sums, 16 * (size_t)kPlanes * Mp, stream);
+    if (e != hipSuccess) return e;
+    for (int first = 0; first < all; first += kChunk) {
+        const int candidates = all - first < kChunk ? all - first : kChunk;
+        e = launch_fill_zero(norms, (size_t)(N + kChunk) * 4, stream);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(screen_h_kernel, dim3((N + 63) / 64, (N + 255) / 256), dim3(256), 0, stream, N, H, diag_max, Hh, unscale, norms);
+        hipLaunchKernelGGL(screen_frobenius_kernel, dim3(1), dim3(1024), 0, stream, N, norms, frobenius);
+        for (int c = 0; c < candidates;) {
+            // tyings of one grid point, as many as there are planes
+            const int g = (first + c) / T, t0 = (first + c) % T;
+            int planes = most_planes < T - t0 ? most_planes : T - t0;
+            planes = planes < candidates - c ? planes : candidates - c;
+            TyingSet set = {};
+            for (int p = 0; p < planes; ++p) set.t[p] = tyings[t0 + p];
+            const auto delta = planes == 1 ? delta_single_kernel<1> : planes == 2 ? delta_single_kernel<2>
+                             : planes == 3 ? delta_single_kernel<3> : delta_single_kernel<4>;
+            hipLaunchKernelGGL(delta, delta_grid, dim3(256), 0, stream, M, Mp, N, n_bits, g, grid, set, W, w.wmin, w.wmax, shift, Dh, tables + c);
+            launch_screen(stream, ScreenArgs{Hh, Dh, unscale, norms, sums, N, M, Mp, planes});
+            hipLaunchKernelGGL(screen_bound_kernel, dim3(rows.x, planes), dim3(64), 0, stream, M, Mp, N, sums, shift, frobenius,
+                               bound + (size_t)c * Mp);
+            c += planes;
+        }
+        // As many rounds as there can be: one candidate per row, then all that are left, Mp at a time.  Nearly always the first two
+        // have work, and a launch that finds an empty list ends at once.
+        round.candidates = candidates;
+        round.first_candidate = listed.first_candidate = first;
+        for (int p = 0; p <= candidates; ++p) {
+            int *const mine = list[p & 1];
+            round.fresh = first == 0 && p == 0;
+            round.start = p == 0;
+            round.end = p == candidates;
+            round.total = totals + p;
+            round.last_total = totals + p - 1;
+            round.row = mine;
+            round.candidate = mine + Mp;
+            round.last_candidate = list[(p & 1) ^ 1] + Mp;
+            hipLaunchKernelGGL(search_round_kernel, rows, dim3(64), 0, stream, M, Mp, n_bits, grid, w.ntile, round, w.part, w.wmin, w.wmax,
+                               w.best, S, qbias, labels);
+            if (round.end) break;
+            listed.count = totals + p;
+            listed.row = mine;
+            listed.candidate = mine + Mp;
+            // (from the third round on the list is nearly always empty: fewer workgroups find that out)
+            hipLaunchKernelGGL(delta_kernel<kListed>, dim3(delta_grid.x, p < 2 ? delta_grid.y : (delta_grid.y + 15) / 16), dim3(256), 0, stream, M, Mp, N, n_bits, 0, grid, Tying{}, W, w.wmin,
+                               w.wmax, w.Dt, shift, Dh, plane, listed, slot_shift);
+            launch_quad_form<kQuadFormSplit>(stream, Dh, plane, slot_shift, w.Dt, Mp, H, N, diag_max, N, w.part, Mp, totals + p);
+        }
+    }
+    return hipSuccess;
+}
+
 static hipError_t search_rows(int M, int N, int n_bits, int q, int grid, const float *W, const float *H, float *S, float *qbias,
                               int8_t *labels, float *err_out, void *workspace, hipStream_t stream)
 {
     const QuantWorkspace w = carve(workspace, M, N);
-    hipLaunchKernelGGL(transpose_kernel, dim3((N + 31) / 32, (w.Mp + 31) / 32), dim3(32, 8), 0, stream, M, w.Mp, N, W,
-                       w.Wt);
-    const int chunks = N / 2 < 64 ? N / 2 : 64;  // Dt (N rows, not yet in use) holds the 2 * chunks partial rows
-    hipLaunchKernelGGL(row_range_partial_kernel, dim3((M + 63) / 64, chunks), dim3(64), 0, stream, M, w.Mp, N, chunks,
-                       w.Wt, w.Dt);
-    hipLaunchKernelGGL(row_range_final_kernel, dim3((M + 63) / 64), dim3(64), 0, stream, M, w.Mp, chunks, w.Dt, w.wmin,
-                       w.wmax);
-    // Split beforehand (in place of Wt, which the row ranges were the last to read) where rows can be read eight weights at a
-    // time; else the product splits what it reads.
+    // From W itself, and with d split beforehand (in place of Wt), where rows can be read eight weights at a time; else from the
+    // transposed copy, and the product splits what it reads.
     const bool split = N % 8 == 0 && (reinterpret_cast<uintptr_t>(W) & 15) == 0;
+    if (split) {
+        hipLaunchKernelGGL(row_range_kernel, dim3((M + 3) / 4), dim3(256), 0, stream, M, N, W, w.wmin, w.wmax);
+    } else {
+        hipLaunchKernelGGL(transpose_kernel, dim3((N + 31) / 32, (w.Mp + 31) / 32), dim3(32, 8), 0, stream, M, w.Mp, N, W, w.Wt);
+        const int chunks = N / 2 < 64 ? N / 2 : 64;  // Dt (N rows, not yet in use) holds the 2 * chunks partial rows
+        hipLaunchKernelGGL(row_range_partial_kernel, dim3((M + 63) / 64, chunks), dim3(64), 0, stream, M, w.Mp, N, chunks,
+                           w.Wt, w.Dt);
+        hipLaunchKernelGGL(row_range_final_kernel, dim3((M + 63) / 64), dim3(64), 0, stream, M, w.Mp, chunks, w.Dt, w.wmin,
+                           w.wmax);
+    }
     auto *halves = reinterpret_cast<uint16_t *>(w.Wt);
     auto *shift = reinterpret_cast<int *>(w.small);
     const size_t plane = (size_t)N * w.Mp;
@@ -557,19 +845,26 @@ static hipError_t search_rows(int M, int N, int n_bits, int q, int grid, const f
     hipLaunchKernelGGL(split_shift_kernel, dim3((w.Mp + 255) / 256 + 1), dim3(256), 0, stream, M, w.Mp, w.wmin, w.wmax, shift, N, H,
                        diag_max);
     const std::vector<Tying> tyings = all_tyings(n_bits, q);
-    bool first = true;
-    for (int g = 0; g < grid; ++g)
-        for (const Tying &t : tyings) {
-            hipLaunchKernelGGL((split ? delta_kernel<true> : delta_kernel<false>), dim3((w.Mp + 63) / 64, (N + 31) / 32), dim3(256), 0,
-                               stream, M, w.Mp, N, n_bits, g, grid, t, split ? W : w.Wt, w.wmin, w.wmax, w.Dt, shift, halves, plane);
-            // d H d^T / 2 row by row: sum_l Dt[l][m] sum_{k <= l} w_kl H[k][l] Dt[k][m], w = 1/2 on the diagonal
-            // (only the upper triangle of H is read), one partial per tile of 128 values of l
-            (split ? launch_quad_form<kQuadFormSplit> : launch_quad_form<kQuadForm>)(stream, halves, plane, shift, w.Dt, w.Mp, H, N,
-                                                                                     diag_max, N, w.part, w.Mp);
-            hipLaunchKernelGGL(keep_best_kernel, dim3((M + 255) / 256), dim3(256), 0, stream, M, w.Mp, n_bits, w.ntile, g,
-                               grid, first ? 1 : 0, t, w.part, w.wmin, w.wmax, w.best, S, qbias, labels);
-            first = false;
-        }
+    const int planes = split && screen_pays(M, N, grid * (int)tyings.size()) ? screen_planes(M, N, (int)tyings.size()) : 0;
+    if (planes > 0) {
+        const hipError_t e = search_screened(M, N, n_bits, grid, tyings, planes, W, H, S, qbias, labels, w, stream);
+        if (e != hipSuccess) return e;
+    } else {
+        bool first = true;
+        for (int g = 0; g < grid; ++g)
+            for (const Tying &t : tyings) {
+                hipLaunchKernelGGL((split ? delta_kernel<kSplit> : delta_kernel<kPlain>), dim3((w.Mp + 63) / 64, (N + 31) / 32), dim3(256),
+                                   0, stream, M, w.Mp, N, n_bits, g, grid, t, split ? W : w.Wt, w.wmin, w.wmax, w.Dt, shift, halves, plane,
+                                   SearchList{}, nullptr);
+                // d H d^T / 2 row by row: sum_l Dt[l][m] sum_{k <= l} w_kl H[k][l] Dt[k][m], w = 1/2 on the diagonal
+                // (only the upper triangle of H is read), one partial per tile of 128 values of l
+                (split ? launch_quad_form<kQuadFormSplit> : launch_quad_form<kQuadForm>)(stream, halves, plane, shift, w.Dt, w.Mp, H, N,
+                                                                                         diag_max, N, w.part, w.Mp, nullptr);
+                hipLaunchKernelGGL(keep_best_kernel, dim3((M + 255) / 256), dim3(256), 0, stream, M, w.Mp, n_bits, w.ntile, g,
+                                   grid, first ? 1 : 0, t, w.part, w.wmin, w.wmax, w.best, S, qbias, labels);
+                first = false;
+            }
+    }
     if (err_out) {
         hipError_t e = hipMemcpyAsync(err_out, w.best, (size_t)M * 4, hipMemcpyDeviceToDevice, stream);
         if (e != hipSuccess) return e;

@@ -1,0 +1,295 @@
+// Quadratic forms of the search from binary16 values, with a bound on what that leaves out (not public).
+//
+// The search evaluates e = d (H / 2) d^T for every row and candidate and keeps the smallest.  With d and H as pairs of binary16
+// numbers that is three matrix products per candidate (bcq_product.h), although nearly all candidates lose by far more than one
+// product with single binary16 numbers is off.  So every candidate is first evaluated that way, together with a lower bound on its
+// error, and only those whose bound does not exceed the smallest error found go through the three products (bcq_quant.hip).
+// The winner and its error are the same bits as if all had.
+//
+// The bound.  Let D be d rounded to binary16 (row scale 2^s, largest magnitude below 2^15 or so), delta = d - D, G the binary16
+// values of H, f the computed form of D and G.
+//   * H is rounded up or down at random (a hash of the position decides), the chance of up being the distance from below: the errors
+//     of its entries are independent with mean 0 and lie in an interval of 2^-10 of the entry, so (Hoeffding) the form of D changes by
+//     more than 9/2 (sum over k <= c of (2^-10 H_kc D_k D_c)^2)^1/2 with a probability of 2 exp(-81/2) = 5e-18.  The sum is at most
+//     2^-21 max |D|^2 sum_c D_c^2 |H_c|^2, |H_c| the norm of a row.
+//   * Rounding in binary32: sums of N terms, 2^-17 |H|_F |D|^2 (a form of the accumulators: 2^-24 a time, up to 2^10 times, and
+//     those do not all point the same way); that covers H's values below 2^-14 of their scale, too.
+//   * With H = 2 X X^T positive semidefinite, (d H d^T)^1/2 is a seminorm of d, so it is at least that of D less that of delta, which is
+//     at most |H|_F^1/2 |delta|, |delta| <= 2^-11 (1 + 2^-10) |D| + 2^-25-s N^1/2.
+//   * The error of the three products themselves: 2^-12 of it and 2^-18 |H|_F |D|^2.
+// Candidates that go on, 7168 x 7168, three bits, two planes, eight scales: 1.17 of 24 per row.
+#pragma once
+#include "bcq_product.h"
+
+namespace bcq {
+
+struct ScreenArgs {
+    const uint16_t *H;      // [k / 8][column c (N)][8 values of k], see screen_h_kernel
+    const uint16_t *D;      // [plane][k / 8][row m (Mp)][8 values of k], a plane per candidate
+    const float *unscale;   // [N] what takes a column's scale out again
+    const float *norms;     // [N] squared norms of H's rows
+    float *sums;            // [plane][4][Mp], zero before: form, sum of D^2, sum of D^2 norms, largest |D|, of D with its scale
+    int N, M, Mp, planes;
+};
+
+// D G D^T of the rows of D (added up over the tiles of columns c by atomics: their order moves the bound by its roundings, not
+// the result of the search), G[k][c] = H with the weight 1 for k < c, 1/2 for k = c and 0 beyond.
+// WR x WC waves, a wave TA x TB accumulators of 16 (columns c) x 16 (rows m).  Both operands are in memory as the matrix
+// instruction takes them and are copied to LDS by buffer loads with an LDS destination, three steps of 32 values of k ahead in
+// four stages; the operands of the next step are read while this one is multiplied (an A operand's registers are
+// free as soon as its products are issued), so that nothing in the loop waits for what it asked for.  7168 x 7168: 309 us per
+// candidate, 1.2 PFLOP/s; registers alone sustain 1.8 with such values, 2.4 with zeros.
+template <int TA, int TB, int WR, int WC>
+__global__ __launch_bounds__(64 * WR * WC, 2) void screen_kernel(ScreenArgs p)
+{
+    constexpr int kRows = 16 * TA * WR, kCols = 16 * TB * WC, kWaves = WR * WC;  // columns c and rows m of a tile
+    constexpr int kPieces = (kRows + kCols) / 16 / kWaves;                       // copies of 1 KB per wave and stage
+    static_assert(kRows == kCols && kPieces == 4, "half of the waves bring each operand");
+    __shared__ __attribute__((aligned(16))) uint8_t st0[2][4][kRows * 16];       // [operand][octet][row]
+    __shared__ __attribute__((aligned(16))) uint8_t st1[2][4][kRows * 16];
+    __shared__ __attribute__((aligned(16))) uint8_t st2[2][4][kRows * 16];
+    __shared__ __attribute__((aligned(16))) uint8_t st3[2][4][kRows * 16];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lo = lane & 15, hi = lane >> 4, wr = wave / WC, wc = wave % WC;
+
+    // Tiles.  Those of the last columns have the longest k range and come first; the tiles of rows of one tile of columns are dealt
+    // to the eight XCDs (workgroup numbers go round them) in contiguous ranges, cut at a place that moves with the column.
+    const int ntc = (p.N + kRows - 1) / kRows, per_plane = (p.M + kCols - 1) / kCols, ntm = p.planes * per_plane, xcd = blockIdx.x & 7;
+    int j = blockIdx.x >> 3, tc = ntc - 1, tm = 0;
+    for (; tc >= 0; --tc) {
+        const int cut = (5 * tc) & 7;
+        const int from = xcd == 0 ? 0 : (xcd * ntm + cut) >> 3, to = xcd == 7 ? ntm : ((xcd + 1) * ntm + cut) >> 3;
+        tm = from + j;
+        if (j < to - from) break;
+        j -= to - from;
+    }
+    if (tc < 0) return;
+    const int plane = tm / per_plane, c0 = tc * kRows, m0 = (tm - plane * per_plane) * kCols;
+    p.D += (size_t)plane * p.N * p.Mp;
+    p.sums += (size_t)plane * 4 * p.Mp;
+    const int k_end = p.N < c0 + kRows ? p.N : c0 + kRows, steps = (k_end + 31) / 32;
+
+    const bool of_d = wave >= kWaves / 2;
+    const uint16_t *const source = of_d ? p.D : p.H;
+    const int pitch = of_d ? p.Mp : p.N, first = of_d ? m0 : c0;
+    const int bytes = 16 * (pitch - first < kRows ? pitch - first : kRows);
+    auto copy = [&](auto &stage, int step) PROD_INLINE {
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) {
+            const int piece = (wave % (kWaves / 2)) * kPieces + i, octet = piece / (kRows / 64), part = piece % (kRows / 64);
+            const int k8 = 4 * step + octet;
+            const bool in = 8 * k8 < k_end;
+            const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<uint16_t *>(source + ((size_t)(in ? k8 : 0) * pitch + first) * 8), 0, in ? bytes : 0, kRawBufferFlags);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void *)&stage[of_d][octet][64 * part * 16],
+                                                     16, 16 * (64 * part + lane), 0, 0, 0);
+        }
+    };
+    prod_f16x8 a[TA], b[2][TB];
+    prod_f32x4 acc[TA][TB];
+#pragma unroll
+    for (int x = 0; x < TA; ++x)
+#pragma unroll
+        for (int y = 0; y < TB; ++y) acc[x][y] = prod_f32x4{0.f, 0.f, 0.f, 0.f};
+    auto read_a = [&](auto &stage, int x) PROD_INLINE {
+        return *reinterpret_cast<const prod_f16x8 *>(&stage[0][hi][(16 * (wr * TA + x) + lo) * 16]);
+    };
+    auto read_b = [&](auto &stage, int y) PROD_INLINE {
+        return *reinterpret_cast<const prod_f16x8 *>(&stage[1][hi][(16 * (wc * TB + y) + lo) * 16]);
+    };
+    auto body = [&](int step, auto odd, auto &next, auto &ahead) PROD_INLINE {
+        constexpr int kOdd = decltype(odd)::value;
+        copy(ahead, step + 3);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int x = 0; x < TA; ++x) {
+#pragma unroll
+            for (int y = 0; y < TB; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[x], b[kOdd][y], acc[x][y], 0, 0, 0);
+            a[x] = read_a(next, x);
+            if (x < TB) b[kOdd ^ 1][x] = read_b(next, x);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kPieces) : "memory");  // the step after the next one has arrived
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    copy(st0, 0);
+    copy(st1, 1);
+    copy(st2, 2);
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kPieces) : "memory");
+#pragma unroll
+    for (int x = 0; x < TA; ++x) a[x] = read_a(st0, x);
+#pragma unroll
+    for (int y = 0; y < TB; ++y) b[0][y] = read_b(st0, y);
+    constexpr std::integral_constant<int, 0> even{};
+    constexpr std::integral_constant<int, 1> odd{};
+    for (int step = 0; step < steps; step += 4) {  // (beyond the last step: zeros)
+        body(step, even, st1, st3);
+        body(step + 1, odd, st2, st0);
+        body(step + 2, even, st3, st1);
+        body(step + 3, odd, st0, st2);
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+
+    // element i of an accumulator: column c 4 hi + i, row m lo
+    float *const red = reinterpret_cast<float *>(&st0[0][0][0]);  // [WR][4][kCols]
+    const __amdgpu_buffer_rsrc_t d_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t *>(p.D + ((size_t)(c0 >> 3) * p.Mp + m0) * 8), 0,
+        16 * ((((p.N < c0 + kRows ? p.N : c0 + kRows) - c0) / 8 - 1) * p.Mp + (p.Mp - m0)), kRawBufferFlags);
+#pragma unroll
+    for (int y = 0; y < TB; ++y) {
+        const int m = 16 * (wc * TB + y) + lo;
+        float form = 0.f, squares = 0.f, weighted = 0.f, most = 0.f;
+#pragma unroll
+        for (int x = 0; x < TA; ++x) {
+            const int c = 16 * (wr * TA + x) + 4 * hi;
+            const bool in = c0 + c < p.N && m0 + m < p.Mp;
+            const prod_u32x2 raw = __builtin_amdgcn_raw_buffer_load_b64(
+                d_rsrc, in ? 16 * ((c >> 3) * p.Mp + m) + 2 * (c & 4) : (int)0xfffffff0u, 0, 0);
+            prod_f32x4 un = {0.f, 0.f, 0.f, 0.f}, nr = un;
+            if (c0 + c < p.N) {
+                un = *reinterpret_cast<const prod_f32x4 *>(p.unscale + c0 + c);
+                nr = *reinterpret_cast<const prod_f32x4 *>(p.norms + c0 + c);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const unsigned word = raw[i >> 1];  // (a cast of the element itself takes the first one)
+                const prod_f16x2 pair = __builtin_bit_cast(prod_f16x2, word);
+                const float d = (float)pair[i & 1];
+                form = fmaf(acc[x][y][i] * un[i], d, form);
+                squares = fmaf(d, d, squares);
+                weighted = fmaf(d * d, nr[i], weighted);
+                most = fmaxf(most, fabsf(d));
+            }
+        }
+#pragma unroll
+        for (int s = 16; s < 64; s <<= 1) {
+            form += __shfl_xor(form, s);
+            squares += __shfl_xor(squares, s);
+            weighted += __shfl_xor(weighted, s);
+            most = fmaxf(most, __shfl_xor(most, s));
+        }
+        if (hi == 0) {
+            red[(wr * 4 + 0) * kCols + m] = form;
+            red[(wr * 4 + 1) * kCols + m] = squares;
+            red[(wr * 4 + 2) * kCols + m] = weighted;
+            red[(wr * 4 + 3) * kCols + m] = most;
+        }
+    }
+    __syncthreads();
+    for (int e = tid; e < 4 * kCols; e += 64 * kWaves) {
+        const int what = e / kCols, m = e % kCols;
+        float v = red[what * kCols + m];
+#pragma unroll
+        for (int w = 1; w < WR; ++w) {
+            const float o = red[(w * 4 + what) * kCols + m];
+            v = what == 3 ? fmaxf(v, o) : v + o;
+        }
+        if (m0 + m >= p.M) continue;
+        float *const to = p.sums + (size_t)what * p.Mp + m0 + m;
+        if (what == 3) atomicMax(reinterpret_cast<unsigned *>(to), __float_as_uint(v));
+        else atomicAdd(to, v);
+    }
+}
+
+// 256 x 256 tiles where there are enough of them to fill the chip.
+constexpr int kScreenTile = 256, kScreenSmallTile = 128;
+static inline int screen_tile(const ScreenArgs &p)
+{
+    return ((p.N + kScreenTile - 1) / kScreenTile) * p.planes * ((p.M + kScreenTile - 1) / kScreenTile) >= 256 ? kScreenTile : kScreenSmallTile;
+}
+
+static void launch_screen(hipStream_t stream, const ScreenArgs &p)
+{
+    const int tile = screen_tile(p);
+    const int ntc = (p.N + tile - 1) / tile, ntm = p.planes * ((p.M + tile - 1) / tile);
+    const dim3 grid((unsigned)(8 * ntc * (ntm / 8 + 1)));
+    if (tile == kScreenTile) hipLaunchKernelGGL((screen_kernel<8, 4, 2, 4>), grid, dim3(512), 0, stream, p);
+    else hipLaunchKernelGGL((screen_kernel<4, 4, 2, 2>), grid, dim3(256), 0, stream, p);
+}
+
+// H's columns as single binary16 numbers, weighted for the form, and what the bound needs of them.  A workgroup takes 64 columns by
+// 256 rows, a wave eight rows at a time.
+__global__ __launch_bounds__(256) void screen_h_kernel(int N, const float *__restrict__ H, const float *__restrict__ diag_max,
+                                                       uint16_t *__restrict__ out, float *__restrict__ unscale, float *__restrict__ norms)
+{
+    const int c = 64 * blockIdx.x + (threadIdx.x & 63), wave = threadIdx.x >> 6, k_begin = 256 * blockIdx.y;
+    if (k_begin >= 64 * (int)blockIdx.x + kScreenTile) return;  // (no tile of columns reads further below the diagonal; uniform)
+    __shared__ float sums[256];
+    // scale of a column: no value of a positive semidefinite H is above sqrt(max_k H[k][k] H[c][c]), which goes to 2^15 at most
+    const float diag = c < N ? H[(size_t)c * N + c] : 1.0f;
+    const int e_max = (int)(__float_as_uint(*diag_max) >> 23) - 127;
+    int e_diag = (int)((__float_as_uint(diag) >> 23) & 0xff) - 127;
+    if (!(diag > 0.0f) || e_diag == 128) e_diag = e_max;
+    int shift = 15 - ((e_max + e_diag + 3) >> 1);
+    shift = shift < -120 ? -120 : (shift > 120 ? 120 : shift);
+    const float s = ldexpf(1.0f, shift);
+    if (blockIdx.y == 0 && wave == 0 && c < N) unscale[c] = ldexpf(1.0f, -shift);
+    float mine = 0.0f;
+    for (int k0 = k_begin + 8 * wave; k0 < k_begin + 256 && k0 < N; k0 += 32) {
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = c < N && k0 + j <= c ? H[(size_t)(k0 + j) * N + c] : 0.0f;  // N is a multiple of 8
+        prod_u32x4 packed;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const float x = (k0 + j == c ? 0.5f : 1.0f) * v[j] * s;
+            // at random up or down to the 11 bits of a binary16 number (below 2^-14 it is rounded once more, to nearest)
+            unsigned h = (unsigned)(k0 + j) * 0x9e3779b1u + (unsigned)c * 0x85ebca77u;
+            h ^= h >> 15; h *= 0x2c1b3c6du; h ^= h >> 12; h *= 0x297a2d39u; h ^= h >> 15;
+            const float up = __uint_as_float((__float_as_uint(x) + (h & 0x1fffu)) & ~0x1fffu);
+            const unsigned half = __builtin_bit_cast(unsigned short, (_Float16)(fabsf(x) < INFINITY ? up : x));
+            packed[j >> 1] = j & 1 ? packed[j >> 1] | half << 16 : half;
+            const float square = v[j] * v[j];
+            mine += square;
+            // the other half of the matrix: row k0 + j (the diagonal is counted once)
+            float row = k0 + j < c ? square : 0.0f;
+#pragma unroll
+            for (int d = 32; d > 0; d >>= 1) row += __shfl_xor(row, d);
+            if ((threadIdx.x & 63) == j && row != 0.0f) atomicAdd(norms + k0 + j, row);
+        }
+        if (c < N) *reinterpret_cast<prod_u32x4 *>(out + ((size_t)(k0 >> 3) * N + c) * 8) = packed;
+    }
+    sums[threadIdx.x] = mine;
+    __syncthreads();
+    if (wave == 0 && c < N) atomicAdd(norms + c, sums[threadIdx.x] + sums[threadIdx.x + 64] + sums[threadIdx.x + 128] + sums[threadIdx.x + 192]);
+}
+
+// frobenius[0] = |H|_F, with something added for the roundings of the norms
+__global__ __launch_bounds__(1024) void screen_frobenius_kernel(int N, const float *__restrict__ norms, float *__restrict__ frobenius)
+{
+    __shared__ double part[16];
+    double s = 0.0;
+    for (int i = threadIdx.x; i < N; i += 1024) s += norms[i];
+    for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        s = 0.0;
+        for (int w = 0; w < 16; ++w) s += part[w];
+        *frobenius = (float)(sqrt(s) * (1.0 + 0x1p-10));
+    }
+}
+
+// Lower bound of the error of the candidate of each plane (blockIdx.y), per row; leaves the sums zero.
+__global__ __launch_bounds__(64) void screen_bound_kernel(int M, int Mp, int N, float *__restrict__ sums, const int *__restrict__ shift,
+                                                          const float *__restrict__ frobenius, float *__restrict__ bound)
+{
+    const int m = blockIdx.x * 64 + threadIdx.x;
+    if (m >= M) return;
+    float *const mine = sums + (size_t)blockIdx.y * 4 * Mp + m;
+    const double form = mine[0], weighted = mine[2 * (size_t)Mp], most = mine[3 * (size_t)Mp], fro = *frobenius;
+    const double squares = mine[Mp] * (1.0 + 0x1p-10);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) mine[k * (size_t)Mp] = 0.0f;
+    const double of_h = 4.5 * 0x1p-10 * sqrt(0.5) * (1.0 + 0x1p-9) * most * sqrt(weighted);
+    const double low = form - of_h - 0x1p-17 * fro * squares;
+    const double delta = 0x1p-11 * (1.0 + 0x1p-9) * sqrt(squares) + 0x1p-25 * sqrt((double)N);
+    const double root = sqrt(2.0 * (low > 0.0 ? low : 0.0)) - sqrt(fro) * delta;
+    double v = root > 0.0 ? 0.5 * root * root * (1.0 - 0x1p-12) - 0x1p-18 * fro * squares : 0.0;
+    v = ldexp(v > 0.0 ? v : 0.0, -2 * shift[m]);
+    // (a form that is not finite says nothing; infinity would say that the candidate is done with)
+    bound[(size_t)blockIdx.y * Mp + m] = !(fabs(form) < (double)INFINITY) || !(v < 0x1p126) ? 0.0f : (float)(v * (1.0 - 0x1p-23));
+}
+
+}  // namespace bcq

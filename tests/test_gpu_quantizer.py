@@ -158,6 +158,56 @@ def test_search_paths(M, N, n, q, grid, shift):
     assert same >= 0.9 * M
 
 
+def _search(W, H, n, q, grid):
+    M, N = W.shape
+    out = [torch.full((M,), 7.0, device="cuda") for _ in range(3)]
+    labels = torch.full((M, n), 9, dtype=torch.int8, device="cuda")
+    ws = torch.empty(bcq.quant_workspace_bytes(M, N), dtype=torch.uint8, device="cuda")
+    bcq.quant_search(M, N, n, q, grid, W, H, out[0], out[1], labels, out[2], ws)
+    torch.cuda.synchronize()
+    return [t.view(torch.int32).cpu() for t in out] + [labels.cpu()]
+
+
+@pytest.mark.parametrize("M,N,n,q,grid,kind", [
+    (256, 256, 3, 2, 3, "samples"), (257, 264, 4, 3, 2, "samples"), (700, 520, 3, 2, 2, "loud"), (513, 776, 2, 2, 4, "samples"),
+    (300, 512, 5, 3, 3, "samples"), (400, 1032, 3, 2, 2, "one direction"), (260, 640, 8, 2, 1, "one direction"), (300, 264, 4, 2, 2, "zero"),
+    (2048, 320, 3, 2, 2, "few samples"), (256, 736, 3, 2, 4, "indefinite"), (300, 296, 3, 2, 2, "infinite")])
+def test_search_screened(M, N, n, q, grid, kind):
+    """Layers of 256 rows or more are screened: a bound excludes candidates before they are evaluated.  The results are the bits of the
+    search of at most 255 rows at a time, which evaluates all: at the edges of tiles, chunks of candidates (48) and planes, with
+    rows that are constant, zero, tiny, huge or hold infinities and no numbers, and with Hessians that let the bound exclude nearly everything or
+    nothing."""
+    g = torch.Generator(device="cuda").manual_seed(7 * M + N + n)
+    W = torch.randn((M, N), device="cuda", generator=g) * 0.02
+    W *= 1.0 + 3.0 * (torch.rand((M, N), device="cuda", generator=g) < 0.01)
+    W[3], W[4], W[5] = 0.01, 0.0, W[5] * 1e-20
+    W[6] *= 1e15
+    W[7, 11], W[8, 5], W[9, N - 1] = float("inf"), float("nan"), -float("inf")
+    W[10, 1:] = W[10, :1]
+    W[M - 1, N // 2] = 3.0
+    T = N // 4 if kind == "few samples" else 2 * N
+    X = torch.randn((T, N), device="cuda", generator=g)
+    X += 0.5 * torch.randn((T, 8), device="cuda", generator=g) @ torch.randn((8, N), device="cuda", generator=g)
+    if kind == "loud":
+        X[:, ::37] *= 2.0 ** 10
+    H = 2.0 * (X.t().contiguous() @ X)
+    if kind == "one direction":  # all candidates close to each other compared with |H|
+        H = 100.0 * H.diagonal().mean() * torch.ones_like(H) + H
+    if kind == "zero":
+        H.zero_()
+    if kind == "infinite":
+        H[17, 200] = H[200, 17] = float("inf")
+    H = ((H + H.t()) * 0.5).contiguous()
+    if kind == "indefinite":  # not what the search is for; here the errors stay positive for nearly all rows
+        H.diagonal().sub_(0.3 * H.diagonal().mean())
+    whole = _search(W, H, n, q, grid)
+    for lo in range(0, M, 255):
+        part = _search(W[lo:lo + 255].clone(), H, n, q, grid)
+        for a, b, what in zip(whole, part, ("S", "qbias", "err", "labels")):
+            same = (a[lo:lo + 255] == b).reshape(len(b), -1).all(1)
+            assert same.all(), (kind, what, lo + torch.nonzero(~same).flatten()[:8])
+
+
 @pytest.mark.parametrize("M,N,n,q", [(70, 320, 3, 2), (40, 256, 4, 3), (9, 96, 3, 3)])
 def test_gptq_pass(M, N, n, q):
     W32, H32 = _layer(M, N, seed=200 + N + n)
