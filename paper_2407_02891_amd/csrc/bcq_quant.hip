@@ -211,102 +211,187 @@ __global__ void damped_copy_kernel(int N, const float *__restrict__ H, const flo
 // place, from the last row j upwards: with the pivot d = x[j][j] and f_i = x[i][j] / d,
 //     x[i][l] -= f_i x[j][l]   for i < j and every l but j,      x[i][j] = -f_i.
 // To the left of the pivot that is the Schur complement of D; the columns from j on are done with as parts of D and hold M,
-// unit upper triangular, the product of the row operations, for which M D M^T = diag(d): V = diag(d)^-1/2 M.  D is
-// symmetric, so x[i][j] is x[j][i] and the one thing a step has to hand round is row j: 128 values through LDS, one barrier.
-// One workgroup of 256 threads with the 128 x 128 block in registers, thread (ty, tx) owning the elements (ty + 16 a, tx +
-// 16 c).  What bounds it is that chain (write, barrier, read, reciprocal, 8 to 64 multiply-adds), so two rows j, j - 1 are
-// handed round at a time: every thread brings the second one up to date for itself, and the next two are written before the
-// multiply-adds of the other rows.  A column that becomes -f starts from 0 with a 1 in the row for it.  The same operations
-// in the same order as with one row: the results are the same bits.  A block takes 39 to 40 us; with one row
-// at a time 50, with the block and its inverse in LDS and the inverse one column per thread 245.
+// unit upper triangular, the product of the row operations, for which M D M^T = diag(d): V = diag(d)^-1/2 M.
+// The rows are taken 16 at a time, J = j0 .. j0 + 15, in the block's place in LDS:
+//   A   the elimination of D's 16 x 16 block by itself, which gives M_J and its pivots d: one wave, a row per lane, row j handed
+//       round by DPP operands;
+//   B   the 16 rows: X[J][:] becomes Y = M_J X[J][:], with M_J itself at J; and G = X[I][J] M_J^T diag(1 / d) for the rows I above
+//       (X[J][I]^T: of the symmetric Schur complement only the tiles on and below the diagonal are kept);
+//   C   the rows above: X[I][:] -= G Y, and X[I][J] = -G M_J.
+// B and C are 16 x 16 tiles of binary32 matrix instructions.  What bounds it is that chain of one workgroup, so the tile that A needs next
+// is C's first, and its wave goes on to A while the other three do the rest.  A block takes 24 us (A eight times
+// 1.0, B 0.6, reading and writing 5); with two rows handed round per barrier and the block in registers 39 to 40, with one row 50.
+constexpr int kDiagPitch = 148, kDiagG = 20;  // floats per row in LDS: a tile's elements in 16 x 4 lanes fall into different banks
+
+// Elimination of a symmetric 16 x 16 block from the last row upwards: lane i of each 16 holds row i.  On return x[l] with l > i
+// holds M[i][l] (unit upper triangular); this lane's pivot and its reciprocal.
+__device__ __forceinline__ void eliminate_16(float (&x)[16], int i, float *pivot, float *inverse)
+{
+    auto step = [&](auto row) PROD_INLINE {
+        constexpr int j = decltype(row)::value;
+        float d;
+        asm volatile("s_nop 1\n\tv_mov_b32_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "=v"(d) : "v"(x[j]), "n"(j));
+        float inv = __builtin_amdgcn_rcpf(d);
+        inv = fmaf(fmaf(-d, inv, 1.0f), inv, inv);
+        inv = d > 0.0f ? inv : __builtin_nanf("");  // not positive definite: no numbers from here on
+        const float nf = i < j ? -(x[j] * inv) : 0.0f;
+        if (i == j) { *pivot = d; *inverse = inv; }
+        asm volatile("" ::"v"(nf));
+#pragma unroll
+        for (int l = 15; l >= 0; --l)
+            if (l != j)
+                asm volatile("v_fmac_f32_dpp %0, %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "+v"(x[l]) : "v"(nf), "n"(j));
+        x[j] = nf;  // (0 in the rows from j on)
+    };
+    step(std::integral_constant<int, 15>{}); step(std::integral_constant<int, 14>{}); step(std::integral_constant<int, 13>{});
+    step(std::integral_constant<int, 12>{}); step(std::integral_constant<int, 11>{}); step(std::integral_constant<int, 10>{});
+    step(std::integral_constant<int, 9>{}); step(std::integral_constant<int, 8>{}); step(std::integral_constant<int, 7>{});
+    step(std::integral_constant<int, 6>{}); step(std::integral_constant<int, 5>{}); step(std::integral_constant<int, 4>{});
+    step(std::integral_constant<int, 3>{}); step(std::integral_constant<int, 2>{}); step(std::integral_constant<int, 1>{});
+    step(std::integral_constant<int, 0>{});
+}
+
 __global__ __launch_bounds__(256) void factor_diag_kernel(int N, int r0, int b, const float *__restrict__ Hw, const float *__restrict__ H,
                                                           const float *__restrict__ lambda, float *__restrict__ U, float *__restrict__ Ut)
 {
-    __shared__ __attribute__((aligned(16))) float rows[2][2][16][8];  // [buffer][j odd, even]: element l at [l % 16][l / 16]
-    __shared__ float pivot[kFactorBlock];
-    __shared__ float V[kFactorBlock][kFactorBlock + 1];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    float x[8][8];
+    __shared__ __attribute__((aligned(16))) float X[kFactorBlock][kDiagPitch];
+    __shared__ float G[kFactorBlock][kDiagG];  // negated
+    __shared__ __attribute__((aligned(16))) float pivot[kFactorBlock], inverse[kFactorBlock];
+    const int tid = threadIdx.x, lane = tid & 63, lo = lane & 15, hi = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // this thread's four columns l .. l + 3 (b and N are multiples of 4) and rows first + 8 k, in and out
+    const int l = 4 * (tid & 31), first = tid >> 5, l_in = l < b ? l : 0;
+    prod_f32x4 v[16], scale;
 #pragma unroll
-    for (int a = 0; a < 8; ++a)
+    for (int k = 0; k < 16; ++k) {
+        const int i = first + 8 * k < b ? first + 8 * k : 0;
+        v[k] = *reinterpret_cast<const prod_f32x4 *>(Hw + (size_t)(r0 + i) * N + r0 + l_in);
+    }
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const int i = ty + 16 * a, l = tx + 16 * c;  // beyond b: the identity, which changes nothing
-            x[a][c] = i < b && l < b ? Hw[(size_t)(r0 + i) * N + r0 + l] : (i == l ? 1.0f : 0.0f);
-        }
-    auto hand_round = [&](const float (&v)[8], int jj) {  // rows jj and jj - 1 (jj odd) of a group of 16
-        if (ty >> 1 == jj >> 1) {
-            float (&to)[16][8] = rows[(jj >> 1) & 1][~ty & 1];
-            *reinterpret_cast<prod_f32x4 *>(&to[tx][0]) = prod_f32x4{v[0], v[1], v[2], v[3]};
-            *reinterpret_cast<prod_f32x4 *>(&to[tx][4]) = prod_f32x4{v[4], v[5], v[6], v[7]};
-        }
-    };
-    auto reciprocal = [](float d) { return d > 0.0f ? 1.0f / d : __builtin_nanf(""); };  // not positive definite: NaNs from here on
-    auto eliminate = [&](auto group) {  // the rows j = 16 g + 15 .. 16 g
-        constexpr int g = decltype(group)::value;
-#pragma unroll 1
-        for (int jj = 15; jj > 0; jj -= 2) {
-            const float (&p)[16][8] = rows[(jj >> 1) & 1][0], (&q)[16][8] = rows[(jj >> 1) & 1][1];
-            __syncthreads();
-            float pl[8], ql[8], pi[8], qi[8];
+    for (int e = 0; e < 4; ++e) scale[e] = H[(size_t)(r0 + l_in + e) * (N + 1)];
+    const float damping = *lambda;
 #pragma unroll
-            for (int k = 0; k < 8; k += 4) {
-                const prod_f32x4 v0 = *reinterpret_cast<const prod_f32x4 *>(&p[tx][k]), v1 = *reinterpret_cast<const prod_f32x4 *>(&q[tx][k]);
-                const prod_f32x4 v2 = *reinterpret_cast<const prod_f32x4 *>(&p[ty][k]), v3 = *reinterpret_cast<const prod_f32x4 *>(&q[ty][k]);
+    for (int k = 0; k < 16; ++k) {
+        const int i = first + 8 * k;
+        if (i >= b || l >= b)  // beyond b: the identity, which changes nothing
+            v[k] = prod_f32x4{i == l ? 1.0f : 0.0f, i == l + 1 ? 1.0f : 0.0f, i == l + 2 ? 1.0f : 0.0f, i == l + 3 ? 1.0f : 0.0f};
+        *reinterpret_cast<prod_f32x4 *>(&X[i][l]) = v[k];
+    }
 #pragma unroll
-                for (int e = 0; e < 4; ++e) { pl[k + e] = v0[e]; ql[k + e] = v1[e]; pi[k + e] = v2[e]; qi[k + e] = v3[e]; }
-            }
-            const float d1 = p[jj][g], cross = p[jj - 1][g];
-            const float inv1 = reciprocal(d1), f = cross * inv1;
-            const float d2 = fmaf(-f, cross, q[jj - 1][g]), inv2 = reciprocal(d2);
-            if (tid == 0) { pivot[16 * g + jj] = d1; pivot[16 * g + jj - 1] = d2; }
-            const bool at1 = tx == jj, at2 = tx == jj - 1;  // (in column group g)
-            pl[g] = at1 ? 1.0f : at2 ? 0.0f : pl[g];
-            ql[g] = at1 ? 0.0f : ql[g];
-#pragma unroll
-            for (int c = 0; c < 8; ++c) ql[c] = fmaf(-f, pl[c], ql[c]);
-            ql[g] = at2 ? 1.0f : ql[g];
-            auto update = [&](int a) {
-                float f1 = pi[a] * inv1, f2 = fmaf(-f, pi[a], qi[a]) * inv2;
-                if (a == g) {
-                    f1 = ty < jj ? f1 : 0.0f;  // i < j
-                    f2 = ty < jj - 1 ? f2 : 0.0f;
-                }
-                x[a][g] = at1 || at2 ? 0.0f : x[a][g];  // (in the rows from j on nobody reads it any more)
-#pragma unroll
-                for (int c = 0; c < 8; ++c) x[a][c] = fmaf(-f2, ql[c], fmaf(-f1, pl[c], x[a][c]));
-            };
-            update(g);
-            if (jj > 1) hand_round(x[g], jj - 2);
-#pragma unroll
-            for (int a = g - 1; a >= 0; --a) update(a);
-        }
-        if (g > 0) hand_round(x[g > 0 ? g - 1 : 0], 15);
-    };
-    hand_round(x[7], 15);
-    eliminate(std::integral_constant<int, 7>{}); eliminate(std::integral_constant<int, 6>{});
-    eliminate(std::integral_constant<int, 5>{}); eliminate(std::integral_constant<int, 4>{});
-    eliminate(std::integral_constant<int, 3>{}); eliminate(std::integral_constant<int, 2>{});
-    eliminate(std::integral_constant<int, 1>{}); eliminate(std::integral_constant<int, 0>{});
+    for (int e = 0; e < 4; ++e) scale[e] = ldexpf(1.0f, -channel_shift(scale[e], damping));
     __syncthreads();
+    auto inner = [&](int J) PROD_INLINE {  // A: M_J in the place of the block, with its zeros and ones
+        float x[16], d = 1.0f, inv = 1.0f;
 #pragma unroll
-    for (int a = 0; a < 8; ++a) {
-        const int i = ty + 16 * a;
-        const float rs = 1.0f / sqrtf(pivot[i]);
+        for (int l = 0; l < 16; l += 4) {
+            const prod_f32x4 v = *reinterpret_cast<const prod_f32x4 *>(&X[16 * J + lo][16 * J + l]);
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const int l = tx + 16 * c;
-            V[i][l] = l > i ? x[a][c] * rs : (l == i ? rs : 0.0f);
+            for (int e = 0; e < 4; ++e) x[l + e] = v[e];
+        }
+        eliminate_16(x, lo, &d, &inv);
+        if (hi == 0) {
+            pivot[16 * J + lo] = d;
+            inverse[16 * J + lo] = inv;
+#pragma unroll
+            for (int l = 0; l < 16; ++l) X[16 * J + lo][16 * J + l] = l > lo ? x[l] : (l == lo ? 1.0f : 0.0f);
+        }
+    };
+    // C for one tile
+    auto update = [&](int J, int I, int L) PROD_INLINE {
+        prod_f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        if (L != J) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] = X[16 * I + 4 * hi + i][16 * L + lo];
+        }
+        float g[4], y[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            g[k] = G[16 * I + lo][4 * k + hi];
+            y[k] = X[16 * J + 4 * k + hi][16 * L + lo];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(g[k], y[k], acc, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) X[16 * I + 4 * hi + i][16 * L + lo] = acc[i];
+    };
+    if (wave == 0) inner(7);
+    __syncthreads();
+    for (int J = 7; J >= 0; --J) {
+        // B, a tile of columns L at a time: the elements of X[J][L] are the operand of both products
+        {
+            float m[4], w[4];
+            const float inv = inverse[16 * J + lo];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                m[k] = X[16 * J + lo][16 * J + 4 * k + hi];
+                w[k] = -(m[k] * inv);
+            }
+            float x[2][4];  // (of the wave's two tiles; M_J itself is left alone)
+            prod_f32x4 y[2], g[2];
+#pragma unroll
+            for (int n = 0; n < 2; ++n) {
+                y[n] = g[n] = prod_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int k = 0; k < 4; ++k) x[n][k] = X[16 * J + 4 * k + hi][16 * (wave + 4 * n) + lo];
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int n = 0; n < 2; ++n) {
+                    y[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(m[k], x[n][k], y[n], 0, 0, 0);
+                    g[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[n][k], w[k], g[n], 0, 0, 0);
+                }
+#pragma unroll
+            for (int n = 0; n < 2; ++n) {
+                const int L = wave + 4 * n;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (L != J) X[16 * J + 4 * hi + i][16 * L + lo] = y[n][i];
+                    if (L < J) G[16 * L + 4 * hi + i][lo] = g[n][i];
+                }
+            }
+        }
+        __syncthreads();
+        if (J == 0) break;
+        // C, and A of the next 16 rows: the tiles (I, L), I < J, with L <= I (the Schur complement) or L >= J (M); tile (J - 1, J - 1)
+        // is the first wave's
+        if (wave == 0) {
+            update(J, J - 1, J - 1);
+            inner(J - 1);
+        } else {
+            int skip = wave - 1;
+            for (int I = J - 1; I >= 0; --I) {
+                const int below = I == J - 1 ? I : I + 1, count = below + 8 - J;
+                for (; skip < count; skip += 3) update(J, I, skip < below ? skip : J + skip - below);
+                skip -= count;
+            }
+        }
+        __syncthreads();
+    }
+    if (tid < kFactorBlock) inverse[tid] = 1.0f / sqrtf(pivot[tid]);
+    __syncthreads();
+#pragma unroll 4
+    for (int k = 0; k < 16; ++k) {
+        const int i = first + 8 * k;
+        const float root = inverse[i];
+        prod_f32x4 u = *reinterpret_cast<const prod_f32x4 *>(&X[i][l]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) u[e] = l + e >= i ? u[e] * root * scale[e] : 0.0f;
+        if (i < b && l < b) *reinterpret_cast<prod_f32x4 *>(U + (size_t)(r0 + i) * N + r0 + l) = u;
+    }
+    // Ut's rows i .. i + 3 from row c of X
+    const int c = tid & (kFactorBlock - 1), half = 64 * (tid >> 7);
+    const float root = inverse[c];
+    if (c < b) {
+#pragma unroll 4
+        for (int i = half; i < half + 64; i += 4) {
+            const prod_f32x4 x = *reinterpret_cast<const prod_f32x4 *>(&X[c][i]);
+            if (i < b) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) Ut[(size_t)(r0 + i + e) * N + r0 + c] = i + e >= c ? x[e] * root : 0.0f;
+            }
         }
     }
-    __syncthreads();
-    const int l = tid & (kFactorBlock - 1);
-    const float scale = l < b ? ldexpf(1.0f, -channel_shift(H[(size_t)(r0 + l) * N + r0 + l], *lambda)) : 1.0f;
-    for (int i = tid / kFactorBlock; i < b; i += 256 / kFactorBlock)
-        if (l < b) {
-            U[(size_t)(r0 + i) * N + r0 + l] = V[i][l] * scale;
-            Ut[(size_t)(r0 + i) * N + r0 + l] = V[l][i];
-        }
 }
 
 // dst[c][r] = src[r][c], without the scale of channel c, for size x size blocks of a matrix of pitch N, block z of them z * stride
@@ -1226,7 +1311,7 @@ __global__ __launch_bounds__(256, 2) void gptq_panel_kernel(int M, int Mp, int N
                 int my_q = (int)wqf;
                 float last = a;
                 // (a deviation without end has made the weights decided before it no numbers)
-                if (__builtin_expect(__any(!(fabsf(t - (r - kRound)) < sure) | !(fabsf(a) < INFINITY) | ((odd >> i) & 1)), 0)) {
+                if (__builtin_expect(__any(!(fabsf(t - (r - kRound)) < sure) || !(fabsf(a) < INFINITY) || ((odd >> i) & 1)), 0)) {
 #pragma unroll
                     for (int k = 0; k < kSlots; ++k) v[k] = w[k];
 #pragma unroll 1
