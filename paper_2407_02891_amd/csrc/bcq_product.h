@@ -56,9 +56,6 @@
 // large library product of that type reaches 1230 on this card), 2 X^T X over 4 x 2048 samples of 7168 channels 7.17 / 1.80 ms.
 // An octet of column c sits at position c ^ ((c >> 4) & 1): the 16 lanes that a 16-byte LDS read serves together then
 // touch 16 different 16-byte columns.
-//
-// Tiles are taken in blocks of 4 x 4 per XCD (workgroup numbers go round the eight XCDs), so that the workgroups that
-// share an L2 at a time share their operand panels.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -103,52 +100,69 @@ struct ProductArgs {
     const int *rows;  // kQuadFormSplit: number of rows that are there, in device memory, or null: R
 };
 
-// Number of workgroups, and the tile of one.  Blocks of 4 x 4 tiles are numbered row by row (only those on and above the
-// diagonal for kAddTwiceSymmetric, on and below it for kSubtractLower; column by column from the last one for the quadratic
-// forms, whose last columns have the longest k range).
-// Each XCD takes a contiguous run of blocks where all tiles cost the same, else every eighth block.
+// Number of workgroups, and the tile of one.  Tiles are taken block by block of 4 x 4 so that the workgroups that share an L2 at a
+// time share their operand panels (workgroup numbers go round the eight XCDs).
+// Where all tiles cost the same (the symmetric sum, on and above the diagonal, and the subtractions) they are numbered block row by
+// block row, only those that exist, and each XCD takes an eighth of the numbers: by whole blocks, as before, the XCD with the most
+// tiles had 9 % more than its share at 7168 channels.  Otherwise each XCD takes every eighth block, for the quadratic
+// forms column by column from the last one, whose columns have the longest k range.
 template <int MODE>
-static inline int product_blocks(int R, int C)
+constexpr bool kProdEven = MODE == kAddTwiceSymmetric || MODE == kSubtract || MODE == kSubtractLower;
+
+template <int MODE>
+static inline int product_groups(int R, int C)
 {
-    const int br = (R + kProdTile * kProdBlock - 1) / (kProdTile * kProdBlock);
-    const int bc = (C + kProdTile * kProdBlock - 1) / (kProdTile * kProdBlock);
-    return MODE == kAddTwiceSymmetric || MODE == kSubtractLower ? br * (br + 1) / 2 : br * bc;
+    const int ntr = (R + kProdTile - 1) / kProdTile, ntc = (C + kProdTile - 1) / kProdTile;
+    const long long tiles = MODE == kSubtract ? (long long)ntr * ntc : (long long)ntr * (ntr + 1) / 2;
+    const int br = (ntr + kProdBlock - 1) / kProdBlock, bc = (ntc + kProdBlock - 1) / kProdBlock;
+    return kProdEven<MODE> ? (int)((tiles + 7) / 8 * 8) : (br * bc + 7) / 8 * 8 * kProdBlock * kProdBlock;
 }
 
 template <int MODE>
 __device__ __forceinline__ bool product_tile(int wg, int wgs, int R, int C, int *tile_row, int *tile_col)
 {
     const int ntr = (R + kProdTile - 1) / kProdTile, ntc = (C + kProdTile - 1) / kProdTile;
-    const int br = (ntr + kProdBlock - 1) / kProdBlock, bc = (ntc + kProdBlock - 1) / kProdBlock;
-    const int xcd = wg & 7, j = wg >> 3, t = j & (kProdBlock * kProdBlock - 1), per_xcd = wgs / (8 * kProdBlock * kProdBlock);
-    const bool uneven = MODE == kQuadForm || MODE == kQuadFormSplit || MODE == kStore || MODE == kStoreNegated;
-    int s = uneven ? (j / (kProdBlock * kProdBlock)) * 8 + xcd : xcd * per_xcd + j / (kProdBlock * kProdBlock);
-    int b_row, b_col;
-    if (MODE == kAddTwiceSymmetric || MODE == kSubtractLower) {
-        if (s >= br * (br + 1) / 2) return false;
-        b_row = 0;
-        while (s >= br - b_row) s -= br - b_row++;
-        b_col = b_row + s;
-        if (MODE == kSubtractLower) {
-            const int swap = b_row;
-            b_row = b_col;
-            b_col = swap;
+    const int xcd = wg & 7, j = wg >> 3;
+    if constexpr (kProdEven<MODE>) {
+        constexpr bool kTriangle = MODE != kSubtract;
+        int t = xcd * (wgs >> 3) + j, b_row = 0, rows, first;
+        for (;; ++b_row) {  // the block row, its first column and its number of tiles
+            if (b_row * kProdBlock >= ntr) return false;
+            rows = ntr - b_row * kProdBlock < kProdBlock ? ntr - b_row * kProdBlock : kProdBlock;
+            first = kTriangle ? b_row * kProdBlock : 0;
+            const int count = rows * (ntc - first) - (kTriangle ? rows * (rows - 1) / 2 : 0);
+            if (t < count) break;
+            t -= count;
         }
-    } else {
-        if (s >= br * bc) return false;
-        if (MODE == kQuadForm || MODE == kQuadFormSplit) {
-            b_col = s / br;
-            b_row = s - b_col * br;
-            b_col = bc - 1 - b_col;
+        int r, c;
+        if (kTriangle && t < rows * (rows + 1) / 2) {  // its block on the diagonal
+            for (r = 0; t >= rows - r; ++r) t -= rows - r;
+            c = first + r + t;
         } else {
-            b_row = s / bc;
-            b_col = s - b_row * bc;
+            if (kTriangle) {
+                t -= rows * (rows + 1) / 2;
+                first += rows;
+            }
+            const int block = t / (rows * kProdBlock), width = ntc - first - block * kProdBlock;
+            t -= block * rows * kProdBlock;
+            const int cols = width < kProdBlock ? width : kProdBlock;
+            r = t / cols;
+            c = first + block * kProdBlock + t % cols;
         }
+        r += b_row * kProdBlock;
+        *tile_row = MODE == kSubtractLower ? c : r;
+        *tile_col = MODE == kSubtractLower ? r : c;
+        return true;
+    } else {
+        const int br = (ntr + kProdBlock - 1) / kProdBlock, bc = (ntc + kProdBlock - 1) / kProdBlock;
+        const int t = j & (kProdBlock * kProdBlock - 1), s = (j / (kProdBlock * kProdBlock)) * 8 + xcd;
+        if (s >= br * bc) return false;
+        const bool by_column = MODE == kQuadForm || MODE == kQuadFormSplit;
+        const int b_row = by_column ? s % br : s / bc, b_col = by_column ? bc - 1 - s / br : s % bc;
+        *tile_row = b_row * kProdBlock + t / kProdBlock;
+        *tile_col = b_col * kProdBlock + t % kProdBlock;
+        return *tile_row < ntr && *tile_col < ntc;
     }
-    *tile_row = b_row * kProdBlock + t / kProdBlock;
-    *tile_col = b_col * kProdBlock + t % kProdBlock;
-    return *tile_row < ntr && *tile_col < ntc && (MODE != kAddTwiceSymmetric || *tile_col >= *tile_row) &&
-           (MODE != kSubtractLower || *tile_col <= *tile_row);
 }
 
 // Exponent of the power of two that puts a magnitude (as float bits) at 2^target .. 2^(target + 1), kept to those a
@@ -595,8 +609,8 @@ static void launch_product(hipStream_t stream, const float *A, int lda, int R, c
                            int ldo, const float *least = nullptr, int least_first = 0)
 {
     ProductArgs p = {A, B, nullptr, out, lda, R, ldb, C, K, ldo, 0, nullptr, 0, nullptr, nullptr, least, least_first, 0, C, 0, 0, nullptr};
-    const int blocks = (product_blocks<MODE>(R, C) + 7) / 8 * 8;
-    hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)(blocks * kProdBlock * kProdBlock)), dim3(256), 0, stream, p);
+    const int groups = product_groups<MODE>(R, C);
+    hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)groups), dim3(256), 0, stream, p);
 }
 
 // `count` products kStore (with B[k][c] = 0 for k > c) or kStoreNegated of size x size x size, see ProductArgs.
@@ -606,8 +620,8 @@ static void launch_products(hipStream_t stream, int count, size_t stride, int co
 {
     ProductArgs p = {A, B, nullptr, out, pitch, size, pitch, size, size, pitch, MODE == kStore ? 1 : 0, nullptr, 0, nullptr, nullptr, nullptr, 0,
                      stride, columns_end, 2 * size, MODE == kStore ? 1 : 0, nullptr};
-    const int blocks = (product_blocks<MODE>(size, size) + 7) / 8 * 8;
-    hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)(blocks * kProdBlock * kProdBlock), (unsigned)count), dim3(256), 0, stream, p);
+    const int groups = product_groups<MODE>(size, size);
+    hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)groups, (unsigned)count), dim3(256), 0, stream, p);
 }
 
 // The quadratic forms of the rows of D: kQuadForm splits them as it reads them, for kQuadFormSplit they come as `split` too
@@ -617,8 +631,8 @@ static void launch_quad_form(hipStream_t stream, const uint16_t *split, size_t p
                              int ldb, const float *diag_max, int C, float *out, int ldo, const int *rows = nullptr)
 {
     ProductArgs p = {D, B, D, out, ldo, R, ldb, C, C, ldo, 0, split, plane, shift, diag_max, nullptr, 0, 0, C, 0, 0, rows};
-    const int blocks = (product_blocks<MODE>(R, C) + 7) / 8 * 8;
-    hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)(blocks * kProdBlock * kProdBlock)), dim3(256), 0, stream, p);
+    const int groups = product_groups<MODE>(R, C);
+    hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)groups), dim3(256), 0, stream, p);
 }
 
 }  // namespace bcq
