@@ -173,20 +173,27 @@ __device__ __forceinline__ int product_shift(unsigned magnitude, int target)
     return e < -126 ? -126 : (e > 126 ? 126 : e);
 }
 
+// LDS of a workgroup
+typedef uint8_t ProductStage[2][4][kProdTile * 16];  // [hi, lo][octet][column]
+typedef unsigned ProductLargest[2][kProdTile];
+typedef int ProductShift[2][kProdTile];
+struct ProductShared {
+    ProductStage stage_a0, stage_a1, stage_b[2];
+    ProductLargest largest;
+    unsigned largest_of_tile[2];
+    ProductShift shift;
+};
+
+// Tile of workgroup wg of wgs.  stage_a0 .. stage_b: the two stages of both operands; largest: largest magnitude per row of A's
+// tile, column of B's tile (float bits); shift: exponents of the scales.
 template <int MODE>
-__global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
+__device__ __forceinline__ void product_tile_of(ProductArgs p, int wg, int wgs, ProductStage &stage_a0, ProductStage &stage_a1,
+                                                ProductStage (&stage_b)[2], ProductLargest &largest, unsigned (&largest_of_tile)[2],
+                                                ProductShift &shift)
 {
     constexpr bool kQuad = MODE == kQuadForm || MODE == kQuadFormSplit, kSplitA = MODE == kQuadFormSplit;
     constexpr int kFirst = kSplitA ? 1 : 0;  // first operand that comes in binary32
     constexpr int kGuess = kQuad ? 1 : 0;    // first operand whose scales are guessed
-    // the two stages of both operands, [hi, lo][octet][column]; A's are two objects so that the compiler can tell the copies
-    // into one (kQuadFormSplit) from the reads of the other
-    __shared__ __attribute__((aligned(16))) uint8_t stage_a0[2][4][kProdTile * 16];
-    __shared__ __attribute__((aligned(16))) uint8_t stage_a1[2][4][kProdTile * 16];
-    __shared__ __attribute__((aligned(16))) uint8_t stage_b[2][2][4][kProdTile * 16];
-    __shared__ unsigned largest[2][kProdTile];  // largest magnitude per row of A's tile, column of B's tile (float bits)
-    __shared__ unsigned largest_of_tile[2];
-    __shared__ int shift[2][kProdTile];  // exponents of the scales
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lo = lane & 15, hi = lane >> 4, wr = wave >> 1, wc = wave & 1;
@@ -199,7 +206,7 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
         if (p.k_is_columns) p.K = p.C;
     }
     int tile_row, tile_col;
-    if (!product_tile<MODE>(blockIdx.x, gridDim.x, p.R, p.C, &tile_row, &tile_col)) return;
+    if (!product_tile<MODE>(wg, wgs, p.R, p.C, &tile_row, &tile_col)) return;
     const int r0 = tile_row * kProdTile, c0 = tile_col * kProdTile;
     if (kSplitA && p.rows && r0 >= *p.rows) return;
 
@@ -605,12 +612,31 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
 }
 
 template <int MODE>
+__global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
+{
+    // (A's stages are two objects so that the compiler can tell the copies into one, of kQuadFormSplit, from the reads of the other)
+    __shared__ __attribute__((aligned(16))) ProductStage stage_a0;
+    __shared__ __attribute__((aligned(16))) ProductStage stage_a1;
+    __shared__ __attribute__((aligned(16))) ProductStage stage_b[2];
+    __shared__ ProductLargest largest;
+    __shared__ unsigned largest_of_tile[2];
+    __shared__ ProductShift shift;
+    product_tile_of<MODE>(p, blockIdx.x, gridDim.x, stage_a0, stage_a1, stage_b, largest, largest_of_tile, shift);
+}
+
+template <int MODE>
+static ProductArgs product_args(const float *A, int lda, int R, const float *B, int ldb, int C, int K, float *out, int ldo,
+                                const float *least = nullptr, int least_first = 0)
+{
+    return {A, B, nullptr, out, lda, R, ldb, C, K, ldo, 0, nullptr, 0, nullptr, nullptr, least, least_first, 0, C, 0, 0, nullptr};
+}
+
+template <int MODE>
 static void launch_product(hipStream_t stream, const float *A, int lda, int R, const float *B, int ldb, int C, int K, float *out,
                            int ldo, const float *least = nullptr, int least_first = 0)
 {
-    ProductArgs p = {A, B, nullptr, out, lda, R, ldb, C, K, ldo, 0, nullptr, 0, nullptr, nullptr, least, least_first, 0, C, 0, 0, nullptr};
-    const int groups = product_groups<MODE>(R, C);
-    hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)groups), dim3(256), 0, stream, p);
+    const ProductArgs p = product_args<MODE>(A, lda, R, B, ldb, C, K, out, ldo, least, least_first);
+    hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)product_groups<MODE>(R, C)), dim3(256), 0, stream, p);
 }
 
 // `count` products kStore (with B[k][c] = 0 for k > c) or kStoreNegated of size x size x size, see ProductArgs.

@@ -1053,19 +1053,27 @@ __device__ __forceinline__ bool ordinary(float d) { return fabsf(d) >= 0x1p-40f 
 enum GptqTable { kEight = 0, kSixteen = 1, kBytes = 2 };  // integers a row can hold: up to 8, up to 16, a byte each in LDS
 
 template <int TABLE>
-__global__ __launch_bounds__(256, 2) void gptq_panel_kernel(int M, int Mp, int N, int n_bits, int p0, int p1,
-                                                            const float *__restrict__ Wt, const float *__restrict__ U,
-                                                            const float *__restrict__ S, const float *__restrict__ qbias,
-                                                            const unsigned long long *__restrict__ nibbles,
-                                                            const uint8_t *__restrict__ bytes, uint8_t *__restrict__ w_int,
-                                                            float *Err, float *__restrict__ least)
+struct GptqShared {
+    float Us[kGptqUs + 32];
+    float Ws[kGptqRows][kGptqBlock + 4];
+    float diag[kGptqBlock];
+    uint8_t Qs[kGptqRows][kGptqBlock + 4];
+    uint8_t table[TABLE == kBytes ? kGptqRows : 1][256];
+};
+
+template <int TABLE>
+__device__ __forceinline__ void gptq_panel(GptqShared<TABLE> &shared, int M, int Mp, int N, int n_bits, int p0, int p1,
+                                           const float *__restrict__ Wt, const float *__restrict__ U,
+                                           const float *__restrict__ S, const float *__restrict__ qbias,
+                                           const unsigned long long *__restrict__ nibbles,
+                                           const uint8_t *__restrict__ bytes, uint8_t *__restrict__ w_int,
+                                           float *Err, float *__restrict__ least)
 {
-    constexpr int kPitch = kGptqBlock + 4;
-    __shared__ __attribute__((aligned(16))) float Us[kGptqUs + 32];
-    __shared__ __attribute__((aligned(16))) float Ws[kGptqRows][kPitch];
-    __shared__ float diag[kGptqBlock];
-    __shared__ __attribute__((aligned(4))) uint8_t Qs[kGptqRows][kGptqBlock + 4];
-    __shared__ uint8_t table[TABLE == kBytes ? kGptqRows : 1][256];
+    auto &Us = shared.Us;
+    auto &Ws = shared.Ws;
+    auto &diag = shared.diag;
+    auto &Qs = shared.Qs;
+    auto &table = shared.table;
     const int tid = threadIdx.x, l = tid & 7, row = tid >> 3, m0 = blockIdx.x * kGptqRows, m = m0 + row;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool live = m < M, aligned = (reinterpret_cast<uintptr_t>(w_int) & 3) == 0;
@@ -1383,31 +1391,71 @@ __global__ __launch_bounds__(256, 2) void gptq_panel_kernel(int M, int Mp, int N
     }
 }
 
+// The first `rows_groups` workgroups (a multiple of 8: workgroup numbers go round the XCDs) take the panel [p0, p1), 32 rows each; the
+// others the tiles of `rest`, the update of the columns beyond the panel by the errors of the panel before.  A panel is a chain that
+// leaves most of the chip's instruction slots and power unused, the update is what uses them.  The panel's waves go
+// first where both want to issue.
+template <int TABLE>
+__global__ __launch_bounds__(256, 2) void gptq_panel_kernel(int M, int Mp, int N, int n_bits, int p0, int p1, int row_groups,
+                                                            const float *__restrict__ Wt, const float *__restrict__ U,
+                                                            const float *__restrict__ S, const float *__restrict__ qbias,
+                                                            const unsigned long long *__restrict__ nibbles,
+                                                            const uint8_t *__restrict__ bytes, uint8_t *__restrict__ w_int,
+                                                            float *Err, float *__restrict__ least, ProductArgs rest)
+{
+    constexpr size_t kPanel = sizeof(GptqShared<TABLE>), kProduct = sizeof(ProductShared);
+    __shared__ __attribute__((aligned(16))) uint8_t shared[kPanel > kProduct ? kPanel : kProduct];
+    if ((int)blockIdx.x < row_groups) {
+        if ((int)blockIdx.x * kGptqRows >= Mp) return;
+        __builtin_amdgcn_s_setprio(3);
+        gptq_panel<TABLE>(*reinterpret_cast<GptqShared<TABLE> *>(shared), M, Mp, N, n_bits, p0, p1, Wt, U, S, qbias, nibbles, bytes, w_int,
+                          Err, least);
+    } else {
+        ProductShared &s = *reinterpret_cast<ProductShared *>(shared);
+        product_tile_of<kSubtract>(rest, blockIdx.x - row_groups, gridDim.x - row_groups, s.stage_a0, s.stage_a1, s.stage_b, s.largest,
+                                   s.largest_of_tile, s.shift);
+    }
+}
+
 // Columns beyond a panel of four blocks are brought up to date once per panel (K = 512): every pass over the remaining weights
 // reads and writes them all, which at one pass per block was most of its time (5.7 ms of a 7168 x 7168 layer, now 1.7).  The panel's own
 // columns are its kernel's: with a launch per block and a product for the rest of the panel after each, 38 us a block, now 22 (a panel of
-// 7168 rows, four bits: updates 25 us, chains 42, staging, errors and integers 20).  The errors of a panel are kept in Dt,
-// which the pass does not use otherwise.  Whole pass 3.78 -> 3.04 ms.
+// 7168 rows, four bits: updates 25 us, chains 42, staging, errors and integers 20).  Only the next panel's columns are updated before it
+// starts (33 us); the update of those beyond runs beside it, in the same launch: 3.05 -> 2.67 ms, 3.78 with none of this.  So the errors
+// of two panels are kept, by turns, in Dt, which the pass does not use otherwise.
 static hipError_t gptq_rows(int M, int N, int n_bits, int q, const float *W, const float *U, const float *S, const float *qbias,
                             const int8_t *labels, uint8_t *w_int, void *workspace, hipStream_t stream)
 {
     const QuantWorkspace w = carve(workspace, M, N);
     auto *nibbles = reinterpret_cast<unsigned long long *>(w.part);  // two of the (ceil(N / 128) + 3) Mp floats from here
     auto *bytes = reinterpret_cast<uint8_t *>(w.small);              // 256 of the 512 bytes per row
-    float *const err = w.Dt;
-    float *const least = w.small + 64 * (size_t)w.Mp;                // 8 floats: smallest diagonals of the blocks of a panel
+    float *const leasts = w.small + 64 * (size_t)w.Mp;               // 2 x 8 floats: smallest diagonals of the blocks of two panels
     hipLaunchKernelGGL(transpose_kernel, dim3((N + 31) / 32, (w.Mp + 31) / 32), dim3(32, 8), 0, stream, M, w.Mp, N, W,
                        w.Wt);
     hipLaunchKernelGGL(gptq_tables_kernel, dim3((M + 63) / 64), dim3(64), 0, stream, M, n_bits, q, labels, nibbles, bytes);
     const auto panel = n_bits <= 3 ? gptq_panel_kernel<kEight> : n_bits == 4 ? gptq_panel_kernel<kSixteen> : gptq_panel_kernel<kBytes>;
-    for (int p0 = 0; p0 < N; p0 += kGptqPanel) {
+    const int row_groups = ((w.Mp + kGptqRows - 1) / kGptqRows + 7) / 8 * 8;
+    for (int p0 = 0, turn = 0; p0 < N; p0 += kGptqPanel, turn ^= 1) {
         const int p1 = p0 + kGptqPanel < N ? p0 + kGptqPanel : N;
-        hipLaunchKernelGGL(panel, dim3((w.Mp + kGptqRows - 1) / kGptqRows), dim3(256), 0, stream, M, w.Mp, N, n_bits, p0, p1, w.Wt, U, S,
-                           qbias, nibbles, bytes, w_int, err, least);
-        // Wt[k][m] -= sum_j U[j][k] Err[j][m] for the columns k beyond the panel and its errors j
-        if (p1 < N)
-            launch_product<kSubtract>(stream, U + (size_t)p0 * N + p1, N, N - p1, err, w.Mp, w.Mp, p1 - p0, w.Wt + (size_t)p1 * w.Mp,
-                                      w.Mp, least, 0);
+        float *const err = w.Dt + (size_t)(turn * kGptqPanel) * w.Mp, *const last = w.Dt + (size_t)((turn ^ 1) * kGptqPanel) * w.Mp;
+        float *const least = leasts + 8 * turn, *const last_least = leasts + 8 * (turn ^ 1);
+        // Wt[k][m] -= sum_j U[j][k] Err[j][m] for the errors j of the panel before and the columns k of [from, to)
+        auto update = [&](int from, int to) {
+            return product_args<kSubtract>(U + (size_t)(p0 - kGptqPanel) * N + from, N, to - from, last, w.Mp, w.Mp, kGptqPanel,
+                                           w.Wt + (size_t)from * w.Mp, w.Mp, last_least, 0);
+        };
+        ProductArgs rest = {};
+        int tiles = 0;
+        if (p0 > 0) {
+            hipLaunchKernelGGL(product_kernel<kSubtract>, dim3((unsigned)product_groups<kSubtract>(p1 - p0, w.Mp)), dim3(256), 0, stream,
+                               update(p0, p1));
+            if (p1 < N) {
+                rest = update(p1, N);
+                tiles = product_groups<kSubtract>(N - p1, w.Mp);
+            }
+        }
+        hipLaunchKernelGGL(panel, dim3((unsigned)(row_groups + tiles)), dim3(256), 0, stream, M, w.Mp, N, n_bits, p0, p1, row_groups, w.Wt, U,
+                           S, qbias, nibbles, bytes, w_int, err, least, rest);
     }
     return hipGetLastError();
 }
