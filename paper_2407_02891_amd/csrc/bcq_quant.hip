@@ -1423,6 +1423,11 @@ __global__ __launch_bounds__(256, 2) void gptq_panel_kernel(int M, int Mp, int N
 // 7168 rows, four bits: updates 25 us, chains 42, staging, errors and integers 20).  Only the next panel's columns are updated before it
 // starts (33 us); the update of those beyond runs beside it, in the same launch: 3.05 -> 2.67 ms, 3.78 with none of this.  So the errors
 // of two panels are kept, by turns, in Dt, which the pass does not use otherwise.
+//
+// Few far columns are updated before the panel with the next ones instead: the extra launch is not made up for (us, all before / from
+// this many tiles on beside: 4096 x 4096 1312 / 1280, 7168 x 4096 1398 / 1286, 7168 x 7168 2814 / 2680; from 1200 on 1317, 1362, 2710).
+constexpr int kBesideTiles = 600;
+
 static hipError_t gptq_rows(int M, int N, int n_bits, int q, const float *W, const float *U, const float *S, const float *qbias,
                             const int8_t *labels, uint8_t *w_int, void *workspace, hipStream_t stream)
 {
@@ -1447,9 +1452,11 @@ static hipError_t gptq_rows(int M, int N, int n_bits, int q, const float *W, con
         ProductArgs rest = {};
         int tiles = 0;
         if (p0 > 0) {
-            hipLaunchKernelGGL(product_kernel<kSubtract>, dim3((unsigned)product_groups<kSubtract>(p1 - p0, w.Mp)), dim3(256), 0, stream,
-                               update(p0, p1));
-            if (p1 < N) {
+            const bool beside = product_groups<kSubtract>(N - p1, w.Mp) >= kBesideTiles;
+            const int to = beside ? p1 : N;
+            hipLaunchKernelGGL(product_kernel<kSubtract>, dim3((unsigned)product_groups<kSubtract>(to - p0, w.Mp)), dim3(256), 0, stream,
+                               update(p0, to));
+            if (beside) {
                 rest = update(p1, N);
                 tiles = product_groups<kSubtract>(N - p1, w.Mp);
             }
