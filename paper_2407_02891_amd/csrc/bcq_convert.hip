@@ -15,6 +15,8 @@
 
 namespace bcq {
 
+typedef uint32_t convert_u32x4 __attribute__((ext_vector_type(4)));
+
 struct ConvertPlan {
     int n_bits, q;
     TyingPlan tying;
@@ -27,8 +29,8 @@ struct CodeTable {
 };
 
 // A thread maps 16 integers (WIDE: both pointers on 16 bytes; the last thread of the array the rest one by one), through a
-// table in LDS: one look-up per weight instead of a scan of the representable set.
-template <bool WIDE>
+// table in LDS: one look-up per weight instead of a scan of the representable set.  PAST: see kReadPastCaches.
+template <bool WIDE, bool PAST>
 __global__ __launch_bounds__(256) void from_linear_codes_kernel(CodeTable table, uint32_t mask, const uint8_t *__restrict__ w_int,
                                                                 uint8_t *__restrict__ codes, size_t total)
 {
@@ -38,7 +40,8 @@ __global__ __launch_bounds__(256) void from_linear_codes_kernel(CodeTable table,
     const size_t at = ((size_t)blockIdx.x * 256 + threadIdx.x) * 16;
     if (at >= total) return;
     if (WIDE && at + 16 <= total) {
-        const uint4 w = *reinterpret_cast<const uint4 *>(w_int + at);
+        const auto *const src = reinterpret_cast<const convert_u32x4 *>(w_int + at);
+        const convert_u32x4 w = PAST ? __builtin_nontemporal_load(src) : *src;
         uint4 c;
         c.x = map_codes(lut, w.x, mask); c.y = map_codes(lut, w.y, mask);
         c.z = map_codes(lut, w.z, mask); c.w = map_codes(lut, w.w, mask);
@@ -83,7 +86,9 @@ hipError_t launch_from_linear(int M, int N, int group, int n_bits, int q, const 
         table.code[w] = code_of(nearest_choice(w, plan.tying.choice, plan.tying.nchoice), plan.tying, q);  // Eq. 6
     const uint32_t mask = ((1u << n_bits) - 1u) * 0x01010101u;
     const bool wide = ((reinterpret_cast<uintptr_t>(w_int) | reinterpret_cast<uintptr_t>(codes)) & 15) == 0;
-    hipLaunchKernelGGL((wide ? from_linear_codes_kernel<true> : from_linear_codes_kernel<false>),
+    const auto codes_kernel = !wide                 ? from_linear_codes_kernel<false, false>
+                              : nw > kReadPastCaches ? from_linear_codes_kernel<true, true> : from_linear_codes_kernel<true, false>;
+    hipLaunchKernelGGL(codes_kernel,
                        dim3((unsigned)((nw + 4095) / 4096)), dim3(256), 0, stream, table, mask, w_int, codes, nw);
     hipLaunchKernelGGL(from_linear_scales_kernel, dim3((unsigned)((ng + 255) / 256)), dim3(256), 0, stream, plan,
                        S, qbias, alpha, offset, ng);

@@ -1491,8 +1491,12 @@ hipError_t launch_quant_gptq(int M, int N, int n_bits, int q, const float *W, co
 // at the same time (a sort each), all threads fill one table of codes per row, and the rows are then mapped WIDTH weights
 // (1, 4 or 16, by the alignment) at a time.  Bound: memory.  28672 x 7168: 441 us (a workgroup per row whose first thread worked out the tying, a scan of the representable
 // set per weight) -> 78 us with the plan worked out in LDS, 74 in registers, 411 MB: 5.5 TB/s; 512 x 64: 8.3 -> 10.8 -> 7.0 us.
+// Many integers are read past the caches (PAST, nontemporal): nobody reads them again, and what the packing reads next, the codes, stays in
+// the 256 MB last-level cache instead: 75 -> 70 us here, and the packing 52 -> 42 with the same integers each time (the two
+// together with others each time 134 -> 131; one tying for all rows 146 -> 132).  Where both fit that cache it is slower:
+// 4097 x 4096 19.7 -> 21.0; 12001 x 5120 the same.
 constexpr int kFuseRows = 16;
-template <int WIDTH>
+template <int WIDTH, bool PAST>
 __global__ __launch_bounds__(256) void from_linear_rows_kernel(int M, int N, int per_group, int n_bits, int q,
                                                                const int8_t *__restrict__ labels,
                                                                const uint8_t *__restrict__ w_int, const float *__restrict__ S,
@@ -1528,7 +1532,8 @@ __global__ __launch_bounds__(256) void from_linear_rows_kernel(int M, int N, int
         for (unsigned k = tid; k < per_row; k += 256) {
             const size_t at = row + (size_t)k * WIDTH;
             if constexpr (WIDTH == 16) {
-                const uint4 w = *reinterpret_cast<const uint4 *>(w_int + at);
+                const auto *const src = reinterpret_cast<const prod_u32x4 *>(w_int + at);
+                const prod_u32x4 w = PAST ? __builtin_nontemporal_load(src) : *src;
                 uint4 c;
                 c.x = map_codes(lut, w.x, mask); c.y = map_codes(lut, w.y, mask);
                 c.z = map_codes(lut, w.z, mask); c.w = map_codes(lut, w.w, mask);
@@ -1547,8 +1552,9 @@ hipError_t launch_from_linear_rows(int M, int N, int n_bits, int q, const int8_t
                                    uint16_t *offset, hipStream_t stream)
 {
     const uintptr_t both = reinterpret_cast<uintptr_t>(w_int) | reinterpret_cast<uintptr_t>(codes);
-    const auto kernel = N % 16 == 0 && both % 16 == 0 ? from_linear_rows_kernel<16>
-                        : both % 4 == 0               ? from_linear_rows_kernel<4> : from_linear_rows_kernel<1>;  // N % 4 == 0
+    const bool past = (size_t)M * N > kReadPastCaches;
+    const auto kernel = N % 16 == 0 && both % 16 == 0 ? (past ? from_linear_rows_kernel<16, true> : from_linear_rows_kernel<16, false>)
+                        : both % 4 == 0               ? from_linear_rows_kernel<4, false> : from_linear_rows_kernel<1, false>;  // N % 4 == 0
     int per_group = M / 2048;  // at least about 2048 workgroups, eight per compute unit
     per_group = per_group < 1 ? 1 : (per_group > kFuseRows ? kFuseRows : per_group);
     hipLaunchKernelGGL(kernel, dim3((M + per_group - 1) / per_group), dim3(256), 0, stream, M, N, per_group, n_bits, q, labels,

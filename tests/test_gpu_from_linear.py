@@ -72,3 +72,28 @@ def test_from_linear_all_partitions_n5_q3_small_groups():
     """All 25 tyings of 5 planes into 3 classes, groups of 64 columns."""
     for k, partition in enumerate(fuse.all_partitions(5, 3)):
         _case(33, 1024, 64, 5, partition, seed=100 + k)
+
+
+@pytest.mark.parametrize("rows", [True, False])
+def test_codes_of_a_large_layer(rows):
+    """More than 2^26 integers are read past the caches: the codes are those of the same rows taken a few at a time."""
+    M, N, n, q = (1 << 26) // 4096 + 3, 4096, 3, 2
+    g = torch.Generator(device="cuda").manual_seed(5)
+    w = torch.randint(0, 1 << n, (M, N), device="cuda", generator=g, dtype=torch.uint8)
+
+    def codes_of(lo, hi):
+        m = hi - lo
+        S, b = torch.ones((m,) if rows else (m, N // 128), device="cuda"), torch.zeros((m,) if rows else (m, N // 128), device="cuda")
+        out = torch.empty((m, N), dtype=torch.uint8, device="cuda")
+        alpha = torch.empty((m, S.numel() // m, q), dtype=torch.float16, device="cuda")
+        off = torch.empty((m, S.numel() // m), dtype=torch.float16, device="cuda")
+        if rows:
+            labels = torch.tensor([[0, 1, 1], [0, 0, 1], [0, 1, 0]], dtype=torch.int8, device="cuda")[(torch.arange(lo, hi, device="cuda") % 3)]
+            bcq.from_linear_rows(m, N, n, q, labels.contiguous(), w[lo:hi], S, b, out, alpha, off)
+        else:
+            bcq.from_linear(m, N, 128, n, q, [0, 1, 1], w[lo:hi], S, b, out, alpha, off)
+        return out
+
+    whole = codes_of(0, M)
+    for lo in range(0, M, 4099):
+        assert torch.equal(whole[lo:lo + 4099], codes_of(lo, min(M, lo + 4099)))
