@@ -12,8 +12,8 @@
 //            column j, divided by U[j][j], is spread over the later columns along row j of U, the
 //            upper Cholesky factor of H^-1 (Eq. 2 in its usual one-factorisation form).
 //
-// The integer decisions (rounding to the linear grid, nearest BCchoice) are taken in binary64 from
-// binary64 copies of the binary32 inputs; the quadratic form and the GPTQ updates accumulate in binary32
+// The integer decisions (rounding to the linear grid, nearest BCchoice) are those of binary64 copies of the binary32
+// inputs (the GPTQ pass takes them from binary32 where that cannot tell otherwise); the quadratic form and the GPTQ updates accumulate in binary32
 // (the dense products with operands split into pairs of binary16 numbers, see bcq_product.h).
 #include <algorithm>
 #include <vector>
@@ -96,8 +96,8 @@ __device__ __forceinline__ int linear_int(double x, double S, double inv_s, doub
 // pitch Mp = M rounded up to 4: one thread per row then reads and writes coalesced, and both dense
 // products (bcq_product.h) take their operands "k-major" (the summation index is the slow one).  Workspace, in floats:
 //   Wt [N][Mp] | Dt [N][Mp] | part [ceil(N/128)][Mp] | wmin, wmax, best [3][Mp] | small [128][Mp]
-// (search: Wt becomes the halves of d, Dt holds d, small the exponents of its scales; GPTQ pass: Dt holds the errors of a panel, part
-// or small the tables, small the smallest diagonals of a panel)
+// (search: Wt becomes the halves of d, Dt holds d, small the exponents of its scales; the screened search: see
+// search_screened; GPTQ pass: Dt holds the errors of two panels, part or small the tables, small the smallest diagonals of two panels)
 struct QuantWorkspace {
     int Mp, ntile;
     float *Wt, *Dt, *part, *wmin, *wmax, *best, *small;
@@ -1024,7 +1024,7 @@ __global__ void gptq_tables_kernel(int M, int n_bits, int q, const int8_t *__res
 // Before a block the errors of the panel's earlier ones are applied to its columns by binary32 matrix instructions.
 // The factors are staged in LDS such that the 16 of a lane for column c, those of the columns 8 (c / 8 + k) + l, come in
 // up to four 16-byte reads: [c][k / 4][l][k % 4], of which columns from 32 g on need 4 - g.
-constexpr int kGptqBlock = 128, kGptqLanes = 8, kGptqRows = 32;  // columns per block, lanes per row, rows per workgroup
+constexpr int kGptqBlock = 128, kGptqRows = 32;  // columns per block, rows per workgroup
 constexpr int kGptqPanel = 4 * kGptqBlock;
 
 // Single instructions, in this order (the compiler leaves the order of volatile ones alone): d = a b + c; w += x u with x
