@@ -1028,7 +1028,9 @@ constexpr int kGptqBlock = 128, kGptqRows = 32;  // columns per block, rows per 
 constexpr int kGptqPanel = 4 * kGptqBlock;
 
 // Single instructions, in this order (the compiler leaves the order of volatile ones alone): d = a b + c; w += x u with x
-// from lane LANE of each group of eight (at least two instructions after x was written, or WAIT); x from that lane.
+// from lane LANE of each group of eight; x from that lane.  A DPP operand must have been written kGptqDppWait instructions before (or
+// WAIT), and the compiler keeps no such distance across inline assembly.
+constexpr int kGptqDppWait = 2;
 #define GPTQ_FMA(d, a, b, c) asm volatile("v_fma_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c))
 template <int LANE, bool WAIT>
 __device__ __forceinline__ void gptq_add_from(float &w, float x, float u)
@@ -1242,6 +1244,8 @@ __device__ __forceinline__ void gptq_panel(GptqShared<TABLE> &shared, int M, int
         // groups of eight columns, with the 4 kChunks columns of a lane that are still to come
         auto groups = [&](auto chunks_of, int i_begin) PROD_INLINE {
             constexpr int kChunks = decltype(chunks_of)::value, g = 4 - kChunks, kSlots = 4 * kChunks;
+            constexpr int kAfter = kGptqDppWait;
+            static_assert(kSlots - 1 >= kAfter, "a step's shares behind the deviation are the wait states of gptq_add_from");
             // factors of the step before, this step and the next (behind the last one, others that nobody uses)
             prod_f32x4 u[4][kChunks];
             auto fetch = [&](int c, prod_f32x4 (&to)[kChunks]) PROD_INLINE {
@@ -1260,11 +1264,13 @@ __device__ __forceinline__ void gptq_panel(GptqShared<TABLE> &shared, int M, int
                     __builtin_amdgcn_sched_barrier(0);
                     fetch(8 * i + kLane + 1, u[(kLane + 1) & 3]);
                     __builtin_amdgcn_sched_barrier(0);
-                    int slot = 1;  // the shares of the step before, between the instructions that wait for each other
+                    // the shares of the step before, between the instructions that wait for each other; kAfter of them are
+                    // kept for behind the last one, whose result DPP operands read
+                    int slot = 1, end = kSlots - kAfter;
                     auto fill = [&](int count) PROD_INLINE {
 #pragma unroll
                         for (int n = 0; n < count; ++n)
-                            if (kLane > 0 && slot < kSlots) {
+                            if (kLane > 0 && slot < end) {
                                 GPTQ_FMA(v[slot], e, u[(kLane + 3) & 3][slot >> 2][slot & 3], kLane == 1 ? w[slot] : v[slot]);
                                 ++slot;
                             }
@@ -1301,14 +1307,15 @@ __device__ __forceinline__ void gptq_panel(GptqShared<TABLE> &shared, int M, int
                     fill(kEach);
                     float qv;
                     GPTQ_FMA(qv, sf, wqf, bf);
-                    fill(kSlots - 1 - slot - 2);
+                    fill(end - 1 - slot);
                     asm volatile("v_sub_f32 %0, %1, %2" : "=v"(a) : "v"(v[0]), "v"(qv));
+                    end = kSlots;
                     fill(kSlots);
                 };
                 auto step = [&](auto lane_of) PROD_INLINE {
                     constexpr int kLane = decltype(lane_of)::value;
                     decide(lane_of);
-                    gptq_add_from<kLane, kLane == 0>(v[0], a, u[kLane & 3][0][0]);
+                    gptq_add_from<kLane, kLane == 0>(v[0], a, u[kLane & 3][0][0]);  // (lane 0's step has no shares)
                     e = gptq_from<kLane>(a);
                 };
                 step(std::integral_constant<int, 0>{}); step(std::integral_constant<int, 1>{});
