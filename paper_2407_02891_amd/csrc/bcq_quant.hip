@@ -1019,8 +1019,11 @@ __global__ void gptq_tables_kernel(int M, int n_bits, int q, const int8_t *__res
 //     lanes), those of the others by the multiply-adds that fill the next step;
 //   * a step's factors are requested from LDS a step ahead.
 // The factors are zero up to the diagonal, so a weight stays as it was when its column was decided, and after the eighth step of a
-// group of eight columns every lane holds the decision of its own: a group with one that is too close to a half, or with a diagonal
-// beyond 2^-40 .. 2^40, is gone through again by the definition: decisions from binary64, errors by division.
+// group of eight columns every lane holds the decision of its own: a group with one that is too close to a half is gone through
+// again with decisions from binary64, and one with a diagonal beyond 2^-40 .. 2^40 with errors by division, too.  The
+// sums are those of the first time, so that a wave's other rows come out the same.  (With U's rows read from memory again a single row
+// of constant weights or with an offset of 2^20 steps took the pass of 7168 x 7168 from 2.7 to
+// 8.7 and 7.9 ms, now 2.8 and 3.2.)  A wave with a row whose quotients the first way hardly ever tells goes the second way at once.
 // Before a block the errors of the panel's earlier ones are applied to its columns by binary32 matrix instructions.
 // The factors are staged in LDS such that the 16 of a lane for column c, those of the columns 8 (c / 8 + k) + l, come in
 // up to four 16-byte reads: [c][k / 4][l][k % 4], of which columns from 32 g on need 4 - g.
@@ -1151,10 +1154,11 @@ __device__ __forceinline__ void gptq_panel(GptqShared<TABLE> &shared, int M, int
             table[r][e & 255] = mr < M && (e & 255) < 1 << n_bits ? bytes[(size_t)mr * 256 + (e & 255)] : 0;
         }
     }
-    const float topf = (float)((1 << n_bits) - 1), inv_f = 1.0f / sf, shift_f = -bf * inv_f;
+    const float topf = (float)((1 << n_bits) - 1), inv_f = sf == 0.0f ? 0.0f : 1.0f / sf, shift_f = -bf * inv_f;
     // how far a quotient may be from its integer without doubt; scales out of the ordinary leave none
     const float steps = ldexpf(1.0f, n_bits) + fabsf(shift_f);
-    const float sure = fabsf(sf) >= 0x1p-60f && fabsf(sf) <= 0x1p60f ? fmaf(steps, -0x1p-22f, 0.5f) : -1.0f;
+    const float sure = sf == 0.0f ? 0.5f : fabsf(sf) >= 0x1p-60f && fabsf(sf) <= 0x1p60f ? fmaf(steps, -0x1p-22f, 0.5f) : -1.0f;
+    const bool far = __any(sure < 0.46875f);  // a group of the wave would nearly always be gone through again
     constexpr float kRound = 0x1.8p23f;
 
     for (int c0 = p0; c0 < p1; c0 += kGptqBlock) {
@@ -1318,39 +1322,63 @@ __device__ __forceinline__ void gptq_panel(GptqShared<TABLE> &shared, int M, int
                     gptq_add_from<kLane, kLane == 0>(v[0], a, u[kLane & 3][0][0]);  // (lane 0's step has no shares)
                     e = gptq_from<kLane>(a);
                 };
-                step(std::integral_constant<int, 0>{}); step(std::integral_constant<int, 1>{});
-                step(std::integral_constant<int, 2>{}); step(std::integral_constant<int, 3>{});
-                step(std::integral_constant<int, 4>{}); step(std::integral_constant<int, 5>{});
-                step(std::integral_constant<int, 6>{});
-                decide(std::integral_constant<int, 7>{});
+                bool again = far;
+                if (far) {
+                    fetch(8 * i + 7, u[3]);
+                    fetch(8 * i + 8, u[0]);
+                } else {
+                    step(std::integral_constant<int, 0>{}); step(std::integral_constant<int, 1>{});
+                    step(std::integral_constant<int, 2>{}); step(std::integral_constant<int, 3>{});
+                    step(std::integral_constant<int, 4>{}); step(std::integral_constant<int, 5>{});
+                    step(std::integral_constant<int, 6>{});
+                    decide(std::integral_constant<int, 7>{});
+                    // (a deviation without end has made the weights decided before it no numbers; a row of one weight, S = 0,
+                    // stays what it is: any integer will do unless something was added to it)
+                    const bool doubt = !(fabsf(t - (r - kRound)) < sure) || !(fabsf(a) < INFINITY) || (sf == 0.0f && a != 0.0f);
+                    again = __any(doubt || ((odd >> i) & 1));
+                }
                 int my_q = (int)wqf;
                 float last = a;
-                // (a deviation without end has made the weights decided before it no numbers)
-                if (__builtin_expect(__any(!(fabsf(t - (r - kRound)) < sure) || !(fabsf(a) < INFINITY) || ((odd >> i) & 1)), 0)) {
+                if (__builtin_expect(again, 0)) {
+                    const bool by_u = (odd >> i) & 1;  // (of all rows)
 #pragma unroll
                     for (int k = 0; k < kSlots; ++k) v[k] = w[k];
+                    const float near = fabsf(sf) >= 0x1p-60f && fabsf(sf) <= 0x1p60f ? 0.5f - ldexpf(1.0f, n_bits - 21) : -1.0f;
+                    float from_prev = 0.0f;
 #pragma unroll 1
                     for (int turn = 0; turn < 8; ++turn) {
-                        const double s = sf, b = bf;
-                        const int lin = linear_int((double)v[0] - b, s, 1.0 / s, topf);
+                        prod_f32x4 f[kChunks];
+                        fetch(8 * i + turn, f);
+                        __builtin_amdgcn_sched_barrier(0);
+                        // the difference is off by 2^-24 of itself, so this quotient by less than 2^(n - 21), whatever qbias is
+                        const float tq = fminf(fmaxf((v[0] - bf) * inv_f, 0.0f), topf), rq = rintf(tq);
+                        int lin = (int)rq;
+                        if (__any(!(fabsf(tq - rq) < near))) lin = linear_int((double)v[0] - (double)bf, sf, 1.0 / (double)sf, topf);
                         int wq;
                         if (TABLE == kBytes) wq = table[row][lin];
                         else wq = (int)((lin & 8 ? (lin & 4 ? tab3 : tab2) : (lin & 4 ? tab1 : tab0)) >> (8 * (lin & 3))) & 0xff;
-                        const float now = v[0] - (float)(s * wq + b);
+                        const float now = v[0] - fmaf(sf, (float)wq, bf);
                         my_q = l == turn ? wq : my_q;
                         a = l == turn ? now : a;
-                        last = a;
+                        from_prev = __shfl(now, turn, 8);
                         if (turn == 7) break;
                         const int c = 8 * i + turn;
-                        const float err = __shfl(now, turn, 8) / diag[c];
-                        const float *const of_u = U + (size_t)(c0 + c) * N + c0 + 8 * i + l;
+                        if (by_u) {
+                            const float err = from_prev / diag[c];
+                            const float *const of_u = U + (size_t)(c0 + c) * N + c0 + 8 * i + l;
 #pragma unroll
-                        for (int k = 0; k < kSlots; ++k)
-                            if (8 * k + l > turn && 8 * (i + k) + l < cols) v[k] = fmaf(-err, of_u[8 * k], v[k]);
+                            for (int k = 0; k < kSlots; ++k)
+                                if (8 * k + l > turn && 8 * (i + k) + l < cols) v[k] = fmaf(-err, of_u[8 * k], v[k]);
+                        } else {
+                            if (l > turn) v[0] = fmaf(from_prev, f[0][0], v[0]);
+#pragma unroll
+                            for (int k = 1; k < kSlots; ++k) v[k] = fmaf(from_prev, f[k >> 2][k & 3], v[k]);
+                        }
                     }
-                    if ((odd >> i) & 1) {  // the last column's share too
+                    last = a;
+                    if (by_u) {  // the last column's share too
                         last = 0.0f;
-                        const float err = __shfl(a, 7, 8) / diag[8 * i + 7];
+                        const float err = from_prev / diag[8 * i + 7];
                         const float *const of_u = U + (size_t)(c0 + 8 * i + 7) * N + c0 + 8 * i + l;
 #pragma unroll
                         for (int k = 1; k < kSlots; ++k)

@@ -372,6 +372,49 @@ def test_gptq_decisions_where_binary32_does_not_tell(n, q):
     assert np.array_equal(got, want), np.argwhere(got != want)[:10]
 
 
+@pytest.mark.parametrize("n,q", [(3, 2), (4, 3), (5, 3)])
+def test_gptq_rows_do_not_depend_on_their_neighbours(n, q):
+    """Within a panel a row's integers are its own: the same beside ordinary rows as beside rows whose decisions binary32 does not
+    tell (offsets of 2^20 steps, constant rows, scales of 2^-70, infinities), which send their wave through every group twice."""
+    M, N = 40960, 512  # (enough that sums rounded otherwise would show in some integer)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    W = torch.randn((M, N), device="cuda", generator=g) * 0.02
+    X = torch.randn((2 * N, N), device="cuda", generator=g)
+    H = (2.0 * (X.t().contiguous() @ X)).cpu().numpy()
+    U = _dev(quantizer.cholesky_factor(H).astype(np.float32))
+    lo, hi = W.min(1).values, W.max(1).values
+    S, b = ((hi - lo) / ((1 << n) - 1) * 0.8).contiguous(), lo.contiguous()
+    parts = torch.tensor(np.stack([_labels_of(p, n) for p in fuse.all_partitions(n, q)]), device="cuda")
+    labels = parts[torch.arange(M, device="cuda") % len(parts)].contiguous()
+
+    def integers(W, S, b):
+        out = torch.full((M, N), 255, dtype=torch.uint8, device="cuda")
+        ws = torch.empty(bcq.quant_workspace_bytes(M, N), dtype=torch.uint8, device="cuda")
+        bcq.quant_gptq(M, N, n, q, W.contiguous(), U, S, b, labels, out, ws)
+        torch.cuda.synchronize()
+        return out
+
+    plain = integers(W, S, b)
+    W, S, b = W.clone(), S.clone(), b.clone()
+    k = torch.arange(0, M, 8, device="cuda")
+    for first, what in enumerate(("far", "constant", "tiny", "infinite")):
+        at = k[first::4]
+        if what == "far":
+            W[at] += S[at][:, None] * 2.0 ** 20
+            b[at] += S[at] * 2.0 ** 20
+        elif what == "constant":
+            W[at], S[at], b[at] = 0.25, 0.0, 0.25
+        elif what == "tiny":
+            W[at], S[at], b[at] = W[at] * 2.0 ** -64, S[at] * 2.0 ** -64, b[at] * 2.0 ** -64
+        else:
+            W[at, 100] = float("inf")
+    beside = integers(W, S, b)
+    same = (plain == beside).all(1)
+    same[k] = True
+    assert same.all(), torch.nonzero(~same).flatten()[:8]
+    assert (beside[k[1::4]] == beside[k[1::4]][:, :1]).all()  # (a constant row: one integer)
+
+
 @pytest.mark.parametrize("M,N,n,q", [(37, 1024, 3, 2), (12, 512, 4, 3), (5, 1536, 5, 3), (8, 512, 4, 4)])
 def test_from_linear_rows(M, N, n, q):
     rng = np.random.default_rng(300 + N + n + q)
