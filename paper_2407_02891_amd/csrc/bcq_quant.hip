@@ -873,7 +873,7 @@ static hipError_t search_screened(int M, int N, int n_bits, int grid, const std:
                              : planes == 3 ? delta_single_kernel<3> : delta_single_kernel<4>;
             hipLaunchKernelGGL(delta, delta_grid, dim3(256), 0, stream, M, Mp, N, n_bits, g, grid, set, W, w.wmin, w.wmax, shift, Dh, tables + c);
             launch_screen(stream, ScreenArgs{Hh, Dh, unscale, norms, sums, N, M, Mp, planes});
-            hipLaunchKernelGGL(screen_bound_kernel, dim3(rows.x, planes), dim3(64), 0, stream, M, Mp, N, sums, shift, frobenius,
+            hipLaunchKernelGGL(screen_bound_kernel, dim3(rows.x, planes), dim3(64), 0, stream, M, Mp, N, sums, shift, diag_max, frobenius,
                                bound + (size_t)c * Mp);
             c += planes;
         }

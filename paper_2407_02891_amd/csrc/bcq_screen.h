@@ -26,11 +26,19 @@ namespace bcq {
 struct ScreenArgs {
     const uint16_t *H;      // [k / 8][column c (N)][8 values of k], see screen_h_kernel
     const uint16_t *D;      // [plane][k / 8][row m (Mp)][8 values of k], a plane per candidate
-    const float *unscale;   // [N] what takes a column's scale out again
-    const float *norms;     // [N] squared norms of H's rows
-    float *sums;            // [plane][4][Mp], zero before: form, sum of D^2, sum of D^2 norms, largest |D|, of D with its scale
+    const float *unscale;   // [N] what takes a column's scale out again, in units of H (screen_unit)
+    const float *norms;     // [N] squared norms of H's rows, in units of H
+    float *sums;            // [plane][4][Mp], zero before: form, sum of D^2, sum of D^2 norms, largest |D|, of D with its scale, H in its units
     int N, M, Mp, planes;
 };
+
+// H is taken in units of 2^e, e the exponent of the largest value on its diagonal: the squares of values far from 1 have no
+// binary32 numbers, and a bound without its norms is none.
+__device__ __forceinline__ int screen_unit(float diag_max)
+{
+    const int e = (int)(__float_as_uint(diag_max) >> 23) - 127;
+    return e < -126 ? -126 : e;
+}
 
 // D G D^T of the rows of D (added up over the tiles of columns c by atomics: their order moves the bound by its roundings, not
 // the result of the search), G[k][c] = H with the weight 1 for k < c, 1/2 for k = c and 0 beyond.
@@ -221,10 +229,10 @@ __global__ __launch_bounds__(256) void screen_h_kernel(int N, const float *__res
     const int e_max = (int)(__float_as_uint(*diag_max) >> 23) - 127;
     int e_diag = (int)((__float_as_uint(diag) >> 23) & 0xff) - 127;
     if (!(diag > 0.0f) || e_diag == 128) e_diag = e_max;
-    int shift = 15 - ((e_max + e_diag + 3) >> 1);
-    shift = shift < -120 ? -120 : (shift > 120 ? 120 : shift);
-    const float s = ldexpf(1.0f, shift);
-    if (blockIdx.y == 0 && wave == 0 && c < N) unscale[c] = ldexpf(1.0f, -shift);
+    const int shift = 15 - ((e_max + e_diag + 3) >> 1), e_unit = screen_unit(*diag_max);
+    const float s = ldexpf(1.0f, shift >> 1), s2 = ldexpf(1.0f, shift - (shift >> 1));  // (one power alone may be beyond binary32)
+    const float unit = ldexpf(1.0f, -e_unit);
+    if (blockIdx.y == 0 && wave == 0 && c < N) unscale[c] = ldexpf(1.0f, -shift - e_unit);
     float mine = 0.0f;
     for (int k0 = k_begin + 8 * wave; k0 < k_begin + 256 && k0 < N; k0 += 32) {
         float v[8];
@@ -233,14 +241,14 @@ __global__ __launch_bounds__(256) void screen_h_kernel(int N, const float *__res
         prod_u32x4 packed;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const float x = (k0 + j == c ? 0.5f : 1.0f) * v[j] * s;
+            const float x = (k0 + j == c ? 0.5f : 1.0f) * v[j] * s * s2;
             // at random up or down to the 11 bits of a binary16 number (below 2^-14 it is rounded once more, to nearest)
             unsigned h = (unsigned)(k0 + j) * 0x9e3779b1u + (unsigned)c * 0x85ebca77u;
             h ^= h >> 15; h *= 0x2c1b3c6du; h ^= h >> 12; h *= 0x297a2d39u; h ^= h >> 15;
             const float up = __uint_as_float((__float_as_uint(x) + (h & 0x1fffu)) & ~0x1fffu);
             const unsigned half = __builtin_bit_cast(unsigned short, (_Float16)(fabsf(x) < INFINITY ? up : x));
             packed[j >> 1] = j & 1 ? packed[j >> 1] | half << 16 : half;
-            const float square = v[j] * v[j];
+            const float square = (v[j] * unit) * (v[j] * unit);
             mine += square;
             // the other half of the matrix: row k0 + j (the diagonal is counted once)
             float row = k0 + j < c ? square : 0.0f;
@@ -255,7 +263,7 @@ __global__ __launch_bounds__(256) void screen_h_kernel(int N, const float *__res
     if (wave == 0 && c < N) atomicAdd(norms + c, sums[threadIdx.x] + sums[threadIdx.x + 64] + sums[threadIdx.x + 128] + sums[threadIdx.x + 192]);
 }
 
-// frobenius[0] = |H|_F, with something added for the roundings of the norms
+// frobenius[0] = |H|_F in units of H, with something added for the roundings of the norms
 __global__ __launch_bounds__(1024) void screen_frobenius_kernel(int N, const float *__restrict__ norms, float *__restrict__ frobenius)
 {
     __shared__ double part[16];
@@ -273,7 +281,8 @@ __global__ __launch_bounds__(1024) void screen_frobenius_kernel(int N, const flo
 
 // Lower bound of the error of the candidate of each plane (blockIdx.y), per row; leaves the sums zero.
 __global__ __launch_bounds__(64) void screen_bound_kernel(int M, int Mp, int N, float *__restrict__ sums, const int *__restrict__ shift,
-                                                          const float *__restrict__ frobenius, float *__restrict__ bound)
+                                                          const float *__restrict__ diag_max, const float *__restrict__ frobenius,
+                                                          float *__restrict__ bound)
 {
     const int m = blockIdx.x * 64 + threadIdx.x;
     if (m >= M) return;
@@ -287,7 +296,7 @@ __global__ __launch_bounds__(64) void screen_bound_kernel(int M, int Mp, int N, 
     const double delta = 0x1p-11 * (1.0 + 0x1p-9) * sqrt(squares) + 0x1p-25 * sqrt((double)N);
     const double root = sqrt(2.0 * (low > 0.0 ? low : 0.0)) - sqrt(fro) * delta;
     double v = root > 0.0 ? 0.5 * root * root * (1.0 - 0x1p-12) - 0x1p-18 * fro * squares : 0.0;
-    v = ldexp(v > 0.0 ? v : 0.0, -2 * shift[m]);
+    v = ldexp(v > 0.0 ? v : 0.0, screen_unit(*diag_max) - 2 * shift[m]);
     // (a form that is not finite says nothing; infinity would say that the candidate is done with)
     bound[(size_t)blockIdx.y * Mp + m] = !(fabs(form) < (double)INFINITY) || !(v < 0x1p126) ? 0.0f : (float)(v * (1.0 - 0x1p-23));
 }

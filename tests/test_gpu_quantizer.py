@@ -171,7 +171,7 @@ def _search(W, H, n, q, grid):
 @pytest.mark.parametrize("M,N,n,q,grid,kind", [
     (256, 256, 3, 2, 3, "samples"), (257, 264, 4, 3, 2, "samples"), (700, 520, 3, 2, 2, "loud"), (513, 776, 2, 2, 4, "samples"),
     (300, 512, 5, 3, 3, "samples"), (400, 1032, 3, 2, 2, "one direction"), (260, 640, 8, 2, 1, "one direction"), (300, 264, 4, 2, 2, "zero"),
-    (2048, 320, 3, 2, 2, "few samples"), (256, 736, 3, 2, 4, "indefinite"), (300, 296, 3, 2, 2, "infinite")])
+    (2048, 320, 3, 2, 2, "few samples"), (256, 736, 3, 2, 4, "indefinite"), (300, 296, 3, 2, 2, "infinite"), (1020, 776, 3, 2, 8, "tiny"), (510, 776, 3, 2, 3, "huge")])
 def test_search_screened(M, N, n, q, grid, kind):
     """Layers of 256 rows or more are screened: a bound excludes candidates before they are evaluated.  The results are the bits of the
     search of at most 255 rows at a time, which evaluates all: at the edges of tiles, chunks of candidates (48) and planes, with
@@ -195,6 +195,10 @@ def test_search_screened(M, N, n, q, grid, kind):
         H = 100.0 * H.diagonal().mean() * torch.ones_like(H) + H
     if kind == "zero":
         H.zero_()
+    if kind in ("tiny", "huge"):  # squares of its values are no binary32 numbers; channels with means, next to which the errors are small
+        mean = 50.0 * torch.randn(N, device="cuda", generator=g)
+        H += 2.0 * T * mean[:, None] * mean[None]
+        H *= 2.0 ** (-110 if kind == "tiny" else 80)
     if kind == "infinite":
         H[17, 200] = H[200, 17] = float("inf")
     H = ((H + H.t()) * 0.5).contiguous()
