@@ -667,8 +667,8 @@ __global__ __launch_bounds__(256) void delta_kernel(int M, int Mp, int N, int n_
     }
 }
 
-// The same d for the screened search: of up to kPlanes tyings of one grid point, each a binary16 number rounded to nearest, in planes
-// of the operand layout; also fills the candidates' tables.  Bound: memory.  7168 x 7168, three tyings: 68 us each one by one, W
+// The same d for the screened search: of up to kPlanes tyings of one grid point, each a binary16 number rounded at random (see bcq_screen.h;
+// `seed` is the first one's number in the search), in planes of the operand layout; also fills the candidates' tables.  Bound: memory.  7168 x 7168, three tyings: 68 us each one by one, W
 // being read each time.
 constexpr int kPlanes = 4;
 struct TyingSet { Tying t[kPlanes]; };
@@ -676,7 +676,7 @@ template <int PLANES>
 __global__ __launch_bounds__(256) void delta_single_kernel(int M, int Mp, int N, int n_bits, int g, int grid, TyingSet set,
                                                            const float *__restrict__ W, const float *__restrict__ wmin,
                                                            const float *__restrict__ wmax, const int *__restrict__ shift,
-                                                           uint16_t *__restrict__ out, CandidateTable *__restrict__ tables)
+                                                           uint16_t *__restrict__ out, CandidateTable *__restrict__ tables, int seed)
 {
     const int m = blockIdx.x * 64 + (threadIdx.x & 63), k0 = 8 * (blockIdx.y * 4 + (threadIdx.x >> 6));
     if (blockIdx.x == 0 && blockIdx.y == 0) {
@@ -698,6 +698,11 @@ __global__ __launch_bounds__(256) void delta_single_kernel(int M, int Mp, int N,
         const prod_f32x4 w0 = src[0], w1 = src[1];
         const double lo = wmin[m], S = grid_scale(lo, wmax[m], n_bits, g, grid), inv_s = 1.0 / S, top = (double)((1 << n_bits) - 1);
         const float s = ldexpf(1.0f, shift[m]);
+        unsigned random[PLANES][4];  // for two values each
+#pragma unroll
+        for (int p = 0; p < PLANES; ++p)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) random[p][j] = screen_hash((unsigned)m, (unsigned)(k0 / 2 + j), (unsigned)(seed + p + 2));
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const double w = j < 4 ? w0[j & 3] : w1[j & 3];
@@ -705,7 +710,7 @@ __global__ __launch_bounds__(256) void delta_single_kernel(int M, int Mp, int N,
 #pragma unroll
             for (int p = 0; p < PLANES; ++p) {
                 const int wq = n_bits <= 4 ? (int)(set.t[p].nibbles >> (4 * lin)) & 15 : nearest_choice(lin, set.t[p].choice, set.t[p].nchoice);
-                d[p][j] = (_Float16)((float)(S * wq + lo - w) * s);
+                d[p][j] = (_Float16)screen_round((float)(S * wq + lo - w) * s, random[p][j >> 1] >> (16 * (j & 1)));
             }
         }
     }
@@ -812,16 +817,27 @@ __global__ __launch_bounds__(256) void search_round_kernel(int M, int Mp, int n_
 }
 
 // The screened search (bcq_screen.h) keeps its matrices in the place of Wt and Dt, where the listed rows' d come afterwards:
-//   Dh binary16 [planes][N / 8][Mp][8] | Hh binary16 [N / 8][N][8]
-// and in `small`: shift [Mp] | diag_max, frobenius | bound [kChunk][Mp] | sums [kPlanes][4][Mp] | slot_shift, row and candidate of two
-// lists, begin, count, index [8][Mp] | unscale, norms [2][N] | totals [kChunk] | tables [kChunk].
+//   Dh binary16 [planes][N / 8][Mp][8] (before that z) | Hh binary16 [N / 8][N][8] | R binary16 [N / 8][projection][8]
+// and in `small`: shift [Mp] | diag_max, frobenius | bound [chunk][Mp] | sums [planes][kScreenSums][Mp] | slot_shift, row and candidate of two
+// lists, begin, count, index [8][Mp] | unscale, norms [2][N] | totals [chunk] | tables [chunk] | R where there was no room for it.
 constexpr int kChunk = 48;
-static int screen_planes(int M, int N, int tyings)  // 0: there is no room
+struct ScreenPlan { int planes, projections, chunk, r_in_small; };  // candidates at a time and per chunk; no planes: there is no room
+static ScreenPlan screen_plan(int M, int N, int tyings, int candidates)
 {
     const long long Mp = pitch_of(M);
-    if ((kChunk + 4 * kPlanes + 9) * Mp + 16 + 2LL * N + kChunk * (1 + (long long)sizeof(CandidateTable) / 4) + 64 > 128 * Mp) return 0;
-    const long long planes = (8 * Mp * N - 2LL * N * N) / (2 * Mp * N);
-    return (int)(planes < 0 ? 0 : planes < tyings ? (planes < kPlanes ? planes : kPlanes) : (tyings < kPlanes ? tyings : kPlanes));
+    for (int planes = tyings < kPlanes ? tyings : kPlanes; planes > 0; --planes)
+        for (int projections = kProjections; projections >= kFewProjections; projections /= 2) {
+            const long long left = 2 * N * Mp - (long long)N * N / 2 - (long long)planes * N * Mp / 2;  // floats
+            const long long r = (long long)N * projections / 2;
+            if (left < 0) continue;
+            const int r_in_small = left < r;
+            const long long fixed = (9 + kScreenSums * planes) * Mp + 16 + 2LL * N + 64 + (r_in_small ? r : 0);
+            long long chunk = (128 * Mp - fixed) / (Mp + 1 + (long long)sizeof(CandidateTable) / 4);
+            chunk = chunk < kChunk ? chunk : kChunk;
+            chunk = chunk < candidates ? chunk : candidates;
+            if (chunk >= (candidates < 8 ? candidates : 8)) return {planes, projections, (int)chunk, r_in_small};
+        }
+    return {0, 0, 0, 0};
 }
 
 // Two rounds of three products each and a product per candidate instead of three per candidate: pays from a few candidates on, down
@@ -830,20 +846,23 @@ static int screen_planes(int M, int N, int tyings)  // 0: there is no room
 // evaluated of 24; a form 309 of 1300), 2500 x 7168 11700 / 5030, 2048 x 2048 2140 / 757, 512 x 512 790 / 365, 256 x 512 (grid 4) 385 / 284.
 static bool screen_pays(int M, int N, int candidates) { return M >= 256 && N >= 256 && candidates >= 4; }
 
-static hipError_t search_screened(int M, int N, int n_bits, int grid, const std::vector<Tying> &tyings, int most_planes, const float *W,
+static hipError_t search_screened(int M, int N, int n_bits, int grid, const std::vector<Tying> &tyings, ScreenPlan plan, const float *W,
                                   const float *H, float *S, float *qbias, int8_t *labels, const QuantWorkspace &w, hipStream_t stream)
 {
     const int Mp = w.Mp, T = (int)tyings.size(), all = grid * T;
     auto *Dh = reinterpret_cast<uint16_t *>(w.Wt);
-    uint16_t *const Hh = Dh + (size_t)most_planes * N * Mp;
+    uint16_t *const Hh = Dh + (size_t)plan.planes * N * Mp;
     auto *shift = reinterpret_cast<int *>(w.small);
-    float *diag_max = w.small + Mp, *frobenius = diag_max + 4, *bound = diag_max + 16, *sums = bound + (size_t)kChunk * Mp;
-    auto *slot_shift = reinterpret_cast<int *>(sums + 4 * (size_t)kPlanes * Mp);
+    float *diag_max = w.small + Mp, *frobenius = diag_max + 4, *bound = diag_max + 16, *sums = bound + (size_t)plan.chunk * Mp;
+    const size_t sums_floats = (size_t)kScreenSums * plan.planes * Mp;
+    auto *slot_shift = reinterpret_cast<int *>(sums + sums_floats);
     int *list[2] = {slot_shift + Mp, slot_shift + 3 * (size_t)Mp};
     int *begin = slot_shift + 5 * (size_t)Mp, *count = begin + Mp, *index = count + Mp;
     float *unscale = reinterpret_cast<float *>(index + Mp), *norms = unscale + N;
     int *totals = reinterpret_cast<int *>(norms + N);
-    auto *tables = reinterpret_cast<CandidateTable *>((reinterpret_cast<uintptr_t>(totals + kChunk) + 15) & ~(uintptr_t)15);
+    auto *tables = reinterpret_cast<CandidateTable *>((reinterpret_cast<uintptr_t>(totals + plan.chunk) + 15) & ~(uintptr_t)15);
+    auto *const R = plan.r_in_small ? reinterpret_cast<uint16_t *>(tables + plan.chunk) : Hh + (size_t)N * N;
+    float *const z = w.Wt;
     const dim3 delta_grid((Mp + 63) / 64, (N + 31) / 32), rows((M + 63) / 64);
     const size_t plane = (size_t)N * Mp;
     SearchRound round = {};
@@ -854,26 +873,28 @@ static hipError_t search_screened(int M, int N, int n_bits, int grid, const std:
     round.index = index;
     round.tables = tables;
     SearchList listed = {nullptr, nullptr, nullptr, tables, 0, T};
-    hipError_t e = launch_fill_zero(sums, 16 * (size_t)kPlanes * Mp, stream);
+    hipError_t e = launch_fill_zero(sums, 4 * sums_floats, stream);
     if (e != hipSuccess) return e;
-    for (int first = 0; first < all; first += kChunk) {
-        const int candidates = all - first < kChunk ? all - first : kChunk;
-        e = launch_fill_zero(norms, (size_t)(N + kChunk) * 4, stream);
+    for (int first = 0; first < all; first += plan.chunk) {
+        const int candidates = all - first < plan.chunk ? all - first : plan.chunk;
+        e = launch_fill_zero(norms, (size_t)(N + plan.chunk) * 4, stream);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(screen_h_kernel, dim3((N + 63) / 64, (N + 255) / 256), dim3(256), 0, stream, N, H, diag_max, Hh, unscale, norms);
-        hipLaunchKernelGGL(screen_frobenius_kernel, dim3(1), dim3(1024), 0, stream, N, norms, frobenius);
+        hipLaunchKernelGGL(screen_frobenius_kernel, dim3(1 + (N * (plan.projections / 2) + 1023) / 1024), dim3(1024), 0, stream, N, norms, frobenius, z,
+                           plan.projections);
+        hipLaunchKernelGGL(screen_project_kernel, dim3((N + 31) / 32), dim3(256), 0, stream, N, H, diag_max, frobenius, z, R, plan.projections);
         for (int c = 0; c < candidates;) {
             // tyings of one grid point, as many as there are planes
             const int g = (first + c) / T, t0 = (first + c) % T;
-            int planes = most_planes < T - t0 ? most_planes : T - t0;
+            int planes = plan.planes < T - t0 ? plan.planes : T - t0;
             planes = planes < candidates - c ? planes : candidates - c;
             TyingSet set = {};
             for (int p = 0; p < planes; ++p) set.t[p] = tyings[t0 + p];
             const auto delta = planes == 1 ? delta_single_kernel<1> : planes == 2 ? delta_single_kernel<2>
                              : planes == 3 ? delta_single_kernel<3> : delta_single_kernel<4>;
-            hipLaunchKernelGGL(delta, delta_grid, dim3(256), 0, stream, M, Mp, N, n_bits, g, grid, set, W, w.wmin, w.wmax, shift, Dh, tables + c);
-            launch_screen(stream, ScreenArgs{Hh, Dh, unscale, norms, sums, N, M, Mp, planes});
-            hipLaunchKernelGGL(screen_bound_kernel, dim3(rows.x, planes), dim3(64), 0, stream, M, Mp, N, sums, shift, diag_max, frobenius,
+            hipLaunchKernelGGL(delta, delta_grid, dim3(256), 0, stream, M, Mp, N, n_bits, g, grid, set, W, w.wmin, w.wmax, shift, Dh, tables + c, first + c);
+            launch_screen(stream, ScreenArgs{Hh, Dh, unscale, norms, sums, N, M, Mp, planes, R, plan.projections});
+            hipLaunchKernelGGL(screen_bound_kernel, dim3(rows.x, planes), dim3(64), 0, stream, M, Mp, N, sums, shift, w.wmin, w.wmax, diag_max, frobenius, plan.projections,
                                bound + (size_t)c * Mp);
             c += planes;
         }
@@ -930,9 +951,10 @@ static hipError_t search_rows(int M, int N, int n_bits, int q, int grid, const f
     hipLaunchKernelGGL(split_shift_kernel, dim3((w.Mp + 255) / 256 + 1), dim3(256), 0, stream, M, w.Mp, w.wmin, w.wmax, shift, N, H,
                        diag_max);
     const std::vector<Tying> tyings = all_tyings(n_bits, q);
-    const int planes = split && screen_pays(M, N, grid * (int)tyings.size()) ? screen_planes(M, N, (int)tyings.size()) : 0;
-    if (planes > 0) {
-        const hipError_t e = search_screened(M, N, n_bits, grid, tyings, planes, W, H, S, qbias, labels, w, stream);
+    const int candidates = grid * (int)tyings.size();
+    const ScreenPlan plan = split && screen_pays(M, N, candidates) ? screen_plan(M, N, (int)tyings.size(), candidates) : ScreenPlan{};
+    if (plan.planes > 0) {
+        const hipError_t e = search_screened(M, N, n_bits, grid, tyings, plan, W, H, S, qbias, labels, w, stream);
         if (e != hipSuccess) return e;
     } else {
         bool first = true;

@@ -6,18 +6,23 @@
 // error, and only those whose bound does not exceed the smallest error found go through the three products (bcq_quant.hip).
 // The winner and its error are the same bits as if all had.
 //
-// The bound.  Let D be d rounded to binary16 (row scale 2^s, largest magnitude below 2^15 or so), delta = d - D, G the binary16
-// values of H, f the computed form of D and G.
-//   * H is rounded up or down at random (a hash of the position decides), the chance of up being the distance from below: the errors
-//     of its entries are independent with mean 0 and lie in an interval of 2^-10 of the entry, so (Hoeffding) the form of D changes by
-//     more than 9/2 (sum over k <= c of (2^-10 H_kc D_k D_c)^2)^1/2 with a probability of 2 exp(-81/2) = 5e-18.  The sum is at most
-//     2^-21 max |D|^2 sum_c D_c^2 |H_c|^2, |H_c| the norm of a row.
+// The bound.  Let d have its row's scale 2^s (largest magnitude below 2^15 or so), D be d rounded to binary16, delta = D - d, G the
+// binary16 values of H, f the computed form of D and G.  H need not be positive semidefinite: what bounds the terms below is measured.
+//   * H and d are rounded up or down at random (a hash of the position decides), the chance of up being the distance from below: the
+//     errors of the entries are independent with mean 0 and lie in an interval of 2^-10 of the entry, so (Hoeffding) sums of them
+//     times anything fixed exceed 9/2 times the root of the sum of the squared intervals with a probability of 2 exp(-81/2) = 5e-18.
+//     - From H: sum over k <= c of (2^-10 H_kc D_k D_c)^2, at most 2^-21 max |D|^2 sum_c D_c^2 |H_c|^2, |H_c| the norm of a row.
+//     - From d: d H delta, at most 9/2 2^-10 max |d| |H d|.  |H d| is measured by projections: z^T H D with z Gaussian has the
+//       variance |H D|^2, and the mean square of 128 of them is below a quarter of it with a probability of (e^(3/4) / 4)^64 = 2e-18
+//       (of 64, where there is room for no more, below a ninth: (e^(8/9) / 9)^32 = 7e-19).
+//       R = H z is one more tile of columns.  (R and D are rounded, and |H delta| <= 2^-10 |H|_F |D|: 2^-9 |H|_F |D|, and 2^-23 a value
+//       of k for the sums of H z.)
+//     - delta H delta / 2, at most |H|_F |delta|^2 / 2.
+//     Values below 2^-14 of their scale are rounded once more, to nearest, by 2^-25 of it.
 //   * Rounding in binary32: sums of N terms, 2^-17 |H|_F |D|^2 (a form of the accumulators: 2^-24 a time, up to 2^10 times, and
-//     those do not all point the same way); that covers H's values below 2^-14 of their scale, too.
-//   * With H = 2 X X^T positive semidefinite, (d H d^T)^1/2 is a seminorm of d, so it is at least that of D less that of delta, which is
-//     at most |H|_F^1/2 |delta|, |delta| <= 2^-11 (1 + 2^-10) |D| + 2^-25-s N^1/2.
-//   * The error of the three products themselves: 2^-12 of it and 2^-18 |H|_F |D|^2.
-// Candidates that go on, 7168 x 7168, three bits, two planes, eight scales: 1.17 of 24 per row.
+//     those do not all point the same way).
+//   * The error of the three products themselves: 2^-12 of it and 2^-18 |H|_F |D|^2; and what falls below binary32's range.
+// Candidates that go on: see screen_pays.
 #pragma once
 #include "bcq_product.h"
 
@@ -28,9 +33,32 @@ struct ScreenArgs {
     const uint16_t *D;      // [plane][k / 8][row m (Mp)][8 values of k], a plane per candidate
     const float *unscale;   // [N] what takes a column's scale out again, in units of H (screen_unit)
     const float *norms;     // [N] squared norms of H's rows, in units of H
-    float *sums;            // [plane][4][Mp], zero before: form, sum of D^2, sum of D^2 norms, largest |D|, of D with its scale, H in its units
+    float *sums;            // [plane][kScreenSums][Mp], zero before: form, sum of D^2, sum of D^2 norms, largest |D|, sum of squared
+                            // projections, of D with its scale, H in its units
     int N, M, Mp, planes;
+    const uint16_t *R;      // [k / 8][projection][8 values of k], see screen_project_kernel
+    int projections;
 };
+
+constexpr int kScreenSums = 5, kProjections = 128, kFewProjections = 64;
+
+// 32 bits from the position of a value.  The multipliers are the first 32 bits of the fractional parts of the square roots of 2, 3, 11,
+// 17 and 19, those that are odd.
+__device__ __forceinline__ unsigned screen_hash(unsigned a, unsigned b, unsigned c)
+{
+    unsigned h = a * 0x6a09e667u + b * 0xbb67ae85u + c * 0x510e527fu;
+    h ^= h >> 17;
+    h *= 0x1f83d9abu;
+    h ^= h >> 14;
+    h *= 0x5be0cd19u;
+    return h ^ (h >> 16);
+}
+
+// x at random up or down to 11 significant bits, by 13 random bits; one that is not finite stays so.
+__device__ __forceinline__ float screen_round(float x, unsigned random)
+{
+    return __uint_as_float((__float_as_uint(x) + (random & 0x1fffu)) & ~0x1fffu);
+}
 
 // H is taken in units of 2^e, e the exponent of the largest value on its diagonal: the squares of values far from 1 have no
 // binary32 numbers, and a bound without its norms is none.
@@ -64,7 +92,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void screen_kernel(ScreenArgs p)
     // Tiles.  Those of the last columns have the longest k range and come first; the tiles of rows of one tile of columns are dealt
     // to the eight XCDs (workgroup numbers go round them) in contiguous ranges, cut at a place that moves with the column.
     const int ntc = (p.N + kRows - 1) / kRows, per_plane = (p.M + kCols - 1) / kCols, ntm = p.planes * per_plane, xcd = blockIdx.x & 7;
-    int j = blockIdx.x >> 3, tc = ntc - 1, tm = 0;
+    int j = blockIdx.x >> 3, tc = ntc, tm = 0;  // (tile ntc of columns: the projections)
     for (; tc >= 0; --tc) {
         const int cut = (5 * tc) & 7;
         const int from = xcd == 0 ? 0 : (xcd * ntm + cut) >> 3, to = xcd == 7 ? ntm : ((xcd + 1) * ntm + cut) >> 3;
@@ -74,13 +102,14 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void screen_kernel(ScreenArgs p)
     }
     if (tc < 0) return;
     const int plane = tm / per_plane, c0 = tc * kRows, m0 = (tm - plane * per_plane) * kCols;
+    const bool projects = tc == ntc;
     p.D += (size_t)plane * p.N * p.Mp;
-    p.sums += (size_t)plane * 4 * p.Mp;
+    p.sums += (size_t)plane * kScreenSums * p.Mp;
     const int k_end = p.N < c0 + kRows ? p.N : c0 + kRows, steps = (k_end + 31) / 32;
 
     const bool of_d = wave >= kWaves / 2;
-    const uint16_t *const source = of_d ? p.D : p.H;
-    const int pitch = of_d ? p.Mp : p.N, first = of_d ? m0 : c0;
+    const uint16_t *const source = of_d ? p.D : projects ? p.R : p.H;
+    const int pitch = of_d ? p.Mp : projects ? p.projections : p.N, first = of_d ? m0 : projects ? 0 : c0;
     const int bytes = 16 * (pitch - first < kRows ? pitch - first : kRows);
     auto copy = [&](auto &stage, int step) PROD_INLINE {
 #pragma unroll
@@ -140,6 +169,21 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void screen_kernel(ScreenArgs p)
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
     // element i of an accumulator: column c 4 hi + i, row m lo
+    if (projects) {  // (those beyond the last one are zeros)
+#pragma unroll
+        for (int y = 0; y < TB; ++y) {
+            const int m = m0 + 16 * (wc * TB + y) + lo;
+            float squares = 0.f;
+#pragma unroll
+            for (int x = 0; x < TA; ++x)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) squares = fmaf(acc[x][y][i], acc[x][y][i], squares);
+#pragma unroll
+            for (int s = 16; s < 64; s <<= 1) squares += __shfl_xor(squares, s);
+            if (hi == 0 && m < p.M) atomicAdd(p.sums + 4 * (size_t)p.Mp + m, squares);
+        }
+        return;
+    }
     float *const red = reinterpret_cast<float *>(&st0[0][0][0]);  // [WR][4][kCols]
     const __amdgpu_buffer_rsrc_t d_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t *>(p.D + ((size_t)(c0 >> 3) * p.Mp + m0) * 8), 0,
@@ -210,7 +254,7 @@ static inline int screen_tile(const ScreenArgs &p)
 static void launch_screen(hipStream_t stream, const ScreenArgs &p)
 {
     const int tile = screen_tile(p);
-    const int ntc = (p.N + tile - 1) / tile, ntm = p.planes * ((p.M + tile - 1) / tile);
+    const int ntc = (p.N + tile - 1) / tile + 1, ntm = p.planes * ((p.M + tile - 1) / tile);
     const dim3 grid((unsigned)(8 * ntc * (ntm / 8 + 1)));
     if (tile == kScreenTile) hipLaunchKernelGGL((screen_kernel<8, 4, 2, 4>), grid, dim3(512), 0, stream, p);
     else hipLaunchKernelGGL((screen_kernel<4, 4, 2, 2>), grid, dim3(256), 0, stream, p);
@@ -243,9 +287,7 @@ __global__ __launch_bounds__(256) void screen_h_kernel(int N, const float *__res
         for (int j = 0; j < 8; ++j) {
             const float x = (k0 + j == c ? 0.5f : 1.0f) * v[j] * s * s2;
             // at random up or down to the 11 bits of a binary16 number (below 2^-14 it is rounded once more, to nearest)
-            unsigned h = (unsigned)(k0 + j) * 0x9e3779b1u + (unsigned)c * 0x85ebca77u;
-            h ^= h >> 15; h *= 0x2c1b3c6du; h ^= h >> 12; h *= 0x297a2d39u; h ^= h >> 15;
-            const float up = __uint_as_float((__float_as_uint(x) + (h & 0x1fffu)) & ~0x1fffu);
+            const float up = screen_round(x, screen_hash((unsigned)(k0 + j), (unsigned)c, 0u));
             const unsigned half = __builtin_bit_cast(unsigned short, (_Float16)(fabsf(x) < INFINITY ? up : x));
             packed[j >> 1] = j & 1 ? packed[j >> 1] | half << 16 : half;
             const float square = (v[j] * unit) * (v[j] * unit);
@@ -263,9 +305,21 @@ __global__ __launch_bounds__(256) void screen_h_kernel(int N, const float *__res
     if (wave == 0 && c < N) atomicAdd(norms + c, sums[threadIdx.x] + sums[threadIdx.x + 64] + sums[threadIdx.x + 128] + sums[threadIdx.x + 192]);
 }
 
-// frobenius[0] = |H|_F in units of H, with something added for the roundings of the norms
-__global__ __launch_bounds__(1024) void screen_frobenius_kernel(int N, const float *__restrict__ norms, float *__restrict__ frobenius)
+// The first workgroup: frobenius[0] = |H|_F in units of H, with something added for the roundings of the norms.  The others: z [N]
+// [projection] standard normal (Box and Muller's transform of two hashes).
+__global__ __launch_bounds__(1024) void screen_frobenius_kernel(int N, const float *__restrict__ norms, float *__restrict__ frobenius,
+                                                                float *__restrict__ z, int projections)
 {
+    if (blockIdx.x > 0) {
+        const unsigned i = (blockIdx.x - 1) * 1024 + threadIdx.x;  // a pair each
+        if (i >= (unsigned)N * ((unsigned)projections / 2)) return;
+        const float u = ((float)(screen_hash(i, 0u, 1u) >> 9) + 0.5f) * 0x1p-23f, t = (float)(screen_hash(i, 1u, 1u) >> 8) * 0x1p-24f;
+        const float r = sqrtf(-2.0f * logf(u));
+        float sine, cosine;
+        sincosf(6.2831853f * t, &sine, &cosine);
+        *reinterpret_cast<prod_f32x2 *>(z + 2 * (size_t)i) = prod_f32x2{r * cosine, r * sine};
+        return;
+    }
     __shared__ double part[16];
     double s = 0.0;
     for (int i = threadIdx.x; i < N; i += 1024) s += norms[i];
@@ -279,26 +333,110 @@ __global__ __launch_bounds__(1024) void screen_frobenius_kernel(int N, const flo
     }
 }
 
+// Exponent of the scale of R: its values, at most about 6 |H|_F, stay below 2^15.
+__device__ __forceinline__ int screen_project_shift(float frobenius)
+{
+    return frobenius > 0.0f ? 11 - ((int)(__float_as_uint(frobenius) >> 23) - 127) : 0;
+}
+
+// R = H z in units of H, as binary16 numbers in the operand layout.  H is symmetric and its upper triangle is what is read.  A workgroup
+// takes 32 rows, a step 32 columns of H, a wave 32 of the projections; binary32 matrix instructions.
+__global__ __launch_bounds__(256) void screen_project_kernel(int N, const float *__restrict__ H, const float *__restrict__ diag_max,
+                                                             const float *__restrict__ frobenius, const float *__restrict__ z,
+                                                             uint16_t *__restrict__ R, int projections)
+{
+    __shared__ __attribute__((aligned(16))) float Hs[32][40], Zs[32][kProjections + 8];  // [column of H][row, projection]
+    const int tid = threadIdx.x, lane = tid & 63, lo = lane & 15, hi = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int k0 = 32 * blockIdx.x, a = tid >> 3, b = 4 * (tid & 7);
+    const float unit = ldexpf(1.0f, -screen_unit(*diag_max)), scale = ldexpf(1.0f, screen_project_shift(*frobenius));
+    prod_f32x4 h, v[4];
+    auto request = [&](int c0) PROD_INLINE {  // (N is a multiple of 8)
+        h = prod_f32x4{0.f, 0.f, 0.f, 0.f};
+        if (c0 == k0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int r = a < b + i ? a : b + i, c = a < b + i ? b + i : a;
+                if (k0 + c < N) h[i] = H[(size_t)(k0 + r) * N + k0 + c];
+            }
+        } else {  // rows k0 + a, columns c0 + b .. of the matrix above the diagonal, or the other way round
+            const int r = c0 > k0 ? k0 : c0, c = c0 > k0 ? c0 : k0;
+            if (r + a < N && c + b < N) h = *reinterpret_cast<const prod_f32x4 *>(H + (size_t)(r + a) * N + c + b);
+        }
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+            const int e = tid + 256 * n, c = c0 + (e >> 5), j = 4 * (e & 31);
+            v[n] = prod_f32x4{0.f, 0.f, 0.f, 0.f};
+            if (c < N && j < projections) v[n] = *reinterpret_cast<const prod_f32x4 *>(z + (size_t)c * projections + j);
+        }
+    };
+    prod_f32x4 acc[2][2];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[t >> 1][t & 1] = prod_f32x4{0.f, 0.f, 0.f, 0.f};
+    request(0);
+    for (int c0 = 0; c0 < N; c0 += 32) {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (c0 > k0) Hs[b + i][a] = h[i] * unit;
+            else Hs[a][b + i] = h[i] * unit;  // (its diagonal block is symmetric)
+        }
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+            const int e = tid + 256 * n;
+            *reinterpret_cast<prod_f32x4 *>(&Zs[e >> 5][4 * (e & 31)]) = v[n];
+        }
+        __syncthreads();
+        if (c0 + 32 < N) request(c0 + 32);
+#pragma unroll
+        for (int c = 0; c < 32; c += 4) {
+            float x[2], y[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                x[t] = Hs[c + hi][16 * t + lo];
+                y[t] = Zs[c + hi][32 * wave + 16 * t + lo];
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                acc[t >> 1][t & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t >> 1], y[t & 1], acc[t >> 1][t & 1], 0, 0, 0);
+        }
+    }
+    // element i: row 16 t + 4 hi + i, projection lo of its 16
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const int k = k0 + 16 * (t >> 1) + 4 * hi, j = 32 * wave + 16 * (t & 1) + lo;
+        const prod_f32x4 r = acc[t >> 1][t & 1];
+        const unsigned low = __builtin_bit_cast(unsigned, prod_f16x2{(_Float16)(r[0] * scale), (_Float16)(r[1] * scale)});
+        const unsigned high = __builtin_bit_cast(unsigned, prod_f16x2{(_Float16)(r[2] * scale), (_Float16)(r[3] * scale)});
+        if (k < N && j < projections)
+            *reinterpret_cast<prod_u32x2 *>(R + ((size_t)(k >> 3) * projections + j) * 8 + (k & 4)) = prod_u32x2{low, high};
+    }
+}
+
 // Lower bound of the error of the candidate of each plane (blockIdx.y), per row; leaves the sums zero.
 __global__ __launch_bounds__(64) void screen_bound_kernel(int M, int Mp, int N, float *__restrict__ sums, const int *__restrict__ shift,
+                                                          const float *__restrict__ wmin, const float *__restrict__ wmax,
                                                           const float *__restrict__ diag_max, const float *__restrict__ frobenius,
-                                                          float *__restrict__ bound)
+                                                          int projections, float *__restrict__ bound)
 {
     const int m = blockIdx.x * 64 + threadIdx.x;
     if (m >= M) return;
-    float *const mine = sums + (size_t)blockIdx.y * 4 * Mp + m;
-    const double form = mine[0], weighted = mine[2 * (size_t)Mp], most = mine[3 * (size_t)Mp], fro = *frobenius;
-    const double squares = mine[Mp] * (1.0 + 0x1p-10);
+    float *const mine = sums + (size_t)blockIdx.y * kScreenSums * Mp + m;
+    const double form = mine[0], weighted = mine[2 * (size_t)Mp], most = mine[3 * (size_t)Mp], projected = mine[4 * (size_t)Mp];
+    const double squares = mine[Mp] * (1.0 + 0x1p-10), fro = *frobenius, length = sqrt(squares), few = sqrt((double)N);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) mine[k * (size_t)Mp] = 0.0f;
+    for (int k = 0; k < kScreenSums; ++k) mine[k * (size_t)Mp] = 0.0f;
+    const double hd = (projections == kProjections ? 2.0 : 3.0) * (1.0 + 0x1p-9) * sqrt(projected / projections) * ldexp(1.0, -screen_project_shift(*frobenius)) +
+                      (0x1p-9 + N * 0x1p-23) * fro * length;
+    const double delta = 0x1p-10 * (1.0 + 0x1p-9) * length + 0x1p-24 * few;
     const double of_h = 4.5 * 0x1p-10 * sqrt(0.5) * (1.0 + 0x1p-9) * most * sqrt(weighted);
-    const double low = form - of_h - 0x1p-17 * fro * squares;
-    const double delta = 0x1p-11 * (1.0 + 0x1p-9) * sqrt(squares) + 0x1p-25 * sqrt((double)N);
-    const double root = sqrt(2.0 * (low > 0.0 ? low : 0.0)) - sqrt(fro) * delta;
-    double v = root > 0.0 ? 0.5 * root * root * (1.0 - 0x1p-12) - 0x1p-18 * fro * squares : 0.0;
-    v = ldexp(v > 0.0 ? v : 0.0, screen_unit(*diag_max) - 2 * shift[m]);
+    const double of_d = hd * (4.5 * (0x1p-10 * (1.0 + 0x1p-9) * most + 0x1p-24) + 0x1p-25 * few) + 0.5 * fro * delta * delta;
+    const double rounding = (0x1p-17 + 0x1p-18) * fro * squares + 0x1p-12 * fabs(form);
+    const int s = shift[m];
+    double v = ldexp(form - of_h - of_d - rounding, screen_unit(*diag_max) - 2 * s) - ldexp(1.0, -130 + (s < 0 ? -s : 0));
+    if (!(wmax[m] > wmin[m]) || fro == 0.0) v = 0.0;  // d or H is zero, and the error nothing else
     // (a form that is not finite says nothing; infinity would say that the candidate is done with)
-    bound[(size_t)blockIdx.y * Mp + m] = !(fabs(form) < (double)INFINITY) || !(v < 0x1p126) ? 0.0f : (float)(v * (1.0 - 0x1p-23));
+    bound[(size_t)blockIdx.y * Mp + m] = !(fabs(form) < (double)INFINITY) || !(fabs(v) < 0x1p126) ? -INFINITY : (float)(v - fabs(v) * 0x1p-23);
 }
 
 }  // namespace bcq

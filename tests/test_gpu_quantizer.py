@@ -171,12 +171,15 @@ def _search(W, H, n, q, grid):
 @pytest.mark.parametrize("M,N,n,q,grid,kind", [
     (256, 256, 3, 2, 3, "samples"), (257, 264, 4, 3, 2, "samples"), (700, 520, 3, 2, 2, "loud"), (513, 776, 2, 2, 4, "samples"),
     (300, 512, 5, 3, 3, "samples"), (400, 1032, 3, 2, 2, "one direction"), (260, 640, 8, 2, 1, "one direction"), (300, 264, 4, 2, 2, "zero"),
-    (2048, 320, 3, 2, 2, "few samples"), (256, 736, 3, 2, 4, "indefinite"), (300, 296, 3, 2, 2, "infinite"), (1020, 776, 3, 2, 8, "tiny"), (510, 776, 3, 2, 3, "huge")])
+    (2048, 320, 3, 2, 2, "few samples"), (256, 736, 3, 2, 4, "indefinite"), (300, 296, 3, 2, 2, "infinite"), (1020, 776, 3, 2, 8, "tiny"), (510, 776, 3, 2, 3, "huge"),
+    (765, 736, 3, 2, 4, "very indefinite"), (510, 520, 4, 2, 3, "low rank"), (1020, 1032, 3, 2, 8, "16 bits"), (640, 2048, 3, 2, 8, "16 bits"),
+    (600, 264, 3, 2, 2, "no diagonal"), (512, 1024, 5, 3, 3, "16 bits"), (264, 760, 3, 2, 4, "very indefinite"), (256, 768, 3, 2, 5, "samples"),
+    (256, 776, 3, 2, 2, "samples")])
 def test_search_screened(M, N, n, q, grid, kind):
     """Layers of 256 rows or more are screened: a bound excludes candidates before they are evaluated.  The results are the bits of the
     search of at most 255 rows at a time, which evaluates all: at the edges of tiles, chunks of candidates (48) and planes, with
     rows that are constant, zero, tiny, huge or hold infinities and no numbers, and with Hessians that let the bound exclude nearly everything or
-    nothing."""
+    nothing, or that are not positive semidefinite (so that errors are negative, too)."""
     g = torch.Generator(device="cuda").manual_seed(7 * M + N + n)
     W = torch.randn((M, N), device="cuda", generator=g) * 0.02
     W *= 1.0 + 3.0 * (torch.rand((M, N), device="cuda", generator=g) < 0.01)
@@ -202,8 +205,18 @@ def test_search_screened(M, N, n, q, grid, kind):
     if kind == "infinite":
         H[17, 200] = H[200, 17] = float("inf")
     H = ((H + H.t()) * 0.5).contiguous()
-    if kind == "indefinite":  # not what the search is for; here the errors stay positive for nearly all rows
-        H.diagonal().sub_(0.3 * H.diagonal().mean())
+    if kind in ("indefinite", "very indefinite"):  # errors positive for nearly all rows, and of both signs
+        H.diagonal().sub_((0.3 if kind == "indefinite" else 1.0) * H.diagonal().mean())
+    if kind == "no diagonal":
+        H.fill_diagonal_(0.0)
+    if kind == "low rank":  # equal channels and weights that fall into line with them: errors of rounding, of either sign
+        X = torch.randn((8, N // 4), device="cuda", generator=g).repeat_interleave(4, 1)
+        X[:, 1::2] *= -1.0
+        H = 2.0 * (X.t().contiguous() @ X)
+        W[20:] = W[20:, ::2].repeat_interleave(2, 1)
+    if kind == "16 bits":  # a Hessian that was kept in bfloat16, with channel means: small eigenvalues of either sign
+        mean = 20.0 * torch.randn(N, device="cuda", generator=g)
+        H = (H + 2.0 * T * mean[:, None] * mean[None]).bfloat16().float()
     whole = _search(W, H, n, q, grid)
     for lo in range(0, M, 255):
         part = _search(W[lo:lo + 255].clone(), H, n, q, grid)
