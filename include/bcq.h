@@ -169,7 +169,7 @@ bcq_status bcq_from_linear(int32_t M, int32_t N, int32_t group, int32_t n_bits, 
  * BCQ_ERR_UNSUPPORTED (all three calls).
  * bcq_quant_search on 256 rows or more evaluates only the candidates that a lower bound of their error (one product of binary16
  * numbers rounded at random; any symmetric H) does not exclude.  The roundings of H and d break it with a probability of 1.2e-17 per
- * row and candidate; for those of its binary32 sums it allows 2^-17 |H|_F |d|^2, which is no worst case.
+ * row and candidate; for those of the binary32 sums it allows their worst case.
  * Integer decisions are those of binary64; the error sums and the compensation accumulate in
  * binary32 on the matrix cores, their operands split into pairs of binary16 numbers (sums
  * of up to 20 terms in binary32 throughout).  Against binary64 that measured no larger errors than binary32 matrix

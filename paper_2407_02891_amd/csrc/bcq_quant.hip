@@ -667,16 +667,16 @@ __global__ __launch_bounds__(256) void delta_kernel(int M, int Mp, int N, int n_
     }
 }
 
-// The same d for the screened search: of up to kPlanes tyings of one grid point, each a binary16 number rounded at random (see bcq_screen.h;
-// `seed` is the first one's number in the search), in planes of the operand layout; also fills the candidates' tables.  Bound: memory.  7168 x 7168, three tyings: 68 us each one by one, W
-// being read each time.
+// The same d for the screened search: of up to kPlanes tyings of one grid point, each a binary16 number rounded at random (see
+// bcq_screen.h), in planes of the operand layout; also fills the candidates' tables.  Bound: memory.  7168 x 7168, three tyings: 68 us each one by one, W
+// being read each time, 32 together, and 35 with the random roundings.
 constexpr int kPlanes = 4;
 struct TyingSet { Tying t[kPlanes]; };
 template <int PLANES>
 __global__ __launch_bounds__(256) void delta_single_kernel(int M, int Mp, int N, int n_bits, int g, int grid, TyingSet set,
                                                            const float *__restrict__ W, const float *__restrict__ wmin,
                                                            const float *__restrict__ wmax, const int *__restrict__ shift,
-                                                           uint16_t *__restrict__ out, CandidateTable *__restrict__ tables, int seed)
+                                                           uint16_t *__restrict__ out, CandidateTable *__restrict__ tables)
 {
     const int m = blockIdx.x * 64 + (threadIdx.x & 63), k0 = 8 * (blockIdx.y * 4 + (threadIdx.x >> 6));
     if (blockIdx.x == 0 && blockIdx.y == 0) {
@@ -698,11 +698,9 @@ __global__ __launch_bounds__(256) void delta_single_kernel(int M, int Mp, int N,
         const prod_f32x4 w0 = src[0], w1 = src[1];
         const double lo = wmin[m], S = grid_scale(lo, wmax[m], n_bits, g, grid), inv_s = 1.0 / S, top = (double)((1 << n_bits) - 1);
         const float s = ldexpf(1.0f, shift[m]);
-        unsigned random[PLANES][4];  // for two values each
+        unsigned random[4];  // for two values each, the same for all candidates (each has a bound of its own)
 #pragma unroll
-        for (int p = 0; p < PLANES; ++p)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) random[p][j] = screen_hash((unsigned)m, (unsigned)(k0 / 2 + j), (unsigned)(seed + p + 2));
+        for (int j = 0; j < 4; ++j) random[j] = screen_hash((unsigned)m, (unsigned)(k0 / 2 + j), 2u);
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const double w = j < 4 ? w0[j & 3] : w1[j & 3];
@@ -710,7 +708,7 @@ __global__ __launch_bounds__(256) void delta_single_kernel(int M, int Mp, int N,
 #pragma unroll
             for (int p = 0; p < PLANES; ++p) {
                 const int wq = n_bits <= 4 ? (int)(set.t[p].nibbles >> (4 * lin)) & 15 : nearest_choice(lin, set.t[p].choice, set.t[p].nchoice);
-                d[p][j] = (_Float16)screen_round((float)(S * wq + lo - w) * s, random[p][j >> 1] >> (16 * (j & 1)));
+                d[p][j] = (_Float16)screen_round((float)(S * wq + lo - w) * s, random[j >> 1] >> (16 * (j & 1)));
             }
         }
     }
@@ -882,7 +880,7 @@ static hipError_t search_screened(int M, int N, int n_bits, int grid, const std:
         hipLaunchKernelGGL(screen_h_kernel, dim3((N + 63) / 64, (N + 255) / 256), dim3(256), 0, stream, N, H, diag_max, Hh, unscale, norms);
         hipLaunchKernelGGL(screen_frobenius_kernel, dim3(1 + (N * (plan.projections / 2) + 1023) / 1024), dim3(1024), 0, stream, N, norms, frobenius, z,
                            plan.projections);
-        hipLaunchKernelGGL(screen_project_kernel, dim3((N + 31) / 32), dim3(256), 0, stream, N, H, diag_max, frobenius, z, R, plan.projections);
+        hipLaunchKernelGGL(screen_project_kernel, dim3((N + 31) / 32), dim3(512), 0, stream, N, H, diag_max, frobenius, z, R, plan.projections);
         for (int c = 0; c < candidates;) {
             // tyings of one grid point, as many as there are planes
             const int g = (first + c) / T, t0 = (first + c) % T;
@@ -892,7 +890,7 @@ static hipError_t search_screened(int M, int N, int n_bits, int grid, const std:
             for (int p = 0; p < planes; ++p) set.t[p] = tyings[t0 + p];
             const auto delta = planes == 1 ? delta_single_kernel<1> : planes == 2 ? delta_single_kernel<2>
                              : planes == 3 ? delta_single_kernel<3> : delta_single_kernel<4>;
-            hipLaunchKernelGGL(delta, delta_grid, dim3(256), 0, stream, M, Mp, N, n_bits, g, grid, set, W, w.wmin, w.wmax, shift, Dh, tables + c, first + c);
+            hipLaunchKernelGGL(delta, delta_grid, dim3(256), 0, stream, M, Mp, N, n_bits, g, grid, set, W, w.wmin, w.wmax, shift, Dh, tables + c);
             launch_screen(stream, ScreenArgs{Hh, Dh, unscale, norms, sums, N, M, Mp, planes, R, plan.projections});
             hipLaunchKernelGGL(screen_bound_kernel, dim3(rows.x, planes), dim3(64), 0, stream, M, Mp, N, sums, shift, w.wmin, w.wmax, diag_max, frobenius, plan.projections,
                                bound + (size_t)c * Mp);

@@ -19,9 +19,15 @@
 //       of k for the sums of H z.)
 //     - delta H delta / 2, at most |H|_F |delta|^2 / 2.
 //     Values below 2^-14 of their scale are rounded once more, to nearest, by 2^-25 of it.
-//   * Rounding in binary32: sums of N terms, 2^-17 |H|_F |D|^2 (a form of the accumulators: 2^-24 a time, up to 2^10 times, and
-//     those do not all point the same way).
-//   * The error of the three products themselves: 2^-12 of it and 2^-18 |H|_F |D|^2; and what falls below binary32's range.
+//   * Rounding in binary32, the worst case.  A matrix instruction over 32 values of k rounds its accumulator twice, by 2^-24 of what it
+//     holds, and column c's counts D_c times.  What the accumulators hold is measured: every 256 values of k a wave takes the largest of a
+//     row's 32 columns in a lane, A; T = sum |D_c| A.  In between they hold at most |H_c'| |D'| more (norms over those 256), and the
+//     sum of |D_c| |H_c'| |D'| over all is at most |H|_F |D|^2.  So the form is off by N / 16 roundings of T and 16 of |H|_F |D|^2;
+//     the three products, whose result counts, round three times as often and start anew every 1024 values, from what the accumulators
+//     hold there: 3/8 N roundings of T, 48 of |H|_F |D|^2.  What follows adds up to less than N / 16 + 128 roundings of T.  The sum of 32
+//     products in an instruction is taken to be off by 15 roundings of their magnitudes (15 |H|_F |D|^2, twice), and splitting the
+//     operands of the three products leaves 2^-22.  With |H|_F / sqrt(2) for a triangle: 5/4 2^-18 |H|_F |D|^2; that T comes from rounded
+//     values adds 2^-35 a value of k.  What falls below binary32's range is added, too.
 // Candidates that go on: see screen_pays.
 #pragma once
 #include "bcq_product.h"
@@ -34,13 +40,13 @@ struct ScreenArgs {
     const float *unscale;   // [N] what takes a column's scale out again, in units of H (screen_unit)
     const float *norms;     // [N] squared norms of H's rows, in units of H
     float *sums;            // [plane][kScreenSums][Mp], zero before: form, sum of D^2, sum of D^2 norms, largest |D|, sum of squared
-                            // projections, of D with its scale, H in its units
+                            // projections, T, of D with its scale, H in its units
     int N, M, Mp, planes;
     const uint16_t *R;      // [k / 8][projection][8 values of k], see screen_project_kernel
     int projections;
 };
 
-constexpr int kScreenSums = 5, kProjections = 128, kFewProjections = 64;
+constexpr int kScreenSums = 6, kProjections = 128, kFewProjections = 64;
 
 // 32 bits from the position of a value.  The multipliers are the first 32 bits of the fractional parts of the square roots of 2, 3, 11,
 // 17 and 19, those that are odd.
@@ -74,7 +80,7 @@ __device__ __forceinline__ int screen_unit(float diag_max)
 // instruction takes them and are copied to LDS by buffer loads with an LDS destination, three steps of 32 values of k ahead in
 // four stages; the operands of the next step are read while this one is multiplied (an A operand's registers are
 // free as soon as its products are issued), so that nothing in the loop waits for what it asked for.  7168 x 7168: 309 us per
-// candidate, 1.2 PFLOP/s; registers alone sustain 1.8 with such values, 2.4 with zeros.
+// candidate, 1.2 PFLOP/s, and 339 with the projections and a look at the accumulators; registers alone sustain 1.8 with such values, 2.4 with zeros.
 template <int TA, int TB, int WR, int WC>
 __global__ __launch_bounds__(64 * WR * WC, 2) void screen_kernel(ScreenArgs p)
 {
@@ -135,6 +141,18 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void screen_kernel(ScreenArgs p)
     auto read_b = [&](auto &stage, int y) PROD_INLINE {
         return *reinterpret_cast<const prod_f16x8 *>(&stage[1][hi][(16 * (wc * TB + y) + lo) * 16]);
     };
+    float held[TB];  // largest magnitude per row in this lane's accumulators, every 256 values of k
+#pragma unroll
+    for (int y = 0; y < TB; ++y) held[y] = 0.f;
+    auto look = [&]() PROD_INLINE {
+#pragma unroll
+        for (int x = 0; x < TA; ++x)
+#pragma unroll
+            for (int y = 0; y < TB; ++y) {
+                held[y] = fmaxf(fmaxf(held[y], fabsf(acc[x][y][0])), fabsf(acc[x][y][1]));
+                held[y] = fmaxf(fmaxf(held[y], fabsf(acc[x][y][2])), fabsf(acc[x][y][3]));
+            }
+    };
     auto body = [&](int step, auto odd, auto &next, auto &ahead) PROD_INLINE {
         constexpr int kOdd = decltype(odd)::value;
         copy(ahead, step + 3);
@@ -165,9 +183,8 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void screen_kernel(ScreenArgs p)
         body(step + 1, odd, st2, st0);
         body(step + 2, even, st3, st1);
         body(step + 3, odd, st0, st2);
+        if (step & 4) look();
     }
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-
     // element i of an accumulator: column c 4 hi + i, row m lo
     if (projects) {  // (those beyond the last one are zeros)
 #pragma unroll
@@ -184,14 +201,16 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void screen_kernel(ScreenArgs p)
         }
         return;
     }
-    float *const red = reinterpret_cast<float *>(&st0[0][0][0]);  // [WR][4][kCols]
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    float *const red = reinterpret_cast<float *>(&st0[0][0][0]);  // [WR][5][kCols]
     const __amdgpu_buffer_rsrc_t d_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t *>(p.D + ((size_t)(c0 >> 3) * p.Mp + m0) * 8), 0,
         16 * ((((p.N < c0 + kRows ? p.N : c0 + kRows) - c0) / 8 - 1) * p.Mp + (p.Mp - m0)), kRawBufferFlags);
+    look();
 #pragma unroll
     for (int y = 0; y < TB; ++y) {
         const int m = 16 * (wc * TB + y) + lo;
-        float form = 0.f, squares = 0.f, weighted = 0.f, most = 0.f;
+        float form = 0.f, squares = 0.f, weighted = 0.f, most = 0.f, rounded = 0.f;
 #pragma unroll
         for (int x = 0; x < TA; ++x) {
             const int c = 16 * (wr * TA + x) + 4 * hi;
@@ -212,33 +231,37 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void screen_kernel(ScreenArgs p)
                 squares = fmaf(d, d, squares);
                 weighted = fmaf(d * d, nr[i], weighted);
                 most = fmaxf(most, fabsf(d));
+                rounded = fmaf(fabsf(d), un[i], rounded);
             }
         }
+        rounded *= held[y];
 #pragma unroll
         for (int s = 16; s < 64; s <<= 1) {
+            rounded += __shfl_xor(rounded, s);
             form += __shfl_xor(form, s);
             squares += __shfl_xor(squares, s);
             weighted += __shfl_xor(weighted, s);
             most = fmaxf(most, __shfl_xor(most, s));
         }
         if (hi == 0) {
-            red[(wr * 4 + 0) * kCols + m] = form;
-            red[(wr * 4 + 1) * kCols + m] = squares;
-            red[(wr * 4 + 2) * kCols + m] = weighted;
-            red[(wr * 4 + 3) * kCols + m] = most;
+            red[(wr * 5 + 0) * kCols + m] = form;
+            red[(wr * 5 + 1) * kCols + m] = squares;
+            red[(wr * 5 + 2) * kCols + m] = weighted;
+            red[(wr * 5 + 3) * kCols + m] = most;
+            red[(wr * 5 + 4) * kCols + m] = rounded;
         }
     }
     __syncthreads();
-    for (int e = tid; e < 4 * kCols; e += 64 * kWaves) {
+    for (int e = tid; e < 5 * kCols; e += 64 * kWaves) {
         const int what = e / kCols, m = e % kCols;
         float v = red[what * kCols + m];
 #pragma unroll
         for (int w = 1; w < WR; ++w) {
-            const float o = red[(w * 4 + what) * kCols + m];
+            const float o = red[(w * 5 + what) * kCols + m];
             v = what == 3 ? fmaxf(v, o) : v + o;
         }
         if (m0 + m >= p.M) continue;
-        float *const to = p.sums + (size_t)what * p.Mp + m0 + m;
+        float *const to = p.sums + (size_t)(what < 4 ? what : 5) * p.Mp + m0 + m;
         if (what == 3) atomicMax(reinterpret_cast<unsigned *>(to), __float_as_uint(v));
         else atomicAdd(to, v);
     }
@@ -340,13 +363,14 @@ __device__ __forceinline__ int screen_project_shift(float frobenius)
 }
 
 // R = H z in units of H, as binary16 numbers in the operand layout.  H is symmetric and its upper triangle is what is read.  A workgroup
-// takes 32 rows, a step 32 columns of H, a wave 32 of the projections; binary32 matrix instructions.
-__global__ __launch_bounds__(256) void screen_project_kernel(int N, const float *__restrict__ H, const float *__restrict__ diag_max,
+// takes 32 rows, a step 64 columns of H, half of the waves 32 of them, a wave 32 of the projections; binary32 matrix instructions.
+// Bound: what arrives, a step at a time and with a workgroup per compute unit (32 columns a step: 273 us at 7168, now 216).
+__global__ __launch_bounds__(512) void screen_project_kernel(int N, const float *__restrict__ H, const float *__restrict__ diag_max,
                                                              const float *__restrict__ frobenius, const float *__restrict__ z,
                                                              uint16_t *__restrict__ R, int projections)
 {
-    __shared__ __attribute__((aligned(16))) float Hs[32][40], Zs[32][kProjections + 8];  // [column of H][row, projection]
-    const int tid = threadIdx.x, lane = tid & 63, lo = lane & 15, hi = lane >> 4;
+    __shared__ __attribute__((aligned(16))) float Hs[2][32][40], Zs[2][32][kProjections + 8];  // [half][column of H][row, projection]
+    const int tid = threadIdx.x & 255, lane = tid & 63, lo = lane & 15, hi = lane >> 4, half = threadIdx.x >> 8;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int k0 = 32 * blockIdx.x, a = tid >> 3, b = 4 * (tid & 7);
     const float unit = ldexpf(1.0f, -screen_unit(*diag_max)), scale = ldexpf(1.0f, screen_project_shift(*frobenius));
@@ -373,28 +397,28 @@ __global__ __launch_bounds__(256) void screen_project_kernel(int N, const float 
     prod_f32x4 acc[2][2];
 #pragma unroll
     for (int t = 0; t < 4; ++t) acc[t >> 1][t & 1] = prod_f32x4{0.f, 0.f, 0.f, 0.f};
-    request(0);
-    for (int c0 = 0; c0 < N; c0 += 32) {
+    request(32 * half);
+    for (int c0 = 32 * half; c0 - 32 * half < N; c0 += 64) {
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            if (c0 > k0) Hs[b + i][a] = h[i] * unit;
-            else Hs[a][b + i] = h[i] * unit;  // (its diagonal block is symmetric)
+            if (c0 > k0) Hs[half][b + i][a] = h[i] * unit;
+            else Hs[half][a][b + i] = h[i] * unit;  // (its diagonal block is symmetric)
         }
 #pragma unroll
         for (int n = 0; n < 4; ++n) {
             const int e = tid + 256 * n;
-            *reinterpret_cast<prod_f32x4 *>(&Zs[e >> 5][4 * (e & 31)]) = v[n];
+            *reinterpret_cast<prod_f32x4 *>(&Zs[half][e >> 5][4 * (e & 31)]) = v[n];
         }
         __syncthreads();
-        if (c0 + 32 < N) request(c0 + 32);
+        request(c0 + 64);  // (behind the last one: zeros)
 #pragma unroll
         for (int c = 0; c < 32; c += 4) {
             float x[2], y[2];
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
-                x[t] = Hs[c + hi][16 * t + lo];
-                y[t] = Zs[c + hi][32 * wave + 16 * t + lo];
+                x[t] = Hs[half][c + hi][16 * t + lo];
+                y[t] = Zs[half][c + hi][32 * wave + 16 * t + lo];
             }
 #pragma unroll
             for (int t = 0; t < 4; ++t)
@@ -402,10 +426,18 @@ __global__ __launch_bounds__(256) void screen_project_kernel(int N, const float 
         }
     }
     // element i: row 16 t + 4 hi + i, projection lo of its 16
+    __syncthreads();
+    auto *const other = reinterpret_cast<prod_f32x4 *>(&Zs[0][0][0]);  // [tile][thread]
+    if (half) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) other[256 * t + tid] = acc[t >> 1][t & 1];
+    }
+    __syncthreads();
+    if (half) return;
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
         const int k = k0 + 16 * (t >> 1) + 4 * hi, j = 32 * wave + 16 * (t & 1) + lo;
-        const prod_f32x4 r = acc[t >> 1][t & 1];
+        const prod_f32x4 r = acc[t >> 1][t & 1] + other[256 * t + tid];
         const unsigned low = __builtin_bit_cast(unsigned, prod_f16x2{(_Float16)(r[0] * scale), (_Float16)(r[1] * scale)});
         const unsigned high = __builtin_bit_cast(unsigned, prod_f16x2{(_Float16)(r[2] * scale), (_Float16)(r[3] * scale)});
         if (k < N && j < projections)
@@ -423,7 +455,7 @@ __global__ __launch_bounds__(64) void screen_bound_kernel(int M, int Mp, int N, 
     if (m >= M) return;
     float *const mine = sums + (size_t)blockIdx.y * kScreenSums * Mp + m;
     const double form = mine[0], weighted = mine[2 * (size_t)Mp], most = mine[3 * (size_t)Mp], projected = mine[4 * (size_t)Mp];
-    const double squares = mine[Mp] * (1.0 + 0x1p-10), fro = *frobenius, length = sqrt(squares), few = sqrt((double)N);
+    const double held = mine[5 * (size_t)Mp] * (1.0 + 0x1p-10), squares = mine[Mp] * (1.0 + 0x1p-10), fro = *frobenius, length = sqrt(squares), few = sqrt((double)N);
 #pragma unroll
     for (int k = 0; k < kScreenSums; ++k) mine[k * (size_t)Mp] = 0.0f;
     const double hd = (projections == kProjections ? 2.0 : 3.0) * (1.0 + 0x1p-9) * sqrt(projected / projections) * ldexp(1.0, -screen_project_shift(*frobenius)) +
@@ -431,7 +463,7 @@ __global__ __launch_bounds__(64) void screen_bound_kernel(int M, int Mp, int N, 
     const double delta = 0x1p-10 * (1.0 + 0x1p-9) * length + 0x1p-24 * few;
     const double of_h = 4.5 * 0x1p-10 * sqrt(0.5) * (1.0 + 0x1p-9) * most * sqrt(weighted);
     const double of_d = hd * (4.5 * (0x1p-10 * (1.0 + 0x1p-9) * most + 0x1p-24) + 0x1p-25 * few) + 0.5 * fro * delta * delta;
-    const double rounding = (0x1p-17 + 0x1p-18) * fro * squares + 0x1p-12 * fabs(form);
+    const double rounding = (0.5 * N + 128.0) * 0x1p-24 * held + (0x1.4p-18 + N * 0x1p-35) * fro * squares;
     const int s = shift[m];
     double v = ldexp(form - of_h - of_d - rounding, screen_unit(*diag_max) - 2 * s) - ldexp(1.0, -130 + (s < 0 ? -s : 0));
     if (!(wmax[m] > wmin[m]) || fro == 0.0) v = 0.0;  // d or H is zero, and the error nothing else

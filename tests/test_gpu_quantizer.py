@@ -174,7 +174,7 @@ def _search(W, H, n, q, grid):
     (2048, 320, 3, 2, 2, "few samples"), (256, 736, 3, 2, 4, "indefinite"), (300, 296, 3, 2, 2, "infinite"), (1020, 776, 3, 2, 8, "tiny"), (510, 776, 3, 2, 3, "huge"),
     (765, 736, 3, 2, 4, "very indefinite"), (510, 520, 4, 2, 3, "low rank"), (1020, 1032, 3, 2, 8, "16 bits"), (640, 2048, 3, 2, 8, "16 bits"),
     (600, 264, 3, 2, 2, "no diagonal"), (512, 1024, 5, 3, 3, "16 bits"), (264, 760, 3, 2, 4, "very indefinite"), (256, 768, 3, 2, 5, "samples"),
-    (256, 776, 3, 2, 2, "samples")])
+    (256, 776, 3, 2, 2, "samples"), (1400, 4096, 3, 2, 3, "one direction")])
 def test_search_screened(M, N, n, q, grid, kind):
     """Layers of 256 rows or more are screened: a bound excludes candidates before they are evaluated.  The results are the bits of the
     search of at most 255 rows at a time, which evaluates all: at the edges of tiles, chunks of candidates (48) and planes, with
