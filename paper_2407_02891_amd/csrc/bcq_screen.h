@@ -268,10 +268,10 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void screen_kernel(ScreenArgs p)
 }
 
 // 256 x 256 tiles where there are enough of them to fill the chip.
-constexpr int kScreenTile = 256, kScreenSmallTile = 128;
+constexpr int kScreenTile = 256, kScreenSmallTile = 128, kScreenLargeFrom = 256;
 static inline int screen_tile(const ScreenArgs &p)
 {
-    return ((p.N + kScreenTile - 1) / kScreenTile) * p.planes * ((p.M + kScreenTile - 1) / kScreenTile) >= 256 ? kScreenTile : kScreenSmallTile;
+    return ((p.N + kScreenTile - 1) / kScreenTile) * p.planes * ((p.M + kScreenTile - 1) / kScreenTile) >= kScreenLargeFrom ? kScreenTile : kScreenSmallTile;
 }
 
 static void launch_screen(hipStream_t stream, const ScreenArgs &p)

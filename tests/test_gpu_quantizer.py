@@ -16,6 +16,10 @@ the error compensation in binary32, so:
     relative error 2^-24 each (twice that for the rounding of the products);
   * fusion with a tying per row: bit-exact against oracle/fuse.py.
 """
+import functools
+import os
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -23,6 +27,7 @@ import torch
 import bcq_synth
 import paper_2407_02891_amd as bcq
 from oracle import fuse, quantizer, ref
+from paper_2407_02891_amd import build as hip_build
 from tests import gpu_util as U
 
 pytestmark = pytest.mark.gpu
@@ -174,12 +179,16 @@ def _search(W, H, n, q, grid):
     (2048, 320, 3, 2, 2, "few samples"), (256, 736, 3, 2, 4, "indefinite"), (300, 296, 3, 2, 2, "infinite"), (1020, 776, 3, 2, 8, "tiny"), (510, 776, 3, 2, 3, "huge"),
     (765, 736, 3, 2, 4, "very indefinite"), (510, 520, 4, 2, 3, "low rank"), (1020, 1032, 3, 2, 8, "16 bits"), (640, 2048, 3, 2, 8, "16 bits"),
     (600, 264, 3, 2, 2, "no diagonal"), (512, 1024, 5, 3, 3, "16 bits"), (264, 760, 3, 2, 4, "very indefinite"), (256, 768, 3, 2, 5, "samples"),
-    (256, 776, 3, 2, 2, "samples"), (1400, 4096, 3, 2, 3, "one direction")])
+    (256, 776, 3, 2, 2, "samples"), (1400, 4096, 3, 2, 3, "one direction"),
+    (5003, 1288, 3, 2, 3, "samples"), (2500, 3592, 4, 2, 2, "few samples")])
 def test_search_screened(M, N, n, q, grid, kind):
     """Layers of 256 rows or more are screened: a bound excludes candidates before they are evaluated.  The results are the bits of the
     search of at most 255 rows at a time, which evaluates all: at the edges of tiles, chunks of candidates (48) and planes, with
     rows that are constant, zero, tiny, huge or hold infinities and no numbers, and with Hessians that let the bound exclude nearly everything or
     nothing, or that are not positive semidefinite (so that errors are negative, too)."""
+    if M > 2048:  # these are for the large tiles
+        tile = _constant("kScreenTile")
+        assert -(-N // tile) * -(-M // tile) * {1288: 3, 3592: 2}[N] >= _constant("kScreenLargeFrom")
     g = torch.Generator(device="cuda").manual_seed(7 * M + N + n)
     W = torch.randn((M, N), device="cuda", generator=g) * 0.02
     W *= 1.0 + 3.0 * (torch.rand((M, N), device="cuda", generator=g) < 0.01)
@@ -281,6 +290,47 @@ def test_gptq_blocks_and_panels(M, N, n, q):
     first = np.array([quantizer.quant_row(W32[m, :1].astype(np.float64), S64[m], b64[m], choices[m], n)[0] for m in range(M)])
     assert np.array_equal(Wq[:, 0], first)
     _assert_gptq_explained(W32, U32, S64, b64, choices, n, Wq, f"gptq {M}x{N} n={n} q={q}")
+
+
+def _constant(name):
+    """A constant of the quantiser's source, so that a test of what it decides notices when it moves."""
+    text = open(os.path.join(hip_build.CSRC, "bcq_quant.hip")).read() + open(os.path.join(hip_build.CSRC, "bcq_screen.h")).read()
+    return int(re.search(r"\b%s = (\d+)[,;]" % name, text)[1])
+
+
+@functools.lru_cache(maxsize=1)
+def _large_factor(N):
+    return quantizer.cholesky_factor(_layer(1, N, seed=N)[1]).astype(np.float32)
+
+
+@pytest.mark.parametrize("n,q", [(3, 2), (4, 3), (5, 3)])
+def test_gptq_far_columns_beside_a_panel(n, q):
+    """Layers with enough tiles beyond a panel have them updated by its errors in the launch of the next panel: two panels with such
+    an update (so that both buffers of errors take both parts), two without, a ragged last one and ragged rows."""
+    M, N = 7001, 2948
+
+    def tiles(p1):  # beyond the panel that ends at p1
+        return ((N - p1 + 127) // 128 * ((M + 127) // 128) + 7) // 8 * 8
+
+    assert [tiles(p1) >= _constant("kBesideTiles") for p1 in (1024, 1536, 2048, 2560)] == [True, True, False, False]
+    g = torch.Generator(device="cuda").manual_seed(n)
+    W = torch.randn((M, N), device="cuda", generator=g) * 0.02
+    W *= 1.0 + 3.0 * (torch.rand((M, N), device="cuda", generator=g) < 0.01)
+    lo, hi = W.min(1).values, W.max(1).values
+    S, b = ((hi - lo) / (2 ** n - 1) * (0.6 + 0.8 * torch.rand(M, device="cuda", generator=g))).contiguous(), lo.contiguous()
+    parts = fuse.all_partitions(n, q)
+    pick = np.arange(M) % len(parts)
+    labels = np.stack([_labels_of(p, n) for p in parts])[pick]
+    w_int = torch.full((M, N), 255, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(bcq.quant_workspace_bytes(M, N), dtype=torch.uint8, device="cuda")
+    ws.fill_(0xff)
+    U32 = _large_factor(N)
+    bcq.quant_gptq(M, N, n, q, W, _dev(U32), S, b, _dev(labels), w_int, ws)
+    torch.cuda.synchronize()
+    rows = [0, 31, 32, 127, 128, 3583, 3584, 6911, 6912, 6999, 7000]
+    Wq = w_int[rows].cpu().numpy().astype(np.int64)
+    _assert_gptq_explained(W[rows].cpu().numpy(), U32, S[rows].double().cpu().numpy(), b[rows].double().cpu().numpy(),
+                           [fuse.bcchoice(parts[pick[m]], n) for m in rows], n, Wq, f"gptq {M}x{N} n={n} q={q}")
 
 
 @pytest.mark.parametrize("M,N", [(2 ** 23 + 2 ** 20 + 165, 132), (2 ** 20 + 37, 8)])
