@@ -670,7 +670,7 @@ __global__ __launch_bounds__(256) void delta_kernel(int M, int Mp, int N, int n_
 // The same d for the screened search: of up to kPlanes tyings of one grid point, each a binary16 number rounded at random (see
 // bcq_screen.h), in planes of the operand layout; also fills the candidates' tables.  Bound: memory.  7168 x 7168, three tyings: 68 us each one by one, W
 // being read each time, 32 together, and 35 with the random roundings.
-constexpr int kPlanes = 4;
+constexpr int kPlanes = 3;  // (the workspace holds 4 - N / M planes, for N <= M three)
 struct TyingSet { Tying t[kPlanes]; };
 template <int PLANES>
 __global__ __launch_bounds__(256) void delta_single_kernel(int M, int Mp, int N, int n_bits, int g, int grid, TyingSet set,
@@ -888,8 +888,7 @@ static hipError_t search_screened(int M, int N, int n_bits, int grid, const std:
             planes = planes < candidates - c ? planes : candidates - c;
             TyingSet set = {};
             for (int p = 0; p < planes; ++p) set.t[p] = tyings[t0 + p];
-            const auto delta = planes == 1 ? delta_single_kernel<1> : planes == 2 ? delta_single_kernel<2>
-                             : planes == 3 ? delta_single_kernel<3> : delta_single_kernel<4>;
+            const auto delta = planes == 1 ? delta_single_kernel<1> : planes == 2 ? delta_single_kernel<2> : delta_single_kernel<3>;
             hipLaunchKernelGGL(delta, delta_grid, dim3(256), 0, stream, M, Mp, N, n_bits, g, grid, set, W, w.wmin, w.wmax, shift, Dh, tables + c);
             launch_screen(stream, ScreenArgs{Hh, Dh, unscale, norms, sums, N, M, Mp, planes, R, plan.projections});
             hipLaunchKernelGGL(screen_bound_kernel, dim3(rows.x, planes), dim3(64), 0, stream, M, Mp, N, sums, shift, w.wmin, w.wmax, diag_max, frobenius, plan.projections,
