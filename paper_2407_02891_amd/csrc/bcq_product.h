@@ -92,7 +92,7 @@ struct ProductArgs {
     const int *split_shift; // quadratic forms: exponent of each row's scale
     const float *diag_max;  // quadratic forms: largest value on B's diagonal
     const float *least;     // kSubtract, errors of the GPTQ pass: smallest divisor of the 128 rows of block k / 128 of B and of its
-    int least_first;        // first 32, at least[2 ((least_first + k / 128) % 4)], for up to four blocks; or null
+                            // first 32, at least[2 (k / 128)], for up to four blocks; or null
     // several products of one shape in a launch (blockIdx.y): operands and result of product y lie y * stride floats on; the
     // last one may have fewer columns, columns_end - y * columns_step of them, and with k_is_columns as many values of k
     size_t stride;
@@ -345,8 +345,6 @@ __device__ __forceinline__ void product_tile_of(ProductArgs p, int wg, int wgs, 
                 for (int tb = 0; tb < 4; ++tb)
                     acc[ta][tb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[x == 0][ta], b[x == 1][tb], acc[ta][tb], 0, 0, 0);
     };
-    // Steps [from, to): while a step is multiplied, the next one is split and stored to the other stage and the one
-    // after it is requested.
     // Up to kProdFew values of k (not a quadratic form): with so few terms the roundings of the operands do not average out, and
     // finding scales takes longer than multiplying.  Such a product is the binary32 instruction's, from one copy of both panels
     // [k][column ^ 16 (k % 4)] in the place of a stage.  512 channels, 8 samples 14.4 -> 12.4 us.
@@ -437,16 +435,13 @@ __device__ __forceinline__ void product_tile_of(ProductArgs p, int wg, int wgs, 
         float hint = 0.0f, ratio = 1.0f;
         if (attempt == 0) {
             if (MODE == kSubtract && p.least) {
-                float all = INFINITY, first = 1.0f, of_block[8];
+                float all = INFINITY, of_block[8];
 #pragma unroll
                 for (int b = 0; b < 8; ++b) of_block[b] = p.least[b];  // (all requested together)
 #pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const int k = ((b - p.least_first) & 3) * kProdTile;  // first row of the block that has slot b
-                    if (k < p.K) all = fminf(all, of_block[2 * b]);
-                    if (k == 0) first = of_block[2 * b + 1];
-                }
-                ratio = first / all;
+                for (int b = 0; b < 4; ++b)
+                    if (b * kProdTile < p.K) all = fminf(all, of_block[2 * b]);
+                ratio = of_block[1] / all;
             }
             if (kQuad && o == 1 && c0 + i < p.C) {
                 hint = p.B[(size_t)(c0 + i) * p.ldb + c0 + i];
@@ -624,18 +619,16 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
     product_tile_of<MODE>(p, blockIdx.x, gridDim.x, stage_a0, stage_a1, stage_b, largest, largest_of_tile, shift);
 }
 
-template <int MODE>
 static ProductArgs product_args(const float *A, int lda, int R, const float *B, int ldb, int C, int K, float *out, int ldo,
-                                const float *least = nullptr, int least_first = 0)
+                                const float *least = nullptr)
 {
-    return {A, B, nullptr, out, lda, R, ldb, C, K, ldo, 0, nullptr, 0, nullptr, nullptr, least, least_first, 0, C, 0, 0, nullptr};
+    return {A, B, nullptr, out, lda, R, ldb, C, K, ldo, 0, nullptr, 0, nullptr, nullptr, least, 0, C, 0, 0, nullptr};
 }
 
 template <int MODE>
-static void launch_product(hipStream_t stream, const float *A, int lda, int R, const float *B, int ldb, int C, int K, float *out,
-                           int ldo, const float *least = nullptr, int least_first = 0)
+static void launch_product(hipStream_t stream, const float *A, int lda, int R, const float *B, int ldb, int C, int K, float *out, int ldo)
 {
-    const ProductArgs p = product_args<MODE>(A, lda, R, B, ldb, C, K, out, ldo, least, least_first);
+    const ProductArgs p = product_args(A, lda, R, B, ldb, C, K, out, ldo);
     hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)product_groups<MODE>(R, C)), dim3(256), 0, stream, p);
 }
 
@@ -644,7 +637,7 @@ template <int MODE>
 static void launch_products(hipStream_t stream, int count, size_t stride, int columns_end, const float *A, const float *B, float *out,
                             int pitch, int size)
 {
-    ProductArgs p = {A, B, nullptr, out, pitch, size, pitch, size, size, pitch, MODE == kStore ? 1 : 0, nullptr, 0, nullptr, nullptr, nullptr, 0,
+    ProductArgs p = {A, B, nullptr, out, pitch, size, pitch, size, size, pitch, MODE == kStore ? 1 : 0, nullptr, 0, nullptr, nullptr, nullptr,
                      stride, columns_end, 2 * size, MODE == kStore ? 1 : 0, nullptr};
     const int groups = product_groups<MODE>(size, size);
     hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)groups, (unsigned)count), dim3(256), 0, stream, p);
@@ -656,7 +649,7 @@ template <int MODE>
 static void launch_quad_form(hipStream_t stream, const uint16_t *split, size_t plane, const int *shift, const float *D, int R, const float *B,
                              int ldb, const float *diag_max, int C, float *out, int ldo, const int *rows = nullptr)
 {
-    ProductArgs p = {D, B, D, out, ldo, R, ldb, C, C, ldo, 0, split, plane, shift, diag_max, nullptr, 0, 0, C, 0, 0, rows};
+    ProductArgs p = {D, B, D, out, ldo, R, ldb, C, C, ldo, 0, split, plane, shift, diag_max, nullptr, 0, C, 0, 0, rows};
     const int groups = product_groups<MODE>(R, C);
     hipLaunchKernelGGL((product_kernel<MODE>), dim3((unsigned)groups), dim3(256), 0, stream, p);
 }

@@ -1500,8 +1500,8 @@ static hipError_t gptq_rows(int M, int N, int n_bits, int q, const float *W, con
         float *const least = leasts + 8 * turn, *const last_least = leasts + 8 * (turn ^ 1);
         // Wt[k][m] -= sum_j U[j][k] Err[j][m] for the errors j of the panel before and the columns k of [from, to)
         auto update = [&](int from, int to) {
-            return product_args<kSubtract>(U + (size_t)(p0 - kGptqPanel) * N + from, N, to - from, last, w.Mp, w.Mp, kGptqPanel,
-                                           w.Wt + (size_t)from * w.Mp, w.Mp, last_least, 0);
+            return product_args(U + (size_t)(p0 - kGptqPanel) * N + from, N, to - from, last, w.Mp, w.Mp, kGptqPanel,
+                                w.Wt + (size_t)from * w.Mp, w.Mp, last_least);
         };
         ProductArgs rest = {};
         int tiles = 0;
