@@ -177,7 +177,7 @@ def _search(W, H, n, q, grid):
     (256, 256, 3, 2, 3, "samples"), (257, 264, 4, 3, 2, "samples"), (700, 520, 3, 2, 2, "loud"), (513, 776, 2, 2, 4, "samples"),
     (300, 512, 5, 3, 3, "samples"), (400, 1032, 3, 2, 2, "one direction"), (260, 640, 8, 2, 1, "one direction"), (300, 264, 4, 2, 2, "zero"),
     (2048, 320, 3, 2, 2, "few samples"), (256, 736, 3, 2, 4, "indefinite"), (300, 296, 3, 2, 2, "infinite"), (1020, 776, 3, 2, 8, "tiny"), (510, 776, 3, 2, 3, "huge"),
-    (765, 736, 3, 2, 4, "very indefinite"), (510, 520, 4, 2, 3, "low rank"), (1020, 1032, 3, 2, 8, "16 bits"), (640, 2048, 3, 2, 8, "16 bits"),
+    (765, 736, 3, 2, 4, "very indefinite"), (765, 1032, 3, 2, 8, "mirrored"), (510, 520, 4, 2, 3, "low rank"), (1020, 1032, 3, 2, 8, "16 bits"), (640, 2048, 3, 2, 8, "16 bits"),
     (600, 264, 3, 2, 2, "no diagonal"), (512, 1024, 5, 3, 3, "16 bits"), (264, 760, 3, 2, 4, "very indefinite"), (256, 768, 3, 2, 5, "samples"),
     (256, 776, 3, 2, 2, "samples"), (1400, 4096, 3, 2, 3, "one direction"),
     (5003, 1288, 3, 2, 3, "samples"), (2500, 3592, 4, 2, 2, "few samples")])
@@ -216,6 +216,10 @@ def test_search_screened(M, N, n, q, grid, kind):
     H = ((H + H.t()) * 0.5).contiguous()
     if kind in ("indefinite", "very indefinite"):  # errors positive for nearly all rows, and of both signs
         H.diagonal().sub_((0.3 if kind == "indefinite" else 1.0) * H.diagonal().mean())
+    if kind == "mirrored":  # as large as a positive semidefinite H of its diagonal, with channel means; errors of either sign
+        mean = 5.0 * torch.randn(N, device="cuda", generator=g)
+        H += 2.0 * T * mean[:, None] * mean[None]
+        H = 2.0 * torch.diag(H.diagonal()) - H
     if kind == "no diagonal":
         H.fill_diagonal_(0.0)
     if kind == "low rank":  # equal channels and weights that fall into line with them: errors of rounding, of either sign
