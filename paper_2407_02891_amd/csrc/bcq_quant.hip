@@ -737,7 +737,7 @@ __global__ void keep_best_kernel(int M, int Mp, int n_bits, int ntile, int g, in
 }
 
 // A round of the screened search, per row: takes the errors of the round before (entries of the row's range in the list), and lists
-// what is to be evaluated next: in a chunk's first round the candidate with the lowest bound, then all whose bound does not exclude
+// what is to be evaluated next: in the first round the candidate with the lowest bound, then all whose bound does not exclude
 // that they are better than the best so far, or as good and earlier.  As much as fits; the rest comes in the next round.
 struct SearchRound {
     float *bound;             // [candidate of the chunk][Mp]; infinite: done with
@@ -798,13 +798,14 @@ __global__ __launch_bounds__(256) void search_round_kernel(int M, int Mp, int n_
                 lowest = c;
             }
         }
-    if (r.start && n > 1) n = 1;
+    const bool one = r.fresh && n > 1;
+    if (one) n = 1;
     int at = n ? atomicAdd(r.total, n) : 0;
     if (at >= Mp) n = 0;  // (the total may run beyond the list; who reads it takes no more than fits)
     else if (at + n > Mp) n = Mp - at;
     r.begin[m] = at;
     r.count[m] = n;
-    for (int c = r.start ? lowest : 0; n > 0 && c < r.candidates; ++c) {
+    for (int c = one ? lowest : 0; n > 0 && c < r.candidates; ++c) {
         float &b = r.bound[(size_t)c * Mp + m];
         if (!(b < INFINITY) || b > best || (b == best && r.first_candidate + c > index)) continue;
         r.row[at] = m;
