@@ -839,11 +839,21 @@ static ScreenPlan screen_plan(int M, int N, int tyings, int candidates)
     return {0, 0, 0, 0};
 }
 
-// Two rounds of three products each and a product per candidate instead of three per candidate: pays from a few candidates on, down
-// to where launches are what counts (three per grid point and three per candidate for rounds that find nothing, instead of three
-// per candidate).  us, all candidates / screened: 7168 x 7168, three bits, two planes, grid 8 32000 / 10360 (1.17 candidates a row
-// evaluated of 24; a form 309 of 1300), 2500 x 7168 11700 / 5030, 2048 x 2048 2140 / 757, 512 x 512 790 / 365, 256 x 512 (grid 4) 385 / 284.
-static bool screen_pays(int M, int N, int candidates) { return M >= 256 && N >= 256 && candidates >= 4; }
+// Screening is two rounds of three products each and a product per candidate instead of three per candidate.  us, all candidates /
+// screened, three bits, two planes, eight scales: 7168 x 7168 31450 / 11230 (before it took any H: 10300), 2500 x 7168 11690 / 5700, 2048 x 2048
+// 2100 / 858, 512 x 512 768 / 380.  Candidates evaluated of 24, 7168 x 7168: 1.15 per row with samples like the tests', 1.3 with channel means of 2
+// sigma, 2.7 of 5, 7.9 of 30 (23.2 ms), 2.2 with two channels 1000 times as loud; 4096 x 4096 with means of 30 sigma 10.8 (6.55 / 6.6 ms).
+// A screened search has about as many launches per candidate for rounds that find nothing (22 here), and H to prepare.  The line
+// lies where that is made up for: from four candidates on for large layers (4096 x 4096 1164 / 1104, 3000 x 3000 653 / 662), from six
+// where three tyings share a launch or from 1024 channels on (256 x 256 158 / 152, 344 x 1024 305 / 307), from eight where two do or from
+// 2^20 weights on (256 x 512 293 / 255 at nine; 7168 x 512 353 / 342, six 274 / 288), below that from 6144 / N (256 x 256 552 / 529,
+// 16 candidates 376 / 382; 512 x 512 392 / 363, eight 270 / 280).
+static bool screen_pays(int M, int N, int planes, int candidates)
+{
+    const long long weights = (long long)M * N;
+    if (candidates >= 8 && (planes > 1 || weights >= 1 << 20 || candidates * N >= 6144)) return true;
+    return candidates >= 6 ? planes == 3 || N >= 1024 || weights >= 1 << 24 : candidates >= 4 && weights >= 1 << 24;
+}
 
 static hipError_t search_screened(int M, int N, int n_bits, int grid, const std::vector<Tying> &tyings, ScreenPlan plan, const float *W,
                                   const float *H, float *S, float *qbias, int8_t *labels, const QuantWorkspace &w, hipStream_t stream)
@@ -950,8 +960,8 @@ static hipError_t search_rows(int M, int N, int n_bits, int q, int grid, const f
                        diag_max);
     const std::vector<Tying> tyings = all_tyings(n_bits, q);
     const int candidates = grid * (int)tyings.size();
-    const ScreenPlan plan = split && screen_pays(M, N, candidates) ? screen_plan(M, N, (int)tyings.size(), candidates) : ScreenPlan{};
-    if (plan.planes > 0) {
+    const ScreenPlan plan = split && M >= 256 && N >= 256 ? screen_plan(M, N, (int)tyings.size(), candidates) : ScreenPlan{};
+    if (plan.planes > 0 && screen_pays(M, N, plan.planes, candidates)) {
         const hipError_t e = search_screened(M, N, n_bits, grid, tyings, plan, W, H, S, qbias, labels, w, stream);
         if (e != hipSuccess) return e;
     } else {
