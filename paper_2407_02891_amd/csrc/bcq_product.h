@@ -103,8 +103,11 @@ struct ProductArgs {
 // Number of workgroups, and the tile of one.  Tiles are taken block by block of 4 x 4 so that the workgroups that share an L2 at a
 // time share their operand panels (workgroup numbers go round the eight XCDs).
 // Where all tiles cost the same (the symmetric sum, on and above the diagonal, and the subtractions) they are numbered block row by
-// block row, only those that exist, and each XCD takes an eighth of the numbers: by whole blocks, as before, the XCD with the most
-// tiles had 9 % more than its share at 7168 channels.  Otherwise each XCD takes every eighth block, for the quadratic
+// block row, only those that exist, and each XCD takes an eighth of the numbers, from their end: by whole blocks the XCD with the most
+// tiles had 9 % more than its share at 7168 channels.  Up to eight tiles are one XCD's, as they share the lines at their edges.  us, whole
+// blocks / numbers / numbers from their end, H += 2 X^T X: 7168 channels, 2048 samples 436 / 421 / 424, 256 samples 105 / 108 / 107; 4096
+// channels 204 / 192 / 190 and 49.7 / 54.1 / 50.4, one sample 29.8 / 32.6 / 28.9; 132 channels, one sample 9.5 / 10.4 / (one XCD) 9.7.  The factor
+// and the GPTQ pass take the same time with all three.  Otherwise each XCD takes every eighth block, for the quadratic
 // forms column by column from the last one, whose columns have the longest k range.
 template <int MODE>
 constexpr bool kProdEven = MODE == kAddTwiceSymmetric || MODE == kSubtract || MODE == kSubtractLower;
@@ -115,7 +118,7 @@ static inline int product_groups(int R, int C)
     const int ntr = (R + kProdTile - 1) / kProdTile, ntc = (C + kProdTile - 1) / kProdTile;
     const long long tiles = MODE == kSubtract ? (long long)ntr * ntc : (long long)ntr * (ntr + 1) / 2;
     const int br = (ntr + kProdBlock - 1) / kProdBlock, bc = (ntc + kProdBlock - 1) / kProdBlock;
-    return kProdEven<MODE> ? (int)((tiles + 7) / 8 * 8) : (br * bc + 7) / 8 * 8 * kProdBlock * kProdBlock;
+    return kProdEven<MODE> ? (tiles <= 8 ? 64 : (int)((tiles + 7) / 8 * 8)) : (br * bc + 7) / 8 * 8 * kProdBlock * kProdBlock;
 }
 
 template <int MODE>
@@ -125,7 +128,7 @@ __device__ __forceinline__ bool product_tile(int wg, int wgs, int R, int C, int 
     const int xcd = wg & 7, j = wg >> 3;
     if constexpr (kProdEven<MODE>) {
         constexpr bool kTriangle = MODE != kSubtract;
-        int t = xcd * (wgs >> 3) + j, b_row = 0, rows, first;
+        int t = xcd * (wgs >> 3) + (wgs >> 3) - 1 - j, b_row = 0, rows, first;
         for (;; ++b_row) {  // the block row, its first column and its number of tiles
             if (b_row * kProdBlock >= ntr) return false;
             rows = ntr - b_row * kProdBlock < kProdBlock ? ntr - b_row * kProdBlock : kProdBlock;
