@@ -26,7 +26,8 @@ __device__ __forceinline__ uint32_t plane_byte(uint2 v, int i)
 // x 7168, two planes with offset, one group per row: 117 us (a thread per dword and plane with byte loads, and a launch for
 // the scales; 76 with loads behind branches) -> 56 us, 257 MB: 4.6 TB/s.  The row tiles come from the last to the first, all slices of
 // one in turn: codes that have just been written are in the last-level cache from their end, and whole rows are read together:
-// 56 -> 52 us behind the fusion (slice by slice over all rows before).  Nontemporal loads, which share their lines with others: 75.
+// 56 -> 52 us behind the fusion (slice by slice over all rows before; the two together 135.5 -> 134.2, one tying for all rows 145.3 -> 136.5).
+// Nontemporal loads, which share their lines with others: 75.
 template <bool ALIGNED>
 __global__ __launch_bounds__(256) void pack_tile_kernel(Geom g, int row0, int rows, const uint8_t *__restrict__ codes,
                                                         const uint16_t *__restrict__ alpha,

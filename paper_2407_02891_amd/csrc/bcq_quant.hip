@@ -1557,9 +1557,9 @@ hipError_t launch_quant_gptq(int M, int N, int n_bits, int q, const float *W, co
 // (1, 4 or 16, by the alignment) at a time.  Bound: memory.  28672 x 7168: 441 us (a workgroup per row whose first thread worked out the tying, a scan of the representable
 // set per weight) -> 78 us with the plan worked out in LDS, 74 in registers, 411 MB: 5.5 TB/s; 512 x 64: 8.3 -> 10.8 -> 7.0 us.
 // Many integers are read past the caches (PAST, nontemporal): nobody reads them again, and what the packing reads next, the codes, stays in
-// the 256 MB last-level cache instead: 75 -> 70 us here, and the packing 52 -> 42 with the same integers each time (the two
-// together with others each time 134 -> 131; one tying for all rows 146 -> 132).  Where both fit that cache it is slower:
-// 4097 x 4096 19.7 -> 21.0; 12001 x 5120 the same.
+// the 256 MB last-level cache instead.  Both calls together, plain / nontemporal: 16 Mi integers 18.9 / 21.0 us, 32 Mi 26.2 / 28.5, 59 Mi
+// 46.9 / 46.4, 78 Mi 59.4 / 58.2, 98 Mi 77.4 / 69.7, 117 Mi 93.8 / 82.9, 196 Mi 134.2 / 130.2 (one tying for all rows 17.1 / 18.4, 25.2 / 27.2,
+// 43.4 / 43.4, 55.8 / 53.9, 72.2 / 66.8, 82.6 / 81.2, 136.5 / 130.5): the line is 2^26, where they are equal.
 constexpr int kFuseRows = 16;
 template <int WIDTH, bool PAST>
 __global__ __launch_bounds__(256) void from_linear_rows_kernel(int M, int N, int per_group, int n_bits, int q,

@@ -108,7 +108,7 @@ BCQ_HD inline uint8_t code_of(int member, const TyingPlan &plan, int q)
 }
 
 #if defined(__HIPCC__)
-// Integers of the fusion, a byte each, beyond which they are read past the caches (see from_linear_rows_kernel).
+// Integers of the fusion, a byte each, beyond which they are read past the caches (measured at from_linear_rows_kernel).
 constexpr size_t kReadPastCaches = (size_t)1 << 26;
 
 // Four integers (a byte each) through a table of codes in LDS.
