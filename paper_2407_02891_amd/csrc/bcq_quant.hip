@@ -842,7 +842,7 @@ static ScreenPlan screen_plan(int M, int N, int tyings, int candidates)
 // Screening is two rounds of three products each and a product per candidate instead of three per candidate.  us, all candidates /
 // screened, three bits, two planes, eight scales: 7168 x 7168 31450 / 11230 (before it took any H: 10300), 2500 x 7168 11690 / 5700, 2048 x 2048
 // 2100 / 858, 512 x 512 768 / 380.  Candidates evaluated of 24, 7168 x 7168: 1.15 per row with samples like the tests', 1.3 with channel means of 2
-// sigma, 2.7 of 5, 7.9 of 30 (23.2 ms), 2.2 with two channels 1000 times as loud; 4096 x 4096 with means of 30 sigma 10.8 (6.55 / 6.6 ms).
+// sigma, 2.7 of 5, 7.9 of 30 (23.4 ms), 2.2 with two channels 1000 times as loud; 4096 x 4096 with means of 30 sigma 11.1 (6.6 / 6.9 ms).
 // A screened search has about as many launches per candidate for rounds that find nothing (22 here), and H to prepare.  The line
 // lies where that is made up for: from four candidates on for large layers (4096 x 4096 1164 / 1104, 3000 x 3000 653 / 662), from six
 // where three tyings share a launch or from 1024 channels on (256 x 256 158 / 152, 344 x 1024 305 / 307), from eight where two do or from
