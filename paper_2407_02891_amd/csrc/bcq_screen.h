@@ -185,6 +185,8 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void screen_kernel(ScreenArgs p)
         body(step + 3, odd, st0, st2);
         if (step & 4) look();
     }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");  // (nothing is on its way to LDS when a wave ends)
+
     // element i of an accumulator: column c 4 hi + i, row m lo
     if (projects) {  // (those beyond the last one are zeros)
 #pragma unroll
@@ -201,7 +203,6 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void screen_kernel(ScreenArgs p)
         }
         return;
     }
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     float *const red = reinterpret_cast<float *>(&st0[0][0][0]);  // [WR][5][kCols]
     const __amdgpu_buffer_rsrc_t d_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t *>(p.D + ((size_t)(c0 >> 3) * p.Mp + m0) * 8), 0,
