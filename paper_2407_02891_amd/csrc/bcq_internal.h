@@ -57,6 +57,12 @@ hipError_t launch_skinny(const Geom &g, const void *packed, const uint16_t *X, i
 bool gemv2_applies(const Geom &g, int batch, const void *workspace);
 hipError_t launch_gemv2(const Geom &g, const void *packed, const uint16_t *X, int ldx, uint16_t *Y, int ldy,
                         void *workspace, const GemvTuning &tuning, hipStream_t stream);
+// Two to four vectors, one scaling group per block, on the 8-bit integer matrix instruction (bcq_few.hip).
+bool few_applies(const Geom &g, int batch, const void *workspace);
+hipError_t launch_few(const Geom &g, const void *packed, const uint16_t *X, int ldx, uint16_t *Y, int ldy, int batch,
+                      void *workspace, const GemvTuning &tuning, hipStream_t stream);
+// Compute units of the current device (asked from the runtime once per device).
+int compute_units();
 hipError_t launch_read_probe(const void *buf, size_t bytes, void *sink, hipStream_t stream);
 
 // Rows the file-scope split-K scratch array covers (bcq_gemv_noalloc): 1 MiB per GPU.

@@ -724,13 +724,16 @@ hipError_t launch_skinny(const Geom &g, const void *packed, const uint16_t *X, i
                          int batch, void *workspace, const GemvTuning &tuning, hipStream_t stream)
 {
     const long long all_tiles = (long long)g.ntile * g.nslice;
-    // Two vectors: the GEMV's decomposition with both vectors' sign sums in one table entry (bcq_gemv2.hip).  Measured
-    // against the best of the kernels below, q = 3: 7168 x 28672 23.6 against 32.4 us, 28672 x 7168 22.5 / 32.1,
-    // 9216 x 36864 36.3 / 49.4, 9216 x 9216 12.7 / 17.4, 7168 x 7168 10.7 / 13.1 (q = 2, 7168 x 28672: 18.0 / 22.8); it
-    // loses where a compute unit gets less than a round of tiles (4096 x 4096 9.1 / 8.6, 1024 x 8192 8.8 / 7.9).
-    if (gemv2_applies(g, batch, workspace) &&
-        (tuning.skinny_version == 5 || (tuning.skinny_version == 0 && all_tiles >= 2048)))
+    // Two vectors on large layers: the GEMV's decomposition with both vectors' sign sums in one table entry (bcq_gemv2.hip).  Measured against
+    // bcq_few.hip (us, theirs first): q = 3 7168 x 28672 22.9 / 23.7, 28672 x 7168 22.1 / 26.1, 9216 x 36864 35.5 / 35.0, 7168 x 7168 9.8 / 10.5;
+    // q = 2 28417 x 2560 8.9 / 11.1; it loses where a compute unit gets less than a round of tiles: 4096 x 4096 7.4 / 6.0, 1024 x 8192 6.7 / 5.2,
+    // 36864 x 512 7.5 / 6.3.
+    const bool two = gemv2_applies(g, batch, workspace);
+    if (two && (tuning.skinny_version == 5 || (tuning.skinny_version == 0 && all_tiles >= 2048)))
         return launch_gemv2(g, packed, X, ldx, Y, ldy, workspace, tuning, stream);
+    // Two to four vectors otherwise: the integer kernel of bcq_few.hip.
+    if (few_applies(g, batch, workspace) && tuning.skinny_version != 1 && tuning.skinny_version != 2)
+        return launch_few(g, packed, X, ldx, Y, ldy, batch, workspace, tuning, stream);
     // (versions 3 to 6 only choose among the kernels for two to four vectors: automatic choice among the others)
     const int version = tuning.skinny_version >= 3 ? 0 : tuning.skinny_version;
     SkinnyParams p;

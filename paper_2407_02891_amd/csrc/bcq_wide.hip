@@ -347,7 +347,7 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void bcq_wide_kernel(WideParams
 // ---------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------
-static int compute_units()
+int compute_units()
 {
     constexpr int kMaxDevices = 64;
     static std::atomic<int> cached[kMaxDevices];

@@ -459,6 +459,62 @@ def test_two_vector_table_kernel(workgroups):
         bcq.set_option("skinny_version", 0)
 
 
+@pytest.mark.parametrize("workgroups", [0, 1, 7, 50])
+@pytest.mark.parametrize("batch", [2, 3, 4])
+def test_integer_kernel_for_up_to_four_vectors(workgroups, batch):
+    """Two to four vectors on the 8-bit integer matrix instruction (bcq_few.hip), the two-vector table kernel switched off: one slice
+    and many, a last slice that is partial, an odd number of row halves, fewer rows than waves, one to four planes with and without
+    offset, row-wise scales; bit for bit the oracle's result on exact inputs, twice in a row, workspace left zero; gate on random inputs."""
+    try:
+        bcq.set_option("skinny_version", 6)
+        bcq.set_option("workgroups", workgroups)
+        for (M, N, q, off, group) in [(96, 2048, 3, False, 128), (300, 5120, 3, True, 128), (70, 1536, 2, True, 128), (1000, 2560, 1, False, 128),
+                                      (203, 3200, 4, True, 128), (96, 2048, 3, True, 2048), (40, 512, 3, False, 128), (16, 512, 2, True, 128),
+                                      (777, 6656, 3, False, 256), (33, 32, 4, False, 32), (1, 7168, 3, True, 128), (500, 13 * 512, 1, True, 256)]:
+            L = bcq_synth.make_exact_layer(M, N, q, group=group, offset=off, batch=batch, seed=M + q + batch)
+            pl = U.upload_and_pack(L, max_batch=batch)
+            expect = ref.gemm(L.planes, L.alpha, L.offset, L.x).astype(np.float16).astype(np.float64)
+            for _ in range(2):
+                assert np.array_equal(U.gpu_gemm(pl, U.x_dev(L)).astype(np.float64), expect), (M, N, q, off, group)
+            assert pl.workspace is None or not pl.workspace.cpu().numpy().any()
+        _run_case(600, 4608, 3, 128, True, batch=batch, seed=batch + workgroups, outlier_frac=0.01)
+        _run_case(1024, 4096, 2, 128, False, batch=batch, seed=workgroups + 1)
+    finally:
+        bcq.set_option("workgroups", 0)
+        bcq.set_option("skinny_version", 0)
+
+
+@pytest.mark.parametrize("N", [512, 2560])
+def test_integer_kernel_range_of_activations(N):
+    """Activations are taken to 2^-22 of the largest one of their block of 128: one of 60000 beside ordinary ones and beside subnormals, a block of
+    zeros, a block of subnormals, within what that and a binary32 sum allow.  A vector with an infinity or a NaN leaves the others of the call
+    as they are, and gives no finite number where nothing goes through the fixed-point accumulators (which wrap: what comes out is unspecified)."""
+    rng = np.random.default_rng(N)
+    L = bcq_synth.make_layer(150, N, 3, group=128, offset=True, batch=4, seed=3)
+    x = L.x.copy()
+    x[0, ::128] = 60000.0
+    x[1, :128] = 0.0
+    x[1, 128:256] = rng.integers(0, 1024, size=128, dtype=np.uint16).view(np.float16)
+    x[2, :128] = rng.integers(0, 1024, size=128, dtype=np.uint16).view(np.float16)
+    x[2, 5] = -60000.0
+    L.x = x
+    pl = U.upload_and_pack(L, max_batch=4)
+    Y = U.gpu_gemm(pl, U.x_dev(L)).astype(np.float64)
+    want = ref.gemm(L.planes, L.alpha, L.offset, L.x)
+    blocks = np.abs(x.astype(np.float64)).reshape(4, N // 128, 128).max(axis=2)
+    weight = np.abs(L.alpha.astype(np.float64)).sum(axis=2) + np.abs(L.offset.astype(np.float64))    # [M][blocks]
+    # half a unit per activation, 128 of them, and as much again for the binary32 sums; then the binary16 rounding
+    bound = 2 * 128 * 2.0 ** -22 * blocks @ weight.T + 2.0 ** -11 * np.abs(want) + 2.0 ** -25
+    assert np.all(np.abs(Y - want) <= bound), np.max(np.abs(Y - want) / bound)
+    for bad in (np.inf, -np.inf, np.nan):
+        L.x = x.copy()
+        L.x[1, 130] = bad
+        Z = U.gpu_gemm(pl, U.x_dev(L)).astype(np.float64)
+        assert N > 512 or not np.isfinite(Z[1]).any()
+        assert np.array_equal(Z[[0, 2, 3]], Y[[0, 2, 3]])
+        assert pl.workspace is None or not pl.workspace.cpu().numpy().any()
+
+
 @pytest.mark.parametrize("workgroups", [1, 4, 7, 11, 29])
 @pytest.mark.parametrize("version", [1, 2])
 def test_skinny_work_split_does_not_change_results(workgroups, version):
