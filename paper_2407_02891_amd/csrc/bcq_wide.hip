@@ -20,6 +20,15 @@
 //    slice of a pair, waves 4-7 the odd one (K groups), and the two partial sums of a row tile meet in LDS when the
 //    workgroup leaves it.  Half the rows per workgroup means half the split-K atomics of eight row tiles for the same number
 //    of workgroups, and they are what the kernel before this one paid most for besides the matrix instructions.
+//  * Groups of 32 or 64 columns per scale have a kernel of their own (bcq_wide_groups_kernel).  The bytes of a scaling group are put in order in
+//    registers (alignbyte, a 4 x 4 byte transpose) and the dwords exchanged through a wave's own piece of LDS, 12 instructions and an LDS round trip
+//    per 16 bytes where lane swaps took 40; the scales lie there too, where the lane that needs a group finds them without selects.  A block's X
+//    operands are in registers, read once for both row halves: while the second half is computed each is replaced by the next block's, so a
+//    stage is free again in the middle of the block that it was filled for, where the barrier stands.  The sums of a finished group are scaled plane by
+//    plane between the matrix instructions that start the next one.  us, before and after: 10855 x 26304 q = 3 groups of 32, 17 columns 113 -> 97,
+//    64 columns 228 -> 197; 13102 x 18880 q = 2 with offset, groups of 64, 45 columns 78 -> 71, 64 columns 98 -> 89; 5000 x 7232 27 columns 19.5 -> 18.7;
+//    q = 1 4755 x 5312 17.8 -> 17.1, 2193 x 17600 19.0 -> 19.5.  With one group per block that way of holding X gains nothing (28672 x 8192, 64 columns 80.7 / 80.8;
+//    24524 x 5824, 32 columns 35.9 / 38.1), so the kernel there reads X for each half.
 //  * Workgroups per row group: a whole number unless that leaves too much of the chip idle (plan_wide), so that no workgroup
 //    holds parts of two row groups; a single one writes its outputs without atomics.
 #include <atomic>
@@ -72,14 +81,14 @@ __device__ __forceinline__ void wide_store(const SkinnyParams &p, int cols, cons
     }
 }
 
-template <int Q, int Z, int SUB, int NB>
+// One scaling group per block.
+template <int Q, int Z, int NB>
 __global__ __launch_bounds__(64 * kWideWaves, 2) void bcq_wide_kernel(WideParams wp)
 {
     constexpr int kRows = 16 * NB;                 // staged vectors
     constexpr int kStage = 2 * kRows * 256;        // one stage: [K group][vector][16 chunks of 16 bytes]
     constexpr int kCopies = kStage / 1024 / kWideWaves;  // copy instructions per wave and stage (each moves four rows)
-    constexpr int kRec = (Q + Z) * SUB;            // dwords of a scale record
-    constexpr int kPer = 4 / SUB;                  // steps per scaling group
+    constexpr int kRec = Q + Z;                    // dwords of a scale record
     static_assert(kCopies >= 1, "a wave copies at least four rows");
     __shared__ __attribute__((aligned(16))) uint8_t stage0[kStage];
     __shared__ __attribute__((aligned(16))) uint8_t stage1[kStage];
@@ -138,10 +147,10 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void bcq_wide_kernel(WideParams
             const_cast<uint8_t *>(p.blob + (ok ? ((size_t)sl * p.ntile + t) * p.tile_bytes : 0)), 0, ok ? (int)p.tile_bytes : 0,
             kRawBufferFlags);
     };
-    TileRegs<Q, Z, SUB> cur;
+    TileRegs<Q, Z, 1> cur;
     const int scale_lane = lane & p.scale_lane_mask;
     copy_stage(stage0, pair, 0);
-    load_tile_buf<Q, Z, SUB>(cur, tile_rsrc(rg, pair, true), lane, scale_lane);
+    load_tile_buf<Q, Z, 1>(cur, tile_rsrc(rg, pair, true), lane, scale_lane);
     build_sign_table<64 * kWideWaves, 16, true>(tab, tid);
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
@@ -163,7 +172,7 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void bcq_wide_kernel(WideParams
             int n_pair = pair + 1, n_rg = rg;
             if (n_pair == wp.pairs) { n_pair = 0; n_rg = rg + 1; }
             const __amdgpu_buffer_rsrc_t n_rsrc = tile_rsrc(n_rg, n_pair, more);
-            TileRegs<Q, Z, SUB> nxt;
+            TileRegs<Q, Z, 1> nxt;
 
             // chunk order, then the 4 x 4 dword transpose across the lanes r, r + 16, r + 32, r + 48:
             // wb[t][i][B] = chunks 4 h .. 4 h + 3 of (row 16 t + r, block B, plane i)
@@ -173,31 +182,13 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void bcq_wide_kernel(WideParams
 #pragma unroll
                 for (int i = 0; i < Q; ++i) {
                     u32x4 w = cur.planes[t][i];
-                    unrotate<SUB>(w, r);
+                    unrotate<1>(w, r);
                     const auto e01 = __builtin_amdgcn_permlane16_swap(w.x, w.y, false, false);
                     const auto e23 = __builtin_amdgcn_permlane16_swap(w.z, w.w, false, false);
                     const auto f02 = __builtin_amdgcn_permlane32_swap(e01[0], e23[0], false, false);
                     const auto f13 = __builtin_amdgcn_permlane32_swap(e01[1], e23[1], false, false);
                     wb[t][i][0] = f02[0]; wb[t][i][1] = f13[0]; wb[t][i][2] = f02[1]; wb[t][i][3] = f13[1];
                 }
-            // Several scaling groups per block: a step has to stay inside one, so a 4 x 4 byte transpose across the same four
-            // lanes makes byte s the chunk 4 s + h (lane group bit 0 against byte bit 0, then bit 1 against bit 1).
-            if (SUB > 1) {
-                const uint32_t sel0 = (h & 1) ? 0x07030501u : 0x06020400u, sel1 = (h & 2) ? 0x07060302u : 0x05040100u;
-#pragma unroll
-                for (int t = 0; t < 2; ++t)
-#pragma unroll
-                    for (int i = 0; i < Q; ++i)
-#pragma unroll
-                        for (int b = 0; b < 4; ++b) {
-                            const auto eo = __builtin_amdgcn_permlane16_swap(wb[t][i][b], wb[t][i][b], false, false);
-                            const uint32_t even = eo[0], odd = eo[1];
-                            const uint32_t w = __builtin_amdgcn_perm(odd, even, sel0);
-                            const auto lu = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-                            const uint32_t low = lu[0], up = lu[1];
-                            wb[t][i][b] = __builtin_amdgcn_perm(up, low, sel1);
-                        }
-            }
             uint32_t rec[kRec];
 #pragma unroll
             for (int e = 0; e < kRec; ++e) rec[e] = cur.scales[e];
@@ -214,9 +205,9 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void bcq_wide_kernel(WideParams
                 __builtin_amdgcn_sched_barrier(0);
                 if (B < 2) {
 #pragma unroll
-                    for (int i = 0; i < Q; ++i) load_tile_piece<Q, Z, SUB>(nxt, n_rsrc, lane, scale_lane, B * Q + i);
+                    for (int i = 0; i < Q; ++i) load_tile_piece<Q, Z, 1>(nxt, n_rsrc, lane, scale_lane, B * Q + i);
                 } else if (B == 2) {
-                    load_tile_piece<Q, Z, SUB>(nxt, n_rsrc, lane, scale_lane, 2 * Q);
+                    load_tile_piece<Q, Z, 1>(nxt, n_rsrc, lane, scale_lane, 2 * Q);
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 // this block's scale record, from the lane group that owns it
@@ -228,7 +219,7 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void bcq_wide_kernel(WideParams
                     const int t = q8 >> 2, s = q8 & 3;
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb)
-                        bx[nb] = *reinterpret_cast<const f16x8 *>(xs + xrow + nb * 4096 + (((SUB == 1 ? 4 * h + s : 4 * s + h) ^ g_r) * 16));
+                        bx[nb] = *reinterpret_cast<const f16x8 *>(xs + xrow + nb * 4096 + (((4 * h + s) ^ g_r) * 16));
 #pragma unroll
                     for (int i = 0; i < Q; ++i) {
                         asm volatile("" : "+v"(wb[t][i][B]));  // keeps the address arithmetic of later steps out of this one
@@ -238,42 +229,32 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void bcq_wide_kernel(WideParams
                 };
                 f16x8 abuf[2][Q], bbuf[2][NB];
                 fetch(0, abuf[0], bbuf[0]);
-                f32x4 C[NB][Q + Z];
-                f32x4 Cz[Z && SUB == 1 ? NB : 1];
+                f32x4 C[NB][Q];
+                f32x4 Cz[Z ? NB : 1];
 #pragma unroll
                 for (int q8 = 0; q8 < 8; ++q8) {
                     const int t = q8 >> 2, s = q8 & 3, cb = q8 & 1;
-                    const bool start = s % kPer == 0, done = s % kPer == kPer - 1;
+                    const bool start = s == 0, done = s == 3;
                     __builtin_amdgcn_sched_barrier(0);
                     if (q8 + 1 < 8) fetch(q8 + 1, abuf[cb ^ 1], bbuf[cb ^ 1]);
                     float v[Q + Z];
                     if (done) {
-                        // scales of the group that is finished by this step, from the byte range of the record that holds it
+                        // scales of the block, which is finished by this step
 #pragma unroll
                         for (int e = 0; e < kRec; ++e) asm volatile("" : "+v"(sc[e]));  // (not earlier)
-                        const int range = subgroup_of_range(s / kPer, r, SUB);
 #pragma unroll
                         for (int c = 0; c < Q + Z; ++c) {
-                            uint32_t bits = 0;
-#pragma unroll
-                            for (int k = 0; k < SUB; ++k) {
-                                const int e = (t * SUB + k) * (Q + Z) + c;
-                                const uint32_t half = (e & 1) ? (sc[e >> 1] >> 16) : (sc[e >> 1] & 0xffffu);
-                                bits = SUB == 1 ? half : (range == k ? half : bits);
-                            }
-                            v[c] = half_bits_to_float(bits);
+                            const int e = t * (Q + Z) + c;
+                            v[c] = half_bits_to_float((e & 1) ? (sc[e >> 1] >> 16) : (sc[e >> 1] & 0xffffu));
                         }
                     }
                     auto mul = [&](int nb, int i) {
                         C[nb][i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bbuf[cb][nb], abuf[cb][i], start ? zero : C[nb][i], 0, 0, 0);
                     };
                     auto sums = [&](int nb) {
-                        if (Z && SUB > 1)  // column sums of X
-                            C[nb][Q + Z - 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                                bbuf[cb][nb], __builtin_bit_cast(f16x8, ones), start ? zero : C[nb][Q + Z - 1], 0, 0, 0);
-                        if (Z && SUB == 1 && t == 0)  // (one group per block: the same for both row halves)
-                            Cz[Z && SUB == 1 ? nb : 0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                                bbuf[cb][nb], __builtin_bit_cast(f16x8, ones), start ? zero : Cz[Z && SUB == 1 ? nb : 0], 0, 0, 0);
+                        if (Z && t == 0)  // column sums of X, the same for both row halves
+                            Cz[Z ? nb : 0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bbuf[cb][nb], __builtin_bit_cast(f16x8, ones),
+                                                                                    start ? zero : Cz[Z ? nb : 0], 0, 0, 0);
                     };
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb) {
@@ -288,7 +269,7 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void bcq_wide_kernel(WideParams
                             for (int c = 0; c < Q + Z; ++c)
 #pragma unroll
                                 for (int j = 0; j < 4; ++j)
-                                    acc[nb][t][j] = fmaf(v[c], (Z && SUB == 1 && c == Q) ? Cz[Z && SUB == 1 ? nb : 0][j] : C[nb][c][j], acc[nb][t][j]);
+                                    acc[nb][t][j] = fmaf(v[c], c == Q ? Cz[Z ? nb : 0][j] : C[nb][c < Q ? c : 0][j], acc[nb][t][j]);
                             // the sums exist here: left alone the compiler moves the scaling of all blocks to the end of the
                             // unit and keeps every block's sums until then
                             asm volatile("" : "+v"(acc[nb][t]));
@@ -344,6 +325,327 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void bcq_wide_kernel(WideParams
     }
 }
 
+// A tile's share of a lane, with the scale record in a vector type: as an array some instances keep it in memory.
+typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
+
+template <int Q>
+struct WideTile {
+    u32x4 planes[2][Q];
+    u32x16 scales;
+};
+
+template <int Q, int Z, int SUB>
+__device__ __forceinline__ void wide_load_scales(WideTile<Q> &r, __amdgpu_buffer_rsrc_t rsrc, int scale_lane)
+{
+    const uint32_t so = 2u * Q * 1024u + 4u * (Q + Z) * SUB * scale_lane;
+#pragma unroll
+    for (int c = 0; c < (Q + Z) * SUB; ++c) r.scales[c] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, so + 4u * c, 0, 2);
+}
+
+template <int Q>
+__device__ __forceinline__ void wide_load_plane(WideTile<Q> &r, __amdgpu_buffer_rsrc_t rsrc, int lane, int t, int i)
+{
+    r.planes[t][i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, 16u * lane + (t * Q + i) * 1024u, 0, 2);
+}
+
+// A lane's scales to LDS, [row half][byte range] 64 BYTES apart.
+template <int Q, int Z, int SUB, int BYTES>
+__device__ __forceinline__ void store_scales(const u32x16 &r, uint8_t *dst)
+{
+#pragma unroll
+    for (int g = 0; g < 2 * SUB; ++g) {
+        uint32_t o[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int c = 0; c < Q + Z; ++c) {
+            const int e = g * (Q + Z) + c;
+            o[c] = (e & 1) ? r[e >> 1] >> 16 : r[e >> 1] & 0xffffu;
+        }
+        if constexpr (BYTES == 4) *reinterpret_cast<uint32_t *>(dst + 64 * BYTES * g) = o[0] | o[1] << 16;
+        else *reinterpret_cast<u32x2 *>(dst + 64 * BYTES * g) = u32x2{o[0] | o[1] << 16, o[2] | o[3] << 16};
+    }
+}
+
+// Two or four scaling groups per block.
+template <int Q, int Z, int SUB, int NB>
+__global__ __launch_bounds__(64 * kWideWaves, 2) void bcq_wide_groups_kernel(WideParams wp)
+{
+    constexpr int kRows = 16 * NB;                 // staged vectors
+    constexpr int kStage = 2 * kRows * 256;        // one stage: [K group][vector][16 chunks of 16 bytes]
+    constexpr int kCopies = kStage / 1024 / kWideWaves;  // copy instructions per wave and stage (each moves four rows)
+    constexpr int kRec = (Q + Z) * SUB;            // dwords of a scale record
+    constexpr int kPer = 4 / SUB;                  // steps per scaling group
+    constexpr int kScaleBytes = Q + Z <= 2 ? 4 : 8;  // the scales of a (row, block, byte range), in LDS
+    constexpr int kAhead = 1, kBufs = kAhead + 1;  // steps that sign operands are requested ahead
+    static_assert(SUB == 2 || SUB == 4, "scaling groups per block");
+    static_assert(kCopies >= 1, "a wave copies at least four rows");
+    __shared__ __attribute__((aligned(16))) uint8_t stages[2 * kStage];
+    __shared__ __attribute__((aligned(16))) uint8_t tab[kTabBytes<16>];
+    // a wave's own piece: sign words on their way between lanes, then the scales of the unit
+    constexpr int kOwn = Q * 1024 > 2 * SUB * 64 * kScaleBytes ? Q * 1024 : 2 * SUB * 64 * kScaleBytes;
+    __shared__ __attribute__((aligned(16))) uint8_t owns[kWideWaves * kOwn];
+    static_assert(sizeof(stages) + sizeof(tab) + sizeof(owns) <= 160 * 1024, "one workgroup per compute unit");
+    const SkinnyParams &p = wp.s;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, h = lane >> 4;
+    const int kg = wave >> 2, rt = wave & 3;
+
+    // this workgroup's units (row group, pair of slices), row group first
+    int u_begin, u_end;
+    const int groups = gridDim.x;
+    if (wp.parts) {
+        const int rg = blockIdx.x / wp.parts, part = blockIdx.x - rg * wp.parts;
+        u_begin = rg * wp.pairs + (int)(((long long)part * wp.pairs) / wp.parts);
+        u_end = rg * wp.pairs + (int)(((long long)(part + 1) * wp.pairs) / wp.parts);
+    } else {
+        u_begin = first_unit<true>(blockIdx.x, p.units, groups, p.unit_base, p.unit_rem);
+        u_end = first_unit<true>(blockIdx.x + 1, p.units, groups, p.unit_base, p.unit_rem);
+    }
+    if (u_begin >= u_end) return;  // uniform for the workgroup, before any barrier
+
+    // ---- copying X: instruction c of this wave fills the four rows 4 (wave kCopies + c) .. + 3 of the stage ----
+    const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t *>(p.X), 0, (int)(2u * ((uint32_t)(p.batch - 1) * (uint32_t)p.ldx + (uint32_t)p.N)), kRawBufferFlags);
+    uint32_t src[kCopies];   // byte offset of the lane's chunk in block 0 of slice 0
+    int chunk8[kCopies];     // first column of that chunk inside a block; beyond all columns for a row without a vector
+#pragma unroll
+    for (int c = 0; c < kCopies; ++c) {
+        const int row = (4 * (wave * kCopies + c) + (lane >> 4)) % kRows;  // the same rows for both K groups
+        const int rho = row & 15, g = rho ^ ((rho & 4) << 1);
+        const int col = (row & ~15) + (rho >> 2) + 4 * (rho & 3);  // staged row 4 h + j holds column h + 4 j (see wide_store)
+        chunk8[c] = col < p.batch ? 8 * ((lane & 15) ^ g) : p.N;
+        src[c] = 2u * ((uint32_t)col * (uint32_t)p.ldx + (uint32_t)chunk8[c]);
+    }
+    auto copy_stage = [&](int which, int pair, int B) {
+        int first = wave * kCopies;
+        asm volatile("" : "+s"(first));  // (the destinations are worked out here, not kept in scalar registers)
+#pragma unroll
+        for (int c = 0; c < kCopies; ++c) {
+            const int group = (first + c) / (kRows / 4);  // K group of these rows
+            const int col0 = kTileCols * (2 * pair + group) + kBlockCols * B;
+            const uint32_t off = col0 + chunk8[c] < p.N ? src[c] + 2u * (uint32_t)col0 : 0xfffffff0u;  // beyond N: zeros
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                xrsrc, (__attribute__((address_space(3))) void *)(stages + which * kStage + 1024 * (first + c)), 16, (int)off, 0, 0, 0);
+        }
+    };
+
+    int rg = u_begin / wp.pairs, pair = u_begin - rg * wp.pairs;
+    auto tile_rsrc = [&](int rgroup, int pr, bool wanted) {
+        const int t = kWideRowTiles * rgroup + rt, sl = 2 * pr + kg;
+        const bool ok = wanted && t < p.ntile && sl < p.nslice;
+        return __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint8_t *>(p.blob + (ok ? ((size_t)sl * p.ntile + t) * p.tile_bytes : 0)), 0, ok ? (int)p.tile_bytes : 0,
+            kRawBufferFlags);
+    };
+    WideTile<Q> nxt;
+    const int scale_lane = lane & p.scale_lane_mask;
+    copy_stage(0, pair, 0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    {
+        const __amdgpu_buffer_rsrc_t rsrc = tile_rsrc(rg, pair, true);
+#pragma unroll
+        for (int k = 0; k < 2 * Q; ++k) wide_load_plane<Q>(nxt, rsrc, lane, k / Q, k % Q);
+        wide_load_scales<Q, Z, SUB>(nxt, rsrc, scale_lane);
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    copy_stage(1, pair, 1);  // (waited for in the middle of the first block)
+    build_sign_table<64 * kWideWaves, 16, true>(tab, tid);
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kCopies) : "memory");
+
+    const uint32_t copy_bits = (lane & 15) * 16;  // this lane's copy of the sign table
+    // staged rows of K group kg: row r of a column group, chunk 4 s + h at position (4 s + h) ^ g(r)
+    const int g_r = r ^ ((r & 4) << 1);
+    const uint8_t *const xrow = stages + kg * kRows * 256 + r * 256;
+    const u32x4 ones = {0x3c003c00u, 0x3c003c00u, 0x3c003c00u, 0x3c003c00u};
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f16x8 X[4][NB];  // the operands of the block at hand
+    auto read_x = [&](int which, int s) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+            X[s][nb] = *reinterpret_cast<const f16x8 *>(xrow + which * kStage + nb * 4096 + (((4 * s + h) ^ g_r) * 16));
+    };
+#pragma unroll
+    for (int s = 0; s < 4; ++s) read_x(0, s);
+
+    uint8_t *const slot = owns + wave * kOwn;
+    const uint32_t turn = (4 - (r & 3)) & 3;
+    // byte s of an outgoing dword comes from dword s xor `group`, which puts the block's scaling groups in order
+    const uint32_t group = SUB == 2 ? (uint32_t)(((8 - (r & 7)) & 7) >> 2 | (r >> 3) << 1) : (uint32_t)(r >> 2);
+    uint32_t sel0 = 0, sel1 = 0;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        const uint32_t d = (uint32_t)s ^ group;  // dword whose byte goes to position s; a0/b0 hold dwords (0,1)/(2,3)
+        const uint32_t lowb = (d & 1) + ((d & 2) ? 4u : 0u);
+        sel0 |= lowb << (8 * s);
+        sel1 |= (lowb + 2u) << (8 * s);
+    }
+
+    const uint32_t own_scale = (subgroup_of_range(0, r, SUB) * 64 + r) * kScaleBytes;
+
+    int u = u_begin;
+    while (u < u_end) {
+        const int seg_end = min(u_end, (rg + 1) * wp.pairs), seg_rg = rg;
+        f32x4 acc[NB][2];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[nb][0] = acc[nb][1] = zero;
+        for (; u < seg_end; ++u) {
+            const bool more = u + 1 < u_end;
+            int n_pair = pair + 1, n_rg = rg;
+            if (n_pair == wp.pairs) { n_pair = 0; n_rg = rg + 1; }
+            const __amdgpu_buffer_rsrc_t n_rsrc = tile_rsrc(n_rg, n_pair, more);
+
+            // wb[t][i][B]: byte s = chunk 4 s + h of (row 16 t + r, block B, plane i)
+            uint32_t wb[2][Q][4];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+#pragma unroll
+                for (int i = 0; i < Q; ++i) {
+                    const u32x4 w = nxt.planes[t][i];
+                    // bytes in order inside a scaling group, then byte s of every dword from dword s (groups in order: sel0, sel1) and
+                    // the dwords of the four lanes exchanged through LDS
+                    u32x4 v;
+                    if constexpr (SUB == 2) {
+                        v = u32x4{__builtin_amdgcn_alignbyte(w.y, w.x, turn), __builtin_amdgcn_alignbyte(w.x, w.y, turn),
+                                  __builtin_amdgcn_alignbyte(w.w, w.z, turn), __builtin_amdgcn_alignbyte(w.z, w.w, turn)};
+                    } else {
+                        v = u32x4{__builtin_amdgcn_alignbyte(w.x, w.x, turn), __builtin_amdgcn_alignbyte(w.y, w.y, turn),
+                                  __builtin_amdgcn_alignbyte(w.z, w.z, turn), __builtin_amdgcn_alignbyte(w.w, w.w, turn)};
+                    }
+                    const uint32_t a0 = __builtin_amdgcn_perm(v.y, v.x, 0x05010400u), a1 = __builtin_amdgcn_perm(v.y, v.x, 0x07030602u);
+                    const uint32_t b0 = __builtin_amdgcn_perm(v.w, v.z, 0x05010400u), b1 = __builtin_amdgcn_perm(v.w, v.z, 0x07030602u);
+                    *reinterpret_cast<u32x4 *>(slot + i * 1024 + lane * 16) =
+                        u32x4{__builtin_amdgcn_perm(b0, a0, sel0), __builtin_amdgcn_perm(b0, a0, sel1), __builtin_amdgcn_perm(b1, a1, sel0),
+                              __builtin_amdgcn_perm(b1, a1, sel1)};
+#pragma unroll
+                    for (int B = 0; B < 4; ++B) wb[t][i][B] = *reinterpret_cast<const uint32_t *>(slot + i * 1024 + 256 * B + 16 * r + 4 * h);
+                }
+            }
+            store_scales<Q, Z, SUB, kScaleBytes>(nxt.scales, slot + lane * kScaleBytes);  // (the sign words are in registers)
+
+            f16x8 abuf[kBufs][Q];
+            auto fetch = [&](int q) {  // sign operands of step q = 8 B + 4 t + s
+                const int B = q >> 3, t = (q >> 2) & 1, s = q & 3;
+#pragma unroll
+                for (int i = 0; i < Q; ++i) {
+                    const uint32_t off = __builtin_amdgcn_perm(wb[t][i][B], copy_bits, 0x0c0c0400u | ((uint32_t)s << 8));
+                    abuf[q % kBufs][i] = *reinterpret_cast<const f16x8 *>(tab + off);
+                }
+            };
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q) fetch(q);
+
+            f32x4 C[NB][Q + Z];
+            float v[Q + Z];
+            // adds term c of the group that has just been finished for row half t
+            auto apply = [&](int t, int c) {
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        acc[nb][t][j] = fmaf(v[c], C[nb][c][j], acc[nb][t][j]);
+            };
+#pragma unroll
+            for (int q = 0; q < 32; ++q) {
+                const int B = q >> 3, t = (q >> 2) & 1, s = q & 3, cb = q % kBufs;
+                const bool start = s % kPer == 0, done = s % kPer == kPer - 1;
+                if ((q & 7) == 4) {
+                    // the next block's X has arrived (what was requested after it may still be under way), everyone has this block's in
+                    // registers: its stage can be filled again
+                    if (B < 3 && B > 0) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(B <= 2 ? Q : 0) : "memory");
+                    else if (B == 3) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((kRec + 3) / 4) : "memory");
+                    else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (B < 2) copy_stage(B & 1, pair, B + 2);
+                    else copy_stage(B & 1, more ? n_pair : wp.pairs, B - 2);  // (beyond the last slice: zeros)
+                    asm volatile("" ::: "memory");
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (B < 2) {
+#pragma unroll
+                        for (int i = 0; i < Q; ++i) wide_load_plane<Q>(nxt, n_rsrc, lane, B, i);
+                    } else if (B == 2) {
+                        wide_load_scales<Q, Z, SUB>(nxt, n_rsrc, scale_lane);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (q + kAhead < 32) fetch(q + kAhead);
+                const int tp = ((q + 31) >> 2) & 1;  // row half of the step before
+#pragma unroll
+                for (int i = 0; i < Q; ++i) {
+                    if (start && q > 0) apply(tp, i);
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+                        C[nb][i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(X[s][nb], abuf[cb][i], start ? zero : C[nb][i], 0, 0, 0);
+                }
+                if (Z) {
+                    if (start && q > 0) apply(tp, Q);
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)  // column sums of X
+                        C[nb][Q + Z - 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(X[s][nb], __builtin_bit_cast(f16x8, ones),
+                                                                                  start ? zero : C[nb][Q + Z - 1], 0, 0, 0);
+                }
+                if (t == 1) read_x((B & 1) ^ 1, s);  // the next block's
+                if (done) {
+                    // scales of the group that is finished by this step, from the lane and the byte range that hold it
+                    const uint8_t *const own = slot + (own_scale ^ ((s / kPer) * 64 * kScaleBytes)) + (t * SUB * 64 + 16 * B) * kScaleBytes;
+                    uint32_t o[2] = {0, 0};
+                    if constexpr (kScaleBytes == 4) {
+                        o[0] = *reinterpret_cast<const uint32_t *>(own);
+                    } else {
+                        const u32x2 both = *reinterpret_cast<const u32x2 *>(own);
+                        o[0] = both.x;
+                        o[1] = both.y;
+                    }
+#pragma unroll
+                    for (int c = 0; c < Q + Z; ++c) v[c] = half_bits_to_float((c & 1) ? o[c >> 1] >> 16 : o[c >> 1] & 0xffffu);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int c = 0; c < Q + Z; ++c) apply(1, c);
+            rg = n_rg; pair = n_pair;
+        }
+        // Flush.  The two K groups of a row tile meet in the first stage's buffer, whose block is in everyone's registers: wave kg keeps
+        // row half kg and hands the other half over.
+        // (The lane index goes through an empty asm so that the per-lane addresses of the flush are not kept in registers
+        // during the units.)
+        int fl = lane;
+        asm volatile("" : "+v"(fl));
+        int cols = p.batch;
+        asm volatile("" : "+s"(cols));
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        float *const meet = reinterpret_cast<float *>(stages) + rt * (NB * 2 * 4 * 64) + fl;  // [K group][column group][j][lane]
+        float *const here = meet + kg * (NB * 4 * 64), *const there = meet + (kg ^ 1) * (NB * 4 * 64);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float give = kg ? acc[nb][0][j] : acc[nb][1][j];
+                here[(4 * nb + j) * 64] = give;
+            }
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        // number of workgroups that contribute to this row group
+        int arrivals = wp.parts;
+        if (arrivals == 0)
+            arrivals = owner_of_unit<true>((seg_rg + 1) * wp.pairs - 1, p.units, groups, p.unit_base, p.unit_rem) -
+                       owner_of_unit<true>(seg_rg * wp.pairs, p.units, groups, p.unit_base, p.unit_rem) + 1;
+        const int row = (kWideRowTiles * seg_rg + rt) * kTileRows + 16 * kg + (fl & 15);
+        if (kWideRowTiles * seg_rg + rt < p.ntile) {  // uniform for the wave
+            f32x4 v[NB];
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    v[nb][j] = (kg ? acc[nb][1][j] : acc[nb][0][j]) + there[(4 * nb + j) * 64];
+            wide_store<NB>(p, cols, v, row, fl >> 4, arrivals);
+        }
+        // (what the others hand over is read before they reach the next barrier, and the buffer is not filled before that)
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing is on its way to LDS when a wave ends
+}
+
 // ---------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------
@@ -391,7 +693,10 @@ static void plan_wide(WideParams &wp, bool single_slice, int forced, int *groups
 template <int Q, int Z, int SUB, int NB>
 static hipError_t launch_one(const WideParams &wp, int groups, hipStream_t stream)
 {
-    hipLaunchKernelGGL((bcq_wide_kernel<Q, Z, SUB, NB>), dim3((unsigned)groups), dim3(64 * kWideWaves), 0, stream, wp);
+    if constexpr (SUB == 1)
+        hipLaunchKernelGGL((bcq_wide_kernel<Q, Z, NB>), dim3((unsigned)groups), dim3(64 * kWideWaves), 0, stream, wp);
+    else
+        hipLaunchKernelGGL((bcq_wide_groups_kernel<Q, Z, SUB, NB>), dim3((unsigned)groups), dim3(64 * kWideWaves), 0, stream, wp);
     return hipGetLastError();
 }
 
