@@ -108,7 +108,10 @@ struct ProductArgs {
 // blocks / numbers / numbers from their end, H += 2 X^T X: 7168 channels, 2048 samples 436 / 421 / 424, 256 samples 105 / 108 / 107; 4096
 // channels 204 / 192 / 190 and 49.7 / 54.1 / 50.4, one sample 29.8 / 32.6 / 28.9; 132 channels, one sample 9.5 / 10.4 / (one XCD) 9.7.  The factor
 // and the GPTQ pass take the same time with all three.  Otherwise each XCD takes every eighth block, for the quadratic
-// forms column by column from the last one, whose columns have the longest k range.
+// forms and the products with a triangular right operand column by column from the last one, whose columns have the longest k range.
+// Several products of a launch go on where the one `before` ended: starting each at the first XCD left all blocks of small products to it
+// (7168 channels, us: 14 pairs of 256 channels 38 + 32 -> 20 + 19, 7 of 512 channels 64 + 50 -> 24 + 25, the longest columns of 4096 first
+// 212 -> 164).  Every other eight blocks go to the XCDs in reverse, so that none has all the longer ones of a triangular operand.
 template <int MODE>
 constexpr bool kProdEven = MODE == kAddTwiceSymmetric || MODE == kSubtract || MODE == kSubtractLower;
 
@@ -122,7 +125,7 @@ static inline int product_groups(int R, int C)
 }
 
 template <int MODE>
-__device__ __forceinline__ bool product_tile(int wg, int wgs, int R, int C, int *tile_row, int *tile_col)
+__device__ __forceinline__ bool product_tile(int wg, int wgs, int R, int C, int before, int *tile_row, int *tile_col)
 {
     const int ntr = (R + kProdTile - 1) / kProdTile, ntc = (C + kProdTile - 1) / kProdTile;
     const int xcd = wg & 7, j = wg >> 3;
@@ -158,9 +161,11 @@ __device__ __forceinline__ bool product_tile(int wg, int wgs, int R, int C, int 
         return true;
     } else {
         const int br = (ntr + kProdBlock - 1) / kProdBlock, bc = (ntc + kProdBlock - 1) / kProdBlock;
-        const int t = j & (kProdBlock * kProdBlock - 1), s = (j / (kProdBlock * kProdBlock)) * 8 + xcd;
+        const int t = j & (kProdBlock * kProdBlock - 1), round = j / (kProdBlock * kProdBlock), at = (xcd - before * br * bc) & 7;
+        constexpr bool kTurns = MODE == kStore || MODE == kStoreNegated;
+        const int s = round * 8 + (kTurns && (round & 1) ? 7 - at : at);
         if (s >= br * bc) return false;
-        const bool by_column = MODE == kQuadForm || MODE == kQuadFormSplit;
+        const bool by_column = MODE == kQuadForm || MODE == kQuadFormSplit || MODE == kStore;
         const int b_row = by_column ? s % br : s / bc, b_col = by_column ? bc - 1 - s / br : s % bc;
         *tile_row = b_row * kProdBlock + t / kProdBlock;
         *tile_col = b_col * kProdBlock + t % kProdBlock;
@@ -209,7 +214,8 @@ __device__ __forceinline__ void product_tile_of(ProductArgs p, int wg, int wgs, 
         if (p.k_is_columns) p.K = p.C;
     }
     int tile_row, tile_col;
-    if (!product_tile<MODE>(wg, wgs, p.R, p.C, &tile_row, &tile_col)) return;
+    const int before = MODE == kStore || MODE == kStoreNegated ? (int)blockIdx.y : 0;  // products of the launch before this one
+    if (!product_tile<MODE>(wg, wgs, p.R, p.C, before, &tile_row, &tile_col)) return;
     const int r0 = tile_row * kProdTile, c0 = tile_col * kProdTile;
     if (kSplitA && p.rows && r0 >= *p.rows) return;
 

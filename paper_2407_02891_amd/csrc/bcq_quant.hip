@@ -162,6 +162,9 @@ hipError_t launch_quant_hessian(int N, int T, const float *X, float *H, hipStrea
 // panels, trailing updates of K = 128 and 512 for R; growing K for the off-diagonal blocks of U).
 // Working matrices (binary32, pitch N): Hw = H_d (consumed), Rt = R^T, Ut = U^T, T = one panel.
 constexpr int kFactorBlock = 128, kFactorPanel = 512;
+// Tiles of a trailing update from which its far part runs beside the next panel: 128 are done in 24 us by themselves, with the rows of the next
+// panel, which alone take as long.
+constexpr int kFactorBeside = 128;
 
 // H_d is factored as D^-1 H_d D^-1, D = diag(2^e) with 2^2e <= H_d[j][j] < 2^(2e + 2): powers of two, so every rounding is that of
 // the unscaled factorisation, but all rows and columns of what the products multiply are of one size.  (They hold an operand
@@ -251,12 +254,11 @@ __device__ __forceinline__ void eliminate_16(float (&x)[16], int i, float *pivot
     step(std::integral_constant<int, 0>{});
 }
 
-__global__ __launch_bounds__(256) void factor_diag_kernel(int N, int r0, int b, const float *__restrict__ Hw, const float *__restrict__ H,
-                                                          const float *__restrict__ lambda, float *__restrict__ U, float *__restrict__ Ut)
+// X, G (negated), pivot, inverse: LDS, objects of their own so that the compiler can tell the reads of one from the writes of another.
+__device__ __forceinline__ void factor_diag(float (&X)[kFactorBlock][kDiagPitch], float (&G)[kFactorBlock][kDiagG], float (&pivot)[kFactorBlock],
+                                            float (&inverse)[kFactorBlock], int N, int r0, int b, const float *Hw, const float *__restrict__ H,
+                                            const float *__restrict__ lambda, float *__restrict__ U, float *__restrict__ Ut)
 {
-    __shared__ __attribute__((aligned(16))) float X[kFactorBlock][kDiagPitch];
-    __shared__ float G[kFactorBlock][kDiagG];  // negated
-    __shared__ __attribute__((aligned(16))) float pivot[kFactorBlock], inverse[kFactorBlock];
     const int tid = threadIdx.x, lane = tid & 63, lo = lane & 15, hi = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // this thread's four columns l .. l + 3 (b and N are multiples of 4) and rows first + 8 k, in and out
@@ -394,6 +396,31 @@ __global__ __launch_bounds__(256) void factor_diag_kernel(int N, int r0, int b, 
     }
 }
 
+// The first workgroup takes the diagonal block, those from the eighth on (workgroup numbers go round the XCDs) the tiles `first_tile`, .. of
+// `far`, the update of the rows above this panel's by the panel before: a diagonal block is one workgroup's chain, and the chip is free
+// beside it.  The LDS makes that one tile per compute unit; with 248 tiles a launch takes 30 to 35 us, 25 without any.  7168 channels, with the
+// order of the products of the inverse (bcq_product.h): 4.36 -> 4.00 ms, of which this is half (in launches of their own the 13 trailing updates are
+// 0.73 ms); 516 channels 294 -> 298 us.
+template <bool FAR>
+__global__ __launch_bounds__(256, FAR ? 2 : 1) void factor_diag_kernel(int N, int r0, int b, float *Hw, const float *__restrict__ H,
+                                                             const float *__restrict__ lambda, float *__restrict__ U, float *__restrict__ Ut,
+                                                             ProductArgs far, int first_tile, int tiles)
+{
+    __shared__ __attribute__((aligned(16))) float X[kFactorBlock][kDiagPitch];
+    __shared__ float G[kFactorBlock][kDiagG];
+    __shared__ __attribute__((aligned(16))) float pivot[kFactorBlock], inverse[kFactorBlock];
+    __shared__ __attribute__((aligned(16))) uint8_t tile[FAR ? sizeof(ProductShared) : 16];
+    if (!FAR || blockIdx.x == 0) {
+        if (FAR && b == 0) return;
+        if (FAR) __builtin_amdgcn_s_setprio(3);
+        factor_diag(X, G, pivot, inverse, N, r0, b, Hw, H, lambda, U, Ut);
+    } else if (FAR && blockIdx.x >= 8) {
+        ProductShared &s = *reinterpret_cast<ProductShared *>(tile);
+        product_tile_of<kSubtractLower>(far, first_tile + (int)blockIdx.x - 8, tiles, s.stage_a0, s.stage_a1, s.stage_b, s.largest,
+                                        s.largest_of_tile, s.shift);
+    }
+}
+
 // dst[c][r] = src[r][c], without the scale of channel c, for size x size blocks of a matrix of pitch N, block z of them z * stride
 // floats on, the last one with columns_end - 2 size z columns; the columns of the first one are the channels from `size` on.
 __global__ void transpose_blocks_kernel(int size, int N, size_t stride, int columns_end, const float *__restrict__ src,
@@ -456,12 +483,25 @@ hipError_t launch_quant_factor(int N, float damp, const float *H, float *U, void
     if (e != hipSuccess) return e;
     // R, from the last block column to the first.  Only the part of Hw on and below its diagonal blocks is kept up to date:
     // after a block the rows of its panel (four blocks), which the next blocks need, after a panel all rows above it, with
-    // the panel's 512 columns at once (a pass over what remains costs its reading and writing however few columns it adds).
+    // the panel's 512 columns at once (a pass over what remains costs its reading and writing however few columns it adds): first
+    // the rows of the next panel, then, beside that panel's diagonal blocks, those above them.
+    ProductArgs far = {};
+    int tiles = 0, done = 0;  // of `far`, in multiples of 8
+    const int beside = (compute_units() - 1) / 8 * 8;
+    auto diag = [&](int r0, int b, int count) {
+        const auto kernel = count > 0 ? factor_diag_kernel<true> : factor_diag_kernel<false>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(count > 0 ? 8 + count : 1)), dim3(256), 0, stream, N, r0, b, Hw, H, lambda, U, Ut, far, done,
+                           tiles);
+        done += count;
+    };
     for (int p1 = N; p1 > 0;) {
         const int p0 = (p1 - 1) / kFactorPanel * kFactorPanel;
+        // (what does not fit beside the panel's blocks)
+        const int blocks = (p1 - p0 + kFactorBlock - 1) / kFactorBlock;
+        if (tiles - done > blocks * beside) diag(0, 0, tiles - done - blocks * beside);
         for (int r1 = p1; r1 > p0;) {
             const int r0 = (r1 - 1) / kFactorBlock * kFactorBlock, b = r1 - r0;
-            hipLaunchKernelGGL(factor_diag_kernel, dim3(1), dim3(256), 0, stream, N, r0, b, Hw, H, lambda, U, Ut);
+            diag(r0, b, tiles - done < beside ? tiles - done : beside);
             if (r0 > 0) {
                 // panel, transposed: Rt[r0 + c][i] = R[i][r0 + c] = sum_m V[c][m] Hw[r0 + m][i]   (Hw symmetric, V = R_kk^-1)
                 launch_product<kStore>(stream, Ut + (size_t)r0 * N + r0, N, b, Hw + (size_t)r0 * N, N, r0, b, Rt + (size_t)r0 * N, N);
@@ -472,9 +512,16 @@ hipError_t launch_quant_factor(int N, float damp, const float *H, float *U, void
             }
             r1 = r0;
         }
-        // Hw[i][j] -= sum_c R[i][p0 + c] R[j][p0 + c] for j <= i < p0 (by tiles)
-        if (p0 > 0)
+        // Hw[i][j] -= sum_c R[i][p0 + c] R[j][p0 + c] for j <= i < p0 (by tiles); where there is much of it, only q0 <= i now
+        const int q0 = p0 > 0 ? (p0 - 1) / kFactorPanel * kFactorPanel : 0;
+        tiles = done = 0;
+        if (p0 > 0 && product_groups<kSubtractLower>(q0, q0) >= kFactorBeside) {
+            launch_product<kSubtract>(stream, Rt + (size_t)p0 * N + q0, N, p0 - q0, Rt + (size_t)p0 * N, N, p0, p1 - p0, Hw + (size_t)q0 * N, N);
+            far = product_args(Rt + (size_t)p0 * N, N, q0, Rt + (size_t)p0 * N, N, q0, p1 - p0, Hw, N);
+            tiles = product_groups<kSubtractLower>(q0, q0);
+        } else if (p0 > 0) {
             launch_product<kSubtractLower>(stream, Rt + (size_t)p0 * N, N, p0, Rt + (size_t)p0 * N, N, p0, p1 - p0, Hw, N);
+        }
         p1 = p0;
     }
     // U = R^-1: Hw is free now and holds the intermediate products

@@ -376,7 +376,7 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void bcq_wide_groups_kernel(Wid
     constexpr int kPer = 4 / SUB;                  // steps per scaling group
     constexpr int kScaleBytes = Q + Z <= 2 ? 4 : 8;  // the scales of a (row, block, byte range), in LDS
     constexpr int kAhead = 1, kBufs = kAhead + 1;  // steps that sign operands are requested ahead
-    static_assert(SUB == 2 || SUB == 4, "scaling groups per block");
+    static_assert((SUB == 2 || SUB == 4) && Q + Z <= 4, "scaling groups per block, scales per record");
     static_assert(kCopies >= 1, "a wave copies at least four rows");
     __shared__ __attribute__((aligned(16))) uint8_t stages[2 * kStage];
     __shared__ __attribute__((aligned(16))) uint8_t tab[kTabBytes<16>];
