@@ -254,11 +254,12 @@ __device__ __forceinline__ void eliminate_16(float (&x)[16], int i, float *pivot
     step(std::integral_constant<int, 0>{});
 }
 
-// X, G (negated), pivot, inverse: LDS, objects of their own so that the compiler can tell the reads of one from the writes of another.
-__device__ __forceinline__ void factor_diag(float (&X)[kFactorBlock][kDiagPitch], float (&G)[kFactorBlock][kDiagG], float (&pivot)[kFactorBlock],
-                                            float (&inverse)[kFactorBlock], int N, int r0, int b, const float *Hw, const float *__restrict__ H,
+__device__ __forceinline__ void factor_diag(int N, int r0, int b, const float *__restrict__ Hw, const float *__restrict__ H,
                                             const float *__restrict__ lambda, float *__restrict__ U, float *__restrict__ Ut)
 {
+    __shared__ __attribute__((aligned(16))) float X[kFactorBlock][kDiagPitch];
+    __shared__ float G[kFactorBlock][kDiagG];  // negated
+    __shared__ __attribute__((aligned(16))) float pivot[kFactorBlock], inverse[kFactorBlock];
     const int tid = threadIdx.x, lane = tid & 63, lo = lane & 15, hi = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // this thread's four columns l .. l + 3 (b and N are multiples of 4) and rows first + 8 k, in and out
@@ -396,26 +397,27 @@ __device__ __forceinline__ void factor_diag(float (&X)[kFactorBlock][kDiagPitch]
     }
 }
 
-// The first workgroup takes the diagonal block, those from the eighth on (workgroup numbers go round the XCDs) the tiles `first_tile`, .. of
-// `far`, the update of the rows above this panel's by the panel before: a diagonal block is one workgroup's chain, and the chip is free
-// beside it.  The LDS makes that one tile per compute unit; with 248 tiles a launch takes 30 to 35 us, 25 without any.  7168 channels, with the
-// order of the products of the inverse (bcq_product.h): 4.36 -> 4.00 ms, of which this is half (in launches of their own the 13 trailing updates are
-// 0.73 ms); 516 channels 294 -> 298 us.
-template <bool FAR>
-__global__ __launch_bounds__(256, FAR ? 2 : 1) void factor_diag_kernel(int N, int r0, int b, float *Hw, const float *__restrict__ H,
-                                                             const float *__restrict__ lambda, float *__restrict__ U, float *__restrict__ Ut,
-                                                             ProductArgs far, int first_tile, int tiles)
+__global__ __launch_bounds__(256) void factor_diag_kernel(int N, int r0, int b, const float *__restrict__ Hw, const float *__restrict__ H,
+                                                          const float *__restrict__ lambda, float *__restrict__ U, float *__restrict__ Ut)
 {
-    __shared__ __attribute__((aligned(16))) float X[kFactorBlock][kDiagPitch];
-    __shared__ float G[kFactorBlock][kDiagG];
-    __shared__ __attribute__((aligned(16))) float pivot[kFactorBlock], inverse[kFactorBlock];
-    __shared__ __attribute__((aligned(16))) uint8_t tile[FAR ? sizeof(ProductShared) : 16];
-    if (!FAR || blockIdx.x == 0) {
-        if (FAR && b == 0) return;
-        if (FAR) __builtin_amdgcn_s_setprio(3);
-        factor_diag(X, G, pivot, inverse, N, r0, b, Hw, H, lambda, U, Ut);
-    } else if (FAR && blockIdx.x >= 8) {
-        ProductShared &s = *reinterpret_cast<ProductShared *>(tile);
+    factor_diag(N, r0, b, Hw, H, lambda, U, Ut);
+}
+
+// The same in the first workgroup, or nothing with b = 0, and in those from the eighth on (workgroup numbers go round the XCDs) the tiles
+// `first_tile`, .. of `far`, the update of the rows above this panel's by the panel before: a diagonal block is one workgroup's chain, and
+// the chip is free beside it.  The LDS makes that one tile per compute unit; with 248 tiles a launch takes 30 to 35 us, 25 without any.
+// 7168 channels, with the order of the products of the inverse (bcq_product.h): 4.36 -> 4.00 ms, of which this is half (in launches of
+// their own the 13 trailing updates are 0.73 ms).
+__global__ __launch_bounds__(256) void factor_diag_far_kernel(int N, int r0, int b, float *Hw, const float *__restrict__ H,
+                                                              const float *__restrict__ lambda, float *__restrict__ U,
+                                                              float *__restrict__ Ut, ProductArgs far, int first_tile, int tiles)
+{
+    __shared__ ProductShared s;
+    if (blockIdx.x == 0) {
+        if (b == 0) return;
+        __builtin_amdgcn_s_setprio(3);
+        factor_diag(N, r0, b, Hw, H, lambda, U, Ut);
+    } else if (blockIdx.x >= 8) {
         product_tile_of<kSubtractLower>(far, first_tile + (int)blockIdx.x - 8, tiles, s.stage_a0, s.stage_a1, s.stage_b, s.largest,
                                         s.largest_of_tile, s.shift);
     }
@@ -489,9 +491,11 @@ hipError_t launch_quant_factor(int N, float damp, const float *H, float *U, void
     int tiles = 0, done = 0;  // of `far`, in multiples of 8
     const int beside = (compute_units() - 1) / 8 * 8;
     auto diag = [&](int r0, int b, int count) {
-        const auto kernel = count > 0 ? factor_diag_kernel<true> : factor_diag_kernel<false>;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)(count > 0 ? 8 + count : 1)), dim3(256), 0, stream, N, r0, b, Hw, H, lambda, U, Ut, far, done,
-                           tiles);
+        if (count > 0)
+            hipLaunchKernelGGL(factor_diag_far_kernel, dim3((unsigned)(8 + count)), dim3(256), 0, stream, N, r0, b, Hw, H, lambda, U, Ut, far, done,
+                               tiles);
+        else
+            hipLaunchKernelGGL(factor_diag_kernel, dim3(1), dim3(256), 0, stream, N, r0, b, Hw, H, lambda, U, Ut);
         done += count;
     };
     for (int p1 = N; p1 > 0;) {
