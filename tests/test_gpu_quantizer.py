@@ -710,6 +710,37 @@ def test_factor_with_loud_channels(N, loud, damp):
     assert err <= 8 * err32
 
 
+@pytest.mark.parametrize("N", [2564, 3072, 6660])
+def test_factor_updates_beside_the_blocks(N):
+    """Layers whose trailing updates run beside the diagonal blocks of the next panel: after a first panel of four channels (four
+    terms, with as many tiles as the rule asks for, and with more than fit beside a panel: the rest goes before it) and after
+    full panels.  Error per column of U against binary64, over that of a binary32 factorisation (LAPACK), as above."""
+    from scipy.linalg import solve_triangular
+    g = torch.Generator(device="cuda").manual_seed(N)
+    X = torch.randn((2 * N, N), device="cuda", generator=g)
+    X[:, :N // 32] *= 6
+    H = 2 * (X.t().contiguous() @ X)
+    H32 = ((H + H.t()) * 0.5).cpu().numpy()
+
+    def factor(dtype):
+        Hd = H32.astype(dtype)
+        Hd[np.diag_indices(N)] += dtype(0.01 * np.mean(np.diag(H32).astype(np.float64)))
+        inv = solve_triangular(np.linalg.cholesky(Hd[::-1, ::-1]), np.eye(N, dtype=dtype), lower=True)
+        return inv[::-1, ::-1].astype(np.float64)
+
+    U_o, U_32 = factor(np.float64), factor(np.float32)
+    U = torch.full((N, N), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.empty(bcq.quant_factor_workspace_bytes(N), dtype=torch.uint8, device="cuda")
+    bcq.quant_factor(N, 0.01, _dev(H32), U, ws)
+    torch.cuda.synchronize()
+    U_g = U.cpu().numpy().astype(np.float64)
+    assert (np.tril(U_g, -1) == 0).all()
+    size = np.linalg.norm(U_o, axis=0)
+    err, err32 = (np.linalg.norm((u - U_o) / size, axis=0) for u in (U_g, U_32))
+    print(f"N={N}: {err.max():.2e}, binary32 {err32.max():.2e}")
+    assert err.max() <= 8 * err32.max()
+
+
 @pytest.mark.parametrize("N", [64, 132, 160, 384, 404, 408, 1000])   # (a last block of 4, 20 and 24 columns: products of as many terms)
 def test_inverse_hessian_factor(N):
     """U with (H + 0.01 mean(diag H) I)^-1 = U^T U, U upper triangular, against the oracle's binary64 factor;
