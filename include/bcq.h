@@ -280,7 +280,7 @@ bcq_status bcq_read_probe(const void *buf, size_t bytes, void *sink, void *strea
  * operands from an LDS table, 16 columns per pass; groups of
  * 32/64 always use 1; 3 and 4 = automatic; 5 = for batch 2 the GEMV's table kernel
  * with two vectors per table entry wherever it applies, 6 = never that one, the others chosen
- * automatically), "skinny_lds_steps" (3 or 4, kernel 2 only); 0 =
+ * automatically; with 1 and 2 the integer kernel for two to four vectors is not used either), "skinny_lds_steps" (3 or 4, kernel 2 only); 0 =
  * automatic.
  * Unknown names or values return BCQ_ERR_INVALID_ARG.
  */
