@@ -14,17 +14,18 @@
 //    four vector instructions where selects and lane swaps take sixteen (9216 x 36864, q = 3: 31.5 -> 30.6 us).
 //  * A workgroup has up to twelve waves (168 registers: three per SIMD; a lone wave issues a vector instruction every 8 clocks, two or
 //    three one every 4): neighbouring slices of the same rows, and where these are few, several groups of rows.  Their sums of
-//    kChunk half tiles meet in LDS; what leaves the workgroup is one number per row and vector, stored if the workgroup has all slices,
+//    8 or 16 half tiles (few_chunk) meet in LDS; what leaves the workgroup is one number per row and vector, stored if the workgroup has all slices,
 //    else added to the row's fixed-point accumulator (encode_partial_f32), whose last contributor stores it.
 //  * What a launch costs besides its steps is the digits (about 100 vector instructions per vector and wave), so how many waves share the
 //    work is a compromise (plan_few).
 //
 // Bound: vector instructions (about 200 per half tile with three planes, 24 matrix instructions; with the loads taken out of the loop a launch
 // on 7168 x 28672 is 2 us shorter, of 23).  Measured against the kernels that took these calls before (us, four vectors, graph replay): 9216 x 36864
-// q = 3 41.1 -> 33.5, 28083 x 10208 38.2 -> 29.6, 7168 x 28672 27.8 -> 23.6, 7168 x 7168 11.6 -> 10.5, 2048 x 4096 q = 2 6.1 -> 5.4, 512 x 512 4.9 -> 4.2;
+// q = 3 41.1 -> 33.0, 28083 x 10208 38.2 -> 29.6, 7168 x 28672 27.8 -> 23.0, 7168 x 7168 11.6 -> 10.5, 2048 x 4096 q = 2 6.1 -> 5.4, 512 x 512 4.9 -> 4.2;
 // two vectors 4096 x 4096 7.4 -> 6.0, 512 x 512 4.9 -> 3.7.  Tried: signs from a table of 8-byte entries in LDS with three digits and a third fewer
 // vector instructions: 40.4 / 27.2 us on the two large layers (30.6 / 22.1 this way, eager); eight vectors per wave: 34 against 28 us there; the activations
-// of a lane strided so that the digits need no exchange between lanes: 1 to 3 % slower.
+// of a lane strided so that the digits need no exchange between lanes: 1 to 3 % slower; the additions of two or four half tiles of a wave's share of a meeting
+// under way at once: 7168 x 28672 the same, small layers 3 to 20 % slower (registers go to scratch).
 #include <atomic>
 
 #include "bcq_internal.h"
@@ -36,7 +37,6 @@ namespace bcq {
 namespace {
 
 constexpr int kFewWaves = 12, kFewBatch = 4;
-constexpr int kChunk = 8;              // half tiles between two meetings of a workgroup's waves
 constexpr int kFewX = 8192;            // bytes of a slice's digits: [block][half of the bits][lane] 16 bytes
 constexpr int kFewStart = 4 * 4 * 16;  // start digits per (block, vector)
 
@@ -54,14 +54,18 @@ struct FewParams {
     int scale_lane_mask;        // 63: one scale record per lane; 15: one per row (group = N)
 };
 
+// Half tiles between two meetings of a workgroup's waves, of at most `most`.  With more than four waves there is one workgroup per compute
+// unit, which stands still meanwhile (8 / 16, us, four vectors: 7168 x 28672 24.2 / 23.0, 9216 x 36864 33.8 / 33.1, 28672 x 8192 with offset 26.3 / 25.5);
+// several of them fill each other's pauses, and their additions are better spread (28672 x 7168 25.5 / 25.9).
+constexpr int few_chunk(int waves, int most) { return waves > 4 && most > 8 ? 16 : 8; }
 // LDS of a workgroup of `waves` waves; behind it a scale per (wave, block, vector), static.
-constexpr size_t few_lds_bytes(int waves) { return (size_t)waves * (kFewX + kFewStart + kChunk * 256); }
-static_assert(few_lds_bytes(kFewWaves) + kFewWaves * 64 <= 160 * 1024, "one workgroup per compute unit");
+constexpr size_t few_lds_bytes(int waves, int chunk) { return (size_t)waves * (kFewX + kFewStart + chunk * 256); }
+static_assert(few_lds_bytes(kFewWaves, 16) + kFewWaves * 64 <= 160 * 1024, "one workgroup per compute unit");
 
 }  // namespace
 
-// V: vectors made into digits, 2 or 4; the operand's other rows are not looked at.
-template <int Q, int Z, int V>
+// V: vectors made into digits, 2 or 4; the operand's other rows are not looked at.  CHUNK: half tiles between two meetings of the waves.
+template <int Q, int Z, int V, int CHUNK>
 __global__ __launch_bounds__(64 * kFewWaves) void bcq_few_kernel(FewParams p)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t few_lds[];
@@ -154,8 +158,8 @@ __global__ __launch_bounds__(64 * kFewWaves) void bcq_few_kernel(FewParams p)
     const uint32_t turn = k & 3;
     const int from = r * 16 + ((h + (k >> 2)) & 3) * 4;
 
-    for (int done = 0; done < most; done += kChunk) {
-        const int c_end = min(h_end, h_begin + done + kChunk);
+    for (int done = 0; done < most; done += CHUNK) {
+        const int c_end = min(h_end, h_begin + done + CHUNK);
         for (int half = h_begin + done; half < c_end; half += 2) {
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
@@ -219,7 +223,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void bcq_few_kernel(FewParams p)
         }
         __syncthreads();
         // one number per row and vector: item = [group of waves][half tile][vector][row]
-        const int each = min(kChunk, most - done) * 64;
+        const int each = min(CHUNK, most - done) * 64;
         for (int item = tid; item < row_groups * each; item += (int)blockDim.x) {
             const int group = item / each, e = item - group * each;
             const int half = first_half(first_part + group) + done + (e >> 6);
@@ -240,7 +244,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void bcq_few_kernel(FewParams p)
                 }
             }
         }
-        if (done + kChunk < most) __syncthreads();
+        if (done + CHUNK < most) __syncthreads();
     }
 }
 
@@ -304,29 +308,32 @@ FewPlan plan_few(const Geom &g, int batch, int forced)
     return best;
 }
 
-template <int Q, int Z, int V>
+template <int Q, int Z, int V, int CHUNK>
 hipError_t launch_few_v(const FewParams &p, int waves, int groups, hipStream_t stream)
 {
-    const size_t lds = few_lds_bytes(waves);
+    const size_t lds = few_lds_bytes(waves, CHUNK);
     // more LDS than a launch gets by itself: asked for once per device
     constexpr int kMaxDevices = 64;
     static std::atomic<bool> asked[kMaxDevices];
     int dev = 0;
     const bool known = hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices;
     if (!known || !asked[dev].load(std::memory_order_relaxed)) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(bcq_few_kernel<Q, Z, V>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)few_lds_bytes(kFewWaves));
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(bcq_few_kernel<Q, Z, V, CHUNK>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)few_lds_bytes(kFewWaves, CHUNK));
         if (e != hipSuccess) return e;
         if (known) asked[dev].store(true, std::memory_order_relaxed);
     }
-    hipLaunchKernelGGL((bcq_few_kernel<Q, Z, V>), dim3((unsigned)groups), dim3(64 * waves), lds, stream, p);
+    hipLaunchKernelGGL((bcq_few_kernel<Q, Z, V, CHUNK>), dim3((unsigned)groups), dim3(64 * waves), lds, stream, p);
     return hipGetLastError();
 }
 
 template <int Q, int Z>
 hipError_t launch_few_qz(const FewParams &p, int waves, int groups, hipStream_t stream)
 {
-    return p.batch == 2 ? launch_few_v<Q, Z, 2>(p, waves, groups, stream) : launch_few_v<Q, Z, 4>(p, waves, groups, stream);
+    const int chunk = few_chunk(waves, p.part_base + (p.part_rem > 0 ? 1 : 0));
+    if (p.batch == 2)
+        return chunk == 8 ? launch_few_v<Q, Z, 2, 8>(p, waves, groups, stream) : launch_few_v<Q, Z, 2, 16>(p, waves, groups, stream);
+    return chunk == 8 ? launch_few_v<Q, Z, 4, 8>(p, waves, groups, stream) : launch_few_v<Q, Z, 4, 16>(p, waves, groups, stream);
 }
 
 }  // namespace

@@ -470,7 +470,7 @@ def test_integer_kernel_for_up_to_four_vectors(workgroups, batch):
         bcq.set_option("workgroups", workgroups)
         for (M, N, q, off, group) in [(96, 2048, 3, False, 128), (300, 5120, 3, True, 128), (70, 1536, 2, True, 128), (1000, 2560, 1, False, 128),
                                       (203, 3200, 4, True, 128), (96, 2048, 3, True, 2048), (40, 512, 3, False, 128), (16, 512, 2, True, 128),
-                                      (777, 6656, 3, False, 256), (33, 32, 4, False, 32), (1, 7168, 3, True, 128), (500, 13 * 512, 1, True, 256)]:
+                                      (777, 6656, 3, False, 256), (513, 5632, 3, True, 128), (33, 32, 4, False, 32), (1, 7168, 3, True, 128), (500, 13 * 512, 1, True, 256)]:
             L = bcq_synth.make_exact_layer(M, N, q, group=group, offset=off, batch=batch, seed=M + q + batch)
             pl = U.upload_and_pack(L, max_batch=batch)
             expect = ref.gemm(L.planes, L.alpha, L.offset, L.x).astype(np.float16).astype(np.float64)
