@@ -552,11 +552,12 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void bcq_wide_groups_kernel(Wid
                 const int B = q >> 3, t = (q >> 2) & 1, s = q & 3, cb = q % kBufs;
                 const bool start = s % kPer == 0, done = s % kPer == kPer - 1;
                 if ((q & 7) == 4) {
-                    // the next block's X has arrived (what was requested after it may still be under way), everyone has this block's in
-                    // registers: its stage can be filled again
-                    if (B < 3 && B > 0) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(B <= 2 ? Q : 0) : "memory");
-                    else if (B == 3) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((kRec + 3) / 4) : "memory");
-                    else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+                    // the next block's X has arrived (what was requested after it may still be under way), and everyone's reads of this
+                    // block's have returned (lgkmcnt: nothing else waits for them before the barrier, and a refill does not wait for
+                    // reads that are queued): its stage can be filled again
+                    if (B == 0) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                    else if (B < 3) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(Q) : "memory");
+                    else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((kRec + 3) / 4) : "memory");
                     __builtin_amdgcn_sched_barrier(0);
                     if (B < 2) copy_stage(B & 1, pair, B + 2);
                     else copy_stage(B & 1, more ? n_pair : wp.pairs, B - 2);  // (beyond the last slice: zeros)
