@@ -622,6 +622,33 @@ def test_wide_kernel_edges(workgroups, M, N, q, offset, group, batch):
         bcq.set_option("waves", 0)
 
 
+# (planes, offset, groups of 64 / 32: the most column groups of 16 that bcq_wide_groups_kernel takes in a pass)
+_GROUPS_KERNEL = {(1, False): (4, 4), (1, True): (4, 4), (2, False): (4, 4), (2, True): (4, 3), (3, False): (3, 3), (3, True): (3, 2),
+                  (4, False): (2, 0)}
+
+
+@pytest.mark.parametrize("q,offset,group,nb", [(q, z, g, nb) for (q, z), most in _GROUPS_KERNEL.items() for g, m in zip((64, 32), most)
+                                               for nb in range(2, m + 1)])
+def test_groups_kernel_instances(q, offset, group, nb):
+    """Every instance of the kernel for groups of 32 and 64 (bcq_wide.hip), with a full last column group and with one vector in it, units that
+    follow one another and a work split inside a row group: bit for bit the oracle's result on exact inputs, workspace left zero; gate
+    on random inputs with outlier channels."""
+    try:
+        bcq.set_option("waves", 8)
+        for batch, workgroups in ((16 * nb, 1), (16 * nb - 15, 3)):
+            bcq.set_option("workgroups", workgroups)
+            L = bcq_synth.make_exact_layer(161, 2560, q, group=group, offset=offset, batch=batch, seed=group + q + batch)
+            pl = U.upload_and_pack(L, max_batch=batch)
+            expect = ref.gemm(L.planes, L.alpha, L.offset, L.x).astype(np.float16).astype(np.float64)
+            assert np.array_equal(U.gpu_gemm(pl, U.x_dev(L)).astype(np.float64), expect), (batch, workgroups)
+            assert not pl.workspace.cpu().numpy().any()
+        bcq.set_option("workgroups", 0)
+        _run_case(300, 3136, q, group, offset, batch=16 * nb - 3, seed=q + nb, outlier_frac=0.01)
+    finally:
+        bcq.set_option("workgroups", 0)
+        bcq.set_option("waves", 0)
+
+
 @pytest.mark.parametrize("group,batch,ldx", [
     (64, 17, 2 ** 27 - 8), (128, 17, 2 ** 27 - 8), (1024, 17, 2 ** 27 - 8),   # 16 rows fit 32-bit byte offsets, 17 do not
     (128, 16, 2 ** 28), (64, 9, 2 ** 28),                                     # 8 fit
