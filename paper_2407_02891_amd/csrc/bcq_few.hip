@@ -3,9 +3,9 @@
 //   y_v[m] = sum_blocks sum_i alpha_i[m,blk] * S_i,v[m,blk]  (+ z[m,blk] * X_v[blk])
 //
 // The sums over the signs are formed by the 8-bit integer matrix instruction, exactly: v_mfma_i32_16x16x64_i8 with the sign bits
-// masked in place as one operand and the activations' digits as the other (bcq_digits.h).  Four vectors of four digits are the
-// sixteen rows of that operand, and lane 16 h + r of the result holds the four digits of vector h's sum for weight row r:
-// two additions, two conversions and an FMA make it a binary32 number.  A sign costs a quarter of a vector instruction and no table.
+// masked in place as one operand and the activations' digits as the other (bcq_digits.h, which says what the digits round).  Four vectors of
+// four digits are the sixteen rows of that operand, and lane 16 h + r of the result holds the four digits of vector h's sum for weight row r:
+// two additions, two conversions and an FMA make it a binary32 number.  A sign costs 9/32 of a vector instruction and no table.
 //
 //  * A wave owns one column slice of 512: its activations are made into digits once and stay in 48 registers, and it streams
 //    the slice's row tiles, which are contiguous in the blob, a tile ahead.  There is no barrier in that stream.
@@ -16,13 +16,15 @@
 //    three one every 4): neighbouring slices of the same rows, and where these are few, several groups of rows.  Their sums of
 //    8 or 16 half tiles (few_chunk) meet in LDS; what leaves the workgroup is one number per row and vector, stored if the workgroup has all slices,
 //    else added to the row's fixed-point accumulator (encode_partial_f32), whose last contributor stores it.
-//  * What a launch costs besides its steps is the digits (about 100 vector instructions per vector and wave), so how many waves share the
+//  * What a launch costs besides its steps is the digits (about 120 vector instructions per vector and wave), so how many waves share the
 //    work is a compromise (plan_few).
 //
-// Bound: vector instructions (about 200 per half tile with three planes, 24 matrix instructions; with the loads taken out of the loop a launch
-// on 7168 x 28672 is 2 us shorter, of 23).  Measured against the kernels that took these calls before (us, four vectors, graph replay): 9216 x 36864
-// q = 3 41.1 -> 33.0, 28083 x 10208 38.2 -> 29.6, 7168 x 28672 27.8 -> 23.0, 7168 x 7168 11.6 -> 10.5, 2048 x 4096 q = 2 6.1 -> 5.4, 512 x 512 4.9 -> 4.2;
-// two vectors 4096 x 4096 7.4 -> 6.0, 512 x 512 4.9 -> 3.7.  Tried: signs from a table of 8-byte entries in LDS with three digits and a third fewer
+// Bound: vector instructions (about 215 per half tile with three planes, 24 matrix instructions; with the loads taken out of the loop a launch
+// on 7168 x 28672 is 2 us shorter, of 22).  Measured against the kernels that took these calls before (us, four vectors, graph replay): 9216 x 36864
+// q = 3 38.8 -> 32.6, 7168 x 28672 25.9 -> 21.8, 28672 x 7168 26.0 -> 24.8, 28083 x 10208 with a scale per row 33.6 -> 29.2, 7168 x 7168 11.6 -> 10.4,
+// 2048 x 4096 q = 2 5.9 -> 4.9, 512 x 512 4.9 -> 4.3; two vectors 4096 x 4096 7.1 -> 5.8, 512 x 512 4.8 -> 3.8.  All eight signs of a byte masked without a
+// shift is 0 to 2 % faster (9216 x 36864 32.2, 7168 x 7168 10.1), but takes 2^7 from the digits' range instead of 2^3: with 22 bits of activations
+// the error where a loud column cancels was ten times that of a sum in binary32, and is a quarter of it now.  Tried: signs from a table of 8-byte entries in LDS with three digits and a third fewer
 // vector instructions: 40.4 / 27.2 us on the two large layers (30.6 / 22.1 this way, eager); eight vectors per wave: 34 against 28 us there; the activations
 // of a lane strided so that the digits need no exchange between lanes: 1 to 3 % slower; the additions of two or four half tiles of a wave's share of a meeting
 // under way at once: 7168 x 28672 the same, small layers 3 to 20 % slower (registers go to scratch).
@@ -38,7 +40,6 @@ namespace {
 
 constexpr int kFewWaves = 12, kFewBatch = 4;
 constexpr int kFewX = 8192;            // bytes of a slice's digits: [block][half of the bits][lane] 16 bytes
-constexpr int kFewStart = 4 * 4 * 16;  // start digits per (block, vector)
 
 struct FewParams {
     const uint8_t *blob;
@@ -58,8 +59,8 @@ struct FewParams {
 // unit, which stands still meanwhile (8 / 16, us, four vectors: 7168 x 28672 24.2 / 23.0, 9216 x 36864 33.8 / 33.1, 28672 x 8192 with offset 26.3 / 25.5);
 // several of them fill each other's pauses, and their additions are better spread (28672 x 7168 25.5 / 25.9).
 constexpr int few_chunk(int waves, int most) { return waves > 4 && most > 8 ? 16 : 8; }
-// LDS of a workgroup of `waves` waves; behind it a scale per (wave, block, vector), static.
-constexpr size_t few_lds_bytes(int waves, int chunk) { return (size_t)waves * (kFewX + kFewStart + chunk * 256); }
+// LDS of a workgroup of `waves` waves; a scale per (wave, block, vector), static, beside it.
+constexpr size_t few_lds_bytes(int waves, int chunk) { return (size_t)waves * (kFewX + chunk * 256); }
 static_assert(few_lds_bytes(kFewWaves, 16) + kFewWaves * 64 <= 160 * 1024, "one workgroup per compute unit");
 
 }  // namespace
@@ -70,12 +71,11 @@ __global__ __launch_bounds__(64 * kFewWaves) void bcq_few_kernel(FewParams p)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t few_lds[];
     __shared__ float block_scale[kFewWaves][4][4];  // [wave][block][vector]
-    __shared__ float block_sum[Z ? kFewWaves : 1][4][4];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int waves = blockDim.x >> 6;
     const int r = lane & 15, h = lane >> 4;
-    uint8_t *const xs = few_lds + wave * (kFewX + kFewStart);
-    float *const partial = reinterpret_cast<float *>(few_lds + waves * (kFewX + kFewStart));
+    uint8_t *const xs = few_lds + wave * kFewX;
+    float *const partial = reinterpret_cast<float *>(few_lds + waves * kFewX);
 
     // this wave: slice `slice`, half tiles [h_begin, h_end)
     const int range = blockIdx.x % p.ranges, row_groups = waves / p.slices, first_part = blockIdx.x / p.ranges * row_groups;
@@ -117,12 +117,11 @@ __global__ __launch_bounds__(64 * kFewWaves) void bcq_few_kernel(FewParams p)
 
     // ---- digits: lane (block h, chunk r) writes, for vector v, what lane group r div 4 of X row 4 v + r mod 4 reads ----
     uint32_t digits[V][8];
-    int sum[V];
     float own_scale[V];
 #pragma unroll
     for (int v = 0; v < V; ++v)
         if (!have || v >= p.batch) xr[v] = u32x4{0u, 0u, 0u, 0u};
-    block_digits<V>(xr, digits, sum, own_scale);
+    block_digits<V>(xr, digits, own_scale);
 #pragma unroll
     for (int v = 0; v < V; ++v) {
         uint8_t *const dst = xs + (h * 128 + (r >> 2) * 16 + 4 * v + (r & 3)) * 16;
@@ -133,11 +132,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void bcq_few_kernel(FewParams p)
     }
     if (r == 0) {
 #pragma unroll
-        for (int v = 0; v < V; ++v) {
-            *reinterpret_cast<i32x4 *>(xs + kFewX + (h * 4 + v) * 16) = start_digits(sum[v]);
-            block_scale[wave][h][v] = own_scale[v];
-            if (Z) block_sum[Z ? wave : 0][h][v] = 64.0f * (float)sum[v];
-        }
+        for (int v = 0; v < V; ++v) block_scale[wave][h][v] = own_scale[v];
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (one wave wrote and reads all of it)
     // this lane's vector is h
@@ -146,10 +141,16 @@ __global__ __launch_bounds__(64 * kFewWaves) void bcq_few_kernel(FewParams p)
 #pragma unroll
     for (int B = 0; B < 4; ++B) {
         scale[B] = block_scale[wave][B][h];
-        if (Z) xsum[Z ? B : 0] = block_sum[Z ? wave : 0][B][h];
-        start[B] = *reinterpret_cast<const i32x4 *>(xs + kFewX + (B * 4 + h) * 16);
         X[B][0] = *reinterpret_cast<const i32x4 *>(xs + (B * 128 + lane) * 16);
         X[B][1] = *reinterpret_cast<const i32x4 *>(xs + (B * 128 + 64 + lane) * 16);
+    }
+#pragma unroll
+    for (int B = 0; B < 4; ++B) {  // all bits set: the digits of S
+        const i32x4 all = masked_signs(0x0f0f0f0fu);
+        i32x4 S = __builtin_amdgcn_mfma_i32_16x16x64_i8(X[B][0], all, i32x4{0, 0, 0, 0}, 0, 0, 0);
+        S = __builtin_amdgcn_mfma_i32_16x16x64_i8(X[B][1], all, S, 0, 0, 0);
+        start[B] = start_digits(S);
+        if (Z) xsum[Z ? B : 0] = 0.5f * digit_value(S);
     }
 
     // The blob's rotation (chunk_of_byte): chunk c of the block is byte (c - r) mod 16, so dword d in chunk order is dword (d + k div 4) mod 4 of the
@@ -207,7 +208,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void bcq_few_kernel(FewParams p)
                     for (int bits = 0; bits < 2; ++bits)
 #pragma unroll
                         for (int i = 0; i < Q; ++i)
-                            acc[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(X[B][bits], masked_signs(wb[i][B], bits),
+                            acc[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(X[B][bits], masked_signs(bits ? wb[i][B] >> 4 : wb[i][B]),
                                                                           bits == 0 ? start[B] : acc[i], 0, 0, 0);
                     float yb = 0.0f;
 #pragma unroll
