@@ -615,8 +615,9 @@ __device__ __forceinline__ void product_tile_of(ProductArgs p, int wg, int wgs, 
     }
 }
 
+// The tiles of a launch are those from `first` (a multiple of 8) on of `all`.
 template <int MODE>
-__global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
+__device__ __forceinline__ void product_tiles(const ProductArgs &p, int first, int all)
 {
     // (A's stages are two objects so that the compiler can tell the copies into one, of kQuadFormSplit, from the reads of the other)
     __shared__ __attribute__((aligned(16))) ProductStage stage_a0;
@@ -625,7 +626,19 @@ __global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
     __shared__ ProductLargest largest;
     __shared__ unsigned largest_of_tile[2];
     __shared__ ProductShift shift;
-    product_tile_of<MODE>(p, blockIdx.x, gridDim.x, stage_a0, stage_a1, stage_b, largest, largest_of_tile, shift);
+    product_tile_of<MODE>(p, first + (int)blockIdx.x, all, stage_a0, stage_a1, stage_b, largest, largest_of_tile, shift);
+}
+
+template <int MODE>
+__global__ __launch_bounds__(256, 2) void product_kernel(ProductArgs p)
+{
+    product_tiles<MODE>(p, 0, gridDim.x);
+}
+
+template <int MODE>
+__global__ __launch_bounds__(256, 2) void product_part_kernel(ProductArgs p, int first, int all)
+{
+    product_tiles<MODE>(p, first, all);
 }
 
 static ProductArgs product_args(const float *A, int lda, int R, const float *B, int ldb, int C, int K, float *out, int ldo,

@@ -403,7 +403,7 @@ __global__ __launch_bounds__(256) void factor_diag_kernel(int N, int r0, int b, 
     factor_diag(N, r0, b, Hw, H, lambda, U, Ut);
 }
 
-// The same in the first workgroup, or nothing with b = 0, and in those from the eighth on (workgroup numbers go round the XCDs) the tiles
+// The same in the first workgroup, and in those from the eighth on (workgroup numbers go round the XCDs) the tiles
 // `first_tile`, .. of `far`, the update of the rows above this panel's by the panel before: a diagonal block is one workgroup's chain, and
 // the chip is free beside it.  The LDS makes that one tile per compute unit; with 248 tiles a launch takes 30 to 35 us, 25 without any.
 // 7168 channels, with the order of the products of the inverse (bcq_product.h): 4.36 -> 4.00 ms, of which this is half (in launches of
@@ -414,7 +414,6 @@ __global__ __launch_bounds__(256) void factor_diag_far_kernel(int N, int r0, int
 {
     __shared__ ProductShared s;
     if (blockIdx.x == 0) {
-        if (b == 0) return;
         __builtin_amdgcn_s_setprio(3);
         factor_diag(N, r0, b, Hw, H, lambda, U, Ut);
     } else if (blockIdx.x >= 8) {
@@ -500,9 +499,15 @@ hipError_t launch_quant_factor(int N, float damp, const float *H, float *U, void
     };
     for (int p1 = N; p1 > 0;) {
         const int p0 = (p1 - 1) / kFactorPanel * kFactorPanel;
-        // (what does not fit beside the panel's blocks)
+        // What does not fit beside the panel's blocks goes before them, two workgroups to a compute unit: 3 % of the tiles at 7168 channels,
+        // 62 % at 14336, 89 % at 28672.  ms, all trailing updates in launches of their own / this / with the rest in the kernel that
+        // has a diagonal block beside, one workgroup to a compute unit: 10240 channels 8.0 / 7.2 / 7.5, 14336 15.3 / 14.1 / 15.3, 28672 88.0 / 80.3 / 93.7,
+        // 32768 138 / 125 / 145.
         const int blocks = (p1 - p0 + kFactorBlock - 1) / kFactorBlock;
-        if (tiles - done > blocks * beside) diag(0, 0, tiles - done - blocks * beside);
+        if (const int rest = tiles - blocks * beside; rest > 0) {
+            hipLaunchKernelGGL(product_part_kernel<kSubtractLower>, dim3((unsigned)rest), dim3(256), 0, stream, far, 0, tiles);
+            done = rest;
+        }
         for (int r1 = p1; r1 > p0;) {
             const int r0 = (r1 - 1) / kFactorBlock * kFactorBlock, b = r1 - r0;
             diag(r0, b, tiles - done < beside ? tiles - done : beside);
