@@ -254,19 +254,23 @@ __global__ __launch_bounds__(64 * kFewWaves) void bcq_few_kernel(FewParams p)
 // ---------------------------------------------------------------------------------
 bool few_applies(const Geom &g, int batch, const void *workspace)
 {
-    // split-K accumulators unless the layer is a single slice
-    // With a single plane the digits are the larger part: one column slice 24184 x 512 4.2 us there, 4.7 here, many slices 5959 x 30464 12.8 / 13.7
-    // (against 25148 x 5120 12.2 / 10.5, 588 x 28928 6.7 / 5.9 from four vectors).
-    if (g.q == 1 && (g.nslice == 1 || (g.nslice >= 48 && g.ntile >= 128))) return false;
+    // One plane on one column slice: a wave has so few steps that what it does once, the digits above all, is the larger part, with two vectors as soon
+    // as one wave per SIMD does not do with a half tile each.  us here / there (bcq_skinny.hip): two vectors 2885 x 512 3.6 / 4.0, 8483 x 512 3.6 / 4.3,
+    // 14869 x 512 3.8 / 4.2, 19085 x 512 4.3 / 4.2, 40487 x 512 5.0 / 4.8; three and four 3733 x 512 4.1 / 3.9, 10967 x 384 4.1 / 3.9, 17301 x 512 4.7 / 4.3,
+    // 52847 x 512 6.1 / 5.1.
+    // With more slices this kernel is as fast or faster (60 layers of 20 to 72 slices and 4096 to 36864 rows: 0.77 to 1.03 of the time there).
+    if (g.q == 1 && g.nslice == 1 && (batch > 2 || g.ntile > 2 * compute_units())) return false;
+    // (split-K accumulators unless the layer is a single slice)
     return batch >= 2 && batch <= kFewBatch && g.sub == 1 && (workspace != nullptr || g.nslice == 1);
 }
 
 namespace {
 
-// Time of a launch in us, fitted to sweeps over all plans of twelve layers of 512 x 512 to 9216 x 36864: what it takes with so many waves on
-// the fullest SIMD before the first half tile is done (512 x 512: 4.0, 5.3, 6.5 us), a step with three planes (7168 x 28672: 13 steps of two
-// waves 23.8, 9 of three 23.6; 7168 x 7168: 7 of one 11.5, 4 of two 10.2, 3 of three 11.0), a second workgroup on a row, a million additions to
-// the accumulators, and waves that wait for eight or more others.
+// Time of a launch in us: what it takes with so many waves on the fullest SIMD before the first half tile is done, a step with three planes, a
+// second workgroup on a row, a million additions to the accumulators, and waves that wait for eight or more others.  Only which plan is
+// least matters.  Over all plans of 378 layers (one to four planes, 1 to 72 slices, 512 to 36864 rows, two and four vectors) the one chosen takes 1.00 to 1.02 of
+// the best one's time in the middle, 1.06 to 1.11 in nine of ten, 1.24 at worst (1152 row tiles and 5 or 11 slices).  Without the term for four planes six of
+// those layers change, five of them to plans 2 to 7 % slower; without the one for eight waves 28, most of them slower, by up to 10 %.
 constexpr double kFewBase[4] = {0, 2.7, 3.5, 3.6}, kFewStep[4] = {0, 1.04, 1.48, 2.15}, kFewJoin = 0.8, kFewAdditions = 2.5, kFewCrowd = 0.5;
 
 struct FewPlan {

@@ -725,9 +725,10 @@ hipError_t launch_skinny(const Geom &g, const void *packed, const uint16_t *X, i
 {
     const long long all_tiles = (long long)g.ntile * g.nslice;
     // Two vectors on large layers: the GEMV's decomposition with both vectors' sign sums in one table entry (bcq_gemv2.hip).  Measured against
-    // bcq_few.hip (us, theirs first): q = 3 7168 x 28672 22.9 / 23.7, 28672 x 7168 22.1 / 26.1, 9216 x 36864 35.5 / 35.0, 7168 x 7168 9.8 / 10.5;
-    // q = 2 28417 x 2560 8.9 / 11.1; it loses where a compute unit gets less than a round of tiles: 4096 x 4096 7.4 / 6.0, 1024 x 8192 6.7 / 5.2,
-    // 36864 x 512 7.5 / 6.3.
+    // bcq_few.hip (us, theirs first), which loses most where its waves do not take whole slices evenly: q = 3 28672 x 7168 22.1 / 26.4, 9216 x 9216 12.0 / 15.0,
+    // 13337 x 16384 24.0 / 27.2, 36864 x 9216 33.1 / 35.1, 7168 x 7168 9.7 / 10.6, 7168 x 28672 23.3 / 23.5; q = 2 28417 x 2560 8.8 / 11.5, with offset 57344 x 8192
+    // 31.6 / 34.5, 30011 x 12288 26.9 / 26.8.  bcq_few.hip is ahead on some (9216 x 36864 36.9 / 36.1, 8192 x 8192 11.0 / 10.6, 11008 x 4096 9.5 / 8.4; with 256, 512 or 1024 row tiles and
+    // 32 or 64 slices by 5 to 20 %), and everywhere below a round of tiles per compute unit: 4096 x 4096 8.3 / 5.9, 1024 x 8192 8.0 / 5.2, 36864 x 512 7.4 / 6.3.
     const bool two = gemv2_applies(g, batch, workspace);
     if (two && (tuning.skinny_version == 5 || (tuning.skinny_version == 0 && all_tiles >= 2048)))
         return launch_gemv2(g, packed, X, ldx, Y, ldy, workspace, tuning, stream);

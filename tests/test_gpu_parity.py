@@ -484,6 +484,23 @@ def test_integer_kernel_for_up_to_four_vectors(workgroups, batch):
         bcq.set_option("skinny_version", 0)
 
 
+@pytest.mark.parametrize("batch", [2, 3, 4])
+@pytest.mark.parametrize("M,N,q,offset", [
+    (16384, 512, 1, False), (16385, 512, 1, True),       # one plane, one slice: up to two tiles per compute unit, and more
+    (16417, 1024, 1, False),                             # two slices
+    (4096, 24576, 1, True), (4097, 48 * 512, 1, False),  # 48 slices, 128 tiles and 129
+    (8192, 4064, 1, False), (8193, 4096, 1, True),       # 2048 tiles and 2056, where two vectors take the two-vector table kernel
+    (8160, 4096, 3, False),                              # 2040
+])
+def test_up_to_four_vectors_on_both_sides_of_the_rules(M, N, q, offset, batch):
+    """Automatic choice next to where it changes: bit for bit the oracle's result on exact inputs, workspace left zero."""
+    L = bcq_synth.make_exact_layer(M, N, q, group=N if N % 128 else 128, offset=offset, batch=batch, seed=M + N + batch)
+    pl = U.upload_and_pack(L, max_batch=batch)
+    expect = ref.gemm(L.planes, L.alpha, L.offset, L.x).astype(np.float16).astype(np.float64)
+    assert np.array_equal(U.gpu_gemm(pl, U.x_dev(L)).astype(np.float64), expect)
+    assert pl.workspace is None or not pl.workspace.cpu().numpy().any()
+
+
 def _block_sums(L):
     """sum(+-x) per plane, and sum(x), over the blocks of 128 columns: [batch][M][N / 128][q (+ 1)]."""
     signs = 2.0 * np.stack([(L.codes() >> i) & 1 for i in range(L.q)], axis=-1) - 1.0
