@@ -274,18 +274,21 @@ bcq_status bcq_read_probe(const void *buf, size_t bytes, void *sink, void *strea
 
 /*
  * Launch-shape overrides for tuning runs (HOST state, process-wide, not
- * thread-safe).  Names: "workgroups" (grid size of the GEMV and of the skinny
- * kernel), "waves" (waves per workgroup, 4 or 8: the GEMV, the table kernel of
- * bcq_gemm_skinny up to 16 columns; beyond them 8 = the kernel for large layers wherever it exists, 4 = never that one), "gemv_early" (1 = the GEMV
- * builds its tables before its first tile has arrived, 2 = never; automatic: when no wave has
- * more than one tile), "skinny_parts" (K
- * split of bcq_gemm_skinny for batch >= 2), "skinny_version" (1 = the kernel
- * that folds alpha into the matrix-core operand, 2 = the kernel that takes +-1
- * operands from an LDS table, 16 columns per pass; groups of
- * 32/64 always use 1; 3 and 4 = automatic; 5 = for batch 2 the GEMV's table kernel
- * with two vectors per table entry wherever it applies, 6 = never that one, the others chosen
- * automatically; with 1 and 2 the integer kernel for two to four vectors is not used either), "skinny_lds_steps" (3 or 4, kernel 2 only); 0 =
- * automatic.
+ * thread-safe).  Names: "workgroups" (grid size of the GEMV and of the
+ * kernels of bcq_gemm_skinny), "waves" (waves per workgroup, 4 or 8: the GEMV
+ * and the table kernel of bcq_gemm_skinny up to 16 columns; beyond them 8 =
+ * the kernel for large layers wherever it exists, 4 = never that one),
+ * "gemv_early" (1 = the GEMV builds its tables before its first tile has
+ * arrived, 2 = never; automatic: when no wave has more than one tile),
+ * "skinny_parts" (K split of the kernels of bcq_gemm_skinny other than those
+ * for two to four vectors), "skinny_version" (1 = the kernel that folds alpha
+ * into the matrix-core operand, 2 = the kernel that takes +-1 operands from an
+ * LDS table, 16 columns per pass; groups of 32/64 always use 1; with 1 and 2
+ * two to four vectors take these kernels too; 3 and 4 = automatic; 5 = for
+ * batch 2 the GEMV's table kernel with two vectors per table entry wherever it
+ * applies, 6 = never that one, the others chosen automatically: the integer
+ * kernel for two to four vectors), "skinny_lds_steps" (3 or 4, kernel 2 only);
+ * 0 = automatic.
  * Unknown names or values return BCQ_ERR_INVALID_ARG.
  */
 bcq_status bcq_set_option(const char *name, int32_t value);

@@ -63,7 +63,7 @@ def test_llama70b_shapes(M, N, q):
 def test_skinny_fullsize(M, N, q, offset, batch):
     """configs[2] (q=2 with offset, batch 8, all three layers), configs[3] (batch 4 and 16, outlier channels,
     all three layers), the dominant layer of configs[1] at the widest batch of one pass (64), 17..32 columns
-    (the table kernel with two column groups, which large layers use), and two vectors (the two-vector table
+    (bcq_wide.hip with two column groups), and two vectors (the two-vector table
     kernel, in the launch shape large layers get)"""
     _check(M, N, q, offset, batch=batch, outlier_frac=0.01 if 9216 in (M, N) else 0.0)
 

@@ -206,13 +206,14 @@ def test_skinny_batches(batch):
     _run_case(96, 1024, 2, 128, False, batch=batch, seed=batch + 50)
 
 
-def test_skinny_strided_rows():
-    L = bcq_synth.make_layer(128, 1024, 3, group=128, offset=True, batch=3, seed=77)
-    pl = U.upload_and_pack(L, max_batch=3)
-    Xbig = torch.zeros((3, L.N + 64), dtype=torch.float16, device="cuda")
+@pytest.mark.parametrize("batch", [3, 7])
+def test_skinny_strided_rows(batch):
+    L = bcq_synth.make_layer(128, 1024, 3, group=128, offset=True, batch=batch, seed=77)
+    pl = U.upload_and_pack(L, max_batch=batch)
+    Xbig = torch.zeros((batch, L.N + 64), dtype=torch.float16, device="cuda")
     Xbig[:, : L.N] = U.x_dev(L)
-    Ybig = torch.full((3, L.M + 7), 123.0, dtype=torch.float16, device="cuda")
-    bcq.gemm_skinny(pl.desc, pl.packed, Xbig, Xbig.stride(0), Ybig, Ybig.stride(0), 3, pl.workspace)
+    Ybig = torch.full((batch, L.M + 7), 123.0, dtype=torch.float16, device="cuda")
+    bcq.gemm_skinny(pl.desc, pl.packed, Xbig, Xbig.stride(0), Ybig, Ybig.stride(0), batch, pl.workspace)
     torch.cuda.synchronize()
     Y = Ybig.cpu().numpy()
     U.gate(Y[:, : L.M], ref.gemm(L.planes, L.alpha, L.offset, L.x))
@@ -243,14 +244,15 @@ def test_skinny_k_split_does_not_change_results(parts):
     assert not pl.workspace.cpu().numpy().any()
 
 
-def test_skinny_negative_alpha_and_ragged():
-    """alpha of either sign (the sign is folded into the plane bits), M % 32 != 0, N % 512 != 0."""
-    L = bcq_synth.make_layer(77, 1120, 3, group=1120, offset=True, batch=3, seed=8)
+@pytest.mark.parametrize("batch", [3, 6])
+def test_skinny_negative_alpha_and_ragged(batch):
+    """alpha of either sign (the sign is folded into the plane bits), M % 32 != 0, N % 512 != 0; integer and table kernel."""
+    L = bcq_synth.make_layer(77, 1120, 3, group=1120, offset=True, batch=batch, seed=8)
     a = L.alpha.copy()
     a[::2, :, 1] = -a[::2, :, 1]
     a[1::3, :, 0] = -a[1::3, :, 0]
     L.alpha = a
-    pl = U.upload_and_pack(L, max_batch=3)
+    pl = U.upload_and_pack(L, max_batch=batch)
     U.gate(U.gpu_gemm(pl, U.x_dev(L)), ref.gemm(L.planes, L.alpha, L.offset, L.x))
     # the batch-1 kernel on the same layer
     y1 = U.gpu_gemv(pl, U.x_dev(L))
@@ -321,8 +323,8 @@ def test_skinny_kernel_variants(option, value, q, offset):
         bcq.set_option(option, value)
         _run_case(203, 3200, q, 128, offset, batch=7, seed=q + value)
         _run_case(64, 1024, q, 256, offset, batch=16, seed=q + value + 1)
-        L = bcq_synth.make_exact_layer(96, 2048, q, group=128, offset=offset, batch=3, seed=50 + q)
-        pl = U.upload_and_pack(L, max_batch=3)
+        L = bcq_synth.make_exact_layer(96, 2048, q, group=128, offset=offset, batch=5, seed=50 + q)  # (fewer: the integer kernel)
+        pl = U.upload_and_pack(L, max_batch=5)
         expect = ref.gemm(L.planes, L.alpha, L.offset, L.x).astype(np.float16).astype(np.float64)
         assert np.array_equal(U.gpu_gemm(pl, U.x_dev(L)).astype(np.float64), expect)
     finally:
@@ -344,7 +346,7 @@ def test_skinny_eight_waves_per_workgroup(workgroups, q, offset):
         assert np.array_equal(U.gpu_gemm(pl, U.x_dev(L)).astype(np.float64), expect)
         assert not pl.workspace.cpu().numpy().any()
         _run_case(203, 3200, q, 128, offset, batch=13, seed=q + workgroups)
-        _run_case(70, 1536, q, 256, offset, batch=2, seed=q + workgroups + 1)
+        _run_case(70, 1536, q, 256, offset, batch=5, seed=q + workgroups + 1)     # (fewer columns: bcq_few.hip)
         _run_case(203, 3200, q, 128, offset, batch=29, seed=q + workgroups + 2)   # (more than 16 columns: bcq_wide.hip)
     finally:
         bcq.set_option("workgroups", 0)
@@ -479,6 +481,22 @@ def test_integer_kernel_for_up_to_four_vectors(workgroups, batch):
             assert pl.workspace is None or not pl.workspace.cpu().numpy().any()
         _run_case(600, 4608, 3, 128, True, batch=batch, seed=batch + workgroups, outlier_frac=0.01)
         _run_case(1024, 4096, 2, 128, False, batch=batch, seed=workgroups + 1)
+        # every alpha and offset a binary16 subnormal, padded rows of X and Y
+        L = bcq_synth.make_exact_layer(150, 2048, 3, group=128, offset=True, batch=batch, seed=92)
+        rng = np.random.default_rng(7)
+        L.alpha = rng.integers(1, 1024, size=L.alpha.shape, dtype=np.uint16).view(np.float16)
+        z = rng.integers(1, 1024, size=L.offset.shape, dtype=np.uint16) | (rng.integers(0, 2, size=L.offset.shape, dtype=np.uint16) << 15)
+        L.offset = z.view(np.float16)
+        expect = ref.gemm(L.planes, L.alpha, L.offset, L.x).astype(np.float16).astype(np.float64)
+        assert np.abs(expect).max() > 2.0 ** -12, "the scales must matter"
+        pl = U.upload_and_pack(L, max_batch=batch)
+        X = torch.full((batch, L.N + 64), 5.0, dtype=torch.float16, device="cuda")
+        X[:, :L.N] = U.x_dev(L)
+        Y = torch.full((batch, L.M + 10), 3.0, dtype=torch.float16, device="cuda")
+        bcq.gemm_skinny(pl.desc, pl.packed, X, X.stride(0), Y, Y.stride(0), batch, pl.workspace)
+        torch.cuda.synchronize()
+        assert np.array_equal(Y[:, :L.M].cpu().numpy().astype(np.float64), expect)
+        assert torch.all(Y[:, L.M:] == 3.0)
     finally:
         bcq.set_option("workgroups", 0)
         bcq.set_option("skinny_version", 0)
@@ -738,7 +756,7 @@ def test_groups_kernel_instances(q, offset, group, nb):
 ])
 def test_far_apart_rows_of_many_vectors(group, batch, ldx):
     """Vectors so far apart that 32-bit byte offsets reach only some of them: taken in passes of those that they reach, with one
-    scaling group per block, row-wise scales and several groups per block."""
+    scaling group per block, row-wise scales and several groups per block.  (Two to four vectors with one group per block: 64-bit addresses, one pass.)"""
     M, N = 2048, 1024
     L = bcq_synth.make_exact_layer(M, N, 2, group=group, offset=False, batch=batch, seed=5)
     pl = U.upload_and_pack(L, max_batch=batch)
@@ -787,12 +805,13 @@ def test_wide_batch_exact_and_strided():
 
 def test_maximum_column_count():
     """N = 523776 = 1023 column slices, the most the 10-bit arrival count of the split-K word holds
-    (one more slice is refused by the descriptor check): GEMV and skinny kernel."""
+    (one more slice is refused by the descriptor check): GEMV, integer and table kernel."""
     N = 1023 * 512
     d = bcq.Desc(40, N + 512, 2, 128, 0, 0)
     assert bcq.packed_bytes(d) == 0
     _run_case(40, N, 2, 128, True, seed=3)
     _run_case(40, N, 2, 128, True, batch=3, seed=4)
+    _run_case(40, N, 2, 128, True, batch=5, seed=5)
 
 
 @pytest.mark.parametrize("q,offset", [(3, True), (2, False), (4, True)])
