@@ -109,9 +109,9 @@ struct ProductArgs {
 // channels 204 / 192 / 190 and 49.7 / 54.1 / 50.4, one sample 29.8 / 32.6 / 28.9; 132 channels, one sample 9.5 / 10.4 / (one XCD) 9.7.  The factor
 // and the GPTQ pass take the same time with all three.  Otherwise each XCD takes every eighth block, for the quadratic
 // forms and the products with a triangular right operand column by column from the last one, whose columns have the longest k range.
-// Several products of a launch go on where the one `before` ended: starting each at the first XCD left all blocks of small products to it
-// (7168 channels, us: 14 pairs of 256 channels 38 + 32 -> 20 + 19, 7 of 512 channels 64 + 50 -> 24 + 25, the longest columns of 4096 first
-// 212 -> 164).  Every other eight blocks go to the XCDs in reverse, so that none has all the longer ones of a triangular operand.
+// Several products of a launch (kStore, kStoreNegated) go on where the one before ended, after `before` blocks: starting each at the first XCD left all
+// blocks of small products to it (7168 channels, us: 14 pairs of 256 channels 38 + 32 -> 20 + 19, 7 of 512 channels 64 + 50 -> 24 + 25, the longest columns of
+// 4096 first 212 -> 164).  In these two modes every other eight blocks go to the XCDs in reverse, so that none has all the longer ones of a triangular operand.
 template <int MODE>
 constexpr bool kProdEven = MODE == kAddTwiceSymmetric || MODE == kSubtract || MODE == kSubtractLower;
 
@@ -161,7 +161,7 @@ __device__ __forceinline__ bool product_tile(int wg, int wgs, int R, int C, int 
         return true;
     } else {
         const int br = (ntr + kProdBlock - 1) / kProdBlock, bc = (ntc + kProdBlock - 1) / kProdBlock;
-        const int t = j & (kProdBlock * kProdBlock - 1), round = j / (kProdBlock * kProdBlock), at = (xcd - before * br * bc) & 7;
+        const int t = j & (kProdBlock * kProdBlock - 1), round = j / (kProdBlock * kProdBlock), at = (xcd - before) & 7;
         constexpr bool kTurns = MODE == kStore || MODE == kStoreNegated;
         const int s = round * 8 + (kTurns && (round & 1) ? 7 - at : at);
         if (s >= br * bc) return false;
@@ -205,7 +205,10 @@ __device__ __forceinline__ void product_tile_of(ProductArgs p, int wg, int wgs, 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lo = lane & 15, hi = lane >> 4, wr = wave >> 1, wc = wave & 1;
+    int before = 0;  // blocks of the launch's products before this one (only the last one may have fewer columns)
     if (MODE == kStore || MODE == kStoreNegated) {
+        constexpr int kEdge = kProdTile * kProdBlock;
+        before = (int)blockIdx.y * ((p.R + kEdge - 1) / kEdge) * ((p.C + kEdge - 1) / kEdge);
         p.A += blockIdx.y * p.stride;
         p.B += blockIdx.y * p.stride;
         p.out += blockIdx.y * p.stride;
@@ -214,7 +217,6 @@ __device__ __forceinline__ void product_tile_of(ProductArgs p, int wg, int wgs, 
         if (p.k_is_columns) p.K = p.C;
     }
     int tile_row, tile_col;
-    const int before = MODE == kStore || MODE == kStoreNegated ? (int)blockIdx.y : 0;  // products of the launch before this one
     if (!product_tile<MODE>(wg, wgs, p.R, p.C, before, &tile_row, &tile_col)) return;
     const int r0 = tile_row * kProdTile, c0 = tile_col * kProdTile;
     if (kSplitA && p.rows && r0 >= *p.rows) return;
