@@ -56,7 +56,7 @@ struct FewParams {
 };
 
 // Half tiles between two meetings of a workgroup's waves, of at most `most`.  With more than four waves there is one workgroup per compute
-// unit, which stands still meanwhile (8 / 16, us, four vectors: 7168 x 28672 24.2 / 23.0, 9216 x 36864 33.8 / 33.1, 28672 x 8192 with offset 26.3 / 25.5);
+// unit, which stands still meanwhile (8 / 16, us, four vectors: 7168 x 28672 23.1 / 21.7, 9216 x 36864 33.0 / 31.9, 28672 x 8192 q = 2 with offset 20.2 / 19.3);
 // several of them fill each other's pauses, and their additions are better spread (28672 x 7168 25.5 / 25.9).
 constexpr int few_chunk(int waves, int most) { return waves > 4 && most > 8 ? 16 : 8; }
 // LDS of a workgroup of `waves` waves; a scale per (wave, block, vector), static, beside it.
@@ -279,33 +279,36 @@ struct FewPlan {
 
 FewPlan plan_few(const Geom &g, int batch, int forced)
 {
-    const int cus = compute_units();
-    const long long halves = (g.M + 15LL) / 16;
+    const unsigned cus = compute_units(), halves = (g.M + 15LL) / 16, nslice = g.nslice;
     FewPlan best = {g.nslice, 1, 1, 1};
     double least = 1e300;
-    for (int most = kFewWaves; most >= 1; --most) {
-        const int ranges = (g.nslice + most - 1) / most, slices = (g.nslice + ranges - 1) / ranges;
+    const double planes = (g.q + 0.2 * g.z + 0.5) / 3.5, half_tiles = halves;
+    for (unsigned most = kFewWaves; most >= 1; --most) {
+        const unsigned ranges = (nslice + most - 1) / most, slices = (nslice + ranges - 1) / ranges;
         if (slices < most) continue;
-        for (int row_groups = 1; row_groups * slices <= kFewWaves; ++row_groups) {
-            const int waves = row_groups * slices;
-            for (int per_cu = 1; per_cu * ((waves + 3) / 4) <= 3; ++per_cu) {
-                long long groups = (forced > 0 ? forced : (long long)cus * per_cu) / ranges;  // workgroups per range
-                if (groups < 1) {
-                    if (forced <= 0) continue;
-                    groups = 1;
-                }
-                if (groups * row_groups > halves) groups = (halves + row_groups - 1) / row_groups;
+        unsigned room[3];  // workgroups per range
+        for (unsigned per_cu = 1; per_cu <= 3; ++per_cu) {
+            room[per_cu - 1] = (forced > 0 ? (unsigned)forced : cus * per_cu) / ranges;
+            if (forced > 0 && room[per_cu - 1] < 1) room[per_cu - 1] = 1;
+        }
+        const double join = ranges > 1 ? kFewJoin + kFewAdditions * 1e-6 * ranges * g.M * batch : 0.0;
+        for (unsigned row_groups = 1; row_groups * slices <= kFewWaves; ++row_groups) {
+            const unsigned waves = row_groups * slices, enough = (halves + row_groups - 1) / row_groups;
+            for (unsigned per_cu = 1; per_cu * ((waves + 3) / 4) <= 3; ++per_cu) {
+                if (per_cu > 1 && room[per_cu - 2] >= enough) break;  // no more workgroups
+                const unsigned groups = room[per_cu - 1] < enough ? room[per_cu - 1] : enough;
+                if (groups < 1) continue;
                 // steps: the mean counts too, only some of a compute unit's waves take one more
-                const double mean = (double)halves / (groups * row_groups);
-                const double steps = 0.3 * mean + 0.7 * ((halves + groups * row_groups - 1) / (groups * row_groups));
-                const int simd = per_cu * ((waves + 3) / 4);
-                double cost = kFewBase[simd] + kFewStep[simd] * steps * (g.q + 0.2 * g.z + 0.5) / 3.5;
-                if (ranges > 1) cost += kFewJoin + kFewAdditions * 1e-6 * ranges * g.M * batch;
+                const double mean = half_tiles / (groups * row_groups);
+                const unsigned whole = (unsigned)mean;
+                const double steps = 0.3 * mean + 0.7 * (whole + (mean > whole ? 1 : 0));
+                const unsigned simd = per_cu * ((waves + 3) / 4);
+                double cost = kFewBase[simd] + kFewStep[simd] * steps * planes + join;
                 if (waves > 8) cost += kFewCrowd;
                 if (g.q == 4 && simd == 3) cost += 0.3 * steps;  // (4096 x 28672: 8 steps of two 20.2, 5 of three 21.1)
                 if (cost < least) {
                     least = cost;
-                    best = {ranges, slices, row_groups, (int)(groups * row_groups)};
+                    best = {(int)ranges, (int)slices, (int)row_groups, (int)(groups * row_groups)};
                 }
             }
         }
@@ -313,32 +316,49 @@ FewPlan plan_few(const Geom &g, int batch, int forced)
     return best;
 }
 
+// The last plans of the calling thread: choosing one takes 0.13 to 0.3 us of the host, which a launch of a small layer waits for (512 x 512, four vectors,
+// eager calls 5.65 us, 5.5 with the plan at hand).  `dev`: the current device, whose compute units count.
+FewPlan kept_plan(const Geom &g, int batch, int forced, int dev)
+{
+    struct Entry {
+        int M, nslice, planes, batch, forced, dev;
+        FewPlan plan;
+    };
+    constexpr unsigned kEntries = 64;
+    static thread_local Entry entries[kEntries];  // (zeros: no layer has no rows)
+    const int planes = 2 * g.q + g.z;
+    Entry &e = entries[((unsigned)g.M * 0x9e3779b1u + (unsigned)(g.nslice * 64 + planes * 4 + batch) * 0x85ebca6bu) >> 26];
+    if (e.M != g.M || e.nslice != g.nslice || e.planes != planes || e.batch != batch || e.forced != forced || e.dev != dev)
+        e = {g.M, g.nslice, planes, batch, forced, dev, plan_few(g, batch, forced)};
+    return e.plan;
+}
+
+// `dev`: the current device, or -1 if it is not known or has a number from kFewDevices on.
+constexpr int kFewDevices = 64;
+
 template <int Q, int Z, int V, int CHUNK>
-hipError_t launch_few_v(const FewParams &p, int waves, int groups, hipStream_t stream)
+hipError_t launch_few_v(const FewParams &p, int waves, int groups, int dev, hipStream_t stream)
 {
     const size_t lds = few_lds_bytes(waves, CHUNK);
     // more LDS than a launch gets by itself: asked for once per device
-    constexpr int kMaxDevices = 64;
-    static std::atomic<bool> asked[kMaxDevices];
-    int dev = 0;
-    const bool known = hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices;
-    if (!known || !asked[dev].load(std::memory_order_relaxed)) {
+    static std::atomic<bool> asked[kFewDevices];
+    if (dev < 0 || !asked[dev].load(std::memory_order_relaxed)) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(bcq_few_kernel<Q, Z, V, CHUNK>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)few_lds_bytes(kFewWaves, CHUNK));
         if (e != hipSuccess) return e;
-        if (known) asked[dev].store(true, std::memory_order_relaxed);
+        if (dev >= 0) asked[dev].store(true, std::memory_order_relaxed);
     }
     hipLaunchKernelGGL((bcq_few_kernel<Q, Z, V, CHUNK>), dim3((unsigned)groups), dim3(64 * waves), lds, stream, p);
     return hipGetLastError();
 }
 
 template <int Q, int Z>
-hipError_t launch_few_qz(const FewParams &p, int waves, int groups, hipStream_t stream)
+hipError_t launch_few_qz(const FewParams &p, int waves, int groups, int dev, hipStream_t stream)
 {
     const int chunk = few_chunk(waves, p.part_base + (p.part_rem > 0 ? 1 : 0));
     if (p.batch == 2)
-        return chunk == 8 ? launch_few_v<Q, Z, 2, 8>(p, waves, groups, stream) : launch_few_v<Q, Z, 2, 16>(p, waves, groups, stream);
-    return chunk == 8 ? launch_few_v<Q, Z, 4, 8>(p, waves, groups, stream) : launch_few_v<Q, Z, 4, 16>(p, waves, groups, stream);
+        return chunk == 8 ? launch_few_v<Q, Z, 2, 8>(p, waves, groups, dev, stream) : launch_few_v<Q, Z, 2, 16>(p, waves, groups, dev, stream);
+    return chunk == 8 ? launch_few_v<Q, Z, 4, 8>(p, waves, groups, dev, stream) : launch_few_v<Q, Z, 4, 16>(p, waves, groups, dev, stream);
 }
 
 }  // namespace
@@ -347,7 +367,9 @@ hipError_t launch_few(const Geom &g, const void *packed, const uint16_t *X, int 
                       const GemvTuning &tuning, hipStream_t stream)
 {
     if (!few_applies(g, batch, workspace)) return hipErrorInvalidValue;
-    const FewPlan plan = plan_few(g, batch, tuning.workgroups);
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kFewDevices) dev = -1;
+    const FewPlan plan = dev < 0 ? plan_few(g, batch, tuning.workgroups) : kept_plan(g, batch, tuning.workgroups, dev);
     const int halves = (int)((g.M + 15LL) / 16), waves = plan.slices * plan.row_groups;
     FewParams p;
     p.blob = static_cast<const uint8_t *>(packed);
@@ -362,14 +384,14 @@ hipError_t launch_few(const Geom &g, const void *packed, const uint16_t *X, int 
     p.scale_lane_mask = g.scale_lanes - 1;
     const int groups = plan.ranges * (plan.parts / plan.row_groups);
     switch (g.q * 2 + g.z) {
-        case 2: return launch_few_qz<1, 0>(p, waves, groups, stream);
-        case 3: return launch_few_qz<1, 1>(p, waves, groups, stream);
-        case 4: return launch_few_qz<2, 0>(p, waves, groups, stream);
-        case 5: return launch_few_qz<2, 1>(p, waves, groups, stream);
-        case 6: return launch_few_qz<3, 0>(p, waves, groups, stream);
-        case 7: return launch_few_qz<3, 1>(p, waves, groups, stream);
-        case 8: return launch_few_qz<4, 0>(p, waves, groups, stream);
-        case 9: return launch_few_qz<4, 1>(p, waves, groups, stream);
+        case 2: return launch_few_qz<1, 0>(p, waves, groups, dev, stream);
+        case 3: return launch_few_qz<1, 1>(p, waves, groups, dev, stream);
+        case 4: return launch_few_qz<2, 0>(p, waves, groups, dev, stream);
+        case 5: return launch_few_qz<2, 1>(p, waves, groups, dev, stream);
+        case 6: return launch_few_qz<3, 0>(p, waves, groups, dev, stream);
+        case 7: return launch_few_qz<3, 1>(p, waves, groups, dev, stream);
+        case 8: return launch_few_qz<4, 0>(p, waves, groups, dev, stream);
+        case 9: return launch_few_qz<4, 1>(p, waves, groups, dev, stream);
     }
     return hipErrorInvalidValue;
 }
