@@ -29,26 +29,26 @@ def _check(M, N, q, offset, batch=1, **kw):
 
 @pytest.mark.parametrize("M,N", [(7168, 7168), (28672, 7168), (7168, 28672)])
 def test_opt30b_q3(M, N):
-    """configs[1]"""
+    """OPT-30B-shaped layers, three planes, batch 1"""
     _check(M, N, 3, False)
 
 
 @pytest.mark.parametrize("M,N", [(7168, 7168), (28672, 7168), (7168, 28672)])
 def test_opt30b_q2_offset(M, N):
-    """configs[2], batch 1"""
+    """OPT-30B-shaped layers, two planes with offset, batch 1"""
     _check(M, N, 2, True)
 
 
 @pytest.mark.parametrize("M,N", [(9216, 9216), (36864, 9216), (9216, 36864)])
 def test_opt66b_q3_outliers(M, N):
-    """configs[3], batch 1"""
+    """OPT-66B-shaped layers with outlier channels, batch 1"""
     _check(M, N, 3, False, outlier_frac=0.01)
 
 
 @pytest.mark.parametrize("q", [2, 3])
 @pytest.mark.parametrize("M,N", [(8192, 8192), (1024, 8192), (28672, 8192), (8192, 28672)])
 def test_llama70b_shapes(M, N, q):
-    """configs[4], each distinct shape on its own: q/o, k/v (GQA), gate/up, down; q = 2 and 3"""
+    """Llama-2-70B-shaped block, each distinct shape on its own: q/o, k/v (GQA), gate/up, down; q = 2 and 3"""
     _check(M, N, q, False)
 
 
@@ -61,8 +61,8 @@ def test_llama70b_shapes(M, N, q):
                                                   (7168, 28672, 3, False, 32), (7168, 7168, 2, True, 24),
                                                   (7168, 28672, 3, False, 2), (9216, 36864, 3, True, 2)])
 def test_skinny_fullsize(M, N, q, offset, batch):
-    """configs[2] (q=2 with offset, batch 8, all three layers), configs[3] (batch 4 and 16, outlier channels,
-    all three layers), the dominant layer of configs[1] at the widest batch of one pass (64), 17..32 columns
+    """OPT-30B-shaped layers with q=2 and offset at batch 8, OPT-66B-shaped ones with outlier channels at batch 4 and 16, the
+    dominant OPT-30B-shaped layer at the widest batch of one pass (64), 17..32 columns
     (bcq_wide.hip with two column groups), and two vectors (the two-vector table
     kernel, in the launch shape large layers get)"""
     _check(M, N, q, offset, batch=batch, outlier_frac=0.01 if 9216 in (M, N) else 0.0)
@@ -70,7 +70,7 @@ def test_skinny_fullsize(M, N, q, offset, batch):
 
 @pytest.mark.parametrize("q", [2, 3])
 def test_llama70b_block_in_sequence(q):
-    """configs[4]: the seven GEMVs of the decoder block (q, k, v, o, gate, up, down) enqueued back to back on
+    """The seven GEMVs of a Llama-2-70B-shaped decoder block (q, k, v, o, gate, up, down) enqueued back to back on
     one stream with ONE shared workspace and no synchronisation in between; every output is then checked
     on sampled rows.  (The workspace is left zero by each call, which is what lets the next one use it.)"""
     import torch
@@ -103,7 +103,7 @@ def test_llama70b_block_in_sequence(q):
 
 
 def test_llama70b_fused_qkv_equals_three_gemvs():
-    """configs[4]: the q, k and v projections (8192, 1024, 1024 rows of 8192 columns) read the
+    """Llama-2-70B-shaped block: the q, k and v projections (8192, 1024, 1024 rows of 8192 columns) read the
     same activations.  Packed row-wise into one blob (bcq_pack_rows) they run as ONE GEMV whose
     output is, bit for bit, the concatenation of the three separate GEMVs, and matches the oracle."""
     import torch

@@ -25,7 +25,7 @@ def _run_case(M, N, q, group, offset, batch=1, seed=0, **kw):
 
 
 def test_config0_768x768_q3():
-    """configs[0]: 768x768, q=3, group 128, no offset, batch 1, seed 0."""
+    """768x768, q=3, group 128, no offset, batch 1, seed 0."""
     worst, normwise = _run_case(768, 768, 3, 128, False)
     print(f"config0 gated {worst:.2e} normwise {normwise:.2e}")
 
@@ -221,7 +221,7 @@ def test_skinny_strided_rows(batch):
 
 
 def test_outlier_channels():
-    """configs[3] activation recipe: 1% of channels scaled x20."""
+    """Activations with 1% of the channels scaled x20."""
     _run_case(512, 9216, 3, 128, False, seed=3, outlier_frac=0.01)
 
 
