@@ -741,6 +741,34 @@ def test_factor_updates_beside_the_blocks(N):
     assert err.max() <= 8 * err32.max()
 
 
+def test_factor_of_many_channels():
+    """9220 channels, where more than half of a trailing update does not fit beside the next panel's blocks: the leading block of
+    U^T U, which every update reaches, against that of H_d^-1 in binary64, over the error of a binary32 factorisation (LAPACK)."""
+    from scipy.linalg import cho_factor, cho_solve
+    N, lead = 9220, 256
+    g = torch.Generator(device="cuda").manual_seed(N)
+    X = torch.randn((2 * N, N), device="cuda", generator=g)
+    X[:, :N // 32] *= 6
+    H = 2 * (X.t().contiguous() @ X)
+    H = ((H + H.t()) * 0.5).contiguous()
+    U = torch.full((N, N), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.empty(bcq.quant_factor_workspace_bytes(N), dtype=torch.uint8, device="cuda")
+    bcq.quant_factor(N, 0.01, H, U, ws)
+    torch.cuda.synchronize()
+    assert not torch.tril(U, -1).any()
+    H32, U_g = H.cpu().numpy(), U[:lead, :lead].cpu().numpy().astype(np.float64)
+
+    def leading(dtype):
+        Hd = H32.astype(dtype)
+        Hd[np.diag_indices(N)] += dtype(0.01 * np.mean(np.diag(H32).astype(np.float64)))
+        return cho_solve(cho_factor(Hd, overwrite_a=True, check_finite=False), np.eye(N, lead, dtype=dtype), check_finite=False)[:lead].astype(np.float64)
+
+    K = leading(np.float64)
+    err, err32 = (np.linalg.norm(k - K) / np.linalg.norm(K) for k in (U_g.T @ U_g, leading(np.float32)))
+    print(f"{err:.2e}, binary32 {err32:.2e}")
+    assert err <= 8 * err32
+
+
 @pytest.mark.parametrize("N", [64, 132, 160, 384, 404, 408, 1000])   # (a last block of 4, 20 and 24 columns: products of as many terms)
 def test_inverse_hessian_factor(N):
     """U with (H + 0.01 mean(diag H) I)^-1 = U^T U, U upper triangular, against the oracle's binary64 factor;
