@@ -254,8 +254,8 @@ bcq_status bcq_gemv_noalloc(const bcq_desc *desc, const void *packed, const uint
  *   workspace as for bcq_gemv with bcq_workspace_bytes(desc, batch)
  * Accumulation: binary32 with the activations as they are, except for batch 2 to 4 with one scale per 128 columns or more on most layers.  There
  * the sums over the signs are exact sums of integers, the activations rounded relative to the largest magnitude of their 128-column
- * block and vector: exact from 2^-17 of it up, otherwise off by at most 2^-28 of it (an addition in binary32 to a sum that holds
- * the largest one loses up to 2^-24 of it).  Resolution of the split over columns, and non-finite inputs, as for bcq_gemv.
+ * block and vector: exact from 1.01 * 2^-17 of it up, otherwise off by at most 1.01 * 2^-28 of it (an addition in binary32 to a sum
+ * that holds the largest one loses up to 2^-24 of it).  Resolution of the split over columns, and non-finite inputs, as for bcq_gemv.
  */
 bcq_status bcq_gemm_skinny(const bcq_desc *desc, const void *packed,
                            const uint16_t *X, int32_t ldx, uint16_t *Y,
